@@ -220,9 +220,10 @@ void layout(kg_ctx *x)
         x->s_px1 = take(R * d * 4);
         x->s_pF = take(R * d * 4);
         x->s_pqkv = take(R * 3 * d * 4);
-        x->s_pactX = take(nb * act_bytes(d));
-        x->s_pactA = take(nb * act_bytes(d));
-        x->s_pactF = take(nb * act_bytes(f));
+        const size_t nba = (nb + 1) / 2 * 2;    // the pair layout (pf_act_ptr) spans two 8-row blocks also where the last one has no partner
+        x->s_pactX = take(nba * act_bytes(d));
+        x->s_pactA = take(nba * act_bytes(d));
+        x->s_pactF = take(nba * act_bytes(f));
         x->s_pssq0 = take(nb * (d / 16) * KG_ROWS * 4);
         x->s_pssq1 = take(nb * (d / 16) * KG_ROWS * 4);
         x->s_popart = take(nbp * c.n_heads * x->n_pages * KG_ROWS * c.head_dim * 4);
