@@ -24,6 +24,9 @@ constexpr size_t ALIGN = 256;
 // 4096-token prompt at the 7B shape: 122 ms in passes of 1024 rows, 109 in passes of 2048, 105 in one).
 // The other cache types keep the 8-row-block kernels, whose attention needs page partials per block.
 constexpr int PF_ROWS_MAX = 1024, PF_ROWS_MAX_HALF = 4096;
+// Passes of up to PF_STREAM_ROWS rows are bound by reading the weights and go through gemm_stream_kernel;
+// its projections along k are cut into at most PF_STREAM_SLICES slices.
+constexpr int PF_STREAM_ROWS = 192, PF_STREAM_SLICES = 8;
 inline size_t up(size_t x, size_t a = ALIGN) { return (x + a - 1) / a * a; }
 
 struct LayerW {
@@ -69,7 +72,7 @@ struct kg_ctx {
     // prompt pass: device copy of the prompt and buffers for pf_rows rows at a time (bf16 weights)
     int pf_rows = 0;
     size_t s_ptok, s_px0, s_px1, s_pF, s_pqkv, s_pactX, s_pactA, s_pactF, s_pssq0, s_pssq1, s_popart, s_pmxs, s_psms,
-        s_pcnt, s_pscale;
+        s_pcnt, s_pscale, s_ppart;
     // bindings
     char *arena = nullptr, *kv = nullptr, *scr = nullptr;
     hipStream_t stream = nullptr;
@@ -231,6 +234,7 @@ void layout(kg_ctx *x)
         x->s_psms = take(nbp * c.n_heads * x->n_pages * KG_ROWS * 4);
         x->s_pcnt = take(nb * c.n_heads * 4);
         x->s_pscale = take(R * 4);
+        x->s_ppart = half ? take((size_t)PF_STREAM_SLICES * std::min<size_t>(R, PF_STREAM_ROWS) * d * 4) : 0;
     }
     x->scratch_bytes = o;
 }
@@ -398,8 +402,11 @@ Epi epi_base(kg_ctx *x, int kind, int M, int N);
 
 // ---- prompt pass (dense MFMA projections over many 8-row blocks) ---------------------------------
 
-enum { PF_PLAN_TW1_RB8 = 17 };     // pf_gemm_plan: TW 1 with workgroups of 64 rows
+enum { PF_PLAN_TW1_RB8 = 17, PF_PLAN_STREAM = 18 };     // pf_gemm_plan: TW 1 with workgroups of 64 rows; gemm_stream_kernel
 int pf_gemm_plan(const kg_ctx *x, int N, int K, int T);
+int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
+// Short passes go through gemm_stream_kernel (half-precision cache only: its prompt rows are not bit-identical to decoded rows)
+inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= PF_STREAM_ROWS; }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
 {
@@ -413,7 +420,101 @@ int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, cons
     hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(d / 16, nb), dim3(128), 0, x->stream, emb, tk, tok_dev, rows, d, T, gain,
                        xout, (void *)(x->scr + x->s_pactX), at<float>(x->scr, x->s_pssq0), act_bytes(d),
                        (d / 16) * KG_ROWS, pf_gemm_plan(x, 3 * d, d, T) ? 1 : 0);
-    return check_launch(x, "prompt pack_rows");
+    KGCHK(check_launch(x, "prompt pack_rows"));
+    return pf_streams(x, T) ? launch_rms_scale(x, at<const float>(x->scr, x->s_pssq0), T) : KG_OK;
+}
+
+// the rows' RMS scales from their tile sums of squares, once per pass and not once per workgroup
+int launch_rms_scale(kg_ctx *x, const float *ssq, int T)
+{
+    const int d = x->c.d_model;
+    hipLaunchKernelGGL(pf_rms_scale_kernel, dim3((T + KG_ROWS - 1) / KG_ROWS), dim3(512), 0, x->stream, ssq, (d / 16) * KG_ROWS, d / 16, T,
+                       1.f / (float)d, x->c.rms_eps, at<float>(x->scr, x->s_pscale));
+    return check_launch(x, "prompt row scales");
+}
+
+// ---- short passes: projections as weight streams (gemm_stream_kernel) ----
+
+struct StreamPlan { int R, gx, ntw, slices, groups; };
+
+// Largest number of weight tiles per workgroup for R pairs of row blocks: what fits the registers of a wave
+// together with the loads in flight (7 tiles x 8 pairs spill at the 13B gate+up: 187 us instead of 113 us with 4 tiles in two rounds).
+constexpr int pf_stream_ntw_max(int R) { return R == 8 ? 6 : R == 6 ? 7 : 8; }
+
+// How a pass of T rows is split over a projection of NT weight tiles and KS k-steps: the workgroup's time in
+// microseconds by a fit to launches at the 7B and 13B shapes, 16 .. 128 rows (within a tenth of them): its
+// weights arrive at a compute unit's share of the memory (27 KB/us), its activations, which come through the L1
+// after them, at 84 KB/us; 1.5 us pass before anything streams and 0.09 us per accumulator tile at the end; and
+// the partial sums of a projection cut along k (`split`) are written and read at 2.5 TB/s.  So one round of
+// workgroups with as many tiles each as that takes wins: 7B shape, 48 rows: q,k,v 3 tiles 25 us, 2 tiles in two
+// rounds 39; gate+up 6 tiles 37, 3 tiles 48; down_proj 4 slices x 4 tiles 22, 2 slices x 2 tiles 28.
+StreamPlan pf_stream_plan(int n_cus, int NT, int KS, int T, bool split)
+{
+    const int pairs = (T + 15) / 16, gx = (pairs + 7) / 8, need = (pairs + gx - 1) / gx;
+    const int R = need <= 4 ? need : need <= 6 ? 6 : 8;
+    StreamPlan best = {R, gx, 1, 1, NT};
+    double best_cost = -1.0;
+    for (int S = 1; S <= (split ? PF_STREAM_SLICES : 1); S *= 2) {
+        if (S > 1 && KS < 16 * S) break;
+        for (int rounds = 1; rounds <= 16; rounds++) {
+            const int groups = std::min(NT, std::max(1, n_cus * rounds / (S * gx)));
+            const int ntw = (NT + groups - 1) / groups;
+            if (ntw > pf_stream_ntw_max(R)) continue;
+            const double steps = (double)KS / S;
+            const double cost = rounds * (steps * (ntw / 27.0 + 2.0 * R / 84.0) + 1.5 + 0.09 * ntw * R) + (split ? S * (double)T * NT * 64 / 2.5e6 : 0.0);
+            if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {R, gx, ntw, S, groups}; }
+        }
+    }
+    return best;
+}
+
+template <int R>
+void launch_stream_tiles(const PfStreamArgs &a, const Epi &e, int ntw, dim3 grid, hipStream_t s)
+{
+    switch (ntw) {
+#define STREAM_CASE(n) \
+    case n: if constexpr (n <= pf_stream_ntw_max(R)) hipLaunchKernelGGL((gemm_stream_kernel<n, R>), grid, dim3(64 * pf_stream_waves(n, R)), 0, s, a, e); break;
+        STREAM_CASE(1) STREAM_CASE(2) STREAM_CASE(3) STREAM_CASE(4) STREAM_CASE(5) STREAM_CASE(6) STREAM_CASE(7) STREAM_CASE(8)
+#undef STREAM_CASE
+    }
+}
+
+// One projection of a short pass.  EPI_PLAIN / EPI_SWIGLU scale their rows by s_pscale (if ssq_in is set);
+// EPI_RESID leaves the rows' next scales there.
+int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T, const Epi &e, int act_out_K)
+{
+    const bool resid = e.kind == EPI_RESID;
+    PfStreamArgs a;
+    memset(&a, 0, sizeof(a));
+    a.W = at<const u32x4_t>(x->arena, w_off);
+    a.KS = (K + 31) / 32; a.NT = N / 16;
+    a.act = (const u32x4_t *)act; a.act_pair16 = 2 * act_bytes(K) / 16; a.T = T;
+    a.act_out_blk = act_out_K ? act_bytes(act_out_K) : 0;
+    const StreamPlan p = pf_stream_plan(x->n_cus, a.NT, a.KS, T, resid);
+    a.slices = p.slices; a.groups = p.groups; a.gx = p.gx;
+    float *scale = at<float>(x->scr, x->s_pscale);
+    Epi e2 = e;
+    e2.scale_in = e.ssq_in ? scale : nullptr;
+    if (resid) a.part = at<float>(x->scr, x->s_ppart);
+    const int per = 8 / p.slices;
+    const dim3 grid(8 * p.gx * ((p.groups + per - 1) / per));
+    {
+        ProfScope ps(x, 3, 2.0 * T * (double)N * K);
+        switch (p.R) {
+        case 1: launch_stream_tiles<1>(a, e2, p.ntw, grid, x->stream); break;
+        case 2: launch_stream_tiles<2>(a, e2, p.ntw, grid, x->stream); break;
+        case 3: launch_stream_tiles<3>(a, e2, p.ntw, grid, x->stream); break;
+        case 4: launch_stream_tiles<4>(a, e2, p.ntw, grid, x->stream); break;
+        case 6: launch_stream_tiles<6>(a, e2, p.ntw, grid, x->stream); break;
+        default: launch_stream_tiles<8>(a, e2, p.ntw, grid, x->stream); break;
+        }
+        KGCHK(check_launch(x, "prompt projection"));
+    }
+    if (!resid) return KG_OK;
+    ProfScope ps(x, 2, 0.0);
+    hipLaunchKernelGGL(pf_reduce_rows_kernel, dim3(T), dim3(1024), 0, x->stream, (const float *)a.part, p.slices, T, N, e.res, e.xout, e.gain,
+                       e.act_out, a.act_out_blk, e.inv_d, e.eps, scale);
+    return check_launch(x, "prompt row sums");
 }
 
 // Y[T][N] = X[T][K] . W^T with the epilogue e applied per 8-row block; in/out block strides follow
@@ -424,8 +525,9 @@ int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, cons
 // (pf_act_ptr: the pair layout for gemm_prefill2_body).
 int pf_gemm_plan(const kg_ctx *x, int N, int K, int T)
 {
+    if (pf_streams(x, T)) return PF_PLAN_STREAM;
     // long passes with the half-precision cache only (its prompt rows are not bit-identical to decoded rows anyway)
-    if (T < 256 || x->kvt != 2 || (K + 31) / 32 > PF2_KS_MAX) return 0;
+    if (x->kvt != 2 || (K + 31) / 32 > PF2_KS_MAX) return 0;
     // Workgroups of 8 * TW weight tiles x 128 rows.  TW is the one with the least operand traffic: per
     // k-step every row group fetches all NT weight tiles and every workgroup its 16 activation tiles,
     // and a last round of workgroups that fills only part of the device costs a whole round; beside the
@@ -463,6 +565,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
                    int act_out_K)
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
+    if (pf_streams(x, T)) return launch_stream_gemm(x, w_off, N, K, act, T, e, act_out_K);
     PfArgs a;
     memset(&a, 0, sizeof(a));
     a.W = at<const u32x4_t>(x->arena, w_off);
@@ -478,12 +581,9 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
         a.gy = (a.NT + 8 * best_tw - 1) / (8 * best_tw);
         const int groups = a.gx * 8 * ((a.gy + 7) / 8);
         Epi e2 = e;
-        if (ssq_in) {       // the rows' RMS scales once per pass, not once per workgroup
-            float *scale = at<float>(x->scr, x->s_pscale);
-            hipLaunchKernelGGL(pf_rms_scale_kernel, dim3(nb), dim3(512), 0, x->stream, e.ssq_in, a.ssq_in_blk, e.nt_in, T, e.inv_d,
-                               e.eps, scale);
-            KGCHK(check_launch(x, "prompt row scales"));
-            e2.scale_in = scale;
+        if (ssq_in) {
+            KGCHK(launch_rms_scale(x, e.ssq_in, T));
+            e2.scale_in = at<float>(x->scr, x->s_pscale);
         }
         ProfScope ps(x, 3, 2.0 * T * (double)N * K);
         if (plan == PF_PLAN_TW1_RB8) hipLaunchKernelGGL(gemm_prefill2_kernel_tw1_rb8, dim3(groups), dim3(768), 0, x->stream, a, e2);
@@ -1072,8 +1172,10 @@ int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int3
     KGCHK(kg_reset(x));
     x->acct_phase = 3;
     float inv_t = p->mode == 1 ? 1.f / p->temperature : 1.f;
-    if (x->pf_rows > 0) {
-        // bf16 weights: the prompt goes through the MFMA projections, pf_rows rows per pass
+    if (x->pf_rows > 0 && !(x->kvt == 2 && n <= KG_ROWS)) {
+        // bf16 weights: the prompt goes through the MFMA projections, pf_rows rows per pass (a prompt that is one
+        // forward of the decode kernels runs as that with the half-precision cache: one launch per projection and
+        // no row sums in between)
         HIPCHK(x, hipMemcpyAsync(x->scr + x->s_ptok, prompt, (size_t)n * 4, hipMemcpyHostToDevice, x->stream));
         for (int pos0 = 0; pos0 < n; pos0 += x->pf_rows) {
             const int T = std::min(x->pf_rows, n - pos0);

@@ -1089,6 +1089,248 @@ __global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw4(PfArgs a, Epi e)
 __global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw1_rb8(PfArgs a, Epi e) { gemm_prefill2_body<1, 8, true, 8>(a, e); }
 
 // ---------------------------------------------------------------------------------------------
+// Projection for short prompt passes (half-precision cache, 9 rows and more): Y[T][N] = X[T][K] . W^T where
+// reading the weights is still what bounds the launch (at the 7B shape up to about 128 rows), so the kernel is
+// built as a weight stream.  A workgroup of 8 waves owns up to NTW weight tiles x R pairs of 8-row blocks (16 R
+// rows); its waves take the k-steps of the row tiles in turn, in the order the tiles are stored, and each wave
+// multiplies its k-steps into accumulators of its own: weights and activations go from memory straight into
+// registers in operand order (the activations in the pair layout of pf_act_ptr, a 16-row operand = one
+// contiguous KB), with no LDS and no barrier until the waves' sums are added at the end.  Per k-step a wave
+// reads NTW + 2 R KB for 2 NTW R multiplications: with both sides this small the L1 (64 bytes a clock) is kept
+// below the memory's share of a compute unit (about 12 bytes a clock) times that ratio.
+//   Loads run D k-steps ahead (a ring of D register sets).  Where the accumulators leave no room for two sets
+// (D = 1) the weights are double-buffered and an activation operand is fetched again, for the next step, as
+// soon as its multiplications are issued.
+//   Projections with few weight tiles (o_proj, down_proj) are cut along k into `slices` (1, 2, 4 or 8; a
+// workgroup's slice is fixed by its XCD, so an XCD's L2 holds one slice of the activations) and write partial
+// sums; pf_reduce_rows_kernel adds them, in slice order, with what follows the projection.
+struct PfStreamArgs {
+    const u32x4_t *W;       // weight tiles [NT][tile_pos(ks)][64]
+    int KS, NT;
+    const u32x4_t *act;     // activations, pair layout; pair p at act + p * act_pair16
+    size_t act_pair16;      // 16-byte units per pair of 8-row blocks
+    int T;
+    int slices, groups, gx; // k slices, groups of weight tiles, groups of 16 R rows
+    float *part;            // partial sums [slice][T][N] for pf_reduce_rows_kernel; null: the epilogue (one slice)
+    size_t act_out_blk;     // bytes per 8-row block of the output activation (SwiGLU)
+};
+
+// k-step held by the tile stored at position p of a row tile: the inverse of tile_pos
+__host__ __device__ __forceinline__ int kstep_at_pos(int p, int KS)
+{
+    const int q = KS >> 3, E = KS - 8 * q;
+    if (p < E) return ((8 * (p + 1) + E - 1) / E - 1) * q + p;      // first tile of the (p + 1)-th long range
+    const int w = (p - E) & 7, j = (p - E) >> 3;
+    return w * q + (((w + 1) * E) >> 3) + j;                        // a long range's first tile lies in front: skipped here
+}
+
+// Waves of a workgroup: 8, of 256 registers each, while those hold the accumulators and the operands of a step
+// and a half; else 4 waves of 512 registers (gate+up of the 7B shape at 96 .. 128 rows: one round of 230
+// workgroups of 6 tiles instead of two rounds of workgroups of 3).
+__host__ __device__ constexpr int pf_stream_waves(int NTW, int R) { return NTW <= (R <= 2 ? 8 : R == 3 ? 7 : R == 4 ? 6 : 4) ? 8 : 4; }
+// register sets of the ring: what a wave's registers leave beside the accumulators and the addresses
+__host__ __device__ constexpr int pf_stream_depth(int NTW, int R)
+{
+    const int free = (pf_stream_waves(NTW, R) == 8 ? 204 : 440) - 4 * NTW * R, set = 4 * (NTW + 2 * R), d = free / set;
+    return d < 2 ? 1 : d > 8 ? 8 : d;
+}
+
+template <int NTW, int R>
+__global__ __launch_bounds__(64 * pf_stream_waves(NTW, R), pf_stream_waves(NTW, R) / 4) void gemm_stream_kernel(const PfStreamArgs a, const Epi e)
+{
+    constexpr int D = pf_stream_depth(NTW, R), NW = pf_stream_waves(NTW, R);
+    constexpr int NACC = NTW * R, CH = NACC < 8 ? NACC : 8;         // accumulator tiles added per round at the end
+    __shared__ f32x4_t red[NW][CH][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int slice = xcd % a.slices, per = 8 / a.slices;
+    const int rg = j % a.gx, tg = (j / a.gx) * per + xcd / a.slices;
+    if (tg >= a.groups) return;
+    // the NT tiles are shared out evenly: groups differ by at most one tile, none has more than NTW
+    const int rt0 = (int)((long long)tg * a.NT / a.groups), ntw = (int)((long long)(tg + 1) * a.NT / a.groups) - rt0;
+    const int KS = a.KS;
+    const int p_lo = (int)((long long)slice * KS / a.slices), p_hi = (int)((long long)(slice + 1) * KS / a.slices);
+    const int p0 = p_lo + wave;
+    const int n = p0 < p_hi ? (p_hi - p0 + NW - 1) / NW : 0;      // the wave's k-steps: positions p0, p0 + NW, ..
+    const int n_pairs = (a.T + 15) >> 4;
+    const u32x4_t *wsrc[NTW], *bsrc[R];
+#pragma unroll
+    for (int t = 0; t < NTW; t++) wsrc[t] = a.W + (size_t)(rt0 + min(t, ntw - 1)) * KS * 64 + lane;
+#pragma unroll
+    for (int r = 0; r < R; r++) bsrc[r] = a.act + (size_t)min(rg * R + r, n_pairs - 1) * a.act_pair16 + lane;
+    f32x4_t acc[NTW][R];
+#pragma unroll
+    for (int t = 0; t < NTW; t++)
+#pragma unroll
+        for (int r = 0; r < R; r++) acc[t][r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto mma = [](const u32x4_t &w, const u32x4_t &b, f32x4_t &c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    };
+    if (D >= 2) {
+        u32x4_t av[D][NTW], bv[D][R][2];
+        auto load = [&](int s, int i) {
+            const int p = p0 + NW * i, ks = kstep_at_pos(p, KS);
+#pragma unroll
+            for (int t = 0; t < NTW; t++) av[s][t] = __builtin_nontemporal_load(wsrc[t] + p * 64);
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                bv[s][r][0] = bsrc[r][ks * 128];
+                bv[s][r][1] = bsrc[r][ks * 128 + 64];
+            }
+        };
+        auto mul = [&](int s) {
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+#pragma unroll
+                for (int r = 0; r < R; r++)
+#pragma unroll
+                    for (int t = 0; t < NTW; t++) mma(av[s][t], bv[s][r][h], acc[t][r]);
+        };
+#pragma unroll
+        for (int s = 0; s < D; s++)
+            if (s < n) load(s, s);
+        int i = 0;
+        for (; i + 2 * D <= n; i += D) {
+#pragma unroll
+            for (int s = 0; s < D; s++) {
+                mul(s);
+                load(s, i + s + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // fewer than 2 D steps are left, the first D of them loaded or on their way
+#pragma unroll
+        for (int s = 0; s < D; s++)
+            if (i + s < n) {
+                mul(s);
+                if (i + s + D < n) load(s, i + s + D);
+            }
+        i += D;
+#pragma unroll
+        for (int s = 0; s < D; s++)
+            if (i + s < n) mul(s);
+    } else if (n > 0) {
+        u32x4_t av[2][NTW], bv[R][2];
+        auto load_w = [&](int s, int i) {
+#pragma unroll
+            for (int t = 0; t < NTW; t++) av[s][t] = __builtin_nontemporal_load(wsrc[t] + (p0 + NW * i) * 64);
+        };
+        // step i on weight set s; the weights of step i + 1 are requested before, its activations under the multiplications
+        auto step = [&](int s, int i) {
+            const int in = min(i + 1, n - 1), ks = kstep_at_pos(p0 + NW * in, KS) * 128;     // (the last step fetches itself again)
+            load_w(s ^ 1, in);
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int t = 0; t < NTW; t++) mma(av[s][t], bv[r][h], acc[t][r]);
+                bv[r][0] = bsrc[r][ks];
+                bv[r][1] = bsrc[r][ks + 64];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        load_w(0, 0);
+        const int ks = kstep_at_pos(p0, KS) * 128;
+#pragma unroll
+        for (int r = 0; r < R; r++) { bv[r][0] = bsrc[r][ks]; bv[r][1] = bsrc[r][ks + 64]; }
+        int i = 0;
+        for (; i + 2 <= n; i += 2) { step(0, i); step(1, i + 1); }
+        if (i < n) step(0, i);
+    }
+    // Add the waves' sums, CH accumulator tiles at a time (wave w finishes tiles c + w, c + w + NW, ..), in wave order.
+    // Lane (column c, group g4) then holds weight rows 4 g4 .. 4 g4 + 3 of a tile for row c % 8 of its block.
+    const int col = lane & 15, g4 = lane >> 4;
+#pragma unroll
+    for (int c = 0; c < NACC; c += CH) {
+        if (c) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < CH; u++)
+            if (c + u < NACC) red[wave][u][lane] = acc[(c + u) / R][(c + u) % R];
+        __syncthreads();
+        for (int u = wave; u < CH; u += NW) {
+            const int at = c + u, ta = at / R, r = at % R;
+            if (at >= NACC || ta >= ntw) continue;
+            f32x4_t y = red[0][u][lane];
+#pragma unroll
+            for (int w = 1; w < NW; w++) y += red[w][u][lane];
+            const int rt = rt0 + ta, n0 = rt * 16 + 4 * g4, row = (rg * R + r) * 16 + col;
+            if (row >= a.T) continue;
+            if (a.part) {
+                *(float4 *)(a.part + ((size_t)slice * a.T + row) * e.N + n0) = make_float4(y[0], y[1], y[2], y[3]);
+                continue;
+            }
+            const float sc = e.scale_in ? e.scale_in[row] : 1.f;
+            if (e.kind == EPI_PLAIN) {
+                *(float4 *)(e.out + (size_t)row * e.N + n0) = make_float4(y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
+            } else {                          // EPI_SWIGLU: rows (2i, 2i+1) = (gate, up) of feature rt*8 + i
+                uint16_t hi[2], lo[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    const float gt = y[2 * i] * sc, up = y[2 * i + 1] * sc;
+                    const float av2 = rounded(gt / (1.f + __expf(-gt)) * up);
+                    hi[i] = f2bf(av2);
+                    lo[i] = f2bf(av2 - bf2f(hi[i]));
+                }
+                int lo_off;
+                uint16_t *pa = pf_act_ptr(e.act_out, a.act_out_blk, row >> 3, row & 7, rt * 8 + 2 * g4, 1, lo_off);
+                *(uint32_t *)pa = hi[0] | ((uint32_t)hi[1] << 16);
+                *(uint32_t *)(pa + lo_off) = lo[0] | ((uint32_t)lo[1] << 16);
+            }
+        }
+    }
+}
+
+// What follows a projection cut along k: x = res + the slices' partial sums (slice order), xout = x, the next
+// projection's input x * gain (pair layout) and the row's RMSNorm scale.  One workgroup per row.
+__global__ __launch_bounds__(1024) void pf_reduce_rows_kernel(const float *part, int slices, int T, int d, const float *res, float *xout,
+                                                             const float *gain, void *act_out, size_t act_blk, float inv_d, float eps,
+                                                             float *scale)
+{
+    __shared__ float red[16];
+    const int row = blockIdx.x, t = threadIdx.x;
+    float ss = 0.f;
+    for (int k = 4 * t; k < d; k += 4096) {
+        float4 v = *(const float4 *)(res + (size_t)row * d + k);
+        float4 p[8];
+#pragma unroll
+        for (int s = 0; s < 8; s++)
+            if (s < slices) p[s] = *(const float4 *)(part + ((size_t)s * T + row) * d + k);
+        float4 y = p[0];
+#pragma unroll
+        for (int s = 1; s < 8; s++)
+            if (s < slices) { y.x += p[s].x; y.y += p[s].y; y.z += p[s].z; y.w += p[s].w; }
+        v.x += y.x; v.y += y.y; v.z += y.z; v.w += y.w;
+        *(float4 *)(xout + (size_t)row * d + k) = v;
+        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        if (act_out) {
+            const float4 g = gain ? *(const float4 *)(gain + k) : make_float4(1.f, 1.f, 1.f, 1.f);
+            const float q[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+            uint16_t hi[4], lo[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float x = rounded(q[i]);
+                hi[i] = f2bf(x);
+                lo[i] = f2bf(x - bf2f(hi[i]));
+            }
+            int lo_off;
+            uint16_t *pa = pf_act_ptr(act_out, act_blk, row >> 3, row & 7, k, 1, lo_off);
+            *(uint2 *)pa = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+            *(uint2 *)(pa + lo_off) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+        }
+    }
+    for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+    if ((t & 63) == 0) red[t >> 6] = ss;
+    __syncthreads();
+    if (t == 0) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; w++) s += red[w];
+        scale[row] = rsqrtf(fmaf(s, inv_d, eps));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Rows -> activation for the first projection of a stack: x[m] = E[tok[m]] (emb != null) or the
 // given fp32 rows; writes xout (optional), act = x * gain (hi/lo), ssq[tile][m].  One block per
 // 16 features.
