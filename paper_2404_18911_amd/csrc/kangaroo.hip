@@ -307,6 +307,17 @@ void prof_collect(kg_ctx *x)   // call after prof_flush and a synchronisation of
 
 // ---- kernel launch helpers ---------------------------------------------------------------------
 
+void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &e, hipStream_t s)
+{
+    const dim3 grid(N / 16), block(256);
+    if ((((uintptr_t)W | (uintptr_t)act) & 15) == 0) {
+        if (e.M <= 1) hipLaunchKernelGGL((gemv_f32_kernel<1, true>), grid, block, 0, s, W, K, act, e);
+        else if (e.M <= 2) hipLaunchKernelGGL((gemv_f32_kernel<2, true>), grid, block, 0, s, W, K, act, e);
+        else if (e.M <= 4) hipLaunchKernelGGL((gemv_f32_kernel<4, true>), grid, block, 0, s, W, K, act, e);
+        else hipLaunchKernelGGL((gemv_f32_kernel<8, true>), grid, block, 0, s, W, K, act, e);
+    } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e);
+}
+
 int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Epi &e)
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
@@ -317,8 +328,7 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
                            at<const u32x4_t>(x->arena, w_off), (K + 31) / 32, e.M, (const u32x4_t *)act, e.ssq_in, e.nt_in,
                            e.N, e.kind == EPI_RESID ? e.res : nullptr, e.gain, e);
     else
-        hipLaunchKernelGGL(gemv_f32_kernel, dim3(N / 16), dim3(256), 0, x->stream, at<const float>(x->arena, w_off),
-                           K, (const float *)act, e);
+        launch_gemv_f32(at<const float>(x->arena, w_off), N, K, (const float *)act, e, x->stream);
     return check_launch(x, "gemv");
 }
 
@@ -2118,7 +2128,7 @@ static int op_linear_launch(int dtype, const void *packed, int N, int K, const f
     } else {
         hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(K / 16), dim3(128), 0, s, (const void *)nullptr, tk, (const int *)nullptr, xd, K, M,
                            (const float *)nullptr, (float *)nullptr, work, (float *)nullptr);
-        hipLaunchKernelGGL(gemv_f32_kernel, dim3(N / 16), dim3(256), 0, s, (const float *)packed, K, (const float *)work, e);
+        launch_gemv_f32((const float *)packed, N, K, (const float *)work, e, s);
     }
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }

@@ -463,35 +463,76 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_valu_kernel(cons
     }
 }
 
-// Projection, fp32 weights (row-major [N][K]) and fp32 activations [8][K]: 16 threads per row.
-// Only the small fp32 correctness configuration uses it.
+// Projection, fp32 weights (row-major [N][K]) and fp32 activations [8][K], K a multiple of 4: 16 threads per weight
+// row, each taking every 16th group of 4 consecutive k.  The models this serves are small (the float32
+// configuration: K of 256 and 688, 16 .. 86 workgroups), so a launch is a chain of memory latencies: the
+// groups of a chunk, the row sums of the scale and the epilogue's operands are requested together before
+// any is used (4.1 us per launch at the float32 configuration; 15.5 us when a thread took one k at a time).
+// MR >= rows (1, 2, 4 or 8); a row's sum runs over the same k in the same order in every instantiation.
+// VEC: weights and activations are 16-byte aligned (a caller of the stand-alone product may pass others).
+template <int MR, bool VEC>
 __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__ W, int K,
                                                        const float *__restrict__ act, Epi e)
 {
+    constexpr int U = MR <= 4 ? 4 : 2;      // groups of 4 k per thread in flight
     __shared__ float yt[16][KG_ROWS];
     __shared__ float sq[16][KG_ROWS];
     __shared__ float sc[KG_ROWS];
     const int rt = blockIdx.x;
     const int row = threadIdx.x >> 4, sub = threadIdx.x & 15;
     const float *wr = W + (size_t)(rt * 16 + row) * K;
-    float acc[KG_ROWS];
+    const int G = K >> 2;
+    auto ld = [](const float *p) {
+        if (VEC) return *(const float4 *)p;
+        return make_float4(p[0], p[1], p[2], p[3]);
+    };
+    float4 w[U], x[U][MR];
+    auto load = [&](int g0) {
 #pragma unroll
-    for (int m = 0; m < KG_ROWS; m++) acc[m] = 0.f;
-    for (int k = sub; k < K; k += 16) {
-        float w = wr[k];
+        for (int u = 0; u < U; u++) {
+            const int g = g0 + 16 * u;
+            w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int m = 0; m < KG_ROWS; m++)
-            if (m < e.M) acc[m] = fmaf(w, act[(size_t)m * K + k], acc[m]);
+            for (int m = 0; m < MR; m++) x[u][m] = w[u];
+            if (g < G) {
+                w[u] = ld(wr + 4 * g);
+#pragma unroll
+                for (int m = 0; m < MR; m++)
+                    if (m < e.M) x[u][m] = ld(act + (size_t)m * K + 4 * g);
+            }
+        }
+    };
+    load(sub);
+    float resv = 0.f, gainv = 1.f;          // epilogue operands of thread (row, m)
+    if (e.kind == EPI_RESID && threadIdx.x < 128 && (int)(threadIdx.x & 7) < e.M) {
+        const int n = rt * 16 + (threadIdx.x >> 3);
+        resv = e.res[(size_t)(threadIdx.x & 7) * e.N + n];
+        if (e.gain) gainv = e.gain[n];
     }
     compute_scale(e, sc);
+    float acc[MR];
 #pragma unroll
-    for (int m = 0; m < KG_ROWS; m++) {
+    for (int m = 0; m < MR; m++) acc[m] = 0.f;
+    for (int g0 = sub; g0 < G; g0 += 16 * U) {
+        if (g0 != sub) load(g0);
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int m = 0; m < MR; m++) {
+                acc[m] = fmaf(w[u].x, x[u][m].x, acc[m]);
+                acc[m] = fmaf(w[u].y, x[u][m].y, acc[m]);
+                acc[m] = fmaf(w[u].z, x[u][m].z, acc[m]);
+                acc[m] = fmaf(w[u].w, x[u][m].w, acc[m]);
+            }
+    }
+#pragma unroll
+    for (int m = 0; m < MR; m++) {
         float v = acc[m];
         for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o);
         if (sub == 0) yt[row][m] = v;
     }
     __syncthreads();
-    epilogue<false>(e, rt, yt, sc, sq);
+    epilogue<false>(e, rt, yt, sc, sq, resv, gainv, true);
 }
 
 // ---------------------------------------------------------------------------------------------
