@@ -431,10 +431,8 @@ def run_micro(args):
             y = torch.empty(M, N, dtype=torch.float32, device=dev)
             t = timed(lambda i=0: L.kg_op_linear(1, packed.data_ptr() + (i % n_copies) * per, N, K, x.data_ptr(), M, y.data_ptr(),
                                                  wk.data_ptr(), st.cuda_stream), 64)
-            # kg_op_linear = clear + pack of the rows + the projection: subtract what the two small launches cost alone
-            res[f"linear_M{M}_us_with_row_packing"] = 1e6 * t
-        # the projection alone at one row, matrix units against vector ALUs (same tiles, same launch shape):
-        # kg_op_linear's row packing is a fixed cost of its own, measured by packing without multiplying
+            res[f"linear_M{M}_us"] = 1e6 * t
+        # the projection at one row on the vector ALUs (same tiles, same launch shape)
         x1 = torch.randn(1, K, dtype=torch.float32, device=dev)
         y1 = torch.empty(1, N, dtype=torch.float32, device=dev)
         t_valu = timed(lambda i=0: L.kg_op_linear_valu(packed.data_ptr() + (i % n_copies) * per, N, K, x1.data_ptr(), y1.data_ptr(),

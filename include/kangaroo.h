@@ -314,7 +314,8 @@ int kg_op_gemm_f32(const float *A_dev, long sam, long sak, const float *B_dev, l
  *   kg_op_packed_bytes: bytes of the tiled form of a [N][K] matrix (N % 16 == 0, K % 8 == 0).
  *   kg_op_pack:   re-tile a row-major dev matrix (dtype 0 f32 / 1 bf16) into packed_dev.
  *   kg_op_linear: x_dev float[M][K], y_dev float[M][N]; work_dev >= kg_op_work_bytes(K) bytes of
- *                 device scratch; M <= KG_MAX_ROWS.  Launches on `hip_stream`, does not synchronise.
+ *                 device scratch (must not be NULL; the present kernels read x_dev directly and leave it
+ *                 alone); M <= KG_MAX_ROWS.  Launches on `hip_stream`, does not synchronise.
  */
 size_t kg_op_packed_bytes(int dtype, int N, int K);
 /* Position (0 .. KS-1) of k-step ks among the KS = ceil(K / 32) weight tiles of one 16-row tile in
@@ -340,14 +341,11 @@ int kg_op_linear_valu(const void *packed_dev, int N, int K, const float *x_dev, 
 /*
  * kg_op_linear for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same product, same kernels
- * and bit-identical results; the activation staging area is a static device array inside the library
- * (KG_OP_STATIC_MAX_K * KG_MAX_ROWS * 4 bytes = 512 KB per GPU, held until the process ends) instead of
- * work_dev.  Allocates nothing (no hipMalloc / hipFree, no memset node: the area is cleared by a
- * kernel), launches on `hip_stream`, does not synchronise.  The device address of the array is looked
- * up on the first call on each device (the current device must be the one the pointers live on).
- * Errors: KG_EINVAL as kg_op_linear, or a device ordinal >= KG_OP_STATIC_MAX_DEVICES; KG_ENOSPC for
- * K > KG_OP_STATIC_MAX_K; KG_EHIP.  Every call on one GPU shares that GPU's array: calls that overlap
- * on one GPU (different streams or threads) race; calls ordered on one stream do not.
+ * and bit-identical results.  Allocates nothing (no hipMalloc / hipFree, no memset node), holds no device
+ * memory, launches one kernel on `hip_stream`, does not synchronise; calls on several streams or threads
+ * do not share anything.
+ * Errors: KG_EINVAL as kg_op_linear, or a current device ordinal >= KG_OP_STATIC_MAX_DEVICES; KG_ENOSPC for
+ * K > KG_OP_STATIC_MAX_K; KG_EHIP.
  */
 #define KG_OP_STATIC_MAX_K 16384
 #define KG_OP_STATIC_MAX_DEVICES 64

@@ -10,7 +10,6 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <vector>
 
 #include "kangaroo.h"
@@ -2105,30 +2104,21 @@ int kg_op_pack(int dtype, const void *src, int N, int K, void *packed, void *hip
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
 
-// Both entry points of the stand-alone projection: the activation staging area `work` comes from the
-// caller (cleared with a memset) or is the library's static array (cleared by a fill kernel, which a
-// stream capture can record).
-static int op_linear_launch(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, void *work,
-                            hipStream_t s, bool clear_by_kernel)
+// Both entry points of the stand-alone projection: one launch that reads the fp32 rows as they are (16-byte
+// loads where the rows are aligned for them), so that neither needs a staging area.
+static int op_linear_launch(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, hipStream_t s)
 {
-    Tok8 tk;
-    memset(&tk, 0, sizeof(tk));
-    Epi e;
-    memset(&e, 0, sizeof(e));
-    e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;
     if (dtype == 1) {
-        if (clear_by_kernel) {
-            const unsigned n16 = (unsigned)(act_bytes(K) / 16);
-            hipLaunchKernelGGL(fill_zero_kernel, dim3((n16 + 255) / 256), dim3(256), 0, s, (u32x4_t *)work, n16);
-        } else if (hipMemsetAsync(work, 0, act_bytes(K), s) != hipSuccess) return KG_EHIP;
-        hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(K / 16), dim3(128), 0, s, (const void *)nullptr, tk, (const int *)nullptr, xd, K, M,
-                           (const float *)nullptr, (float *)nullptr, work, (float *)nullptr);
-        hipLaunchKernelGGL(gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, s, (const u32x4_t *)packed, (K + 31) / 32,
-                           e.M, (const u32x4_t *)work, e.ssq_in, e.nt_in, e.N, (const float *)nullptr, e.gain, e);
+        const dim3 grid(N / 16), block(64 * GEMV_WAVES);
+        const u32x4_t *W = (const u32x4_t *)packed;
+        const int KS = (K + 31) / 32;
+        if (((uintptr_t)xd & 15) == 0) hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
+        else hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS_UNALIGNED>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
     } else {
-        hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(K / 16), dim3(128), 0, s, (const void *)nullptr, tk, (const int *)nullptr, xd, K, M,
-                           (const float *)nullptr, (float *)nullptr, work, (float *)nullptr);
-        launch_gemv_f32((const float *)packed, N, K, (const float *)work, e, s);
+        Epi e;
+        memset(&e, 0, sizeof(e));
+        e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;
+        launch_gemv_f32((const float *)packed, N, K, xd, e, s);
     }
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
@@ -2143,7 +2133,7 @@ int kg_op_linear(int dtype, const void *packed, int N, int K, const float *xd, i
                  void *hip_stream)
 {
     if (!op_linear_args_ok(dtype, packed, N, K, xd, M, yd) || !work) return KG_EINVAL;
-    return op_linear_launch(dtype, packed, N, K, xd, M, yd, work, (hipStream_t)hip_stream, false);
+    return op_linear_launch(dtype, packed, N, K, xd, M, yd, (hipStream_t)hip_stream);
 }
 
 int kg_op_linear_valu(const void *packed, int N, int K, const float *xd, float *yd, void *hip_stream)
@@ -2154,13 +2144,6 @@ int kg_op_linear_valu(const void *packed, int N, int K, const float *xd, float *
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
 
-// The staging area of kg_op_linear_static: one array per GPU, held until the process ends.  Host code
-// never uses the array's name as an address: the device address is asked for once per device.
-static __device__ __align__(256) unsigned char scratch[KG_OP_STATIC_MAX_K * KG_ROWS * 4];
-static_assert(sizeof(scratch) >= (size_t)KG_OP_STATIC_MAX_K / 32 * 1024, "bf16 staging fits");
-static std::mutex static_scratch_lock;
-static void *static_scratch_ptr[KG_OP_STATIC_MAX_DEVICES];      // per device, NULL until first use
-
 int kg_op_linear_static(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, void *hip_stream)
 {
     if (!op_linear_args_ok(dtype, packed, N, K, xd, M, yd)) return KG_EINVAL;
@@ -2168,17 +2151,7 @@ int kg_op_linear_static(int dtype, const void *packed, int N, int K, const float
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return KG_EHIP;
     if (dev < 0 || dev >= KG_OP_STATIC_MAX_DEVICES) return KG_EINVAL;
-    void *ptr = nullptr;
-    {
-        std::lock_guard<std::mutex> g(static_scratch_lock);
-        if (!static_scratch_ptr[dev]) {
-            void *q = nullptr;
-            if (hipGetSymbolAddress(&q, HIP_SYMBOL(scratch)) != hipSuccess || !q) return KG_EHIP;
-            static_scratch_ptr[dev] = q;
-        }
-        ptr = static_scratch_ptr[dev];
-    }
-    return op_linear_launch(dtype, packed, N, K, xd, M, yd, ptr, (hipStream_t)hip_stream, true);
+    return op_linear_launch(dtype, packed, N, K, xd, M, yd, (hipStream_t)hip_stream);
 }
 
 int kg_op_philox_words(uint64_t seed, uint32_t pos0, uint32_t purpose, int n, uint32_t *out_dev, void *hip_stream)

@@ -115,7 +115,6 @@ __device__ __forceinline__ void scale_fetch(const float *ssq_in, int M, int nt_i
         r.v[j] = (ssq_in && wave < M && i < nt_in) ? ssq_in[(size_t)i * KG_ROWS + wave] : 0.f;
     }
 }
-__device__ __forceinline__ void scale_fetch(const Epi &e, ScaleRegs &r) { scale_fetch(e.ssq_in, e.M, e.nt_in, r); }
 __device__ __forceinline__ void scale_finish(const Epi &e, const ScaleRegs &r, float *sc)
 {
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -280,33 +279,77 @@ __host__ __device__ __forceinline__ int tile_pos(int ks, int KS) { return tile_p
 // streams its 1 KB weight tiles with 16-byte non-temporal loads and issues one MFMA per tile.
 // W: tiles [rt][tile_pos(ks)][64 lanes][8 bf16]; act: B-operand tiles [ks][64 lanes][8 bf16].
 
-template <int U>
-__device__ __forceinline__ void gemv_steps(const u32x4_t *&wp, const u32x4_t *&bp, bool bact, f32x4_t &acc)
-{
-    const u32x4_t zero = {0u, 0u, 0u, 0u};
-    u32x4_t a[U], b[U];
+// B operand of one k-step as a lane loads it, and the 16 bytes the multiplication takes.
+// FROM_ACT: activation tiles written by the producer (hi / lo parts, see store_act).
+// FROM_ROWS, FROM_ROWS_UNALIGNED: plain fp32 rows x[M][K] (the stand-alone product), split by the lanes
+// themselves into the very parts store_act would have stored.  Of the 8 consecutive k of a row that lanes j (hi
+// part) and j + 8 (lo part) share, each lane reads four, splits them, keeps the part it stands for and passes
+// the other one on: as many bytes through the L1 as the activation tiles take, and 20 vector operations a tile
+// (4096 x 4096, one row: 11.1 us a call with two launches that clear and fill activation tiles, 8.0 without; 13840 x
+// 5136, 8 rows: 35.9 -> 32.3; with every lane reading and splitting all 8 k it was 37.9 us there).
+enum { FROM_ACT = 0, FROM_ROWS = 1, FROM_ROWS_UNALIGNED = 2 };
+template <int SRC> struct BRaw { float v[4]; };
+template <> struct BRaw<FROM_ACT> { u32x4_t v; };
+
+template <int SRC> struct BSource {
+    const u32x4_t *tiles;       // FROM_ACT: this lane's slot of k-step 0
+    const float *row;           // else this lane's row at its four k of k-step 0
+    int k, K;                   // first of the pair's 8 k, features
+    bool on, lo;                // the lane's column stands for a live row; for the lo part of it
+    __device__ __forceinline__ BSource(const void *act, int M, int lane, int K_)
+    {
+        on = (lane & 7) < M;
+        lo = (lane & 8) != 0;
+        k = (lane >> 4) * 8;
+        K = K_;
+        tiles = (const u32x4_t *)act + b_slot(lane);
+        row = (const float *)act + (size_t)(lane & 7) * K_ + k + (lo ? 4 : 0);
+    }
+    __device__ __forceinline__ BRaw<SRC> load(int ks) const
+    {
+        BRaw<SRC> r;
+        if constexpr (SRC == FROM_ACT) {
+            r.v = on ? tiles[ks * 64] : u32x4_t{0u, 0u, 0u, 0u};
+        } else {
+            const bool in = on && k + 32 * ks + 8 <= K;             // (K is a multiple of 16: the last k-step may be half empty)
+            const float *p = row + 32 * ks;
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (in) a = SRC == FROM_ROWS ? *(const float4 *)p : make_float4(p[0], p[1], p[2], p[3]);
+            r.v[0] = a.x; r.v[1] = a.y; r.v[2] = a.z; r.v[3] = a.w;
+        }
+        return r;
+    }
+    // all 64 lanes call it
+    __device__ __forceinline__ bf16x8_t operand(const BRaw<SRC> &r) const
+    {
+        if constexpr (SRC == FROM_ACT) {
+            return __builtin_bit_cast(bf16x8_t, r.v);
+        } else {
+            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+            uint32_t h[2], l[2], o[2];
 #pragma unroll
-    for (int u = 0; u < U; u++) a[u] = __builtin_nontemporal_load(wp + u * 512);
-#pragma unroll
-    for (int u = 0; u < U; u++) b[u] = bact ? bp[u * 64] : zero;
-#pragma unroll
-    for (int u = 0; u < U; u++)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u]),
-                                                      __builtin_bit_cast(bf16x8_t, b[u]), acc, 0, 0, 0);
-    wp += U * 512;
-    bp += U * 64;
-}
+            for (int i = 0; i < 2; i++) {                           // nearest even, as f2bf
+                bf16x2_t hi, lw;
+                hi[0] = (__bf16)r.v[2 * i]; hi[1] = (__bf16)r.v[2 * i + 1];
+                lw[0] = (__bf16)(r.v[2 * i] - (float)hi[0]); lw[1] = (__bf16)(r.v[2 * i + 1] - (float)hi[1]);
+                h[i] = __builtin_bit_cast(uint32_t, hi);
+                l[i] = __builtin_bit_cast(uint32_t, lw);
+                o[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(lo ? h[i] : l[i]), 0x128, 0xF, 0xF, false);    // lane ^ 8 (row_ror:8)
+            }
+            u32x4_t v;
+            v[0] = lo ? o[0] : h[0]; v[1] = lo ? o[1] : h[1];
+            v[2] = lo ? l[0] : o[0]; v[3] = lo ? l[1] : o[1];
+            return __builtin_bit_cast(bf16x8_t, v);
+        }
+    }
+};
 
 #define GEMV_WAVES 8
 
-// Everything a wave needs before its first weight load is a leading scalar argument (a copy of the
-// fields of e named alike): those arrive preloaded in SGPRs, a field of the by-value struct costs a
-// scalar load from the argument block at the start of every launch.
-// 14 dwords fit: W, KS, M, act, ssq_in, nt_in, N, res (null unless the epilogue adds a residual), gain.
-__global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32x4_t *__restrict__ W, int KS, int M,
-                                                                   const u32x4_t *__restrict__ act,
-                                                                   const float *ssq_in, int nt_in, int N,
-                                                                   const float *res, const float *gain, Epi e)
+template <int SRC>
+__device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, int KS, int M, const void *__restrict__ act,
+                                               const float *ssq_in, int nt_in, int N, const float *res, const float *gain,
+                                               int K, const Epi &e)
 {
     __shared__ float part[GEMV_WAVES][16][KG_ROWS];
     __shared__ float yt[16][KG_ROWS];
@@ -326,8 +369,8 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
     const bool long_range = ks1 - ks0 > q;
     const u32x4_t *wbase = W + (size_t)rt * KS * 64 + lane;
     const u32x4_t *wp = wbase + (size_t)(n_long + wave) * 64;
-    const u32x4_t *bp = act + (size_t)(ks0 + (long_range ? 1 : 0)) * 64 + b_slot(lane);
-    const bool bact = (lane & 7) < M;
+    const BSource<SRC> bsrc(act, M, lane, K);
+    int ks = ks0 + (long_range ? 1 : 0);
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     ScaleRegs sr;
     scale_fetch(ssq_in, M, nt_in, sr);
@@ -337,45 +380,49 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
         resv = res[(size_t)(threadIdx.x & 7) * N + nn];
         if (gain) gainv = gain[nn];
     }
+    auto mma = [&](const u32x4_t &w, const BRaw<SRC> &b) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), bsrc.operand(b), acc, 0, 0, 0);
+    };
+    // chunks of U tiles: all loads of a chunk are issued before its multiplications
+    auto load = [&](auto &A, auto &Bv, int U) {
+#pragma unroll
+        for (int u = 0; u < U; u++) A[u] = __builtin_nontemporal_load(wp + u * 512);
+#pragma unroll
+        for (int u = 0; u < U; u++) Bv[u] = bsrc.load(ks + u);
+        wp += U * 512;
+        ks += U;
+    };
+    auto mul = [&](const auto &A, const auto &Bv, int U) {
+#pragma unroll
+        for (int u = 0; u < U; u++) mma(A[u], Bv[u]);
+    };
     int n = q;
     {
         // chunks of 4 tiles, double-buffered: the loads of chunk i+1 are in flight while chunk i is
         // multiplied, so a wave never drains its memory pipe between chunks
-        const u32x4_t zero = {0u, 0u, 0u, 0u};
-        u32x4_t a0[4], b0[4], a1[4], b1[4];
-        u32x4_t ax = zero, bx = zero;                      // first tile of a long range (k-step ks0)
+        u32x4_t a0[4], a1[4];
+        BRaw<SRC> b0[4], b1[4];
+        u32x4_t ax = {0u, 0u, 0u, 0u};                     // first tile of a long range (k-step ks0)
+        BRaw<SRC> bx;
         if (long_range) {
             ax = __builtin_nontemporal_load(wbase + (size_t)(ks0 - wave * q) * 64);
-            if (bact) bx = act[(size_t)ks0 * 64 + b_slot(lane)];
+            bx = bsrc.load(ks0);
         }
         int rem = n >> 2;
         n &= 3;
-#define LD4(A, B)                                                                  \
-    {                                                                              \
-        _Pragma("unroll") for (int u = 0; u < 4; u++) A[u] = __builtin_nontemporal_load(wp + u * 512); \
-        _Pragma("unroll") for (int u = 0; u < 4; u++) B[u] = bact ? bp[u * 64] : zero;                \
-        wp += 2048; bp += 256;                                                     \
-    }
-#define MMA4(A, B)                                                                 \
-    _Pragma("unroll") for (int u = 0; u < 4; u++)                                  \
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A[u]), __builtin_bit_cast(bf16x8_t, B[u]), acc, 0, 0, 0);
-        if (rem) LD4(a0, b0)
-        if (long_range)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ax), __builtin_bit_cast(bf16x8_t, bx), acc, 0, 0, 0);
+        if (rem) load(a0, b0, 4);
+        if (long_range) mma(ax, bx);
         while (rem >= 2) {
-            LD4(a1, b1)
-            MMA4(a0, b0)
-            if (rem > 2) LD4(a0, b0)
-            MMA4(a1, b1)
+            load(a1, b1, 4);
+            mul(a0, b0, 4);
+            if (rem > 2) load(a0, b0, 4);
+            mul(a1, b1, 4);
             rem -= 2;
         }
-        if (rem == 1) { MMA4(a0, b0) }
-#undef LD4
-#undef MMA4
+        if (rem == 1) mul(a0, b0, 4);
+        if (n >= 2) { load(a0, b0, 2); mul(a0, b0, 2); n -= 2; }
+        if (n >= 1) { load(a0, b0, 1); mul(a0, b0, 1); }
     }
-    if (n >= 4) { gemv_steps<4>(wp, bp, bact, acc); n -= 4; }
-    if (n >= 2) { gemv_steps<2>(wp, bp, bact, acc); n -= 2; }
-    if (n >= 1) { gemv_steps<1>(wp, bp, bact, acc); }
     scale_finish(e, sr, sc);
     // D layout: lane holds column (lane & 15) and tile rows 4*(lane >> 4) + r.  Columns m and m+8
     // are the hi and lo parts of batch row m: fold them.
@@ -394,6 +441,28 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
     }
     __syncthreads();
     epilogue<true>(e, rt, yt, sc, sq, resv, gainv, true);
+}
+
+// Everything a wave needs before its first weight load is a leading scalar argument (a copy of the
+// fields of e named alike): those arrive preloaded in SGPRs, a field of the by-value struct costs a
+// scalar load from the argument block at the start of every launch.
+// 14 dwords fit: W, KS, M, act, ssq_in, nt_in, N, res (null unless the epilogue adds a residual), gain.
+__global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32x4_t *__restrict__ W, int KS, int M,
+                                                                   const u32x4_t *__restrict__ act,
+                                                                   const float *ssq_in, int nt_in, int N,
+                                                                   const float *res, const float *gain, Epi e)
+{
+    gemv_bf16_body<FROM_ACT>(W, KS, M, act, ssq_in, nt_in, N, res, gain, 0, e);
+}
+
+// the same product from plain rows x[M][K] (stand-alone product: no scale, no residual); y[m][n] fp32
+template <int SRC>
+__global__ __launch_bounds__(64 * GEMV_WAVES, 4) void gemv_bf16_rows_kernel(const u32x4_t *__restrict__ W, int KS, int M,
+                                                                        const float *__restrict__ x, int K, int N, float *y)
+{
+    Epi e = {};
+    e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = y;
+    gemv_bf16_body<SRC>(W, KS, M, x, nullptr, 0, N, nullptr, nullptr, K, e);
 }
 
 // The one-row projection on the vector ALUs instead of the matrix units, over the same weight tiles,
@@ -2536,13 +2605,6 @@ __global__ __launch_bounds__(512, 2) void stream_read_kernel(const u32x4_t *__re
     }
     for (int o = 32; o >= 1; o >>= 1) x ^= __shfl_xor(x, o);
     if (lane == 0) atomicXor(&out[blockIdx.x], x);
-}
-
-// Zero n16 16-byte pieces (a launch that a stream capture can record, unlike a memset node).
-__global__ void fill_zero_kernel(u32x4_t *p, unsigned n16)
-{
-    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n16) p[i] = u32x4_t{0u, 0u, 0u, 0u};
 }
 
 // Copy cached k and v rows of one position, widened to float (test / debug access).

@@ -1,0 +1,42 @@
+"""The stand-alone projection over the forms of its input: every row count, K of whole and half k-steps, fewer
+k-steps than waves, rows that are 16-byte aligned and rows that are not (another load path, the same sums)."""
+import numpy as np
+import pytest
+
+from paper_2404_18911_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(1, 16, 16), (2, 48, 48), (3, 64, 272), (4, 1024, 688), (5, 128, 2064), (8, 256, 4096), (7, 4112, 1040)])
+def test_linear_of_aligned_and_unaligned_rows(dtype, M, N, K):
+    import torch
+    from paper_2404_18911_amd import binding as B
+    L = B.lib()
+    rng = np.random.default_rng(M * 1000 + K)
+    wf = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+    wh = I.f32_to_bf16_bits(wf) if dtype == "bf16" else wf
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    code = 1 if dtype == "bf16" else 0
+    w = torch.from_numpy(wh.view(np.int16) if code else wh).cuda()
+    packed = torch.empty(L.kg_op_packed_bytes(code, N, K), dtype=torch.uint8, device="cuda")
+    work = torch.empty(L.kg_op_work_bytes(K), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    assert L.kg_op_pack(code, w.data_ptr(), N, K, packed.data_ptr(), s) == B.KG_OK
+    got = []
+    for off in (0, 1):
+        buf = torch.full((M * K + 1,), float("nan"), device="cuda")
+        xd = buf[off:off + M * K]
+        xd.copy_(torch.from_numpy(x.reshape(-1)))
+        y = torch.full((M + 1, N), 7.0, device="cuda")
+        assert L.kg_op_linear(code, packed.data_ptr(), N, K, xd.data_ptr(), M, y.data_ptr(), work.data_ptr(), s) == B.KG_OK
+        torch.cuda.synchronize()
+        assert bool((y[M] == 7.0).all())
+        got.append(y[:M].cpu().numpy())
+    np.testing.assert_array_equal(got[0], got[1])
+    w64 = (I.bf16_bits_to_f32(wh) if code else wf).astype(np.float64)
+    ref = x.astype(np.float64) @ w64.T
+    # rows in two bf16 parts: 2^-17 of a product; float32 sums
+    bound = (np.abs(x).astype(np.float64) @ np.abs(w64).T) * 2.0 ** -15 + 1e-7
+    assert np.all(np.abs(got[0] - ref) <= bound)
