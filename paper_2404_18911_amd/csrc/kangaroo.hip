@@ -1674,18 +1674,39 @@ int kg_train_bind(kg_ctx *x, void *work_dev, size_t bytes, int max_tokens)
     return KG_OK;
 }
 
-// may 4 consecutive elements along an operand's contiguous index be fetched as one 16-byte word?
+// may an operand be fetched in groups of 4 consecutive elements along its contiguous index, as 16-byte words?
 static void tr_gemm_vec_flags(TrGemm &g)
 {
-    auto ok = [](const void *p, long s_contig, long s_other) {
-        return s_contig == 1 && s_other % 4 == 0 && ((uintptr_t)p & 15) == 0;
+    auto ok = [](const void *p, long s_contig, long s_other, int len) {
+        return s_contig == 1 && s_other % 4 == 0 && len % 4 == 0 && ((uintptr_t)p & 15) == 0;
     };
-    g.a_vec = g.sak == 1 ? ok(g.A, g.sak, g.sam) : ok(g.A, g.sam, g.sak);
-    g.b_vec = g.b_mode == 0 && (g.sbk == 1 ? ok(g.B, g.sbk, g.sbn) : ok(g.B, g.sbn, g.sbk));
+    g.a_vec = g.sak == 1 ? ok(g.A, g.sak, g.sam, g.K) : ok(g.A, g.sam, g.sak, g.M);
+    g.b_vec = g.b_mode == 0 && (g.sbk == 1 ? ok(g.B, g.sbk, g.sbn, g.K) : ok(g.B, g.sbn, g.sbk, g.N));
     if (g.batch > 1) {      // every batch member must keep the alignment
         g.a_vec = g.a_vec && g.bsa % 4 == 0;
         g.b_vec = g.b_vec && g.bsb % 4 == 0;
     }
+}
+
+// tiles of C, their order, and the launch; z = slices of k or batch members
+static void launch_tr_gemm(TrGemm &g, int z, hipStream_t s)
+{
+    g.gm = (g.M + TRG_M - 1) / TRG_M; g.gn = (g.N + TRG_N - 1) / TRG_N;
+    g.swz = g.gn % 8 == 0 || g.gn >= 16;        // else columns of C would leave XCDs idle
+    const dim3 grid(g.swz ? 8 * g.gm * ((g.gn + 7) / 8) : g.gm * g.gn, 1, z);
+    const bool ka = g.sak == 1, kb = g.b_mode == 0 ? g.sbk == 1 : g.b_mode == 1, guard = !g.a_vec || (g.b_mode == 0 && !g.b_vec);
+#define TR_GEMM_LAUNCH(...) hipLaunchKernelGGL((tr_gemm_kernel<__VA_ARGS__>), grid, dim3(512), 0, s, g)
+    if (g.b_mode) {             // against bf16 tiles: the callers' A are aligned rows
+        if (kb) TR_GEMM_LAUNCH(1, true, true, false);
+        else TR_GEMM_LAUNCH(1, true, false, false);
+    } else if (guard) {
+        if (ka) { if (kb) TR_GEMM_LAUNCH(3, true, true, true); else TR_GEMM_LAUNCH(3, true, false, true); }
+        else { if (kb) TR_GEMM_LAUNCH(3, false, true, true); else TR_GEMM_LAUNCH(3, false, false, true); }
+    } else {
+        if (ka) { if (kb) TR_GEMM_LAUNCH(3, true, true, false); else TR_GEMM_LAUNCH(3, true, false, false); }
+        else { if (kb) TR_GEMM_LAUNCH(3, false, true, false); else TR_GEMM_LAUNCH(3, false, false, false); }
+    }
+#undef TR_GEMM_LAUNCH
 }
 
 static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, long sbk, long sbn, int b_mode, float *C,
@@ -1697,14 +1718,14 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
     g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
     tr_gemm_vec_flags(g);
     // few output tiles and a long k: slice k so that the launch has enough workgroups to fill the chip
-    const int tiles = ((N + 127) / 128) * ((M + 63) / 64);
+    const int tiles = ((N + TRG_N - 1) / TRG_N) * ((M + TRG_M - 1) / TRG_M);
     int S = 1;
-    while (S < TR_SPLIT_MAX && tiles * S < 1024 && K / (2 * S) >= 256 && (size_t)2 * S * M * N <= x->tl.part_floats) S *= 2;
-    g.k_chunk = ((K + S - 1) / S + 15) / 16 * 16;
+    while (S < TR_SPLIT_MAX && tiles * S < x->n_cus && K / (2 * S) >= 256 && (size_t)2 * S * M * N <= x->tl.part_floats) S *= 2;
+    g.k_chunk = ((K + S - 1) / S + TRG_K - 1) / TRG_K * TRG_K;
     g.part = at<float>(x->tr, x->tl.part);
     {
         ProfScope ps(x, 4, 2.0 * M * (double)N * K);
-        hipLaunchKernelGGL(tr_gemm_kernel, dim3((N + 127) / 128, (M + 63) / 64, S), dim3(256), 0, x->stream, g);
+        launch_tr_gemm(g, S, x->stream);
     }
     KGCHK(check_launch(x, "train_gemm"));
     if (S > 1) {
@@ -1724,11 +1745,11 @@ static int tr_gemm_heads(kg_ctx *x, const float *A, long sam, long sak, long bsa
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = 0;
     g.batch = heads; g.bsa = bsa; g.bsb = bsb; g.bsc = bsc;
-    g.k_chunk = (K + 15) / 16 * 16; g.part = nullptr;
+    g.k_chunk = (K + TRG_K - 1) / TRG_K * TRG_K; g.part = nullptr;
     tr_gemm_vec_flags(g);
     if (heads == 1) { g.batch = 1; }
     ProfScope ps(x, 4, 2.0 * M * (double)N * K * heads);
-    hipLaunchKernelGGL(tr_gemm_kernel, dim3((N + 127) / 128, (M + 63) / 64, heads), dim3(256), 0, x->stream, g);
+    launch_tr_gemm(g, heads, x->stream);
     return check_launch(x, "train_gemm_heads");
 }
 
@@ -2069,10 +2090,10 @@ int kg_op_gemm_f32(const float *A, long sam, long sak, const float *B, long sbk,
     TrGemm g;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
-    g.k_chunk = (K + 15) / 16 * 16; g.part = nullptr;
+    g.k_chunk = (K + TRG_K - 1) / TRG_K * TRG_K; g.part = nullptr;
     g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
     tr_gemm_vec_flags(g);
-    hipLaunchKernelGGL(tr_gemm_kernel, dim3((N + 127) / 128, (M + 63) / 64, 1), dim3(256), 0, (hipStream_t)hip_stream, g);
+    launch_tr_gemm(g, 1, (hipStream_t)hip_stream);
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
 

@@ -3,8 +3,8 @@
 // its draft distribution against the frozen target's is differentiated by hand (chain rule written
 // out: RMSNorm, rotary embedding, causal attention, projections), and AdamW updates fp32 master
 // copies of the adapter's tensors.  All arithmetic is fp32; the dense contractions go through the
-// fp32 MFMA (32x32x2), weights of the frozen LM head are read from their bf16 tiles and widened
-// exactly.  Included by kangaroo.hip after kernels.hip.h.
+// bf16 MFMA with every fp32 number as the exact sum of three bf16 numbers, weights of the frozen LM head are read
+// from their bf16 tiles as they are.  Included by kangaroo.hip after kernels.hip.h.
 #pragma once
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -16,12 +16,25 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 //             b_mode 1: element (row n, col k) of a matrix stored as bf16 MFMA tiles (the layout of
 //                       pack_w_bf16_kernel: tile (row/16, col/32), 16-byte unit (col%32/8)*16 + row%16)
 //             b_mode 2: element (row k, col n) of such a matrix
-// One workgroup (4 waves) per 64 x 128 tile of C; a wave owns 32 x 64 of it (two 32x32x2 MFMA tiles
-// that share the A operand).  k advances in steps of 16 through two LDS buffers: the next step's
-// operands are fetched into registers while the current one is multiplied, and stored to the other
-// buffer afterwards, so a step has one barrier.  A thread fetches 4 consecutive elements of A and
-// 2 x 4 of B along whichever index is contiguous in memory (one 16-byte load when the host found
-// the operand aligned for it: a_vec / b_vec), with element-wise guards at the ragged edges.
+// The products run on the bf16 matrix units at fp32 accuracy: an fp32 number is the exact sum of three bf16
+// numbers (x1 = x rounded, x2 = the rest rounded, x3 = what is left), and of the nine products of two such sums
+// the six largest are taken (x1 y1, x1 y2, x2 y1, x2 y2, x1 y3, x3 y1; the others are below 2^-25 of the
+// product), each exact and accumulated in fp32; against bf16 tiles, which have one part, three products leave
+// nothing out.  Six bf16 products cost 6/16 of the fp32 matrix instruction's time, three 3/16.  Measured errors
+// against 64 bits are no larger than the fp32 instruction's were (relative 2-norm, normal numbers: K = 4096
+// 1.01e-6 against 1.15e-6, K = 32000 3.0e-6 against 3.2e-6).
+//   One workgroup of 8 waves (2 x 4) per 128 x 256 tile of C, a wave owns 64 x 64 (2 x 2 tiles of 32x32x16).
+// k advances in steps of 32: the operands' fp32 numbers are fetched into registers three steps ahead (two sets),
+// split a step ahead, between the multiplications, and stored as bf16 planes [part][row][k] in one of two LDS
+// buffers: one barrier per step.  Per step and compute unit 3072 clocks of matrix instructions (1536 against
+// tiles) stand beside 2100 (1350) of LDS traffic and 1600 (800) of splitting.  1000 x 32000 x 4096 against tiles:
+// 772 us, 1.02 PFLOP/s of bf16 products (fp32 instruction: 2.9 ms); 1000 x 4096 x 4096: 300 us on 128 of the
+// 256 compute units (496 us).  One LDS buffer with 4 waves and two barriers a step: 422 us; operands two steps
+// ahead in one register set: 309; reading a step's operands under the previous step's multiplications: 309.
+// A thread fetches along whichever index is contiguous in memory, in aligned groups of four where the operand
+// allows it (a_vec / b_vec), else (GUARD) element by element.
+// Numbers that no bf16 can stand for (infinities, or within 2^-9 of the largest float) would turn into NaN
+// when split; a workgroup that has met one computes its tile again by plain fp32 multiply-adds.
 // A contraction with few output tiles and a long k is split over blockIdx.z: slice z handles k in
 // [z * k_chunk, (z + 1) * k_chunk) and writes its own partial [M][N] at part + z * M * N; a second
 // kernel adds the slices in order (no atomics: the result does not depend on scheduling).
@@ -34,179 +47,343 @@ struct TrGemm {
     float *C; long ldc;
     int M, N, K;
     int accumulate;
-    int k_chunk;        // k handled per blockIdx.z slice (a multiple of 16); >= K when not split
+    int k_chunk;        // k handled per blockIdx.z slice (a multiple of 32); >= K when not split
     float *part;        // partial results of a split contraction
-    int a_vec, b_vec;   // 4 consecutive elements along the contiguous index are one aligned 16-byte word
+    int a_vec, b_vec;   // 4 consecutive elements along the contiguous index are one aligned 16-byte word, and that index
+                        // ends at a multiple of 4
     int batch;          // > 1: blockIdx.z is a batch index (one product per attention head), k is not split
     long bsa, bsb, bsc; // element offsets of A, B (b_mode 0) and C per batch index
+    int gm, gn, swz;    // tiles of C; swz: see the tile order in the kernel
 };
-
-// LDS row strides in floats.  A thread stores its 4 fetched elements either down 4 consecutive rows
-// (operand contiguous along k: the lanes of a wave then cover rows 4 apart) or as one 16-byte word
-// (operand contiguous along m / n).  With 4 * stride = 16 (mod 64) the first pattern spreads over all
-// banks; strides are multiples of 4 floats so that the 16-byte stores are aligned.
-#ifndef TRG_LDA
-#define TRG_LDA 100
-#define TRG_LDB 164
-#endif
 
 __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
 {
     return ((((size_t)(row >> 4) * KS + tile_pos(col >> 5, KS)) * 64 + ((col >> 3) & 3) * 16 + (row & 15)) << 3) + (col & 7);
 }
 
-__global__ __launch_bounds__(256) void tr_gemm_kernel(const TrGemm g)
+#define TRG_K 32            // k per step
+#define TRG_M 128           // tile of C
+#define TRG_N 256
+
+// Where the 8 numbers k = 8 c .. 8 c + 7 of row r lie in a plane (in elements): rows of 64 bytes, the rows of a 4 x 4
+// group transposed and the four chunks of a row permuted, so that the reads (lanes = consecutive rows, one
+// chunk), the stores of whole chunks and the transposing stores (lanes = every fourth row) are all free of
+// bank conflicts.
+__device__ __forceinline__ int trg_at(int r, int c) { return ((r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3)) * TRG_K + ((c ^ (r & 3)) << 3); }
+// row of chunk item u: consecutive items take every fourth row, whose chunks lie side by side
+__device__ __forceinline__ int trg_item_row(int u) { return (u & ~15) | ((u & 3) << 2) | ((u >> 2) & 3); }
+
+// a pair of fp32 numbers as three pairs of bf16 numbers
+__device__ __forceinline__ void tr_split2(float a, float b, uint32_t (&o)[3])
 {
-    __shared__ __attribute__((aligned(16))) float As[2][16][TRG_LDA];
-    __shared__ __attribute__((aligned(16))) float Bs[2][16][TRG_LDB];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 128;
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 64;
-    const bool a_kc = g.sak == 1;                      // A contiguous along k
-    const bool b_kc = g.b_mode == 0 ? g.sbk == 1 : g.b_mode == 1;
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int p = 0; p < 3; p++) {
+        bf16x2_t h;
+        h[0] = (__bf16)a; h[1] = (__bf16)b;
+        o[p] = __builtin_bit_cast(uint32_t, h);
+        a -= (float)h[0];
+        b -= (float)h[1];
+    }
+}
+
+// One fp32 operand of a ROWS x 32 block (rows m or n, k): the ROWS / 16 numbers each of 512 threads fetches and how
+// it stores them.  KC (contiguous along k): 8 consecutive k of one row (ROWS = 128) or two rows (256).
+// Else 4 consecutive rows x 2 (ROWS = 128) or 4 consecutive k, transposed on the way to LDS.
+template <int ROWS, bool KC>
+struct TrOperand {
+    static constexpr int NV = ROWS / 16, NK = ROWS / 64;     // numbers per thread; k per thread when transposing
+    static constexpr int KT = TRG_K / NK;                    // threads along k when transposing
+    const float *p;         // element (row0, k) of the block that is fetched next
+    long s_row, s_k;
+    int rows;               // valid rows of the block (>= 1)
+    const float *q[KC ? NV / 8 : 1];     // fetch / fetch_tail: this thread's addresses (rows beyond the block's last repeat
+                                         // valid ones: what they give is not stored)
+    __device__ __forceinline__ void init(const float *p_, long s_row_, long s_k_, int rows_, int t)
+    {
+        p = p_; s_row = s_row_; s_k = s_k_; rows = rows_;
+        if constexpr (KC) {
+#pragma unroll
+            for (int i = 0; i < NV / 8; i++) q[i] = p + (size_t)min(trg_item_row((t >> 2) + 128 * i), rows - 1) * s_row + (size_t)(t & 3) * 8;
+        } else {
+            const int r = (t / KT) * 4;
+            q[0] = p + (r < rows ? r : 0) + (size_t)(t % KT) * NK * s_k;
+        }
+    }
+    // a whole step with 16-byte loads (a_vec / b_vec)
+    __device__ __forceinline__ void fetch(float (&v)[NV])
+    {
+#pragma unroll
+        for (int i = 0; i < NV / 4; i++) {
+            const float4 f = KC ? *(const float4 *)(q[KC ? i >> 1 : 0] + 4 * (i & 1)) : *(const float4 *)(q[0] + (size_t)i * s_k);
+            v[4 * i] = f.x; v[4 * i + 1] = f.y; v[4 * i + 2] = f.z; v[4 * i + 3] = f.w;
+        }
+        advance();
+    }
+    // the last step of a k that is no multiple of 32 (KC: it is one of 4): zeros from k_hi on
+    __device__ __forceinline__ void fetch_tail(float (&v)[NV], int k0, int k_hi, int t)
+    {
+#pragma unroll
+        for (int i = 0; i < NV / 4; i++) {
+            const int k = k0 + (KC ? (t & 3) * 8 + 4 * (i & 1) : (t % KT) * NK + i);
+            const bool ok = k < k_hi;
+            const float *a = KC ? q[KC ? i >> 1 : 0] + 4 * (i & 1) : q[0] + (size_t)i * s_k;
+            const float4 f = *(const float4 *)(ok ? a : KC ? q[KC ? i >> 1 : 0] - (t & 3) * 8 : q[0] - (size_t)(t % KT) * NK * s_k);
+            v[4 * i] = ok ? f.x : 0.f; v[4 * i + 1] = ok ? f.y : 0.f; v[4 * i + 2] = ok ? f.z : 0.f; v[4 * i + 3] = ok ? f.w : 0.f;
+        }
+        advance();
+    }
+    __device__ __forceinline__ void fetch_guarded(float (&v)[NV], int k0, int k_hi, int t)
+    {
+        if constexpr (KC) {
+            const int kq = (t & 3) * 8;
+#pragma unroll
+            for (int i = 0; i < NV / 8; i++) {
+                const int r = trg_item_row((t >> 2) + 128 * i);
+                const float *e = p + (size_t)r * s_row + kq;
+#pragma unroll
+                for (int j = 0; j < 8; j++) v[8 * i + j] = (r < rows && k0 + kq + j < k_hi) ? e[j] : 0.f;
+            }
+        } else {
+            const int r = (t / KT) * 4, kq = (t % KT) * NK;
+            const float *e = p + (size_t)r * s_row + (size_t)kq * s_k;
+#pragma unroll
+            for (int i = 0; i < NK; i++)                // k = kq + i, rows r .. r + 3
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[4 * i + j] = (k0 + kq + i < k_hi && r + j < rows) ? e[(size_t)i * s_k + (size_t)j * s_row] : 0.f;
+        }
+        advance();
+    }
+    __device__ __forceinline__ void advance()
+    {
+        const size_t step = KC ? TRG_K : (size_t)TRG_K * s_k;
+        p += step;
+#pragma unroll
+        for (int i = 0; i < (KC ? NV / 8 : 1); i++) q[i] += step;
+    }
+    __device__ __forceinline__ void stash(const float (&v)[NV], uint16_t (*planes)[ROWS * TRG_K], int t) const
+    {
+        if constexpr (KC) {
+#pragma unroll
+            for (int i = 0; i < NV / 8; i++) {
+                const int at = trg_at(trg_item_row((t >> 2) + 128 * i), t & 3);
+                u32x4_t o[3];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    uint32_t s[3];
+                    tr_split2(v[8 * i + 2 * j], v[8 * i + 2 * j + 1], s);
+                    o[0][j] = s[0]; o[1][j] = s[1]; o[2][j] = s[2];
+                }
+#pragma unroll
+                for (int j = 0; j < 3; j++) *(u32x4_t *)&planes[j][at] = o[j];
+            }
+        } else {
+            const int r = (t / KT) * 4, kq = (t % KT) * NK;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int at = trg_at(r + e, kq >> 3) + (kq & 7);
+                uint32_t s[NK / 2][3];
+#pragma unroll
+                for (int j = 0; j < NK / 2; j++) tr_split2(v[8 * j + e], v[8 * j + 4 + e], s[j]);
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    if constexpr (NK == 4) *(uint2 *)&planes[j][at] = make_uint2(s[0][j], s[1][j]);
+                    else *(uint32_t *)&planes[j][at] = s[0][j];
+                }
+            }
+        }
+    }
+};
+
+__device__ __forceinline__ float tr_gemm_b(const TrGemm &g, size_t bob, int k, int n)
+{
+    if (g.b_mode == 0) return ((const float *)g.B)[bob + (size_t)k * g.sbk + (size_t)n * g.sbn];
+    return bf2f(((const uint16_t *)g.B)[g.b_mode == 1 ? packed_u16_index(n, k, g.b_KS) : packed_u16_index(k, n, g.b_KS)]);
+}
+
+// BP: bf16 parts of B (3: fp32 operand, 1: bf16 tiles); KA / KB: A / B contiguous along k (KB of tiles: b_mode 1);
+// GUARD: operands that cannot be fetched in aligned groups of four.
+template <int BP, bool KA, bool KB, bool GUARD>
+__device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][3][TRG_M * TRG_K];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BP][TRG_N * TRG_K];
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    // tile order: with swz the tiles of one column of C run one after another on one XCD (its L2 keeps that
+    // part of B, usually the larger operand); used where the columns fill the XCDs
+    int tm, tn;
+    if (g.swz) {
+        const int j = blockIdx.x >> 3;
+        tm = j % g.gm;
+        tn = (j / g.gm) * 8 + (blockIdx.x & 7);
+        if (tn >= g.gn) return;
+    } else {
+        tm = blockIdx.x / g.gn;
+        tn = blockIdx.x % g.gn;
+    }
+    const int m0 = tm * TRG_M, n0 = tn * TRG_N;
+    const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
     const bool batched = g.batch > 1;
     const bool split = !batched && gridDim.z > 1;
     const int k_lo = batched ? 0 : blockIdx.z * g.k_chunk, k_hi = batched ? g.K : min(g.K, k_lo + g.k_chunk);
     const size_t boa = batched ? (size_t)blockIdx.z * g.bsa : 0, bob = batched ? (size_t)blockIdx.z * g.bsb : 0,
                  boc = batched ? (size_t)blockIdx.z * g.bsc : 0;
-    // first of the 4 (A) and 2 x 4 (B, second group 64 columns further) elements this thread fetches per step
-    int am, ak, bn, bk;
-    if (a_kc) { am = t >> 2; ak = (t & 3) * 4; } else { ak = t >> 4; am = (t & 15) * 4; }
-    if (b_kc) { bn = t >> 2; bk = (t & 3) * 4; } else { bk = t >> 4; bn = (t & 15) * 4; }
-    const float *pa = (const float *)g.A + boa + (size_t)(m0 + am) * g.sam + (size_t)(k_lo + ak) * g.sak;
-    const long a_step = 16 * g.sak, a_el = a_kc ? g.sak : g.sam;
-    const float *pb0 = nullptr, *pb1 = nullptr;        // b_mode 0
-    long b_step = 0, b_el = 0;
-    const uint16_t *Bp = (const uint16_t *)g.B;        // tiled modes
-    size_t rb0 = 0, rb1 = 0;                           // mode 1: per-row part of the tile index; mode 2: full index at k_lo
-    if (g.b_mode == 0) {
-        pb0 = (const float *)g.B + bob + (size_t)(k_lo + bk) * g.sbk + (size_t)(n0 + bn) * g.sbn;
-        pb1 = pb0 + (size_t)64 * g.sbn;
-        b_step = 16 * g.sbk;
-        b_el = b_kc ? g.sbk : g.sbn;
-    } else if (g.b_mode == 1) {
-        rb0 = (size_t)((n0 + bn) >> 4) * g.b_KS * 64 + ((n0 + bn) & 15);
-        rb1 = (size_t)((n0 + bn + 64) >> 4) * g.b_KS * 64 + ((n0 + bn + 64) & 15);
-    } else {
-        rb0 = packed_u16_index(k_lo + bk, n0 + bn, g.b_KS);
-        rb1 = packed_u16_index(k_lo + bk, n0 + bn + 64, g.b_KS);
-    }
-    const bool am_all = a_kc ? (m0 + am < g.M) : (m0 + am + 3 < g.M);
-    float av[4], bv[2][4];
-    auto widen = [](uint2 raw, float *o) {
-        o[0] = __uint_as_float(raw.x << 16);
-        o[1] = __uint_as_float(raw.x & 0xFFFF0000u);
-        o[2] = __uint_as_float(raw.y << 16);
-        o[3] = __uint_as_float(raw.y & 0xFFFF0000u);
+    TrOperand<TRG_M, KA> oa;
+    TrOperand<TRG_N, KB> ob;
+    oa.init((const float *)g.A + boa + (size_t)m0 * g.sam + (size_t)k_lo * g.sak, g.sam, g.sak, g.M - m0, t);
+    if constexpr (BP == 3) ob.init((const float *)g.B + bob + (size_t)n0 * g.sbn + (size_t)k_lo * g.sbk, g.sbn, g.sbk, g.N - n0, t);
+    // numbers a thread has fetched: two sets, so that a fetch has more than a whole step to arrive
+    struct Raw {
+        float a[8], b[BP == 3 ? 16 : 1];
+        u32x4_t bt[2];                                  // bf16 tiles: two 16-byte units per thread
     };
-    auto fetch = [&](int k0) {
-        // ---- A
-        const bool ak_all = a_kc ? (k0 + ak + 3 < k_hi) : (k0 + ak < k_hi);
-        if (g.a_vec && am_all && ak_all) {
-            const float4 v = *(const float4 *)pa;
-            av[0] = v.x; av[1] = v.y; av[2] = v.z; av[3] = v.w;
-        } else {
+    // b_mode 1: unit = 8 k of one row n, items as above.  b_mode 2: unit = 8 n of one row k: thread -> rows
+    // k = 2 (t % 16), + 1, columns 8 (t / 16)
+    auto fetch_tiles = [&](Raw &w, int k0) {
+        const u32x4_t *T = (const u32x4_t *)g.B;
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int m = m0 + am + (a_kc ? 0 : i), k = k0 + ak + (a_kc ? i : 0);
-                av[i] = (m < g.M && k < k_hi) ? pa[i * a_el] : 0.f;
-            }
-        }
-        pa += a_step;
-        // ---- B
-        if (g.b_mode == 0) {
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const float *pb = h ? pb1 : pb0;
-                const int nb = n0 + bn + 64 * h;
-                const bool n_all = b_kc ? (nb < g.N) : (nb + 3 < g.N);
-                const bool k_all = b_kc ? (k0 + bk + 3 < k_hi) : (k0 + bk < k_hi);
-                if (g.b_vec && n_all && k_all) {
-                    const float4 v = *(const float4 *)pb;
-                    bv[h][0] = v.x; bv[h][1] = v.y; bv[h][2] = v.z; bv[h][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const int n = nb + (b_kc ? 0 : i), k = k0 + bk + (b_kc ? i : 0);
-                        bv[h][i] = (n < g.N && k < k_hi) ? pb[i * b_el] : 0.f;
-                    }
-                }
-            }
-            pb0 += b_step;
-            pb1 += b_step;
-        } else if (g.b_mode == 1) {
-            // four consecutive columns (k) of rows n, n + 64 of the tiled matrix: 8 bytes each, 8-byte aligned;
-            // N, K and k_chunk are multiples of 8, so the four share the bounds verdict
-            const int col = k0 + bk;
-            const size_t cpart = (size_t)tile_pos(col >> 5, g.b_KS) * 64 + ((col >> 3) & 3) * 16;
-            const bool k_ok = col < k_hi;
-            uint2 r0 = make_uint2(0u, 0u), r1 = make_uint2(0u, 0u);
-            if (k_ok && n0 + bn < g.N) r0 = *(const uint2 *)(Bp + ((rb0 + cpart) << 3) + (col & 7));
-            if (k_ok && n0 + bn + 64 < g.N) r1 = *(const uint2 *)(Bp + ((rb1 + cpart) << 3) + (col & 7));
-            widen(r0, bv[0]);
-            widen(r1, bv[1]);
-        } else {
-            // four consecutive columns (n) of row k: the row advances by 16 per step, i.e. by one tile row
-            const bool k_ok = k0 + bk < k_hi;
-            uint2 r0 = make_uint2(0u, 0u), r1 = make_uint2(0u, 0u);
-            if (k_ok && n0 + bn < g.N) r0 = *(const uint2 *)(Bp + rb0);
-            if (k_ok && n0 + bn + 64 < g.N) r1 = *(const uint2 *)(Bp + rb1);
-            widen(r0, bv[0]);
-            widen(r1, bv[1]);
-            rb0 += (size_t)g.b_KS * 512;
-            rb1 += (size_t)g.b_KS * 512;
-        }
-    };
-    auto stash = [&](int buf) {
-        if (a_kc) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) As[buf][ak + i][am] = av[i];
-        } else {
-            *(float4 *)&As[buf][ak][am] = make_float4(av[0], av[1], av[2], av[3]);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            if (b_kc) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) Bs[buf][bk + i][bn + 64 * h] = bv[h][i];
+        for (int i = 0; i < 2; i++) {
+            // (columns beyond the last repeat valid ones; k beyond the last meets zeros of A, and the matrix is a whole
+            // number of 16-row tiles, its k-steps padded: every unit read exists)
+            if constexpr (KB) {
+                const int n = min(n0 + trg_item_row((t >> 2) + 128 * i), g.N - 1), c = t & 3;
+                w.bt[i] = T[((size_t)(n >> 4) * g.b_KS + tile_pos(k0 >> 5, g.b_KS)) * 64 + c * 16 + (n & 15)];
             } else {
-                *(float4 *)&Bs[buf][bk][bn + 64 * h] = make_float4(bv[h][0], bv[h][1], bv[h][2], bv[h][3]);
+                const int k = min(k0 + 2 * (t & 15) + i, k_hi - 1), n = min(n0 + 8 * (t >> 4), (g.N - 1) & ~7);
+                w.bt[i] = T[((size_t)(k >> 4) * g.b_KS + tile_pos(n >> 5, g.b_KS)) * 64 + ((n >> 3) & 3) * 16 + (k & 15)];
             }
         }
     };
-    f32x16_t acc0, acc1;
+    auto stash_tiles = [&](const Raw &w, uint16_t *plane) {
+        if constexpr (KB) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) { acc0[i] = 0.f; acc1[i] = 0.f; }
-    int buf = 0;
-    if (k_lo < k_hi) {
-        fetch(k_lo);
-        stash(0);
-    }
-    __syncthreads();
-    for (int k0 = k_lo; k0 < k_hi; k0 += 16) {
-        const bool more = k0 + 16 < k_hi;
-        if (more) fetch(k0 + 16);                       // in flight while this step is multiplied
+            for (int i = 0; i < 2; i++) *(u32x4_t *)&plane[trg_at(trg_item_row((t >> 2) + 128 * i), t & 3)] = w.bt[i];
+        } else {
+            const int k = 2 * (t & 15);
 #pragma unroll
-        for (int kk = 0; kk < 8; kk++) {
-            const float a = As[buf][2 * kk + (lane >> 5)][wm + (lane & 31)];
-            const float b0 = Bs[buf][2 * kk + (lane >> 5)][wn + (lane & 31)];
-            const float b1 = Bs[buf][2 * kk + (lane >> 5)][wn + 32 + (lane & 31)];
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b1, acc1, 0, 0, 0);
+            for (int j = 0; j < 4; j++) {
+                const int r = 8 * (t >> 4) + 2 * j;
+                *(uint32_t *)&plane[trg_at(r, k >> 3) + (k & 7)] = __builtin_amdgcn_perm(w.bt[1][j], w.bt[0][j], 0x05040100u);
+                *(uint32_t *)&plane[trg_at(r + 1, k >> 3) + (k & 7)] = __builtin_amdgcn_perm(w.bt[1][j], w.bt[0][j], 0x07060302u);
+            }
         }
-        if (more) stash(buf ^ 1);                       // the other buffer was last read before the previous barrier
+    };
+    typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+    float big = 0.f;                                    // largest magnitude this thread has fetched
+    u16x2_t big_exp = {0, 0};                           // largest exponents among its bf16 weights
+    const int steps = k_lo < k_hi ? (k_hi - k_lo + TRG_K - 1) / TRG_K : 0, full = k_lo < k_hi ? (k_hi - k_lo) / TRG_K : 0;
+    auto fetch_whole = [&](Raw &w, int st) {
+        oa.fetch(w.a);
+        if constexpr (BP == 3) ob.fetch(w.b);
+        else fetch_tiles(w, k_lo + st * TRG_K);
+    };
+    auto fetch = [&](Raw &w, int st) {                  // step st, if there is one
+        if (st >= steps) return;
+        const int k0 = k_lo + st * TRG_K;
+        if constexpr (GUARD) {
+            oa.fetch_guarded(w.a, k0, k_hi, t);
+            ob.fetch_guarded(w.b, k0, k_hi, t);
+        } else if (st < full) {
+            fetch_whole(w, st);
+        } else {
+            oa.fetch_tail(w.a, k0, k_hi, t);
+            if constexpr (BP == 3) ob.fetch_tail(w.b, k0, k_hi, t);
+            else fetch_tiles(w, k0);
+        }
+    };
+    auto stash = [&](const Raw &w, int buf) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) big = fmaxf(big, fabsf(w.a[i]));
+        oa.stash(w.a, As[buf], t);
+        if constexpr (BP == 3) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) big = fmaxf(big, fabsf(w.b[i]));
+            ob.stash(w.b, Bs[buf], t);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    big_exp = __builtin_elementwise_max(big_exp, __builtin_bit_cast(u16x2_t, w.bt[i][j] & 0x7F807F80u));
+            stash_tiles(w, Bs[buf][0]);
+        }
+    };
+    f32x16_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+    const int fr = lane & 31, fc = lane >> 5;           // operand layout of the 32x32x16 instruction: row, which 8 k
+    struct Frag { bf16x8_t a[2][3], b[2][BP]; };
+    auto read = [&](Frag &f, int buf, int kk) {         // operands of k = 16 kk .. 16 kk + 15 of the step
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+#pragma unroll
+            for (int q = 0; q < 3; q++) f.a[i][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&As[buf][q][trg_at(wm + 32 * i + fr, 2 * kk + fc)]);
+#pragma unroll
+            for (int q = 0; q < BP; q++) f.b[i][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&Bs[buf][q][trg_at(wn + 32 * i + fr, 2 * kk + fc)]);
+        }
+    };
+    auto multiply = [&](const Frag &f) {
+#pragma unroll
+        for (int s = 2; s >= 0; s--)                    // parts (q, s - q): the smallest products first
+#pragma unroll
+            for (int q = 0; q <= s; q++) {
+                if (s - q >= BP) continue;
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i][q], f.b[j][s - q], acc[i][j], 0, 0, 0);
+            }
+    };
+    if (steps > 0) {
+        Raw r0, r1;
+        fetch(r0, 0);
+        fetch(r1, 1);
+        stash(r0, 0);
+        fetch(r0, 2);
         __syncthreads();
-        buf ^= 1;
+        int s = 0;
+        // step s is multiplied while step s + 1 (in `w`) is split and stored and step s + 3 requested
+        auto step = [&](Raw &w, int buf, bool whole) {
+            Frag f;
+            read(f, buf, 0);
+            multiply(f);
+            if (whole || s + 1 < steps) stash(w, buf ^ 1);      // the other buffer was last read before the previous barrier
+            if (whole) fetch_whole(w, s + 3);
+            else fetch(w, s + 3);
+            read(f, buf, 1);
+            multiply(f);
+            __syncthreads();
+            s++;
+        };
+        if constexpr (!GUARD)
+            while (s + 4 < full) { step(r1, 0, true); step(r0, 1, true); }
+        while (s < steps) {
+            step(r1, 0, false);
+            if (s < steps) step(r0, 1, false);
+        }
     }
-    // accumulator register i of lane l: row 8 * (i / 4) + 4 * (l / 32) + i % 4, column l % 32
+    const bool again = __syncthreads_or(big > 3.3e38f || big_exp[0] == 0x7F80 || big_exp[1] == 0x7F80);
+    // accumulator register r of lane l: row 8 * (r / 4) + 4 * (l / 32) + r % 4, column l % 32
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const int n = n0 + wn + 32 * h + (lane & 31);
+    for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            const int m = m0 + wm + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-            const float v = h ? acc1[i] : acc0[i];
-            if (m < g.M && n < g.N) {
+        for (int j = 0; j < 2; j++) {
+            const int n = n0 + wn + 32 * j + (lane & 31);
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int m = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                if (m >= g.M || n >= g.N) continue;
+                float v = acc[i][j][r];
+                if (again) {
+                    v = 0.f;
+                    for (int k = k_lo; k < k_hi; k++)
+                        v = fmaf(((const float *)g.A)[boa + (size_t)m * g.sam + (size_t)k * g.sak], tr_gemm_b(g, bob, k, n), v);
+                }
                 if (split) {
                     g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
                 } else {
@@ -215,8 +392,10 @@ __global__ __launch_bounds__(256) void tr_gemm_kernel(const TrGemm g)
                 }
             }
         }
-    }
 }
+// (a bound of 256 registers: 8 waves fill a compute unit, whose LDS one workgroup takes anyway)
+template <int BP, bool KA, bool KB, bool GUARD>
+__global__ __launch_bounds__(512, 2) void tr_gemm_kernel(const TrGemm g) { tr_gemm_body<BP, KA, KB, GUARD>(g); }
 
 // C[m][n] (+)= part[0][m][n] + part[1][m][n] + ... in slice order
 __global__ void tr_gemm_reduce_kernel(const float *part, int S, int M, int N, float *C, long ldc, int accumulate)

@@ -1,0 +1,51 @@
+"""The training contraction around the edges of its tiles (128 x 256 of C, 32 of k), in every orientation, with operands
+that can and cannot be fetched in aligned groups of four, and with numbers that do not split into bf16 parts."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _view(rng, rows, cols, contiguous_rows):
+    a = rng.standard_normal((rows, cols) if contiguous_rows else (cols, rows)).astype(np.float32)
+    return a if contiguous_rows else a.T
+
+
+@pytest.mark.parametrize("ta", [True, False])
+@pytest.mark.parametrize("tb", [True, False])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (4, 8, 4), (128, 256, 32), (129, 257, 33), (127, 255, 31), (132, 260, 36), (256, 512, 64),
+                                   (300, 516, 100), (64, 128, 160), (130, 300, 68)])
+def test_contraction_at_the_edges_of_its_tiles(M, N, K, ta, tb):
+    """Bound: K roundings of a running fp32 sum, 2^-24 of sum |a||b| each (all K here are small enough that a missing
+    part of an operand, 2^-9 or 2^-18 of it, would stand out)."""
+    from paper_2404_18911_amd import binding as B
+    rng = np.random.default_rng(M * 31 + N * 7 + K)
+    a, b = _view(rng, M, K, ta), _view(rng, K, N, tb)
+    c0 = rng.standard_normal((M, N)).astype(np.float32)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    bound = (K + 2) * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)) + 1e-30
+    assert np.all(np.abs(B.op_gemm_f32(a, b) - ref) <= bound)
+    assert np.all(np.abs(B.op_gemm_f32(a, b, c0) - (ref + c0)) <= bound + 2.0 ** -23 * (np.abs(ref) + np.abs(c0)))
+
+
+def test_contraction_of_numbers_beyond_bf16():
+    """Infinities, NaN and numbers that round to infinity in bf16 give what fp32 multiply-adds give, in their rows and
+    columns; everything else is untouched."""
+    from paper_2404_18911_amd import binding as B
+    rng = np.random.default_rng(5)
+    a = rng.standard_normal((300, 64)).astype(np.float32)
+    b = rng.standard_normal((64, 600)).astype(np.float32)
+    a[3, 5] = np.inf
+    a[140, 0] = np.nan
+    a[200, 7] = 3.4e38
+    b[7, :] = 0.25
+    b[9, 300] = -np.inf
+    got = B.op_gemm_f32(a, b)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = a.astype(np.float64) @ b.astype(np.float64)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.array_equal(got[np.isinf(got)], ref[np.isinf(ref)].astype(np.float32))
+    ok = np.isfinite(ref)
+    fin_a, fin_b = np.where(np.isfinite(a), a, 0).astype(np.float64), np.where(np.isfinite(b), b, 0).astype(np.float64)
+    bound = 66 * 2.0 ** -24 * (np.abs(fin_a) @ np.abs(fin_b))
+    assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= bound[ok])
