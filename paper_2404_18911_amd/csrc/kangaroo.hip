@@ -23,9 +23,10 @@ constexpr size_t ALIGN = 256;
 // 4096-token prompt at the 7B shape: 122 ms in passes of 1024 rows, 109 in passes of 2048, 105 in one).
 // The other cache types keep the 8-row-block kernels, whose attention needs page partials per block.
 constexpr int PF_ROWS_MAX = 1024, PF_ROWS_MAX_HALF = 4096;
-// Passes of up to PF_STREAM_ROWS rows are bound by reading the weights and go through gemm_stream_kernel;
-// its projections along k are cut into at most PF_STREAM_SLICES slices.
-constexpr int PF_STREAM_ROWS = 192, PF_STREAM_SLICES = 8;
+// Passes of up to PF_STREAM_ROWS rows are bound by reading the weights and go through gemm_stream_kernel (7B shape, us
+// per layer of a pass: 160 rows 255 against 272 .. 285 with the larger tiles, 200 rows 335 against 258).
+// Projections cut along k write at most PF_SLICES partial sums per output, PF_PART_ROWS rows of them in all.
+constexpr int PF_STREAM_ROWS = 192, PF_SLICES = 8, PF_PART_ROWS = 4096;
 inline size_t up(size_t x, size_t a = ALIGN) { return (x + a - 1) / a * a; }
 
 struct LayerW {
@@ -233,7 +234,7 @@ void layout(kg_ctx *x)
         x->s_psms = take(nbp * c.n_heads * x->n_pages * KG_ROWS * 4);
         x->s_pcnt = take(nb * c.n_heads * 4);
         x->s_pscale = take(R * 4);
-        x->s_ppart = half ? take((size_t)PF_STREAM_SLICES * std::min<size_t>(R, PF_STREAM_ROWS) * d * 4) : 0;
+        x->s_ppart = half ? take(std::min<size_t>(PF_SLICES * R, PF_PART_ROWS) * d * 4) : 0;
     }
     x->scratch_bytes = o;
 }
@@ -411,11 +412,13 @@ Epi epi_base(kg_ctx *x, int kind, int M, int N);
 
 // ---- prompt pass (dense MFMA projections over many 8-row blocks) ---------------------------------
 
-enum { PF_PLAN_TW1_RB8 = 17, PF_PLAN_STREAM = 18 };     // pf_gemm_plan: TW 1 with workgroups of 64 rows; gemm_stream_kernel
-int pf_gemm_plan(const kg_ctx *x, int N, int K, int T);
 int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
-// Short passes go through gemm_stream_kernel (half-precision cache only: its prompt rows are not bit-identical to decoded rows)
+// Which kernels a pass of T rows goes through.  With the half-precision cache its rows need not be bit-identical to
+// decoded rows: short passes take gemm_stream_kernel, others gemm_prefill2_body (whose table of k-steps bounds K).
+// Both read activations in the pair layout (pf_act_ptr) and the rows' RMS scales from s_pscale, where whatever
+// produced the rows leaves them.  Else the 8-row-block kernels (gemm_prefill_body), with their layout and tile sums.
 inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= PF_STREAM_ROWS; }
+inline bool pf_pairs(const kg_ctx *x, int T) { return x->kvt == 2 && (T <= PF_STREAM_ROWS || std::max(x->KSd, x->KSf) <= PF2_KS_MAX); }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
 {
@@ -428,9 +431,9 @@ int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, cons
     // the rows feed a q,k,v projection: stored in the layout its kernel reads
     hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(d / 16, nb), dim3(128), 0, x->stream, emb, tk, tok_dev, rows, d, T, gain,
                        xout, (void *)(x->scr + x->s_pactX), at<float>(x->scr, x->s_pssq0), act_bytes(d),
-                       (d / 16) * KG_ROWS, pf_gemm_plan(x, 3 * d, d, T) ? 1 : 0);
+                       (d / 16) * KG_ROWS, pf_pairs(x, T) ? 1 : 0);
     KGCHK(check_launch(x, "prompt pack_rows"));
-    return pf_streams(x, T) ? launch_rms_scale(x, at<const float>(x->scr, x->s_pssq0), T) : KG_OK;
+    return pf_pairs(x, T) ? launch_rms_scale(x, at<const float>(x->scr, x->s_pssq0), T) : KG_OK;
 }
 
 // the rows' RMS scales from their tile sums of squares, once per pass and not once per workgroup
@@ -463,7 +466,7 @@ StreamPlan pf_stream_plan(int n_cus, int NT, int KS, int T, bool split)
     const int R = need <= 4 ? need : need <= 6 ? 6 : 8;
     StreamPlan best = {R, gx, 1, 1, NT};
     double best_cost = -1.0;
-    for (int S = 1; S <= (split ? PF_STREAM_SLICES : 1); S *= 2) {
+    for (int S = 1; S <= (split ? PF_SLICES : 1); S *= 2) {
         if (S > 1 && KS < 16 * S) break;
         for (int rounds = 1; rounds <= 16; rounds++) {
             const int groups = std::min(NT, std::max(1, n_cus * rounds / (S * gx)));
@@ -486,6 +489,15 @@ void launch_stream_tiles(const PfStreamArgs &a, const Epi &e, int ntw, dim3 grid
         STREAM_CASE(1) STREAM_CASE(2) STREAM_CASE(3) STREAM_CASE(4) STREAM_CASE(5) STREAM_CASE(6) STREAM_CASE(7) STREAM_CASE(8)
 #undef STREAM_CASE
     }
+}
+
+// the partial sums in s_ppart, added, with what follows an EPI_RESID projection
+int launch_reduce_rows(kg_ctx *x, int slices, int T, const Epi &e, size_t act_out_blk)
+{
+    ProfScope ps(x, 2, 0.0);
+    hipLaunchKernelGGL(pf_reduce_rows_kernel, dim3(T), dim3(1024), 0, x->stream, at<const float>(x->scr, x->s_ppart), slices, T, e.N, e.res,
+                       e.xout, e.gain, e.act_out, act_out_blk, e.inv_d, e.eps, at<float>(x->scr, x->s_pscale));
+    return check_launch(x, "prompt row sums");
 }
 
 // One projection of a short pass.  EPI_PLAIN / EPI_SWIGLU scale their rows by s_pscale (if ssq_in is set);
@@ -519,57 +531,46 @@ int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, i
         }
         KGCHK(check_launch(x, "prompt projection"));
     }
-    if (!resid) return KG_OK;
-    ProfScope ps(x, 2, 0.0);
-    hipLaunchKernelGGL(pf_reduce_rows_kernel, dim3(T), dim3(1024), 0, x->stream, (const float *)a.part, p.slices, T, N, e.res, e.xout, e.gain,
-                       e.act_out, a.act_out_blk, e.inv_d, e.eps, scale);
-    return check_launch(x, "prompt row sums");
+    return resid ? launch_reduce_rows(x, p.slices, T, e, a.act_out_blk) : KG_OK;
 }
 
-// Y[T][N] = X[T][K] . W^T with the epilogue e applied per 8-row block; in/out block strides follow
-// the prompt buffers (activation tiles of K features per block, d/16 tile sums per block)
-// Which kernel multiplies a prompt pass of T rows by a matrix [N][K]: 0 = the 8-row-block kernels
-// (gemm_prefill_body: rows bit-identical to one-token decoding), else the TW of gemm_prefill2_body.
-// The answer also fixes the layout in which the producer of the projection's input has to store it
-// (pf_act_ptr: the pair layout for gemm_prefill2_body).
-int pf_gemm_plan(const kg_ctx *x, int N, int K, int T)
+// ---- longer passes: projections in workgroups of 128 rows (gemm_prefill2_body) ----
+
+// The kernel's variants: weight tiles per workgroup, and microseconds per k-step of a workgroup where all compute
+// units have one (random data at the 7B and 13B shapes; a round also takes about 4 us besides its k-steps).
+struct Pf2Variant { void (*kernel)(PfArgs, Epi); int ntw; double step_us; };
+const Pf2Variant pf2_variants[] = {{gemm_prefill2_kernel_n6, 6, 0.38}, {gemm_prefill2_kernel_tw1, 8, 0.46}, {gemm_prefill2_kernel_n12, 12, 0.63},
+                                   {gemm_prefill2_kernel_tw2, 16, 0.775}, {gemm_prefill2_kernel_tw4, 32, 1.51}};
+
+// Which variant, in how many slices along k (`split` allowed: EPI_RESID).  A workgroup fills a compute unit, so a
+// launch takes whole rounds of them; a partly filled last round runs at a higher clock (0.68 of a round when nearly
+// empty).  Partial sums are written at 5 TB/s and added by pf_reduce_rows_kernel (4 us + what it moves at 6 TB/s, against
+// 5 us for the scales of rows that are finished in place).  The model is within a tenth of the measured launches (us,
+// real passes): 7B shape, 256 rows: q,k,v 6 tiles 54, 8 tiles 59, 12 tiles 71; gate+up 12 tiles 81, 16 tiles 89; down_proj
+// 16 tiles in 7 slices 45, 8 tiles in 4 slices 48, 8 tiles uncut 138; 1024 rows: gate+up 16 tiles 288, 12 tiles 313, 32
+// tiles 359; down_proj 16 tiles in 2 slices 138, 8 tiles uncut 163; 4096 rows: q,k,v 32 tiles 607, 16 tiles 660;
+// gate+up 16 tiles 1133, 32 tiles 1152.  (At 4096 rows the card is at its power limit: passes with either choice for
+// gate+up take the same 99 ms, all in 16 tiles 101.5 ms.)
+struct Pf2Plan { int variant, slices; };
+Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
 {
-    if (pf_streams(x, T)) return PF_PLAN_STREAM;
-    // long passes with the half-precision cache only (its prompt rows are not bit-identical to decoded rows anyway)
-    if (x->kvt != 2 || (K + 31) / 32 > PF2_KS_MAX) return 0;
-    // Workgroups of 8 * TW weight tiles x 128 rows.  TW is the one with the least operand traffic: per
-    // k-step every row group fetches all NT weight tiles and every workgroup its 16 activation tiles,
-    // and a last round of workgroups that fills only part of the device costs a whole round; beside the
-    // traffic, the kernels that read the next k-step's operands under the current one's multiplications
-    // (TW 1 and 2) take 0.95 and 1.0 of the model's time and TW 4 takes 1.2.  Measured at the 7B shape under a
-    // kernel trace, microseconds per launch for TW 1 / 2 / 4: 1024 rows: q,k,v 190 / 191 / 180, gate+up 359 / 296 /
-    // 364, o_proj and down_proj 119 / 164 / 313; 2048 rows: q,k,v 390 / 323 / 367, gate+up 686 / 599 / 589, o_proj
-    // and down_proj 245 / 204 / 331 (the model picks the fastest of each); 256 rows: q,k,v TW 1 58, gate+up TW 2 91.
-    // At 4096 rows the model picks TW 4 for every projection (3 .. 11 full rounds of workgroups): a 4096-token
-    // prompt took 104.5 ms so, 108.4 ms with TW 2 for gate+up and 114.2 ms with TW 2 for q,k,v as well.
-    const int NT = N / 16, nb = (T + KG_ROWS - 1) / KG_ROWS, gx2 = (nb + 15) / 16;
-    int best_tw = 1;
-    double best_cost = -1.0, best_wgs = 0.0;
-    for (int tw = 4; tw >= 1; tw >>= 1) {
-        const int gy = (NT + 8 * tw - 1) / (8 * tw);
-        const double wgs = (double)gx2 * gy;
-        const double rounds = std::ceil(wgs / x->n_cus);
-        const double cost = ((double)NT * gx2 + 16.0 * wgs) * rounds * x->n_cus / wgs * (tw == 4 ? 1.2 : tw == 2 ? 1.0 : 0.95);
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best_tw = tw; best_wgs = wgs; }
-    }
-    // few weight tiles (o_proj and down_proj at 256 rows: 64 workgroups of 128 rows): workgroups of 64 rows
-    // where those reach that fill (70 us per launch against 84 us of the 8-row-block kernel), else that kernel.
-    // A workgroup of 64 rows takes 0.55 of the time of one of 128 rows, so the 64-row kernel also wins where it
-    // needs no more rounds of workgroups than TW 1 does (o_proj and down_proj at 512 rows: 256 workgroups instead
-    // of 128, a 512-token prompt 15.9 -> 14.6 ms; at 768 rows 384 instead of 192: two rounds, no gain).
-    const double wgs8 = (double)((nb + 7) / 8) * ((NT + 7) / 8);
-    if (best_wgs >= 0.45 * x->n_cus) {
-        if (best_tw == 1 && 0.55 * std::ceil(wgs8 / x->n_cus) < std::ceil(best_wgs / x->n_cus)) return PF_PLAN_TW1_RB8;
-        return best_tw;
-    }
-    return wgs8 >= 0.45 * x->n_cus ? PF_PLAN_TW1_RB8 : 0;
+    const int gx = (T + 127) / 128;
+    Pf2Plan best = {0, 1};
+    double best_cost = -1.0;
+    for (int v = 0; v < (int)(sizeof(pf2_variants) / sizeof(pf2_variants[0])); v++)
+        for (int S = 1; S <= (split ? PF_SLICES : 1); S++) {
+            if (S > 1 && (S * T > PF_PART_ROWS || KS < 8 * S || pf2_variants[v].ntw == 32)) break;
+            const Pf2Variant &pv = pf2_variants[v];
+            const double wgs = (double)gx * ((NT + pv.ntw - 1) / pv.ntw) * S, whole = std::floor(wgs / n_cus), rest = wgs / n_cus - whole;
+            const double rounds = whole + (rest > 0 ? 0.68 + 0.32 * rest : 0.0), bytes = (double)T * NT * 64;
+            const double cost = rounds * ((double)KS / S * pv.step_us + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
+            if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {v, S}; }
+        }
+    return best;
 }
 
+// Y[T][N] = X[T][K] . W^T with the epilogue e; in/out block strides follow the prompt buffers (activation tiles of K
+// features per block, d/16 tile sums per block)
 int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T, const Epi &e, bool ssq_in, bool ssq_out,
                    int act_out_K)
 {
@@ -584,22 +585,22 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
     a.ssq_in_blk = ssq_in ? sq : 0; a.ssq_out_blk = ssq_out ? sq : 0;
     a.act_out_blk = act_out_K ? act_bytes(act_out_K) : 0;
     const int nb = (T + KG_ROWS - 1) / KG_ROWS;
-    if (const int plan = pf_gemm_plan(x, N, K, T)) {
-        const int best_tw = plan == PF_PLAN_TW1_RB8 ? 1 : plan;
-        a.gx = plan == PF_PLAN_TW1_RB8 ? (nb + 7) / 8 : (nb + 15) / 16;
-        a.gy = (a.NT + 8 * best_tw - 1) / (8 * best_tw);
-        const int groups = a.gx * 8 * ((a.gy + 7) / 8);
+    if (pf_pairs(x, T)) {
+        const bool resid = e.kind == EPI_RESID;
+        const Pf2Plan p = pf2_plan(x->n_cus, a.NT, a.KS, T, resid);
+        const Pf2Variant &v = pf2_variants[p.variant];
+        a.gx = (nb + 15) / 16;
+        a.gy = (a.NT + v.ntw - 1) / v.ntw;
+        if (p.slices > 1) a.part = at<float>(x->scr, x->s_ppart);
         Epi e2 = e;
-        if (ssq_in) {
-            KGCHK(launch_rms_scale(x, e.ssq_in, T));
-            e2.scale_in = at<float>(x->scr, x->s_pscale);
+        e2.scale_in = ssq_in ? at<float>(x->scr, x->s_pscale) : nullptr;
+        {
+            ProfScope ps(x, 3, 2.0 * T * (double)N * K);
+            hipLaunchKernelGGL(v.kernel, dim3(8 * ((a.gx * a.gy + 7) / 8), p.slices), dim3(768), 0, x->stream, a, e2);
+            KGCHK(check_launch(x, "prompt projection"));
         }
-        ProfScope ps(x, 3, 2.0 * T * (double)N * K);
-        if (plan == PF_PLAN_TW1_RB8) hipLaunchKernelGGL(gemm_prefill2_kernel_tw1_rb8, dim3(groups), dim3(768), 0, x->stream, a, e2);
-        else if (best_tw == 4) hipLaunchKernelGGL(gemm_prefill2_kernel_tw4, dim3(groups), dim3(768), 0, x->stream, a, e2);
-        else if (best_tw == 2) hipLaunchKernelGGL(gemm_prefill2_kernel_tw2, dim3(groups), dim3(768), 0, x->stream, a, e2);
-        else hipLaunchKernelGGL(gemm_prefill2_kernel_tw1, dim3(groups), dim3(768), 0, x->stream, a, e2);
-        return check_launch(x, "prompt projection");
+        if (p.slices > 1) return launch_reduce_rows(x, p.slices, T, e, a.act_out_blk);
+        return resid && e.act_out ? launch_rms_scale(x, e.ssq_out, T) : KG_OK;
     }
     // two weight tiles per multiplying wave where that still leaves enough workgroups for the device
     const int tw = a.NT >= 512 ? 2 : 1;
@@ -608,7 +609,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
     int cbw = PF_CBW;
     if (tw == 1 && ((nb + PF_CBW - 1) / PF_CBW) * a.gy < x->n_cus && nb > 4) cbw = 4;
     a.gx = (nb + cbw - 1) / cbw;
-    const int groups = a.gx * 8 * ((a.gy + 7) / 8);
+    const int groups = 8 * ((a.gx * a.gy + 7) / 8);
     ProfScope ps(x, 3, 2.0 * T * (double)N * K);
     if (tw == 2) hipLaunchKernelGGL(gemm_prefill_kernel_tw2, dim3(groups), dim3(768), 0, x->stream, a, e);
     else if (cbw == 4) hipLaunchKernelGGL(gemm_prefill_kernel_tw1_cb4, dim3(groups), dim3(768), 0, x->stream, a, e);
@@ -654,7 +655,7 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
         pa.kv = (const kvhalf_t *)x->kv; pa.slot = slot; pa.n_slots = c.n_layers + 1;
         pa.rope = at<const float2>(x->scr, x->s_rope);
         pa.act_out = actA; pa.act_blk_bytes = act_bytes(d);
-        pa.act_pair = pf_gemm_plan(x, d, d, T) ? 1 : 0;               // read by the output projection
+        pa.act_pair = pf_pairs(x, T) ? 1 : 0;
         ProfScope ps(x, 1, 0.0);
         // workgroups of 128 rows (8 waves, a compute unit each) where those alone fill the device, else of 64 rows
         if ((size_t)c.n_heads * ((T + 127) / 128) >= (size_t)x->n_cus) {
@@ -675,18 +676,18 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
 
     e = epi_base(x, EPI_RESID, KG_ROWS, d);
     e.res = x_in; e.xout = x_mid; e.act_out = actX; e.act_K = d; e.gain = g2; e.ssq_out = ssq1;
-    e.act_pair = pf_gemm_plan(x, 2 * f, d, T) ? 1 : 0;                // read by gate+up
+    e.act_pair = pf_pairs(x, T) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, wo_off, d, d, actA, T, e, false, true, d));
 
     e = epi_base(x, EPI_SWIGLU, KG_ROWS, 2 * f);
     e.ssq_in = ssq1; e.act_out = actF; e.act_K = f;
-    e.act_pair = pf_gemm_plan(x, d, f, T) ? 1 : 0;                    // read by down_proj
+    e.act_pair = pf_pairs(x, T) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, gu_off, 2 * f, d, actX, T, e, true, false, f));
 
     e = epi_base(x, EPI_RESID, KG_ROWS, d);
     e.res = x_mid; e.xout = x_out; e.act_out = next_gain ? actX : nullptr; e.act_K = d; e.gain = next_gain;
     e.ssq_out = ssq0;
-    e.act_pair = pf_gemm_plan(x, 3 * d, d, T) ? 1 : 0;                // read by the next block's q,k,v
+    e.act_pair = pf_pairs(x, T) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, wd_off, d, f, actF, T, e, false, true, next_gain ? d : 0));
     return KG_OK;
 }

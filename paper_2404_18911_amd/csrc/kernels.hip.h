@@ -274,6 +274,15 @@ __host__ __device__ __forceinline__ int tile_pos_in_range(int w, int ks, int KS)
 }
 __host__ __device__ __forceinline__ int tile_pos(int ks, int KS) { return tile_pos_in_range((8 * ks + 7) / KS, ks, KS); }
 
+// k-step held by the tile stored at position p of a row tile: the inverse of tile_pos
+__host__ __device__ __forceinline__ int kstep_at_pos(int p, int KS)
+{
+    const int q = KS >> 3, E = KS - 8 * q;
+    if (p < E) return ((8 * (p + 1) + E - 1) / E - 1) * q + p;      // first tile of the (p + 1)-th long range
+    const int w = (p - E) & 7, j = (p - E) >> 3;
+    return w * q + (((w + 1) * E) >> 3) + j;                        // a long range's first tile lies in front: skipped here
+}
+
 // ---------------------------------------------------------------------------------------------
 // Projection, bf16 weights: one block (8 waves) per 16-row tile; the waves split K; each wave
 // streams its 1 KB weight tiles with 16-byte non-temporal loads and issues one MFMA per tile.
@@ -624,9 +633,8 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__
 //   will use), so a read touches 64 consecutive 16-byte pieces, free of bank conflicts.  Rows
 //   beyond the last one of a block are not masked: an MFMA column only depends on its own column of
 //   B, and the results of those columns are never stored.
-//   The grid is one-dimensional: workgroup id -> (XCD = id % 8, j = id / 8), row group = j % gx,
-//   tile group = (j / gx) * 8 + XCD, so the workgroups that stream the same weight tiles for
-//   different row groups run next to each other on one XCD and share its L2.
+//   The workgroups that stream the same weight tiles for different row groups run next to each other on
+//   one XCD and share its L2 (pf_work).
 #define PF_KC 2
 #define PF_CBW 8
 #define PF_NB 3
@@ -639,7 +647,8 @@ struct PfArgs {
     int T;                  // rows in this pass
     int ssq_in_blk, ssq_out_blk;   // floats per 8-row block of the sum-of-squares arrays
     size_t act_out_blk;     // bytes per 8-row block of the output activation
-    int gx, gy;             // row groups, tile groups (the grid holds gx * 8 * ceil(gy / 8) workgroups)
+    int gx, gy;             // row groups, tile groups (the grid holds 8 * ceil(gx * gy / 8) workgroups, see pf_work)
+    float *part;            // gemm_prefill2_body: partial sums [slice = blockIdx.y][T][N] for pf_reduce_rows_kernel; null: the epilogue
 };
 
 __device__ __forceinline__ Epi pf_block_epi(const Epi &e, const PfArgs &a, int b)
@@ -653,6 +662,19 @@ __device__ __forceinline__ Epi pf_block_epi(const Epi &e, const PfArgs &a, int b
     if (eb.act_out) eb.act_out = (char *)eb.act_out + (size_t)b * a.act_out_blk;
     if (eb.ssq_out) eb.ssq_out += (size_t)b * a.ssq_out_blk;
     return eb;
+}
+
+// (row group, group of weight tiles) of this workgroup.  Workgroups go to the 8 XCDs in turn; XCD x takes the x-th
+// eighth of the pairs in the order "all row groups of a tile group, then the next tile group".  (Whole tile
+// groups dealt out to the XCDs leave some with twice the work of others where there are few: 10 groups of 32
+// tiles, o_proj of the 13B shape at 3000 rows, took 488 us, two rounds on two XCDs.)
+__device__ __forceinline__ bool pf_work(const PfArgs &a, int &row_group, int &tile_group)
+{
+    const int total = a.gx * a.gy, per = (total + 7) >> 3, j = blockIdx.x >> 3, i = (blockIdx.x & 7) * per + j;
+    if (j >= per || i >= total) return false;
+    row_group = __builtin_amdgcn_readfirstlane(i % a.gx);       // (scalars: they are needed again after the main loop)
+    tile_group = __builtin_amdgcn_readfirstlane(i / a.gx);
+    return true;
 }
 
 struct PfStage { int r, k, n; };   // k-range index (0..7, 8 = end), first k-step, k-steps in the stage
@@ -679,10 +701,9 @@ __device__ __forceinline__ void gemm_prefill_body(const PfArgs &a, const Epi &e)
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const bool mover = wave >= 8;
     const int nb = (a.T + 7) >> 3;
-    const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
-    const int gyi = (jj / a.gx) * 8 + xcd;
-    if (gyi >= a.gy) return;
-    const int b0 = (jj % a.gx) * CBW;
+    int rgi, gyi;
+    if (!pf_work(a, rgi, gyi)) return;
+    const int b0 = rgi * CBW;
     const int nbw = min(CBW, nb - b0);
     const int rt0 = (gyi * 8 + (wave & 7)) * PF_TW;
     const int KS = a.KS;
@@ -962,11 +983,13 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Projection for long prompt passes: the same contraction as gemm_prefill_body for passes of 256 rows
-// and more (where the launch fills at least 45 % of the compute units), organised for reuse instead of
-// for the one-token kernel's summation order (a prompt row then differs from the same row decoded alone
-// in the order of its sums only, far inside the logit tolerance).  A workgroup owns 8 * TW weight tiles
-// x 128 rows.  The hi and lo halves of the activations are two B operands of 16 distinct rows each (two
+// Projection for prompt passes of more than 192 rows (half-precision cache): the same contraction as
+// gemm_prefill_body, organised for reuse instead of for the one-token kernel's summation order (a prompt row then
+// differs from the same row decoded alone in the order of its sums only, far inside the logit tolerance).  A
+// workgroup owns 6 .. 32 weight tiles x 128 rows (pf2_plan picks the number that fills whole rounds of
+// workgroups best); a projection with few weight tiles (o_proj, down_proj) is also cut along k, one slice per
+// blockIdx.y, into partial sums that pf_reduce_rows_kernel adds with what follows the projection.  The hi and lo
+// halves of the activations are two B operands of 16 distinct rows each (two
 // 8-row blocks) that are multiplied into the SAME accumulator, so nothing is folded and no per-range
 // totals are kept: a weight tile fetched from the L2 serves 128 rows and an activation tile serves up to
 // 512 weight rows.  The activations arrive in the pair layout of pf_act_ptr (a B operand = one KB).
@@ -976,20 +999,17 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 // once, and the k loop walks a row tile's weight tiles in the order they are stored (contiguous memory;
 // the sum over k may take any order here) and takes the k-step each one holds from a table, the inverse
 // of tile_pos filled at the start, to pick the matching activation tile.
-//   PIPE (TW 1, 2): the multiplying waves are arranged 4 x 2, a wave owns 2 TW weight tiles x 4 pairs of
-// row blocks (2 TW + 8 operand reads from LDS per 16 TW multiplications instead of TW + 16), all reads
-// of a k-step are issued together, the hi halves are multiplied into every accumulator before the lo
-// halves, and the operands of k-step ks + 1 are read under the second half of step ks (two register
-// sets).  Without PIPE (TW 4, whose 128 accumulator registers leave no room for a second set) a wave
-// owns TW weight tiles x all 8 pairs.
+//   PIPE (all but 32 tiles): the multiplying waves are arranged 4 x 2 (2 x 4 for 6 tiles), so that a wave reads
+// few operands from LDS per multiplication; all reads of a k-step are issued together, the hi halves are
+// multiplied into every accumulator before the lo halves, and the operands of k-step ks + 1 are read under the
+// second half of step ks (two register sets).  Without PIPE (32 tiles, whose 128 accumulator registers leave no
+// room for a second set) a wave owns 4 weight tiles x all 8 pairs.
 #define PF2_KS_MAX 1024
-template <int TW, int NB, bool PIPE, int RB = 16>            // RB = 8-row blocks per workgroup: 16, or 8 for launches with few weight tiles
+// AW x (8 / AW) multiplying waves; a wave owns WA weight tiles x WP pairs of 8-row blocks; NB stage buffers
+template <int AW, int WA, int WP, int NB, bool PIPE>
 __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e)
 {
-    constexpr int NTW = 8 * TW;
-    static_assert(RB == 16 || (RB == 8 && PIPE), "128 rows, or 64 with the 4 x 2 wave arrangement");
-    constexpr int WA = PIPE ? 2 * TW : TW;                  // weight tiles of a multiplying wave
-    constexpr int WP = PIPE ? RB / 4 : RB / 2;              // its pairs of row blocks (hi and lo operand each)
+    constexpr int NTW = AW * WA, RB = 2 * WP * (8 / AW);    // weight tiles and 8-row blocks of the workgroup
     __shared__ u32x4_t As[NB][NTW][64];                     // ring of NB stage buffers, one k-step each
     __shared__ u32x4_t Bs[NB][RB / 2][2][64];
     __shared__ float scs[RB][KG_ROWS];
@@ -997,25 +1017,26 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const bool mover = wave >= 8;
     const int nb = (a.T + 7) >> 3;
-    const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
-    const int gyi = (jj / a.gx) * 8 + xcd;
-    if (gyi >= a.gy) return;
-    const int b0 = (jj % a.gx) * RB;
+    int rgi, gyi;
+    if (!pf_work(a, rgi, gyi)) return;
+    const int b0 = rgi * RB;
     const int nbw = min(RB, nb - b0);
     const int KS = a.KS;
+    // a projection cut along k: this workgroup's slice of the positions of a row tile
+    const int p_lo = PIPE ? __builtin_amdgcn_readfirstlane((int)(blockIdx.y * KS / gridDim.y)) : 0;
+    const int p_hi = PIPE ? __builtin_amdgcn_readfirstlane((int)((blockIdx.y + 1) * KS / gridDim.y)) : KS;
     const int col = lane & 15, g4 = lane >> 4;
-    const int a0 = PIPE ? (wave & 3) * WA : wave * TW;      // first weight tile and first pair of a multiplying wave
-    const int g0 = PIPE ? ((wave >> 2) & 1) * WP : 0;
+    const int a0 = (wave % AW) * WA;                        // first weight tile and first pair of a multiplying wave
+    const int g0 = ((wave & 7) / AW) * WP;
 
     // RMS scales of the group's rows (computed once per pass by pf_rms_scale_kernel: every workgroup summing
     // the tile sums of its 128 rows again cost a tenth of a short pass); the table of k-steps by position
     if (t < nbw * KG_ROWS) scs[t >> 3][t & 7] = e.scale_in ? e.scale_in[(size_t)b0 * KG_ROWS + t] : 1.f;
-    for (int i = t; i < KS; i += 768) kstep_at[tile_pos(i, KS)] = (uint16_t)i;
+    for (int i = p_lo + t; i < p_hi; i += 768) kstep_at[i] = (uint16_t)kstep_at_pos(i, KS);
     __syncthreads();
 
     constexpr int TL = NTW + RB;                            // tile loads of a stage
-    constexpr int LPW = TL / 4;
-    static_assert(TL % 4 == 0 && NTW % 4 == 0, "tile loads spread evenly over the 4 mover waves, weight tiles first");
+    constexpr int LPW = (TL + 3) / 4;                       // ... per mover wave (one too many for some: it repeats the last tile)
     auto meet = [&]() {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -1030,8 +1051,8 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
         const u32x4_t *src0[LPW];                           // the wave's tiles at k-step 0 (tile j = wave - 8 + 4 i: uniform in the wave)
 #pragma unroll
         for (int i = 0; i < LPW; i++) {
-            const int j = (wave - 8) + 4 * i;
-            if (i < NTW / 4) {
+            const int j = min((wave - 8) + 4 * i, TL - 1);
+            if (j < NTW) {
                 const int rt = min(gyi * NTW + j, a.NT - 1);
                 src0[i] = a.W + (size_t)rt * KS * 64 + lane;
             } else {
@@ -1040,21 +1061,21 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                 src0[i] = a.act + (size_t)pr * 2 * a.act_blk + part * 64 + lane;
             }
         }
-        auto issue = [&](int ks, int bf) {                  // operands of step ks (clamped: late stages reload a valid one)
-            const int kk = min(ks, KS - 1);
+        auto issue = [&](int ks, int bf) {                  // operands of position ks (clamped: late stages reload a valid one)
+            const int kk = min(ks, p_hi - 1);
             const int wpos = kk * 64, apos = __builtin_amdgcn_readfirstlane((int)kstep_at[kk]) * 128;
 #pragma unroll
             for (int i = 0; i < LPW; i++) {
-                const int j = (wave - 8) + 4 * i;
-                if (i < NTW / 4) __builtin_amdgcn_global_load_lds(src0[i] + wpos, &As[bf][j][0], 16, 0, 0);
+                const int j = min((wave - 8) + 4 * i, TL - 1);
+                if (j < NTW) __builtin_amdgcn_global_load_lds(src0[i] + wpos, &As[bf][j][0], 16, 0, 0);
                 else __builtin_amdgcn_global_load_lds(src0[i] + apos, &Bs[bf][(j - NTW) >> 1][(j - NTW) & 1][0], 16, 0, 0);
             }
         };
 #pragma unroll
-        for (int s0 = 0; s0 < NB - 1; s0++) issue(s0, s0);
+        for (int s0 = 0; s0 < NB - 1; s0++) issue(p_lo + s0, s0);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * LPW) : "memory");
         __syncthreads();
-        for (int ks = 0; ks < KS; ks++) {
+        for (int ks = p_lo; ks < p_hi; ks++) {
             issue(ks + NB - 1, buf >= 1 ? buf - 1 : NB - 1);
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * LPW) : "memory");
             meet();
@@ -1103,13 +1124,13 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
         Frag fa, fb;
         fetch(fa, 0);
         // (the reads after the last step's barrier fetch a stage the movers filled with a valid, unused k-step)
-        for (int ks = 0; ks < KS; ks += 2) {
+        for (int ks = p_lo; ks < p_hi; ks += 2) {
             step(fa, fb);
-            if (ks + 1 < KS) step(fb, fa);
+            if (ks + 1 < p_hi) step(fb, fa);
         }
     } else {
         __syncthreads();
-        for (int ks = 0; ks < KS; ks++) {
+        for (int ks = p_lo; ks < p_hi; ks++) {
             bf16x8_t av[WA];
 #pragma unroll
             for (int ta = 0; ta < WA; ta++) av[ta] = __builtin_bit_cast(bf16x8_t, As[buf][a0 + ta][lane]);
@@ -1129,27 +1150,30 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
     }
 
     // Epilogue from the accumulators: lane (column c, group g4) holds weight rows 4 g4 .. 4 g4 + 3 of a
-    // tile for row c % 8 of block b0 + 2 (g0 + gb) + c / 8.
+    // tile for row c of its pair of blocks.  (Rows are addressed from the launch's own pointers: copies per
+    // 8-row block spilled registers here, 35 us per round of workgroups of 32 tiles.)
+    const int rt0 = gyi * NTW + a0;
 #pragma unroll
-    for (int ta = 0; ta < WA; ta++) {
-        const int rt = gyi * NTW + a0 + ta;
-        const bool valid = rt < a.NT;
-        const int n0 = rt * 16 + 4 * g4;
+    for (int gb = 0; gb < WP; gb++) {
+        const int lrow = (g0 + gb) * 16 + col, row = b0 * KG_ROWS + lrow;      // row in the group, in the pass
+        const bool row_ok = row < a.T;
+        const float sc = (e.kind != EPI_RESID && row_ok) ? scs[lrow >> 3][lrow & 7] : 1.f;
 #pragma unroll
-        for (int gb = 0; gb < WP; gb++) {
-            const int blk = 2 * (g0 + gb) + (col >> 3), m = col & 7;
-            const bool in_group = blk < nbw;
-            const Epi eb = pf_block_epi(e, a, b0 + min(blk, nbw - 1));
-            const bool live = valid && in_group && m < eb.M;
+        for (int ta = 0; ta < WA; ta++) {
+            const int rt = rt0 + ta, n0 = rt * 16 + 4 * g4;
+            const bool live = rt < a.NT && row_ok;
             const f32x4_t y = acc[ta][gb];
-            if (e.kind == EPI_RESID) {
+            if (PIPE && a.part) {
+                if (live) *(float4 *)(a.part + ((size_t)blockIdx.y * a.T + row) * e.N + n0) = make_float4(y[0], y[1], y[2], y[3]);
+            } else if (e.kind == EPI_RESID) {
                 float v[4] = {0.f, 0.f, 0.f, 0.f};
                 if (live) {
-                    const float4 rv = *(const float4 *)(eb.res + (size_t)m * eb.N + n0);
+                    const size_t at = (size_t)row * e.N + n0;
+                    const float4 rv = *(const float4 *)(e.res + at);
                     v[0] = rv.x + y[0]; v[1] = rv.y + y[1]; v[2] = rv.z + y[2]; v[3] = rv.w + y[3];
-                    *(float4 *)(eb.xout + (size_t)m * eb.N + n0) = make_float4(v[0], v[1], v[2], v[3]);
-                    if (eb.act_out) {
-                        const float4 gv = eb.gain ? *(const float4 *)(eb.gain + n0) : make_float4(1.f, 1.f, 1.f, 1.f);
+                    *(float4 *)(e.xout + at) = make_float4(v[0], v[1], v[2], v[3]);
+                    if (e.act_out) {
+                        const float4 gv = e.gain ? *(const float4 *)(e.gain + n0) : make_float4(1.f, 1.f, 1.f, 1.f);
                         const float gq4[4] = {gv.x, gv.y, gv.z, gv.w};
                         uint16_t hi[4], lo[4];
 #pragma unroll
@@ -1159,7 +1183,7 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                             lo[r] = f2bf(xv - bf2f(hi[r]));
                         }
                         int lo_off;
-                        uint16_t *pa = pf_act_ptr(e.act_out, a.act_out_blk, b0 + blk, m, n0, e.act_pair, lo_off);
+                        uint16_t *pa = pf_act_ptr(e.act_out, a.act_out_blk, row >> 3, row & 7, n0, 1, lo_off);
                         *(uint2 *)pa = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
                         *(uint2 *)(pa + lo_off) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
                     }
@@ -1168,12 +1192,11 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                     float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
                     sq += __shfl_xor(sq, 16);
                     sq += __shfl_xor(sq, 32);
-                    if (live && g4 == 0) eb.ssq_out[(size_t)rt * KG_ROWS + m] = sq;
+                    if (live && g4 == 0) e.ssq_out[(size_t)(row >> 3) * a.ssq_out_blk + (size_t)rt * KG_ROWS + (row & 7)] = sq;
                 }
             } else if (live) {
-                const float sc = scs[blk][m];
                 if (e.kind == EPI_PLAIN) {
-                    *(float4 *)(eb.out + (size_t)m * eb.N + n0) = make_float4(y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
+                    *(float4 *)(e.out + (size_t)row * e.N + n0) = make_float4(y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
                 } else {                          // EPI_SWIGLU: rows (2i, 2i+1) = (gate, up) of feature rt*8 + i
                     uint16_t hi[2], lo[2];
 #pragma unroll
@@ -1183,9 +1206,8 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                         hi[i] = f2bf(av2);
                         lo[i] = f2bf(av2 - bf2f(hi[i]));
                     }
-                    const int k0 = rt * 8 + 2 * g4;
                     int lo_off;
-                    uint16_t *pa = pf_act_ptr(e.act_out, a.act_out_blk, b0 + blk, m, k0, e.act_pair, lo_off);
+                    uint16_t *pa = pf_act_ptr(e.act_out, a.act_out_blk, row >> 3, row & 7, rt * 8 + 2 * g4, 1, lo_off);
                     *(uint32_t *)pa = hi[0] | ((uint32_t)hi[1] << 16);
                     *(uint32_t *)(pa + lo_off) = lo[0] | ((uint32_t)lo[1] << 16);
                 }
@@ -1193,10 +1215,11 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
         }
     }
 }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw1(PfArgs a, Epi e) { gemm_prefill2_body<1, 6, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw2(PfArgs a, Epi e) { gemm_prefill2_body<2, 4, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw4(PfArgs a, Epi e) { gemm_prefill2_body<4, 3, false>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw1_rb8(PfArgs a, Epi e) { gemm_prefill2_body<1, 8, true, 8>(a, e); }
+__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw1(PfArgs a, Epi e) { gemm_prefill2_body<4, 2, 4, 6, true>(a, e); }
+__global__ __launch_bounds__(768) void gemm_prefill2_kernel_n12(PfArgs a, Epi e) { gemm_prefill2_body<4, 3, 4, 5, true>(a, e); }
+__global__ __launch_bounds__(768) void gemm_prefill2_kernel_n6(PfArgs a, Epi e) { gemm_prefill2_body<2, 3, 2, 6, true>(a, e); }
+__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw2(PfArgs a, Epi e) { gemm_prefill2_body<4, 4, 4, 4, true>(a, e); }
+__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw4(PfArgs a, Epi e) { gemm_prefill2_body<8, 4, 8, 3, false>(a, e); }
 
 // ---------------------------------------------------------------------------------------------
 // Projection for short prompt passes (half-precision cache, 9 rows and more): Y[T][N] = X[T][K] . W^T where
@@ -1224,15 +1247,6 @@ struct PfStreamArgs {
     float *part;            // partial sums [slice][T][N] for pf_reduce_rows_kernel; null: the epilogue (one slice)
     size_t act_out_blk;     // bytes per 8-row block of the output activation (SwiGLU)
 };
-
-// k-step held by the tile stored at position p of a row tile: the inverse of tile_pos
-__host__ __device__ __forceinline__ int kstep_at_pos(int p, int KS)
-{
-    const int q = KS >> 3, E = KS - 8 * q;
-    if (p < E) return ((8 * (p + 1) + E - 1) / E - 1) * q + p;      // first tile of the (p + 1)-th long range
-    const int w = (p - E) & 7, j = (p - E) >> 3;
-    return w * q + (((w + 1) * E) >> 3) + j;                        // a long range's first tile lies in front: skipped here
-}
 
 // Waves of a workgroup: 8, of 256 registers each, while those hold the accumulators and the operands of a step
 // and a half; else 4 waves of 512 registers (gate+up of the 7B shape at 96 .. 128 rows: one round of 230
