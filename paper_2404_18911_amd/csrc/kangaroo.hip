@@ -318,12 +318,36 @@ void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &
     } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e);
 }
 
+// Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, else gemv_multi_kernel, whose time hardly
+// depends on M.  Measured (us, stand-alone product, 4096 features): 12288 outputs (3 tiles) 18.4 against 18.0 of
+// gemv_bf16_body with 4 rows, 19.0 with 6, 20.7 with 8; 22016 outputs (6 tiles, on 230 of 256 compute units) 31.7
+// against 31.2, 33.3, 36.4; 13840 x 5136 (4 tiles) 27.0 against 27.1, 29.3, 32.2: from 5 rows on.  Not with 2 tiles (8192
+// outputs: 16.5 against 15.2 with 8 rows) and not with 8 (32000 outputs: 45.5 against 44.0 with 6 rows, 49 with 8) or
+// more than a round of workgroups.
+inline int gemv_tiles(int n_cus, int N, int M)
+{
+    const int ntw = (N / 16 + n_cus - 1) / n_cus;
+    return M >= 5 && ntw >= 3 && ntw <= 7 ? ntw : 1;
+}
+template <int SRC>
+void launch_gemv_multi(const u32x4_t *W, int N, int KS, int M, const void *act, int K, const Epi &e, int ntw, hipStream_t s)
+{
+    const dim3 grid((N / 16 + ntw - 1) / ntw), block(64 * GEMV_WAVES);
+    switch (ntw) {
+#define MULTI_CASE(n) case n: hipLaunchKernelGGL((gemv_multi_kernel<SRC, n>), grid, block, 0, s, W, KS, M, act, e.ssq_in, e.nt_in, N, K, e); break;
+        MULTI_CASE(3) MULTI_CASE(4) MULTI_CASE(5) MULTI_CASE(6) MULTI_CASE(7)
+#undef MULTI_CASE
+    }
+}
+
 int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Epi &e)
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
     ProfScope ps(x, 0, (double)N * K * x->esz);
     x->acct[x->acct_phase] += (double)N * K * x->esz;
-    if (x->bf)
+    if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, e.M) : 1; ntw > 1)
+        launch_gemv_multi<FROM_ACT>(at<const u32x4_t>(x->arena, w_off), N, (K + 31) / 32, e.M, act, 0, e, ntw, x->stream);
+    else if (x->bf)
         hipLaunchKernelGGL(gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream,
                            at<const u32x4_t>(x->arena, w_off), (K + 31) / 32, e.M, (const u32x4_t *)act, e.ssq_in, e.nt_in,
                            e.N, e.kind == EPI_RESID ? e.res : nullptr, e.gain, e);
@@ -2134,7 +2158,13 @@ static int op_linear_launch(int dtype, const void *packed, int N, int K, const f
         const dim3 grid(N / 16), block(64 * GEMV_WAVES);
         const u32x4_t *W = (const u32x4_t *)packed;
         const int KS = (K + 31) / 32;
-        if (((uintptr_t)xd & 15) == 0) hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
+        if (const int ntw = gemv_tiles(256, N, M); ntw > 1) {
+            Epi e;
+            memset(&e, 0, sizeof(e));
+            e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;
+            if (((uintptr_t)xd & 15) == 0) launch_gemv_multi<FROM_ROWS>(W, N, KS, M, xd, K, e, ntw, s);
+            else launch_gemv_multi<FROM_ROWS_UNALIGNED>(W, N, KS, M, xd, K, e, ntw, s);
+        } else if (((uintptr_t)xd & 15) == 0) hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
         else hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS_UNALIGNED>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
     } else {
         Epi e;

@@ -185,9 +185,8 @@ __device__ __forceinline__ void store_act_pf(void *base, size_t blk_bytes, int b
 template <bool BF>
 __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_ROWS], const float *sc,
                                          float (*sq)[KG_ROWS], float resv = 0.f, float gainv = 1.f,
-                                         bool prefetched = false)
+                                         bool prefetched = false, int t = threadIdx.x)
 {
-    int t = threadIdx.x;
     if (e.kind == EPI_PLAIN || e.kind == EPI_HEAD) {
         if (t < 128) {
             int row = t >> 3, m = t & 7;
@@ -294,8 +293,9 @@ __host__ __device__ __forceinline__ int kstep_at_pos(int p, int KS)
 // themselves into the very parts store_act would have stored.  Of the 8 consecutive k of a row that lanes j (hi
 // part) and j + 8 (lo part) share, each lane reads four, splits them, keeps the part it stands for and passes
 // the other one on: as many bytes through the L1 as the activation tiles take, and 20 vector operations a tile
-// (4096 x 4096, one row: 11.1 us a call with two launches that clear and fill activation tiles, 8.0 without; 13840 x
-// 5136, 8 rows: 35.9 -> 32.3; with every lane reading and splitting all 8 k it was 37.9 us there).
+// (4096 x 4096, one row: 11.1 us a call with two launches that clear and fill activation tiles, 8.0 without; 32000 x
+// 4096: 42.8 -> 39.1; with every lane reading and splitting all 8 k, 13840 x 5136 with 7 rows took 35.9 us against
+// 34.1 with the two launches).
 enum { FROM_ACT = 0, FROM_ROWS = 1, FROM_ROWS_UNALIGNED = 2 };
 template <int SRC> struct BRaw { float v[4]; };
 template <> struct BRaw<FROM_ACT> { u32x4_t v; };
@@ -472,6 +472,102 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 4) void gemv_bf16_rows_kernel(cons
     Epi e = {};
     e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = y;
     gemv_bf16_body<SRC>(W, KS, M, x, nullptr, 0, N, nullptr, nullptr, K, e);
+}
+
+// Projections of several rows with more weight tiles than compute units: one workgroup per compute unit and NTW tiles per
+// workgroup.  gemv_bf16_kernel fetches the activations of a k-step through the L1 once per weight tile (M / 8 of the
+// weights' bytes, and they come after them: gate+up of the 7B shape takes 29.3 us with one row and 36.5 us with eight);
+// here they serve NTW tiles.  Every tile's sums run over the same k in the same order as there: the results are
+// the same bits for any number of rows.  The tiles are shared out evenly (no group has more than NTW).
+// D k-steps of loads are in flight per wave.  (Two tiles per workgroup in gemv_bf16_body instead, 16 waves a compute
+// unit: slower at every row count, 33 .. 36 us for gate+up.)
+template <int NTW> __host__ __device__ constexpr int gemv_multi_depth() { return (204 - 4 * NTW) / (4 * (NTW + 1)) > 8 ? 8 : (204 - 4 * NTW) / (4 * (NTW + 1)); }
+
+template <int SRC, int NTW>
+__global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_multi_kernel(const u32x4_t *__restrict__ W, int KS, int M,
+                                                                    const void *__restrict__ act, const float *ssq_in, int nt_in, int N,
+                                                                    int K, Epi e)
+{
+    constexpr int D = gemv_multi_depth<NTW>(), NY = (NTW + 3) / 4 * 4;      // tiles in the epilogue: four at a time
+    __shared__ float part[GEMV_WAVES][NTW][16][KG_ROWS];
+    __shared__ float yt[NY][16][KG_ROWS];
+    __shared__ float sq[NY][16][KG_ROWS];
+    __shared__ float sc[KG_ROWS];
+    const int NT = N >> 4, groups = gridDim.x;
+    const int rt0 = (int)((long long)blockIdx.x * NT / groups), ntw = (int)((long long)(blockIdx.x + 1) * NT / groups) - rt0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int ks0 = (wave * KS) / GEMV_WAVES, n = ((wave + 1) * KS) / GEMV_WAVES - ks0;     // the wave's k-steps
+    const int q = KS >> 3, n_long = KS - 8 * q;
+    // position of the wave's i-th k-step (see tile_pos): p_rest + 8 i, except the first of a long range
+    const int p_first = n > q ? ks0 - wave * q : n_long + wave, p_rest = n > q ? n_long + wave - 8 : n_long + wave;
+    const u32x4_t *wsrc[NTW];
+#pragma unroll
+    for (int t = 0; t < NTW; t++) wsrc[t] = W + (size_t)(rt0 + min(t, ntw - 1)) * KS * 64 + lane;
+    const BSource<SRC> bsrc(act, M, lane, K);
+    ScaleRegs sr;
+    scale_fetch(ssq_in, M, nt_in, sr);
+    f32x4_t acc[NTW];
+#pragma unroll
+    for (int t = 0; t < NTW; t++) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t av[D][NTW];
+    BRaw<SRC> bv[D];
+    auto load = [&](int s, int i) {
+        const int p = i ? p_rest + 8 * i : p_first;
+#pragma unroll
+        for (int t = 0; t < NTW; t++) av[s][t] = __builtin_nontemporal_load(wsrc[t] + p * 64);
+        bv[s] = bsrc.load(ks0 + i);
+    };
+    auto mul = [&](int s) {
+        const bf16x8_t b = bsrc.operand(bv[s]);
+#pragma unroll
+        for (int t = 0; t < NTW; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[s][t]), b, acc[t], 0, 0, 0);
+    };
+#pragma unroll
+    for (int s = 0; s < D; s++)
+        if (s < n) load(s, s);
+    int i = 0;
+    for (; i + 2 * D <= n; i += D) {
+#pragma unroll
+        for (int s = 0; s < D; s++) {
+            mul(s);
+            load(s, i + s + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // fewer than 2 D steps are left, the first D of them loaded or on their way
+#pragma unroll
+    for (int s = 0; s < D; s++)
+        if (i + s < n) {
+            mul(s);
+            if (i + s + D < n) load(s, i + s + D);
+        }
+    i += D;
+#pragma unroll
+    for (int s = 0; s < D; s++)
+        if (i + s < n) mul(s);
+    scale_finish(e, sr, sc);
+    // fold the hi and lo columns, add the waves' sums in wave order (as gemv_bf16_body)
+#pragma unroll
+    for (int t = 0; t < NTW; t++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const float v = acc[t][r] + __shfl_xor(acc[t][r], 8);
+            if ((lane & 15) < 8) part[wave][t][4 * (lane >> 4) + r][lane & 7] = v;
+        }
+    __syncthreads();
+    for (int j = threadIdx.x; j < NTW * 128; j += 64 * GEMV_WAVES) {
+        const int t = j >> 7, row = (j >> 3) & 15, m = j & 7;
+        float v = part[0][t][row][m];
+#pragma unroll
+        for (int w = 1; w < GEMV_WAVES; w++) v += part[w][t][row][m];
+        yt[t][row][m] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t0 = 0; t0 < NTW; t0 += 4) {
+        const int t = t0 + (threadIdx.x >> 7);                              // 128 threads per tile (none where there is no tile)
+        epilogue<true>(e, rt0 + t, yt[t], sc, sq[t], 0.f, 1.f, false, t < ntw ? (int)(threadIdx.x & 127) : 1 << 20);
+    }
 }
 
 // The one-row projection on the vector ALUs instead of the matrix units, over the same weight tiles,

@@ -40,3 +40,29 @@ def test_linear_of_aligned_and_unaligned_rows(dtype, M, N, K):
     # rows in two bf16 parts: 2^-17 of a product; float32 sums
     bound = (np.abs(x).astype(np.float64) @ np.abs(w64).T) * 2.0 ** -15 + 1e-7
     assert np.all(np.abs(got[0] - ref) <= bound)
+
+
+@pytest.mark.parametrize("N,K", [(12288, 528), (13840, 1040), (27648, 272), (22016, 4096)])
+def test_a_row_of_linear_does_not_depend_on_the_others(N, K):
+    """5 .. 8 rows through 3 .. 7 weight tiles per workgroup give the bits of one row alone (uneven shares of tiles,
+    k ranges of unequal length, a half k-step)."""
+    import torch
+    from paper_2404_18911_amd import binding as B
+    L = B.lib()
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    w = (torch.randn(N, K, generator=g, device="cuda") * 0.05).bfloat16()
+    x = torch.randn(8, K, generator=g, device="cuda")
+    packed = torch.empty(L.kg_op_packed_bytes(1, N, K), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    assert L.kg_op_pack(1, w.data_ptr(), N, K, packed.data_ptr(), s) == B.KG_OK
+
+    def linear(rows):
+        y = torch.full((rows.shape[0], N), float("nan"), device="cuda")
+        assert L.kg_op_linear(1, packed.data_ptr(), N, K, rows.data_ptr(), rows.shape[0], y.data_ptr(), packed.data_ptr(), s) == B.KG_OK
+        return y
+    one = torch.cat([linear(x[m:m + 1]) for m in range(8)])
+    for M in (5, 6, 7, 8):
+        assert torch.equal(linear(x[:M]), one[:M])
+    ref = x.double() @ w.double().T
+    bound = (x.abs().double() @ w.abs().double().T) * 2.0 ** -15 + 1e-7
+    assert bool(((one.double() - ref).abs() <= bound).all())
