@@ -1964,8 +1964,8 @@ static int train_graph(kg_ctx *x, int n, double *loss)
     else KGCHK(tr_gemm(x, f(t.Mm), d, 1, head, 1, d, hm_nt, f(t.Z), V, n, V, d, 0));
     // Eq. 3 and its gradient with respect to the draft logits
     other();
-    hipLaunchKernelGGL(tr_loss_kernel, dim3(n), dim3(256), 0, x->stream, (const float *)f(t.Z), (const float *)f(t.Zt), V, f(t.dZ),
-                       f(t.loss));
+    hipLaunchKernelGGL((V <= TR_LOSS_V ? tr_loss_kernel<true> : tr_loss_kernel<false>), dim3(n), dim3(1024), 0, x->stream, (const float *)f(t.Z),
+                       (const float *)f(t.Zt), V, f(t.dZ), f(t.loss));
     KGCHK(check_launch(x, "train_loss"));
     // ---- backward
     if (own_head) {

@@ -560,30 +560,65 @@ __global__ __launch_bounds__(256) void tr_dsoftmax_kernel(const float *P, float 
 }
 
 // Eq. 3 for one position: loss[t] = - sum_n p_n log q_n with p = softmax(zt[t]), q = softmax(z[t]);
-// dz[t] = q - p (the gradient of the loss with respect to the draft logits).  One block per row.
-__global__ __launch_bounds__(256) void tr_loss_kernel(const float *z, const float *zt, int V, float *dz, float *loss)
+// dz[t] = q - p (the gradient of the loss with respect to the draft logits).  One block of 1024 threads per row, which
+// keeps both rows in registers (up to TR_LOSS_V logits each), so that the launch reads them once, all loads issued
+// together, instead of three times: 1000 rows of 32000 logits 234 -> 164 us.  Longer rows are read three times.
+#define TR_LOSS_V 32768
+template <bool REGS>
+__global__ __launch_bounds__(1024) void tr_loss_kernel(const float *z, const float *zt, int V, float *dz, float *loss)
 {
-    __shared__ float red[4];
-    const int row = blockIdx.x;
+    constexpr int NR = REGS ? TR_LOSS_V / 4096 : 1;         // groups of 4 logits per thread
+    __shared__ float red[16];
+    const int row = blockIdx.x, t = threadIdx.x;
     const float *zr = z + (size_t)row * V, *tr = zt + (size_t)row * V;
+    float4 a[NR], b[NR];
+    const float4 low = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (REGS) {
+#pragma unroll
+        for (int i = 0; i < NR; i++) {
+            const int n = 4 * (t + 1024 * i);
+            a[i] = n < V ? *(const float4 *)(zr + n) : low;
+            b[i] = n < V ? *(const float4 *)(tr + n) : low;
+        }
+    }
+    // f(draft logit, target logit, index) over the row, four logits at a time (V is a multiple of 16)
+    auto each = [&](auto f) {
+        if (REGS) {
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                const int n = 4 * (t + 1024 * i);
+                if (n < V) f(a[i], b[i], n);
+            }
+        } else {
+            for (int n = 4 * t; n < V; n += 4096) f(*(const float4 *)(zr + n), *(const float4 *)(tr + n), n);
+        }
+    };
     float mz = -INFINITY, mt = -INFINITY;
-    for (int n = threadIdx.x; n < V; n += 256) { mz = fmaxf(mz, zr[n]); mt = fmaxf(mt, tr[n]); }
+    each([&](const float4 &u, const float4 &v, int) {
+        mz = fmaxf(fmaxf(mz, fmaxf(u.x, u.y)), fmaxf(u.z, u.w));
+        mt = fmaxf(fmaxf(mt, fmaxf(v.x, v.y)), fmaxf(v.z, v.w));
+    });
     mz = tr_block_max(mz, red);
     mt = tr_block_max(mt, red);
     float sz = 0.f, st = 0.f;
-    for (int n = threadIdx.x; n < V; n += 256) { sz += expf(zr[n] - mz); st += expf(tr[n] - mt); }
+    each([&](const float4 &u, const float4 &v, int) {
+        sz += (expf(u.x - mz) + expf(u.y - mz)) + (expf(u.z - mz) + expf(u.w - mz));
+        st += (expf(v.x - mt) + expf(v.y - mt)) + (expf(v.z - mt) + expf(v.w - mt));
+    });
     sz = tr_block_sum(sz, red);
     st = tr_block_sum(st, red);
     const float lz = logf(sz);
     float l = 0.f;
-    for (int n = threadIdx.x; n < V; n += 256) {
-        const float p = expf(tr[n] - mt) / st;
-        const float lq = zr[n] - mz - lz;
+    auto one = [&](float zv, float tv) {
+        const float p = expf(tv - mt) / st, lq = zv - mz - lz;
         l -= p * lq;
-        dz[(size_t)row * V + n] = expf(lq) - p;
-    }
+        return expf(lq) - p;
+    };
+    each([&](const float4 &u, const float4 &v, int n) {
+        *(float4 *)(dz + (size_t)row * V + n) = make_float4(one(u.x, v.x), one(u.y, v.y), one(u.z, v.z), one(u.w, v.w));
+    });
     l = tr_block_sum(l, red);
-    if (threadIdx.x == 0) loss[row] = l;
+    if (t == 0) loss[row] = l;
 }
 
 // AdamW with bias correction and decoupled weight decay; c1 = 1 - beta1^step, c2 = 1 - beta2^step
