@@ -564,17 +564,19 @@ int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, i
 // units have one (random data at the 7B and 13B shapes; a round also takes about 4 us besides its k-steps).
 struct Pf2Variant { void (*kernel)(PfArgs, Epi); int ntw; double step_us; };
 const Pf2Variant pf2_variants[] = {{gemm_prefill2_kernel_n6, 6, 0.38}, {gemm_prefill2_kernel_tw1, 8, 0.46}, {gemm_prefill2_kernel_n12, 12, 0.63},
-                                   {gemm_prefill2_kernel_tw2, 16, 0.775}, {gemm_prefill2_kernel_tw4, 32, 1.51}};
+                                   {gemm_prefill2_kernel_tw2, 16, 0.775}, {gemm_prefill2_kernel_tw4, 32, 1.465}};
 
 // Which variant, in how many slices along k (`split` allowed: EPI_RESID).  A workgroup fills a compute unit, so a
-// launch takes whole rounds of them; a partly filled last round runs at a higher clock (0.68 of a round when nearly
+// launch takes whole rounds of them; a partly filled last round runs at a higher clock (0.75 of a round when nearly
 // empty).  Partial sums are written at 5 TB/s and added by pf_reduce_rows_kernel (4 us + what it moves at 6 TB/s, against
 // 5 us for the scales of rows that are finished in place).  The model is within a tenth of the measured launches (us,
 // real passes): 7B shape, 256 rows: q,k,v 6 tiles 54, 8 tiles 59, 12 tiles 71; gate+up 12 tiles 81, 16 tiles 89; down_proj
 // 16 tiles in 7 slices 45, 8 tiles in 4 slices 48, 8 tiles uncut 138; 1024 rows: gate+up 16 tiles 288, 12 tiles 313, 32
 // tiles 359; down_proj 16 tiles in 2 slices 138, 8 tiles uncut 163; 4096 rows: q,k,v 32 tiles 607, 16 tiles 660;
-// gate+up 16 tiles 1133, 32 tiles 1152.  (At 4096 rows the card is at its power limit: passes with either choice for
-// gate+up take the same 99 ms, all in 16 tiles 101.5 ms.)
+// gate+up 16 tiles 1133, 32 tiles 1152.  Passes that long run at the card's power limit, where the tile that moves
+// fewer bytes per multiplication also leaves the other launches a higher clock: 32 tiles are entered 3 % cheaper than
+// they measure alone (4096 rows, whole pass: 94.5 ms with 32 tiles for gate+up, 96.9 ms with 16; 3000 rows, where 32
+// tiles need a fifth round for the last 8 workgroups: 76.4 against 74.6 ms).
 struct Pf2Plan { int variant, slices; };
 Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
 {
@@ -586,7 +588,7 @@ Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
             if (S > 1 && (S * T > PF_PART_ROWS || KS < 8 * S || pf2_variants[v].ntw == 32)) break;
             const Pf2Variant &pv = pf2_variants[v];
             const double wgs = (double)gx * ((NT + pv.ntw - 1) / pv.ntw) * S, whole = std::floor(wgs / n_cus), rest = wgs / n_cus - whole;
-            const double rounds = whole + (rest > 0 ? 0.68 + 0.32 * rest : 0.0), bytes = (double)T * NT * 64;
+            const double rounds = whole + (rest > 0 ? 0.75 + 0.25 * rest : 0.0), bytes = (double)T * NT * 64;
             const double cost = rounds * ((double)KS / S * pv.step_us + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {v, S}; }
         }
