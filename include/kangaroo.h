@@ -314,8 +314,10 @@ int kg_op_gemm_f32(const float *A_dev, long sam, long sak, const float *B_dev, l
  *   kg_op_packed_bytes: bytes of the tiled form of a [N][K] matrix (N % 16 == 0, K % 8 == 0).
  *   kg_op_pack:   re-tile a row-major dev matrix (dtype 0 f32 / 1 bf16) into packed_dev.
  *   kg_op_linear: x_dev float[M][K], y_dev float[M][N]; work_dev >= kg_op_work_bytes(K) bytes of
- *                 device scratch (must not be NULL; the present kernels read x_dev directly and leave it
- *                 alone); M <= KG_MAX_ROWS.  Launches on `hip_stream`, does not synchronise.
+ *                 device scratch, must not be NULL; M <= KG_MAX_ROWS.  y_dev may overlap
+ *                 x_dev (also in part): the rows are then copied to work_dev first; otherwise the kernel
+ *                 reads x_dev directly and leaves work_dev alone.  Launches on `hip_stream`, does not
+ *                 synchronise.
  */
 size_t kg_op_packed_bytes(int dtype, int N, int K);
 /* Position (0 .. KS-1) of k-step ks among the KS = ceil(K / 32) weight tiles of one 16-row tile in
@@ -341,9 +343,11 @@ int kg_op_linear_valu(const void *packed_dev, int N, int K, const float *x_dev, 
 /*
  * kg_op_linear for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same product, same kernels
- * and bit-identical results.  Allocates nothing (no hipMalloc / hipFree, no memset node), holds no device
- * memory, launches one kernel on `hip_stream`, does not synchronise; calls on several streams or threads
- * do not share anything.
+ * and bit-identical results.  Allocates nothing (no hipMalloc / hipFree, no memset node), launches on
+ * `hip_stream`, does not synchronise.  Calls whose y_dev overlaps their x_dev first copy the rows to a static
+ * device array inside the library (KG_OP_STATIC_MAX_K * KG_MAX_ROWS * 4 bytes = 512 KB per GPU, its address
+ * looked up on the first such call on each device): such calls on one GPU race with each other unless they are
+ * ordered on one stream.  All other calls share nothing.
  * Errors: KG_EINVAL as kg_op_linear, or a current device ordinal >= KG_OP_STATIC_MAX_DEVICES; KG_ENOSPC for
  * K > KG_OP_STATIC_MAX_K; KG_EHIP.
  */

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "kangaroo.h"
@@ -2152,10 +2153,24 @@ int kg_op_pack(int dtype, const void *src, int N, int K, void *packed, void *hip
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
 
-// Both entry points of the stand-alone projection: one launch that reads the fp32 rows as they are (16-byte
-// loads where the rows are aligned for them), so that neither needs a staging area.
-static int op_linear_launch(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, hipStream_t s)
+// Do x[M][K] and y[M][N] share memory?  The workgroups of a projection read all of x and write their own part of y
+// in no order, so x has to be out of y's way first.
+static bool op_linear_overlaps(int N, int K, const float *xd, int M, const float *yd)
 {
+    const uintptr_t x0 = (uintptr_t)xd, x1 = x0 + (size_t)M * K * 4, y0 = (uintptr_t)yd, y1 = y0 + (size_t)M * N * 4;
+    return x0 < y1 && y0 < x1;
+}
+
+// Both entry points of the stand-alone projection: one launch that reads the fp32 rows as they are (16-byte
+// loads where the rows are aligned for them).  `stage` (M * K floats) takes a copy of the rows where
+// y shares memory with them, else null.
+static int op_linear_launch(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, void *stage, hipStream_t s)
+{
+    if (stage) {
+        const size_t n = (size_t)M * K;
+        hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, xd, n, (float *)stage);
+        xd = (const float *)stage;
+    }
     if (dtype == 1) {
         const dim3 grid(N / 16), block(64 * GEMV_WAVES);
         const u32x4_t *W = (const u32x4_t *)packed;
@@ -2187,7 +2202,7 @@ int kg_op_linear(int dtype, const void *packed, int N, int K, const float *xd, i
                  void *hip_stream)
 {
     if (!op_linear_args_ok(dtype, packed, N, K, xd, M, yd) || !work) return KG_EINVAL;
-    return op_linear_launch(dtype, packed, N, K, xd, M, yd, (hipStream_t)hip_stream);
+    return op_linear_launch(dtype, packed, N, K, xd, M, yd, op_linear_overlaps(N, K, xd, M, yd) ? work : nullptr, (hipStream_t)hip_stream);
 }
 
 int kg_op_linear_valu(const void *packed, int N, int K, const float *xd, float *yd, void *hip_stream)
@@ -2198,6 +2213,12 @@ int kg_op_linear_valu(const void *packed, int N, int K, const float *xd, float *
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }
 
+// Where kg_op_linear_static keeps the rows of a call whose output shares memory with them: one array per GPU, held until
+// the process ends.  Host code never uses the array's name as an address: the device address is asked for once per device.
+static __device__ __align__(256) unsigned char static_stage[KG_OP_STATIC_MAX_K * KG_ROWS * 4];
+static std::mutex static_stage_lock;
+static void *static_stage_ptr[KG_OP_STATIC_MAX_DEVICES];        // per device, NULL until first use
+
 int kg_op_linear_static(int dtype, const void *packed, int N, int K, const float *xd, int M, float *yd, void *hip_stream)
 {
     if (!op_linear_args_ok(dtype, packed, N, K, xd, M, yd)) return KG_EINVAL;
@@ -2205,7 +2226,17 @@ int kg_op_linear_static(int dtype, const void *packed, int N, int K, const float
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return KG_EHIP;
     if (dev < 0 || dev >= KG_OP_STATIC_MAX_DEVICES) return KG_EINVAL;
-    return op_linear_launch(dtype, packed, N, K, xd, M, yd, (hipStream_t)hip_stream);
+    void *stage = nullptr;
+    if (op_linear_overlaps(N, K, xd, M, yd)) {
+        std::lock_guard<std::mutex> g(static_stage_lock);
+        if (!static_stage_ptr[dev]) {
+            void *q = nullptr;
+            if (hipGetSymbolAddress(&q, HIP_SYMBOL(static_stage)) != hipSuccess || !q) return KG_EHIP;
+            static_stage_ptr[dev] = q;
+        }
+        stage = static_stage_ptr[dev];
+    }
+    return op_linear_launch(dtype, packed, N, K, xd, M, yd, stage, (hipStream_t)hip_stream);
 }
 
 int kg_op_philox_words(uint64_t seed, uint32_t pos0, uint32_t purpose, int n, uint32_t *out_dev, void *hip_stream)

@@ -2717,6 +2717,13 @@ __global__ __launch_bounds__(512, 2) void stream_read_kernel(const u32x4_t *__re
     if (lane == 0) atomicXor(&out[blockIdx.x], x);
 }
 
+// dst[i] = src[i] (a launch that a stream capture records like any other)
+__global__ void copy_rows_kernel(const float *src, size_t n, float *dst)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
 // Copy cached k and v rows of one position, widened to float (test / debug access).
 template <typename T>
 __global__ void kv_read_kernel(const void *kv, const int *page_table, int slot, int n_slots, int H, int hd,
