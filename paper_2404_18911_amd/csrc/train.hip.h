@@ -33,8 +33,9 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // ahead in one register set: 309; reading a step's operands under the previous step's multiplications: 309.
 // A thread fetches along whichever index is contiguous in memory, in aligned groups of four where the operand
 // allows it (a_vec / b_vec), else (GUARD) element by element.
-// Numbers that no bf16 can stand for (infinities, or within 2^-9 of the largest float) would turn into NaN
-// when split; a workgroup that has met one computes its tile again by plain fp32 multiply-adds.
+// Numbers that no bf16 can stand for (infinities, or within 2^-9 of the largest float) turn into NaN when split, and
+// a product that overflows may do so in parts of both signs: a workgroup with a sum that is not finite computes
+// its tile again by the fp32 matrix instruction.
 // A contraction with few output tiles and a long k is split over blockIdx.z: slice z handles k in
 // [z * k_chunk, (z + 1) * k_chunk) and writes its own partial [M][N] at part + z * M * N; a second
 // kernel adds the slices in order (no atomics: the result does not depend on scheduling).
@@ -201,6 +202,87 @@ __device__ __forceinline__ float tr_gemm_b(const TrGemm &g, size_t bob, int k, i
     return bf2f(((const uint16_t *)g.B)[g.b_mode == 1 ? packed_u16_index(n, k, g.b_KS) : packed_u16_index(k, n, g.b_KS)]);
 }
 
+__device__ __forceinline__ void tr_zero(f32x16_t (&c)[2][2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) c[i][j][r] = 0.f;
+}
+
+// A wave's 64 x 64 of C at (m0, n0) by the fp32 matrix instruction (32x32x2), operands straight from memory: what the
+// products are by definition, for any fp32 numbers.  Of eight k a lane takes four consecutive ones of its row and
+// of its column, lanes 0..31 the first four.
+__device__ __forceinline__ void tr_gemm_plain(const TrGemm &g, size_t boa, size_t bob, int m0, int n0, int k_lo, int k_hi, int lane,
+                                              f32x16_t (&acc)[2][2])
+{
+    tr_zero(acc);
+    if (m0 >= g.M || n0 >= g.N) return;
+    const int fr = lane & 31, fc = lane >> 5;
+    const float *pa[2], *pb[2];
+    int n[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {                       // rows and columns beyond the last repeat it: they are not stored
+        n[i] = min(n0 + 32 * i + fr, g.N - 1);
+        pa[i] = (const float *)g.A + boa + (size_t)min(m0 + 32 * i + fr, g.M - 1) * g.sam;
+        pb[i] = (const float *)g.B + bob + (size_t)n[i] * g.sbn;
+    }
+    const bool va = g.a_vec && g.sak == 1, vb = g.b_vec && g.sbk == 1;
+    auto load = [&](float (&v)[4], const float *p, int k, long s_k, bool vec) {
+        if (vec) {                                      // (k_hi is a multiple of 4 then)
+            const float4 f = k < k_hi ? *(const float4 *)(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) v[j] = k + j < k_hi ? p[(size_t)(k + j) * s_k] : 0.f;
+        }
+    };
+    for (int k0 = k_lo; k0 < k_hi; k0 += 8) {
+        const int k = k0 + 4 * fc;
+        float a[2][4], b[2][4];
+#pragma unroll
+        for (int i = 0; i < 2; i++) load(a[i], pa[i], k, g.sak, va);
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            if (g.b_mode == 0) load(b[i], pb[i], k, g.sbk, vb);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; j++) b[i][j] = k + j < k_hi ? tr_gemm_b(g, bob, k + j, n[i]) : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
+    }
+}
+
+// accumulator register r of lane l: row 8 * (r / 4) + 4 * (l / 32) + r % 4, column l % 32
+__device__ __forceinline__ void tr_gemm_store(const TrGemm &g, size_t boc, int m0, int n0, bool split, int lane, const f32x16_t (&acc)[2][2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int n = n0 + 32 * j + (lane & 31);
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int m = m0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                if (m >= g.M || n >= g.N) continue;
+                const float v = acc[i][j][r];
+                if (split) {
+                    g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
+                } else {
+                    float *c = g.C + boc + (size_t)m * g.ldc + n;
+                    *c = g.accumulate ? *c + v : v;
+                }
+            }
+        }
+}
+
 // BP: bf16 parts of B (3: fp32 operand, 1: bf16 tiles); KA / KB: A / B contiguous along k (KB of tiles: b_mode 1);
 // GUARD: operands that cannot be fetched in aligned groups of four.
 template <int BP, bool KA, bool KB, bool GUARD>
@@ -268,9 +350,6 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
             }
         }
     };
-    typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
-    float big = 0.f;                                    // largest magnitude this thread has fetched
-    u16x2_t big_exp = {0, 0};                           // largest exponents among its bf16 weights
     const int steps = k_lo < k_hi ? (k_hi - k_lo + TRG_K - 1) / TRG_K : 0, full = k_lo < k_hi ? (k_hi - k_lo) / TRG_K : 0;
     auto fetch_whole = [&](Raw &w, int st) {
         oa.fetch(w.a);
@@ -292,29 +371,12 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
         }
     };
     auto stash = [&](const Raw &w, int buf) {
-#pragma unroll
-        for (int i = 0; i < 8; i++) big = fmaxf(big, fabsf(w.a[i]));
         oa.stash(w.a, As[buf], t);
-        if constexpr (BP == 3) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) big = fmaxf(big, fabsf(w.b[i]));
-            ob.stash(w.b, Bs[buf], t);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 2; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    big_exp = __builtin_elementwise_max(big_exp, __builtin_bit_cast(u16x2_t, w.bt[i][j] & 0x7F807F80u));
-            stash_tiles(w, Bs[buf][0]);
-        }
+        if constexpr (BP == 3) ob.stash(w.b, Bs[buf], t);
+        else stash_tiles(w, Bs[buf][0]);
     };
     f32x16_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+    tr_zero(acc);
     const int fr = lane & 31, fc = lane >> 5;           // operand layout of the 32x32x16 instruction: row, which 8 k
     struct Frag { bf16x8_t a[2][3], b[2][BP]; };
     auto read = [&](Frag &f, int buf, int kk) {         // operands of k = 16 kk .. 16 kk + 15 of the step
@@ -367,31 +429,19 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
             if (s < steps) step(r0, 1, false);
         }
     }
-    const bool again = __syncthreads_or(big > 3.3e38f || big_exp[0] == 0x7F80 || big_exp[1] == 0x7F80);
-    // accumulator register r of lane l: row 8 * (r / 4) + 4 * (l / 32) + r % 4, column l % 32
+    // a number no bf16 can stand for leaves its whole row or column of sums without a finite value
+    bool odd = false;
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int n = n0 + wn + 32 * j + (lane & 31);
+        for (int j = 0; j < 2; j++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-                const int m = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (m >= g.M || n >= g.N) continue;
-                float v = acc[i][j][r];
-                if (again) {
-                    v = 0.f;
-                    for (int k = k_lo; k < k_hi; k++)
-                        v = fmaf(((const float *)g.A)[boa + (size_t)m * g.sam + (size_t)k * g.sak], tr_gemm_b(g, bob, k, n), v);
-                }
-                if (split) {
-                    g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
-                } else {
-                    float *c = g.C + boc + (size_t)m * g.ldc + n;
-                    *c = g.accumulate ? *c + v : v;
-                }
-            }
-        }
+            for (int r = 0; r < 16; r++) odd |= !(fabsf(acc[i][j][r]) < INFINITY);
+    if (__syncthreads_or(odd)) {
+        tr_gemm_plain(g, boa, bob, m0 + wm, n0 + wn, k_lo, k_hi, lane, acc);
+        __syncthreads();                                // (C may be an operand of a product of one tile)
+    }
+    tr_gemm_store(g, boc, m0 + wm, n0 + wn, split, lane, acc);
 }
 // (a bound of 256 registers: 8 waves fill a compute unit, whose LDS one workgroup takes anyway)
 template <int BP, bool KA, bool KB, bool GUARD>

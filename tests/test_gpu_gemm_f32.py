@@ -49,3 +49,21 @@ def test_contraction_of_numbers_beyond_bf16():
     fin_a, fin_b = np.where(np.isfinite(a), a, 0).astype(np.float64), np.where(np.isfinite(b), b, 0).astype(np.float64)
     bound = 66 * 2.0 ** -24 * (np.abs(fin_a) @ np.abs(fin_b))
     assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= bound[ok])
+
+
+@pytest.mark.parametrize("M,N,K", [(5, 7, 1), (130, 300, 40), (128, 256, 192)])
+def test_products_and_sums_that_overflow(M, N, K):
+    """Finite operands beyond the largest float: infinities of the right sign and no NaN (every sum here has one sign), and
+    columns whose sums stay finite are as exact as ever."""
+    from paper_2404_18911_amd import binding as B
+    rng = np.random.default_rng(K)
+    a = rng.uniform(0.5, 2.0, (M, K)).astype(np.float32) * np.float32(1e30)
+    b = rng.uniform(0.5, 2.0, (K, N)).astype(np.float32) * np.float32(1e30)
+    b[:, ::3] *= np.float32(1e-40)
+    a[1::2] *= -1
+    got = B.op_gemm_f32(a, b)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    over = np.abs(ref) > 3.5e38
+    assert np.array_equal(got[over], np.sign(ref[over]).astype(np.float32) * np.float32(np.inf)) and np.any(over)
+    fine = np.abs(ref) < 3.3e38
+    assert np.all(np.abs(got[fine] - ref[fine]) <= (K + 2) * 2.0 ** -24 * np.abs(ref[fine]))
