@@ -33,9 +33,12 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // ahead in one register set: 309; reading a step's operands under the previous step's multiplications: 309.
 // A thread fetches along whichever index is contiguous in memory, in aligned groups of four where the operand
 // allows it (a_vec / b_vec), else (GUARD) element by element.
-// Numbers that no bf16 can stand for (infinities, or within 2^-9 of the largest float) turn into NaN when split, and
-// a product that overflows may do so in parts of both signs: a workgroup with a sum that is not finite computes
-// its tile again by the fp32 matrix instruction.
+// Every fp32 operand is multiplied by 2^24 before it is split and the sums are multiplied by the inverse at the
+// end: an fp32 number is a multiple of 2^-149, so that the parts of a scaled one are multiples of 2^-125, none of
+// them below bf16's smallest normal number, and the split is exact for all fp32 numbers, subnormal ones included.  At
+// the other end operands from 2^104 and sums from 2^80 on leave fp32's range when scaled; infinities and NaN
+// turn into NaN when split: a workgroup with a sum that is not finite computes its tile again by the fp32
+// matrix instruction.
 // A contraction with few output tiles and a long k is split over blockIdx.z: slice z handles k in
 // [z * k_chunk, (z + 1) * k_chunk) and writes its own partial [M][N] at part + z * M * N; a second
 // kernel adds the slices in order (no atomics: the result does not depend on scheduling).
@@ -65,6 +68,7 @@ __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
 #define TRG_K 32            // k per step
 #define TRG_M 128           // tile of C
 #define TRG_N 256
+#define TRG_SCALE 0x1p24f   // of the fp32 operands before they are split
 
 // Where the 8 numbers k = 8 c .. 8 c + 7 of row r lie in a plane (in elements): rows of 64 bytes, the rows of a 4 x 4
 // group transposed and the four chunks of a row permuted, so that the reads (lanes = consecutive rows, one
@@ -74,10 +78,12 @@ __device__ __forceinline__ int trg_at(int r, int c) { return ((r & ~15) | ((r & 
 // row of chunk item u: consecutive items take every fourth row, whose chunks lie side by side
 __device__ __forceinline__ int trg_item_row(int u) { return (u & ~15) | ((u & 3) << 2) | ((u >> 2) & 3); }
 
-// a pair of fp32 numbers as three pairs of bf16 numbers
+// a pair of fp32 numbers, times TRG_SCALE, as three pairs of bf16 numbers
 __device__ __forceinline__ void tr_split2(float a, float b, uint32_t (&o)[3])
 {
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    a *= TRG_SCALE;
+    b *= TRG_SCALE;
 #pragma unroll
     for (int p = 0; p < 3; p++) {
         bf16x2_t h;
@@ -429,14 +435,17 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
             if (s < steps) step(r0, 1, false);
         }
     }
-    // a number no bf16 can stand for leaves its whole row or column of sums without a finite value
+    // a number that is not finite once scaled and split leaves its whole row or column of sums without a finite value
     bool odd = false;
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
         for (int j = 0; j < 2; j++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) odd |= !(fabsf(acc[i][j][r]) < INFINITY);
+            for (int r = 0; r < 16; r++) {
+                odd |= !(fabsf(acc[i][j][r]) < INFINITY);
+                acc[i][j][r] *= BP == 3 ? 1.f / (TRG_SCALE * TRG_SCALE) : 1.f / TRG_SCALE;
+            }
     if (__syncthreads_or(odd)) {
         tr_gemm_plain(g, boa, bob, m0 + wm, n0 + wn, k_lo, k_hi, lane, acc);
         __syncthreads();                                // (C may be an operand of a product of one tile)

@@ -67,3 +67,20 @@ def test_products_and_sums_that_overflow(M, N, K):
     assert np.array_equal(got[over], np.sign(ref[over]).astype(np.float32) * np.float32(np.inf)) and np.any(over)
     fine = np.abs(ref) < 3.3e38
     assert np.all(np.abs(got[fine] - ref[fine]) <= (K + 2) * 2.0 ** -24 * np.abs(ref[fine]))
+
+
+@pytest.mark.parametrize("sa,sb", [(1e-36, 1e30), (1e-38, 1e20), (1e-42, 1e20), (1e-44, 1e36), (1e30, 1e-42), (1e-30, 1e-30), (3e31, 1e-8), (1e13, 1e13)])
+def test_operands_of_any_size(sa, sb):
+    """Operands down to the smallest subnormal numbers and beyond the range that is split into parts: the bound of
+    ordinary ones, and the spacing of subnormal results.  (1e36: five deviations of a sum of 200 products stay below 1e38.)"""
+    from paper_2404_18911_amd import binding as B
+    rng = np.random.default_rng(11)
+    for M, N, K in ((150, 300, 36), (40, 20, 200)):
+        a = (rng.standard_normal((M, K)) * sa).astype(np.float32)
+        b = (rng.standard_normal((K, N)) * sb).astype(np.float32)
+        a[::7] = rng.standard_normal(a[::7].shape).astype(np.float32)       # rows of ordinary size in the same tiles
+        a64, b64 = a.astype(np.float64), b.astype(np.float64)
+        with np.errstate(over="ignore"):
+            got = B.op_gemm_f32(a, b).astype(np.float64)
+        bound = (K + 2) * 2.0 ** -24 * (np.abs(a64) @ np.abs(b64)) + 2.0 ** -149
+        assert np.all(np.abs(got - a64 @ b64) <= bound)
