@@ -301,8 +301,13 @@ int kg_train_read(kg_ctx *ctx, int what, float *host_out, size_t n_floats);
 /*
  * The dense contraction of the training step (the products with the LM head and the gradient
  * products of Eq. 3's chain rule), exposed for kernel-level tests: C[M][N] (+)= sum_k A(m,k) B(k,n)
- * in fp32 on the matrix units, A(m,k) = A_dev[m*sam + k*sak], B(k,n) = B_dev[k*sbk + n*sbn],
- * C row-major with leading dimension ldc >= N.  Launches on `hip_stream`, does not synchronise.
+ * in fp32, A(m,k) = A_dev[m*sam + k*sak], B(k,n) = B_dev[k*sbk + n*sbn], C row-major with leading
+ * dimension ldc >= N.  Any fp32 operands: infinities, NaN, subnormal numbers and sums that overflow give
+ * what IEEE arithmetic gives.  The products are formed on the bf16 matrix units from three exact parts of
+ * each operand; the error of a sum is below that of a running fp32 sum, except that a sum which one product
+ * dominates is within 2^-23 of it and not within 2^-24 (K = 1: within 2^-24).  Operands of 2^104 and more
+ * or sums of 2^80 and more are slower (fp32 matrix instruction).  Launches on `hip_stream`, does not
+ * synchronise.
  */
 int kg_op_gemm_f32(const float *A_dev, long sam, long sak, const float *B_dev, long sbk, long sbn, float *C_dev, long ldc,
                    int M, int N, int K, int accumulate, void *hip_stream);

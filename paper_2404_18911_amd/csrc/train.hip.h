@@ -18,11 +18,15 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 //             b_mode 2: element (row k, col n) of such a matrix
 // The products run on the bf16 matrix units at fp32 accuracy: an fp32 number is the exact sum of three bf16
 // numbers (x1 = x rounded, x2 = the rest rounded, x3 = what is left), and of the nine products of two such sums
-// the six largest are taken (x1 y1, x1 y2, x2 y1, x2 y2, x1 y3, x3 y1; the others are below 2^-25 of the
-// product), each exact and accumulated in fp32; against bf16 tiles, which have one part, three products leave
-// nothing out.  Six bf16 products cost 6/16 of the fp32 matrix instruction's time, three 3/16.  Measured errors
-// against 64 bits are no larger than the fp32 instruction's were (relative 2-norm, normal numbers: K = 4096
-// 1.01e-6 against 1.15e-6, K = 32000 3.0e-6 against 3.2e-6).
+// the six largest are taken (x1 y1, x1 y2, x2 y1, x2 y2, x1 y3, x3 y1; the others add up to at most 2^-24 of the
+// product), each exact; against bf16 tiles, which have one part, three products leave nothing out.  The products
+// x1 y1 have an accumulator of their own, the small ones another, and the two are added at the end: a sum is rounded
+// once per 16 k and not six times, and a small sum is not cut off at the last place of a large one.  Six bf16
+// products cost 6/16 of the fp32 matrix instruction's time, three 3/16.  Errors against 64 bits (relative 2-norm,
+// normal numbers; fp32 instruction / all products in one accumulator / here): K = 16 7.4e-8 / 3.3e-8 / 3.2e-8, K = 128
+// 2.0e-7 / 1.6e-7 / 6.5e-8, K = 4096 1.15e-6 / 1.01e-6 / 4.0e-7.  A sum that one product dominates has 2.60e-8
+// (at most 9.0e-8) where the fp32 instruction rounds once, 2.54e-8 (6.0e-8); eight products would give 2.54e-8,
+// and 5.62 instead of 5.09 ms for a 1000-token step from stored features.
 //   One workgroup of 8 waves (2 x 4) per 128 x 256 tile of C, a wave owns 64 x 64 (2 x 2 tiles of 32x32x16).
 // k advances in steps of 32: the operands' fp32 numbers are fetched into registers three steps ahead (two sets),
 // split a step ahead, between the multiplications, and stored as bf16 planes [part][row][k] in one of two LDS
@@ -381,31 +385,32 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
         if constexpr (BP == 3) ob.stash(w.b, Bs[buf], t);
         else stash_tiles(w, Bs[buf][0]);
     };
-    f32x16_t acc[2][2];
+    f32x16_t acc[2][2], rest[2][2];                     // sums of the products of first parts, and of all others
     tr_zero(acc);
+    tr_zero(rest);
     const int fr = lane & 31, fc = lane >> 5;           // operand layout of the 32x32x16 instruction: row, which 8 k
-    struct Frag { bf16x8_t a[2][3], b[2][BP]; };
-    auto read = [&](Frag &f, int buf, int kk) {         // operands of k = 16 kk .. 16 kk + 15 of the step
+    auto multiply = [&](int buf, int kk) {              // k = 16 kk .. 16 kk + 15 of the step
+        bf16x8_t a[3], b[2][BP];
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int q = 0; q < BP; q++) b[j][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&Bs[buf][q][trg_at(wn + 32 * j + fr, 2 * kk + fc)]);
 #pragma unroll
         for (int i = 0; i < 2; i++) {
 #pragma unroll
-            for (int q = 0; q < 3; q++) f.a[i][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&As[buf][q][trg_at(wm + 32 * i + fr, 2 * kk + fc)]);
+            for (int q = 0; q < 3; q++) a[q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&As[buf][q][trg_at(wm + 32 * i + fr, 2 * kk + fc)]);
 #pragma unroll
-            for (int q = 0; q < BP; q++) f.b[i][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&Bs[buf][q][trg_at(wn + 32 * i + fr, 2 * kk + fc)]);
+            for (int s = 2; s >= 0; s--)                // parts (q, s - q): the smallest products first
+#pragma unroll
+                for (int q = 0; q <= s; q++) {
+                    if (s - q >= BP) continue;
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        f32x16_t &c = s ? rest[i][j] : acc[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q], b[j][s - q], c, 0, 0, 0);
+                    }
+                }
         }
-    };
-    auto multiply = [&](const Frag &f) {
-#pragma unroll
-        for (int s = 2; s >= 0; s--)                    // parts (q, s - q): the smallest products first
-#pragma unroll
-            for (int q = 0; q <= s; q++) {
-                if (s - q >= BP) continue;
-#pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int j = 0; j < 2; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i][q], f.b[j][s - q], acc[i][j], 0, 0, 0);
-            }
     };
     if (steps > 0) {
         Raw r0, r1;
@@ -417,14 +422,11 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
         int s = 0;
         // step s is multiplied while step s + 1 (in `w`) is split and stored and step s + 3 requested
         auto step = [&](Raw &w, int buf, bool whole) {
-            Frag f;
-            read(f, buf, 0);
-            multiply(f);
+            multiply(buf, 0);
             if (whole || s + 1 < steps) stash(w, buf ^ 1);      // the other buffer was last read before the previous barrier
             if (whole) fetch_whole(w, s + 3);
             else fetch(w, s + 3);
-            read(f, buf, 1);
-            multiply(f);
+            multiply(buf, 1);
             __syncthreads();
             s++;
         };
@@ -443,10 +445,11 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int r = 0; r < 16; r++) {
-                odd |= !(fabsf(acc[i][j][r]) < INFINITY);
-                acc[i][j][r] *= BP == 3 ? 1.f / (TRG_SCALE * TRG_SCALE) : 1.f / TRG_SCALE;
+                const float v = acc[i][j][r] + rest[i][j][r];
+                odd |= !(fabsf(v) < INFINITY);
+                acc[i][j][r] = v * (BP == 3 ? 1.f / (TRG_SCALE * TRG_SCALE) : 1.f / TRG_SCALE);
             }
-    if (__syncthreads_or(odd)) {
+    if (__syncthreads_or(odd) || g.K == 1) {            // (one product per sum: rounded once)
         tr_gemm_plain(g, boa, bob, m0 + wm, n0 + wn, k_lo, k_hi, lane, acc);
         __syncthreads();                                // (C may be an operand of a product of one tile)
     }
