@@ -439,11 +439,11 @@ Epi epi_base(kg_ctx *x, int kind, int M, int N);
 
 int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
 // Which kernels a pass of T rows goes through.  With the half-precision cache its rows need not be bit-identical to
-// decoded rows: short passes take gemm_stream_kernel, others gemm_prefill2_body (whose table of k-steps bounds K).
+// decoded rows: short passes take gemm_stream_kernel, others gemm_prefill2_body.
 // Both read activations in the pair layout (pf_act_ptr) and the rows' RMS scales from s_pscale, where whatever
 // produced the rows leaves them.  Else the 8-row-block kernels (gemm_prefill_body), with their layout and tile sums.
 inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= PF_STREAM_ROWS; }
-inline bool pf_pairs(const kg_ctx *x, int T) { return x->kvt == 2 && (T <= PF_STREAM_ROWS || std::max(x->KSd, x->KSf) <= PF2_KS_MAX); }
+inline bool pf_pairs(const kg_ctx *x) { return x->kvt == 2; }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
 {
@@ -456,9 +456,9 @@ int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, cons
     // the rows feed a q,k,v projection: stored in the layout its kernel reads
     hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(d / 16, nb), dim3(128), 0, x->stream, emb, tk, tok_dev, rows, d, T, gain,
                        xout, (void *)(x->scr + x->s_pactX), at<float>(x->scr, x->s_pssq0), act_bytes(d),
-                       (d / 16) * KG_ROWS, pf_pairs(x, T) ? 1 : 0);
+                       (d / 16) * KG_ROWS, pf_pairs(x) ? 1 : 0);
     KGCHK(check_launch(x, "prompt pack_rows"));
-    return pf_pairs(x, T) ? launch_rms_scale(x, at<const float>(x->scr, x->s_pssq0), T) : KG_OK;
+    return pf_pairs(x) ? launch_rms_scale(x, at<const float>(x->scr, x->s_pssq0), T) : KG_OK;
 }
 
 // the rows' RMS scales from their tile sums of squares, once per pass and not once per workgroup
@@ -612,7 +612,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
     a.ssq_in_blk = ssq_in ? sq : 0; a.ssq_out_blk = ssq_out ? sq : 0;
     a.act_out_blk = act_out_K ? act_bytes(act_out_K) : 0;
     const int nb = (T + KG_ROWS - 1) / KG_ROWS;
-    if (pf_pairs(x, T)) {
+    if (pf_pairs(x)) {
         const bool resid = e.kind == EPI_RESID;
         const Pf2Plan p = pf2_plan(x->n_cus, a.NT, a.KS, T, resid);
         const Pf2Variant &v = pf2_variants[p.variant];
@@ -682,7 +682,7 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
         pa.kv = (const kvhalf_t *)x->kv; pa.slot = slot; pa.n_slots = c.n_layers + 1;
         pa.rope = at<const float2>(x->scr, x->s_rope);
         pa.act_out = actA; pa.act_blk_bytes = act_bytes(d);
-        pa.act_pair = pf_pairs(x, T) ? 1 : 0;
+        pa.act_pair = pf_pairs(x) ? 1 : 0;
         ProfScope ps(x, 1, 0.0);
         // workgroups of 128 rows (8 waves, a compute unit each) where those alone fill the device, else of 64 rows
         if ((size_t)c.n_heads * ((T + 127) / 128) >= (size_t)x->n_cus) {
@@ -703,18 +703,18 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
 
     e = epi_base(x, EPI_RESID, KG_ROWS, d);
     e.res = x_in; e.xout = x_mid; e.act_out = actX; e.act_K = d; e.gain = g2; e.ssq_out = ssq1;
-    e.act_pair = pf_pairs(x, T) ? 1 : 0;
+    e.act_pair = pf_pairs(x) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, wo_off, d, d, actA, T, e, false, true, d));
 
     e = epi_base(x, EPI_SWIGLU, KG_ROWS, 2 * f);
     e.ssq_in = ssq1; e.act_out = actF; e.act_K = f;
-    e.act_pair = pf_pairs(x, T) ? 1 : 0;
+    e.act_pair = pf_pairs(x) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, gu_off, 2 * f, d, actX, T, e, true, false, f));
 
     e = epi_base(x, EPI_RESID, KG_ROWS, d);
     e.res = x_mid; e.xout = x_out; e.act_out = next_gain ? actX : nullptr; e.act_K = d; e.gain = next_gain;
     e.ssq_out = ssq0;
-    e.act_pair = pf_pairs(x, T) ? 1 : 0;
+    e.act_pair = pf_pairs(x) ? 1 : 0;
     KGCHK(launch_pf_gemm(x, wd_off, d, f, actF, T, e, false, true, next_gain ? d : 0));
     return KG_OK;
 }

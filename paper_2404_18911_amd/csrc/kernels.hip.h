@@ -1093,14 +1093,13 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 // straight into an LDS ring of NB stage buffers (global_load_lds), NB - 1 stages ahead, and wait with
 // exact counts; their loop holds nothing but the loads: every tile's address at step 0 is computed
 // once, and the k loop walks a row tile's weight tiles in the order they are stored (contiguous memory;
-// the sum over k may take any order here) and takes the k-step each one holds from a table, the inverse
-// of tile_pos filled at the start, to pick the matching activation tile.
+// the sum over k may take any order here) and works out the k-step each one holds (kstep_at_pos) to pick the
+// matching activation tile.
 //   PIPE (all but 32 tiles): the multiplying waves are arranged 4 x 2 (2 x 4 for 6 tiles), so that a wave reads
 // few operands from LDS per multiplication; all reads of a k-step are issued together, the hi halves are
 // multiplied into every accumulator before the lo halves, and the operands of k-step ks + 1 are read under the
 // second half of step ks (two register sets).  Without PIPE (32 tiles, whose 128 accumulator registers leave no
 // room for a second set) a wave owns 4 weight tiles x all 8 pairs.
-#define PF2_KS_MAX 1024
 // AW x (8 / AW) multiplying waves; a wave owns WA weight tiles x WP pairs of 8-row blocks; NB stage buffers
 template <int AW, int WA, int WP, int NB, bool PIPE>
 __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e)
@@ -1109,7 +1108,6 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
     __shared__ u32x4_t As[NB][NTW][64];                     // ring of NB stage buffers, one k-step each
     __shared__ u32x4_t Bs[NB][RB / 2][2][64];
     __shared__ float scs[RB][KG_ROWS];
-    __shared__ uint16_t kstep_at[PF2_KS_MAX];               // k-step held by the tile at position p of a row tile
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const bool mover = wave >= 8;
     const int nb = (a.T + 7) >> 3;
@@ -1126,10 +1124,8 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
     const int g0 = ((wave & 7) / AW) * WP;
 
     // RMS scales of the group's rows (computed once per pass by pf_rms_scale_kernel: every workgroup summing
-    // the tile sums of its 128 rows again cost a tenth of a short pass); the table of k-steps by position
+    // the tile sums of its 128 rows again cost a tenth of a short pass); read after the main loop's barriers
     if (t < nbw * KG_ROWS) scs[t >> 3][t & 7] = e.scale_in ? e.scale_in[(size_t)b0 * KG_ROWS + t] : 1.f;
-    for (int i = p_lo + t; i < p_hi; i += 768) kstep_at[i] = (uint16_t)kstep_at_pos(i, KS);
-    __syncthreads();
 
     constexpr int TL = NTW + RB;                            // tile loads of a stage
     constexpr int LPW = (TL + 3) / 4;                       // ... per mover wave (one too many for some: it repeats the last tile)
@@ -1157,9 +1153,10 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                 src0[i] = a.act + (size_t)pr * 2 * a.act_blk + part * 64 + lane;
             }
         }
+        int next_apos = kstep_at_pos(p_lo, KS) * 128;       // worked out a stage ahead, under the loads (in place: 0.4 % of a 777-token prompt)
         auto issue = [&](int ks, int bf) {                  // operands of position ks (clamped: late stages reload a valid one)
-            const int kk = min(ks, p_hi - 1);
-            const int wpos = kk * 64, apos = __builtin_amdgcn_readfirstlane((int)kstep_at[kk]) * 128;
+            const int wpos = min(ks, p_hi - 1) * 64, apos = next_apos;
+            next_apos = kstep_at_pos(min(ks + 1, p_hi - 1), KS) * 128;
 #pragma unroll
             for (int i = 0; i < LPW; i++) {
                 const int j = min((wave - 8) + 4 * i, TL - 1);

@@ -1,7 +1,8 @@
 """Prompt passes of every length class against the same tokens fed one at a time through the decode
 kernels: the half-precision cache and the logits after each prompt length.  Shapes: the 7B and 13B layer
 widths (they reach every number of weight tiles per workgroup) and a narrow one whose feed-forward width
-is no multiple of 32 and whose k-steps do not divide by the eight k ranges of a weight tile row."""
+is no multiple of 32 and whose k-steps do not divide by the eight k ranges of a weight tile row, and one whose
+down_proj has more than 1024 k-steps."""
 import numpy as np
 import pytest
 
@@ -13,6 +14,7 @@ SHAPES = {
     "7b": I.ModelShape("7b_1", 1, 4096, 32, 128, 11008, 1024, 1),
     "13b": I.ModelShape("13b_1", 1, 5120, 40, 128, 13824, 1024, 1),
     "uneven": I.ModelShape("uneven_2", 2, 1344, 21, 64, 3416, 1024, 1),
+    "long": I.ModelShape("long_1", 1, 512, 8, 64, 33800, 1024, 1),
 }
 # around the edges of 16-row pairs, of the row groups of the stream kernel (16, 32, 48, 64, 96, 128 rows), of its range
 # (9 .. 192 rows) and of the decode kernels' (8 rows)
