@@ -16,8 +16,9 @@ def _view(rng, rows, cols, contiguous_rows):
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (4, 8, 4), (128, 256, 32), (129, 257, 33), (127, 255, 31), (132, 260, 36), (256, 512, 64),
                                    (300, 516, 100), (64, 128, 160), (130, 300, 68)])
 def test_contraction_at_the_edges_of_its_tiles(M, N, K, ta, tb):
-    """Bound: K roundings of a running fp32 sum, 2^-24 of sum |a||b| each (all K here are small enough that a missing
-    part of an operand, 2^-9 or 2^-18 of it, would stand out)."""
+    """Bound: K roundings of a running fp32 sum, 2^-24 of sum |a||b| each.  It finds wrong elements, a missing second part
+    of an operand (2^-8 of it) at every K here, and a missing third part (2^-16) up to K = 36; beyond that
+    test_sums_of_one_product does, for every step along k (test_contraction_bounds.py emulates both)."""
     from paper_2404_18911_amd import binding as B
     rng = np.random.default_rng(M * 31 + N * 7 + K)
     a, b = _view(rng, M, K, ta), _view(rng, K, N, tb)
@@ -91,7 +92,7 @@ def test_operands_of_any_size(sa, sb):
 def test_sums_of_one_product(M, N, K, ta):
     """One number that is not zero per row of A, so that a result is one product, whatever K: rounded once for K = 1, and
     else within 2^-24 for the rounding and 2^-24 for the products of small parts that are left out.  (An operand's
-    third part missing anywhere along k would be an error of up to 2^-16.)"""
+    third part missing anywhere along k would be an error of up to 2^-17.)"""
     from paper_2404_18911_amd import binding as B
     rng = np.random.default_rng(K)
     a = np.zeros((M, K), np.float32)
