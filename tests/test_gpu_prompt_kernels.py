@@ -17,8 +17,9 @@ SHAPES = {
     "long": I.ModelShape("long_1", 1, 512, 8, 64, 33800, 1024, 1),
 }
 # around the edges of 16-row pairs, of the row groups of the stream kernel (16, 32, 48, 64, 96, 128 rows), of its range
-# (9 .. 192 rows) and of the decode kernels' (8 rows)
-LENGTHS = [1, 8, 9, 16, 17, 31, 33, 48, 49, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257]
+# (9 .. 192 rows) and of the decode kernels' (8 rows); then longer passes, which take every tile size and number of
+# slices along k of the 128-row kernels, with last row groups of 1, 9, 44, 57, 81 and 127 rows
+LENGTHS = [1, 8, 9, 16, 17, 31, 33, 48, 49, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 300, 385, 511, 777, 1025, 1465, 2001, 3001]
 
 
 @pytest.fixture(scope="module", params=list(SHAPES))
@@ -37,7 +38,8 @@ def reference(request):
     logits = {1: kg.read_logits(1, 0)}
     for i in range(1, n):
         kg.plain_step(p, prompt[i])
-        logits[i + 1] = kg.read_logits(1, 0)
+        if i + 1 in LENGTHS:
+            logits[i + 1] = kg.read_logits(1, 0)
     torch.cuda.synchronize()
     cache = _cache(kg, shape).clone()
     yield shape, kg, p, prompt, cache, logits
@@ -66,3 +68,36 @@ def test_a_prompt_of_n_tokens_agrees_with_one_token_decoding(reference, n):
     assert err <= 2e-3, err
     z = kg.read_logits(1, 0)
     np.testing.assert_allclose(z, logits[n], rtol=0, atol=2e-3 * max(1.0, float(np.std(logits[n]))))
+
+
+@pytest.mark.parametrize("max_seq", [24, 40, 200, 296, 344, 776])
+def test_a_prompt_that_fills_the_context_s_last_block(max_seq):
+    """Contexts of an odd number of 8-row blocks, filled to the last row a prompt may have: the last block has no partner in
+    the pair layout of the activations.  Every cache, the adapter's included, and the logits agree with the same prompt in
+    a context with room to spare, bit for bit, and no byte behind the scratch buffer changes."""
+    import torch
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = SHAPES["uneven"]
+    W = I.gen_weights(shape, seed=5, alpha=1.0)
+    p, _ = B.make_params(gamma=1)
+    n = max_seq - 3
+    prompt = [int(t) for t in I.gen_prompt(shape.vocab, n, seed=7)]
+    got = []
+    for room in (0, 136):
+        kg = P.load_model(shape, W, max_seq + room, gamma_max=1)
+        guard = torch.full((kg.scratch_bytes + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+        kg.scratch = guard[:kg.scratch_bytes]
+        kg._chk(kg.L.kg_bind(kg.h, kg.arena.data_ptr(), kg.weight_bytes, kg.kv.data_ptr(), kg.kv_bytes, kg.scratch.data_ptr(),
+                             kg.scratch_bytes, kg.stream.cuda_stream))
+        kg.load_weights((k, l, W[(k, l)]) for k, l, _, _ in I.tensor_list(shape))
+        kg.kv.zero_()
+        token = kg.prefill(p, prompt)
+        torch.cuda.synchronize()
+        assert bool((guard[kg.scratch_bytes:] == 0xA5).all())
+        got.append((token, kg.read_logits(1, 0), [kg.read_kv(s, i) for s in range(shape.n_layers + 1) for i in (0, 1, 7, 8, 15, 16, n // 2, n - 1)]))
+        kg.close()
+    assert got[0][0] == got[1][0]
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    for a, b in zip(got[0][2], got[1][2]):
+        np.testing.assert_array_equal(np.stack(a), np.stack(b))
