@@ -1,7 +1,7 @@
 """The entry point that allocates nothing, kg_op_linear_static, against kg_op_linear: same product,
-bit-identical results, on two calls in a row that share the library's static staging array, the
-second with a smaller input (fewer rows, shorter K, a K that leaves half of the last activation tile
-unwritten), for bf16 and fp32 weights.  Also its limits: K beyond the static array is refused."""
+bit-identical results, on two calls in a row, the second with a smaller input (fewer rows, shorter K, a K
+that is half a k-step longer than a whole number of them), for bf16 and fp32 weights.  Also its limits: K beyond the
+static array that calls with overlapping input and output use (test_gpu_linear_overlap.py) is refused always."""
 import numpy as np
 import pytest
 
@@ -36,8 +36,8 @@ def test_static_scratch_entry_point_equals_workspace_entry_point(dtype):
     L = B.lib()
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
-    # first call: the largest K the static array takes, 8 rows; second call: smaller in every way,
-    # K = 1040 = 32 * 32 + 16 (the upper half of its last activation tile is never written)
+    # first call: the largest K the entry point takes, 8 rows; second call: smaller in every way,
+    # K = 1040 = 32 * 32 + 16
     for N, K, M, seed in ((1024, 16384, 8, 5), (272, 1040, 3, 6)):
         y0, y1, Wh, x = _pair(L, B, torch, dev, dtype, N, K, M, seed)
         assert np.isfinite(y0).all() and np.isfinite(y1).all()
