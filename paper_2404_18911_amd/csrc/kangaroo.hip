@@ -319,16 +319,22 @@ void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &
     } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e);
 }
 
-// Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, else gemv_multi_kernel, whose time hardly
-// depends on M.  Measured (us, stand-alone product, 4096 features): 12288 outputs (3 tiles) 18.4 against 18.0 of
-// gemv_bf16_body with 4 rows, 19.0 with 6, 20.7 with 8; 22016 outputs (6 tiles, on 230 of 256 compute units) 31.7
-// against 31.2, 33.3, 36.4; 13840 x 5136 (4 tiles) 27.0 against 27.1, 29.3, 32.2: from 5 rows on.  Not with 2 tiles (8192
-// outputs: 16.5 against 15.2 with 8 rows) and not with 8 (32000 outputs: 45.5 against 44.0 with 6 rows, 49 with 8) or
-// more than a round of workgroups.
+// Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, whose time grows with M, else
+// gemv_multi_kernel, whose time hardly does.  Measured (us, stand-alone product over weights that no cache holds; gemv_bf16_body with
+// 5, 6, 7, 8 rows / gemv_multi_kernel):
+//   tiles   4096 features                    5120 features                    11008 features
+//   2       13.5 14.0 14.7 15.2 / 16.2       16.7 17.3 18.0 18.9 / 17.0       32.0 33.2 34.7 36.4 / 32.1
+//   3       18.2 18.9 19.9 20.6 / 17.9       22.1 23.4 24.9 26.0 / 22.1       44.4 46.4 48.7 51.4 / 45.8
+//   4       23.0 24.0 24.9 26.5 / 25.0       28.2 29.7 31.4 33.0 / 28.3       57.7 60.5 63.6 67.0 / 57.3
+//   5       28.0 29.1 30.4 32.3 / 28.6       34.4 36.1 38.0 40.4 / 34.7       71.1 74.4 78.2 82.7 / 69.1
+//   6       32.8 34.2 35.6 37.4 / 34.2       40.6 42.6 44.9 47.7 / 40.4       84.5 88.2 92.9 97.9 / 86.0
+//   7       37.9 39.3 40.9 43.3 / 38.7       46.7 49.2 51.6 54.7 / 46.5       97.9 102  108  113  / 96.3
+//   8       42.6 44.4 46.1 48.6 / 46.1       52.8 55.5 58.3 62.0 / 52.4       111  116  122  129  / 110
+// So from 6 rows on with 3 to 7 tiles, with 4 tiles from 7; not with 2, nor with 8 (6 and 7 rows of 4096 features).
 inline int gemv_tiles(int n_cus, int N, int M)
 {
     const int ntw = (N / 16 + n_cus - 1) / n_cus;
-    return M >= 5 && ntw >= 3 && ntw <= 7 ? ntw : 1;
+    return M >= (ntw == 4 ? 7 : 6) && ntw >= 3 && ntw <= 7 ? ntw : 1;
 }
 template <int SRC>
 void launch_gemv_multi(const u32x4_t *W, int N, int KS, int M, const void *act, int K, const Epi &e, int ntw, hipStream_t s)
@@ -2175,7 +2181,7 @@ static int op_linear_launch(int dtype, const void *packed, int N, int K, const f
         const dim3 grid(N / 16), block(64 * GEMV_WAVES);
         const u32x4_t *W = (const u32x4_t *)packed;
         const int KS = (K + 31) / 32;
-        if (const int ntw = gemv_tiles(256, N, M); ntw > 1) {
+        if (const int ntw = gemv_tiles(256, N, M); ntw > 1) {      // (an MI355X's compute units; the results do not depend on it)
             Epi e;
             memset(&e, 0, sizeof(e));
             e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;

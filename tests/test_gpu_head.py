@@ -1,4 +1,4 @@
-"""The LM head over verification rows where several weight tiles share a workgroup (5 rows and more, vocabularies of 3 to 7
+"""The LM head over verification rows where several weight tiles share a workgroup (6 rows and more, vocabularies of 3 to 7
 tiles per compute unit): the logits and choices of one-token decoding, bit for bit."""
 import numpy as np
 import pytest

@@ -44,8 +44,8 @@ def test_linear_of_aligned_and_unaligned_rows(dtype, M, N, K):
 
 @pytest.mark.parametrize("N,K", [(12288, 528), (13840, 1040), (16400, 528), (19968, 1040), (27648, 272), (22016, 4096)])
 def test_a_row_of_linear_does_not_depend_on_the_others(N, K):
-    """5 .. 8 rows through 3, 4, 5, 5, 7 and 6 weight tiles per workgroup (256 compute units) give the bits of one row
-    alone (uneven shares of tiles, k ranges of unequal length, a half k-step)."""
+    """6 .. 8 rows (7 and 8 of the second shape) through 3, 4, 5, 5, 7 and 6 weight tiles per workgroup (256 compute units)
+    give the bits of one row alone (uneven shares of tiles, k ranges of unequal length, a half k-step)."""
     import torch
     from paper_2404_18911_amd import binding as B
     L = B.lib()
