@@ -32,15 +32,21 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // split a step ahead, between the multiplications, and stored as bf16 planes [part][row][k] in one of two LDS
 // buffers: one barrier per step.  Per step and compute unit 3072 clocks of matrix instructions (1536 against
 // tiles) stand beside 2100 (1350) of LDS traffic and 1600 (800) of splitting.  1000 x 32000 x 4096 against tiles:
-// 772 us, 1.02 PFLOP/s of bf16 products (fp32 instruction: 2.9 ms); 1000 x 4096 x 4096: 300 us on 128 of the
-// 256 compute units (496 us).  One LDS buffer with 4 waves and two barriers a step: 422 us; operands two steps
-// ahead in one register set: 309; reading a step's operands under the previous step's multiplications: 309.
+// 721 us, 1.09 PFLOP/s of bf16 products, matrix units busy 59 % (fp32 instruction: 2.9 ms); 1000 x 4096 x 4096: 271 us
+// on 128 of the 256 compute units (fp32 instruction: 467 us).  The operands of one row of tiles are read at a time: with
+// all of a block's operands in registers beside both accumulators, 12 to 60 bytes spill and it takes 289 us.  Variants of an
+// earlier form that took 300 us: one LDS buffer with 4 waves and two barriers a step 422 us; operands two steps
+// ahead in one register set 309; reading a step's operands under the previous step's multiplications 309.
+//   Not faster everywhere than tiles of 64 x 128 by the fp32 instruction: for k up to 16 the fixed parts of a tile count
+// (12288 x 4096 x 16: 63 us against 47; from k = 32 on 63 against 62), and a stand-alone contraction of a few tiles fills
+// few compute units (64 x 64 x 64: 12.5 us against 9.2).  Waves that split operands straight from memory, without LDS:
+// 78 us; the fp32 instruction straight from memory: 45 us, but twice the error at k = 16.
 // A thread fetches along whichever index is contiguous in memory, in aligned groups of four where the operand
 // allows it (a_vec / b_vec), else (GUARD) element by element.
 // Every fp32 operand is multiplied by 2^24 before it is split and the sums are multiplied by the inverse at the
 // end: an fp32 number is a multiple of 2^-149, so that the parts of a scaled one are multiples of 2^-125, none of
 // them below bf16's smallest normal number, and the split is exact for all fp32 numbers, subnormal ones included.  At
-// the other end operands from 2^104 and sums from 2^80 on leave fp32's range when scaled; infinities and NaN
+// the other end operands from 2^104 and sums from 2^80 (against tiles 2^104) on leave fp32's range when scaled; infinities and NaN
 // turn into NaN when split: a workgroup with a sum that is not finite computes its tile again by the fp32
 // matrix instruction.
 // A contraction with few output tiles and a long k is split over blockIdx.z: slice z handles k in
