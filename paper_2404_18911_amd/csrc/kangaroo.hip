@@ -19,15 +19,20 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 // Prompt rows handled per pass of the prompt kernels.  With the half-precision cache the projections
-// run in workgroups of 128 rows x 8 TW weight tiles, one per compute unit at a time: a pass of 1024
+// run in workgroups of up to 128 rows x 32 weight tiles, one per compute unit at a time: a pass of 1024
 // rows gives some launches 0.75 or 2.7 rounds of workgroups, a pass of 4096 rows 3 .. 11 rounds (a
 // 4096-token prompt at the 7B shape: 122 ms in passes of 1024 rows, 109 in passes of 2048, 105 in one).
 // The other cache types keep the 8-row-block kernels, whose attention needs page partials per block.
 constexpr int PF_ROWS_MAX = 1024, PF_ROWS_MAX_HALF = 4096;
-// Passes of up to PF_STREAM_ROWS rows are bound by reading the weights and go through gemm_stream_kernel (7B shape, us
-// per layer of a pass: 160 rows 255 against 272 .. 285 with the larger tiles, 200 rows 335 against 258).
+// Passes of up to pf_stream_rows(d_model) rows are bound by reading the weights, in a narrow model by the latency of their launches, and go
+// through gemm_stream_kernel, longer ones through gemm_prefill2_body.  Whole passes, ms, stream / the larger tiles: 7B shape with 6
+// layers: 64 rows 0.95 / 1.09, 96 rows 1.11 / 1.14, 100 rows 1.23 / 1.18, 128 rows 1.26 / 1.24, 129 rows (two groups of rows in the
+// stream) 1.61 / 1.28, 192 rows 1.62 / 1.41; 13B, 4 layers: 96 rows 1.05 / 1.08, 112 rows 1.25 / 1.10, 160 rows 1.60 / 1.25; 33B, 3
+// layers: 96 rows 1.24 / 1.32, 112 rows 1.42 / 1.40; d_model 3072, 6 layers: 100 rows 0.90 / 0.86, 192 rows 1.14 / 0.99; 2560: 0.77 / 0.74,
+// 0.88 / 0.82; 2048: 0.64 / 0.64, 0.71 / 0.71; 1280: 0.48 / 0.50, 0.52 / 0.56; 768: 0.39 / 0.43, 0.42 / 0.46.
+inline int pf_stream_rows(int d_model) { return d_model <= 2048 ? 192 : 96; }
 // Projections cut along k write at most PF_SLICES partial sums per output, PF_PART_ROWS rows of them in all.
-constexpr int PF_STREAM_ROWS = 192, PF_SLICES = 8, PF_PART_ROWS = 4096;
+constexpr int PF_SLICES = 8, PF_PART_ROWS = 4096;
 inline size_t up(size_t x, size_t a = ALIGN) { return (x + a - 1) / a * a; }
 
 struct LayerW {
@@ -448,7 +453,7 @@ int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
 // decoded rows: short passes take gemm_stream_kernel, others gemm_prefill2_body.
 // Both read activations in the pair layout (pf_act_ptr) and the rows' RMS scales from s_pscale, where whatever
 // produced the rows leaves them.  Else the 8-row-block kernels (gemm_prefill_body), with their layout and tile sums.
-inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= PF_STREAM_ROWS; }
+inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= pf_stream_rows(x->c.d_model); }
 inline bool pf_pairs(const kg_ctx *x) { return x->kvt == 2; }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
@@ -565,13 +570,18 @@ int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, i
     return resid ? launch_reduce_rows(x, p.slices, T, e, a.act_out_blk) : KG_OK;
 }
 
-// ---- longer passes: projections in workgroups of 128 rows (gemm_prefill2_body) ----
+// ---- longer passes: projections in workgroups of 80 .. 128 rows (gemm_prefill2_body) ----
 
-// The kernel's variants: weight tiles per workgroup, and microseconds per k-step of a workgroup where all compute
-// units have one (random data at the 7B and 13B shapes; a round also takes about 4 us besides its k-steps).
-struct Pf2Variant { void (*kernel)(PfArgs, Epi); int ntw; double step_us; };
-const Pf2Variant pf2_variants[] = {{gemm_prefill2_kernel_n6, 6, 0.38}, {gemm_prefill2_kernel_tw1, 8, 0.46}, {gemm_prefill2_kernel_n12, 12, 0.63},
-                                   {gemm_prefill2_kernel_tw2, 16, 0.775}, {gemm_prefill2_kernel_tw4, 32, 1.465}};
+// The kernel's variants: weight tiles and pairs of 8-row blocks of a workgroup, and microseconds per k-step of a workgroup where
+// all compute units have one (s with 8 pairs; a share f of it does not depend on the pairs: 0.29 us with 5 pairs and 0.41 with 8 at 8
+// tiles, 0.39 / 0.54 at 12, 0.47 / 0.68 at 16, 1.09 / 1.69 at 32).
+struct Pf2Variant { void (*kernel)(PfArgs, Epi); int ntw, pairs; double step_us; };
+#define PF2_V(t, p, s, f) {gemm_prefill2_kernel_t##t##_p##p, t, p, s * (f + (1.0 - f) * p / 8)}
+#define PF2_VS(t, s, f) PF2_V(t, 5, s, f), PF2_V(t, 6, s, f), PF2_V(t, 7, s, f), PF2_V(t, 8, s, f)
+const Pf2Variant pf2_variants[] = {PF2_V(6, 8, 0.38, 0.2), PF2_VS(8, 0.46, 0.216), PF2_VS(12, 0.63, 0.152), PF2_VS(16, 0.775, 0.149),
+                                   PF2_VS(32, 1.465, 0.1)};
+#undef PF2_VS
+#undef PF2_V
 
 // Which variant, in how many slices along k (`split` allowed: EPI_RESID).  A workgroup fills a compute unit, so a
 // launch takes whole rounds of them; a partly filled last round runs at a higher clock (0.75 of a round when nearly
@@ -584,19 +594,27 @@ const Pf2Variant pf2_variants[] = {{gemm_prefill2_kernel_n6, 6, 0.38}, {gemm_pre
 // fewer bytes per multiplication also leaves the other launches a higher clock: 32 tiles are entered 3 % cheaper than
 // they measure alone (4096 rows, whole pass: 94.5 ms with 32 tiles for gate+up, 96.9 ms with 16; 3000 rows, where 32
 // tiles need a fifth round for the last 8 workgroups: 76.4 against 74.6 ms).
+//   Groups of 80, 96 or 112 rows where they fit the pass's rows or the rounds better than groups of 128: rows multiplied for nothing
+// cost as much as the others, in time and in power (these launches run at 1.6 .. 1.9 GHz on random data, at 2.4 GHz on zeros).  us,
+// 128 rows at their best / the group picked: 7B, 300 rows: q,k,v 78 / 57 (12 tiles, 80 rows), gate+up 156 / 132 (12, 80), down_proj 60 / 51
+// (16, 80, 4 slices); 400 rows: 87 / 68, 194 / 151, 71 / 62; 777 rows: q,k,v 184 / 144 (32, 80); 13B, 777 rows: 275 / 245 (32, 112),
+// gate+up 443 / 401 (16, 112), o_proj 92 / 79 (12, 96).  They have to be 4 % ahead: nearer than that the fit does not rank them
+// (7B, 512 rows, whole pass: 2.69 ms with 128 rows, 2.75 where it took 32 tiles x 112 rows for gate+up as 2 % ahead).
 struct Pf2Plan { int variant, slices; };
 Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
 {
-    const int gx = (T + 127) / 128;
+    const int pairs = (T + 15) / 16;
     Pf2Plan best = {0, 1};
     double best_cost = -1.0;
     for (int v = 0; v < (int)(sizeof(pf2_variants) / sizeof(pf2_variants[0])); v++)
         for (int S = 1; S <= (split ? PF_SLICES : 1); S++) {
             if (S > 1 && (S * T > PF_PART_ROWS || KS < 8 * S || pf2_variants[v].ntw == 32)) break;
             const Pf2Variant &pv = pf2_variants[v];
+            const int gx = (pairs + pv.pairs - 1) / pv.pairs;
             const double wgs = (double)gx * ((NT + pv.ntw - 1) / pv.ntw) * S, whole = std::floor(wgs / n_cus), rest = wgs / n_cus - whole;
             const double rounds = whole + (rest > 0 ? 0.75 + 0.25 * rest : 0.0), bytes = (double)T * NT * 64;
-            const double cost = rounds * ((double)KS / S * pv.step_us + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
+            const double step = pv.step_us * (pv.pairs < 8 ? 1.04 : 1.0);
+            const double cost = rounds * ((double)KS / S * step + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {v, S}; }
         }
     return best;
@@ -622,7 +640,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
         const bool resid = e.kind == EPI_RESID;
         const Pf2Plan p = pf2_plan(x->n_cus, a.NT, a.KS, T, resid);
         const Pf2Variant &v = pf2_variants[p.variant];
-        a.gx = (nb + 15) / 16;
+        a.gx = (nb + 2 * v.pairs - 1) / (2 * v.pairs);
         a.gy = (a.NT + v.ntw - 1) / v.ntw;
         if (p.slices > 1) a.part = at<float>(x->scr, x->s_ppart);
         Epi e2 = e;

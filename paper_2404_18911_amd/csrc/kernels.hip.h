@@ -1079,15 +1079,15 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Projection for prompt passes of more than 192 rows (half-precision cache): the same contraction as
+// Projection for prompt passes of more than 96 rows (192 in narrow models; half-precision cache): the same contraction as
 // gemm_prefill_body, organised for reuse instead of for the one-token kernel's summation order (a prompt row then
 // differs from the same row decoded alone in the order of its sums only, far inside the logit tolerance).  A
-// workgroup owns 6 .. 32 weight tiles x 128 rows (pf2_plan picks the number that fills whole rounds of
-// workgroups best); a projection with few weight tiles (o_proj, down_proj) is also cut along k, one slice per
+// workgroup owns 6 .. 32 weight tiles x 80 .. 128 rows (pf2_plan picks the numbers that fill whole rounds of
+// workgroups, and the rows of the pass, best); a projection with few weight tiles (o_proj, down_proj) is also cut along k, one slice per
 // blockIdx.y, into partial sums that pf_reduce_rows_kernel adds with what follows the projection.  The hi and lo
 // halves of the activations are two B operands of 16 distinct rows each (two
 // 8-row blocks) that are multiplied into the SAME accumulator, so nothing is folded and no per-range
-// totals are kept: a weight tile fetched from the L2 serves 128 rows and an activation tile serves up to
+// totals are kept: a weight tile fetched from the L2 serves all rows of the group and an activation tile serves up to
 // 512 weight rows.  The activations arrive in the pair layout of pf_act_ptr (a B operand = one KB).
 //   12 waves: waves 8..11 move, waves 0..7 multiply.  The movers bring the operand tiles of a k-step
 // straight into an LDS ring of NB stage buffers (global_load_lds), NB - 1 stages ahead, and wait with
@@ -1100,13 +1100,16 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 // multiplied into every accumulator before the lo halves, and the operands of k-step ks + 1 are read under the
 // second half of step ks (two register sets).  Without PIPE (32 tiles, whose 128 accumulator registers leave no
 // room for a second set) a wave owns 4 weight tiles x all 8 pairs.
-// AW x (8 / AW) multiplying waves; a wave owns WA weight tiles x WP pairs of 8-row blocks; NB stage buffers
-template <int AW, int WA, int WP, int NB, bool PIPE>
+// AW x (8 / AW) multiplying waves; a wave owns WA weight tiles x its share of the workgroup's NP pairs of 8-row blocks; NB
+// stage buffers
+template <int AW, int WA, int NP, int NB, bool PIPE>
 __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e)
 {
-    constexpr int NTW = AW * WA, RB = 2 * WP * (8 / AW);    // weight tiles and 8-row blocks of the workgroup
+    constexpr int NTW = AW * WA, RB = 2 * NP;               // weight tiles and 8-row blocks of the workgroup
+    constexpr int PG = 8 / AW, WPM = (NP + PG - 1) / PG;    // the pairs are shared out to PG groups of waves: WPM pairs, the last group the rest
+    static_assert(PG <= 2 || NP % PG == 0, "with more than two groups of waves every group owns as many pairs");
     __shared__ u32x4_t As[NB][NTW][64];                     // ring of NB stage buffers, one k-step each
-    __shared__ u32x4_t Bs[NB][RB / 2][2][64];
+    __shared__ u32x4_t Bs[NB][NP][2][64];
     __shared__ float scs[RB][KG_ROWS];
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const bool mover = wave >= 8;
@@ -1121,10 +1124,10 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
     const int p_hi = PIPE ? __builtin_amdgcn_readfirstlane((int)((blockIdx.y + 1) * KS / gridDim.y)) : KS;
     const int col = lane & 15, g4 = lane >> 4;
     const int a0 = (wave % AW) * WA;                        // first weight tile and first pair of a multiplying wave
-    const int g0 = ((wave & 7) / AW) * WP;
+    const int wg = (wave & 7) / AW, g0 = wg * WPM;
 
     // RMS scales of the group's rows (computed once per pass by pf_rms_scale_kernel: every workgroup summing
-    // the tile sums of its 128 rows again cost a tenth of a short pass); read after the main loop's barriers
+    // the tile sums of its rows again cost a tenth of a short pass); read after the main loop's barriers
     if (t < nbw * KG_ROWS) scs[t >> 3][t & 7] = e.scale_in ? e.scale_in[(size_t)b0 * KG_ROWS + t] : 1.f;
 
     constexpr int TL = NTW + RB;                            // tile loads of a stage
@@ -1177,6 +1180,9 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
+    // a multiplying wave with WP pairs from pair g0 on
+    auto multiply = [&](auto pairs) {
+    constexpr int WP = decltype(pairs)::value;
     f32x4_t acc[WA][WP];
 #pragma unroll
     for (int ta = 0; ta < WA; ta++)
@@ -1307,16 +1313,26 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
             }
         }
     }
+    };
+    if (NP % PG == 0 || wg == 0) multiply(std::integral_constant<int, WPM>{});
+    else multiply(std::integral_constant<int, NP - (PG - 1) * WPM>{});
 }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw1(PfArgs a, Epi e) { gemm_prefill2_body<4, 2, 4, 6, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_n12(PfArgs a, Epi e) { gemm_prefill2_body<4, 3, 4, 5, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_n6(PfArgs a, Epi e) { gemm_prefill2_body<2, 3, 2, 6, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw2(PfArgs a, Epi e) { gemm_prefill2_body<4, 4, 4, 4, true>(a, e); }
-__global__ __launch_bounds__(768) void gemm_prefill2_kernel_tw4(PfArgs a, Epi e) { gemm_prefill2_body<8, 4, 8, 3, false>(a, e); }
+// named by the weight tiles and the pairs of 8-row blocks of a workgroup
+#define PF2_KERNEL(tiles, np, AW, WA, NB, PIPE) \
+    __global__ __launch_bounds__(768) void gemm_prefill2_kernel_t##tiles##_p##np(PfArgs a, Epi e) { gemm_prefill2_body<AW, WA, np, NB, PIPE>(a, e); }
+#define PF2_KERNELS(tiles, AW, WA, NB, PIPE) \
+    PF2_KERNEL(tiles, 5, AW, WA, NB, PIPE) PF2_KERNEL(tiles, 6, AW, WA, NB, PIPE) PF2_KERNEL(tiles, 7, AW, WA, NB, PIPE) PF2_KERNEL(tiles, 8, AW, WA, NB, PIPE)
+PF2_KERNEL(6, 8, 2, 3, 6, true)
+PF2_KERNELS(8, 4, 2, 6, true)
+PF2_KERNELS(12, 4, 3, 5, true)
+PF2_KERNELS(16, 4, 4, 4, true)
+PF2_KERNELS(32, 8, 4, 3, false)
+#undef PF2_KERNELS
+#undef PF2_KERNEL
 
 // ---------------------------------------------------------------------------------------------
 // Projection for short prompt passes (half-precision cache, 9 rows and more): Y[T][N] = X[T][K] . W^T where
-// reading the weights is still what bounds the launch (at the 7B shape up to about 128 rows), so the kernel is
+// reading the weights is still what bounds the launch (up to about 96 rows, in narrow models its latency), so the kernel is
 // built as a weight stream.  A workgroup of 8 waves owns up to NTW weight tiles x R pairs of 8-row blocks (16 R
 // rows); its waves take the k-steps of the row tiles in turn, in the order the tiles are stored, and each wave
 // multiplies its k-steps into accumulators of its own: weights and activations go from memory straight into

@@ -17,9 +17,11 @@ SHAPES = {
     "long": I.ModelShape("long_1", 1, 512, 8, 64, 33800, 1024, 1),
 }
 # around the edges of 16-row pairs, of the row groups of the stream kernel (16, 32, 48, 64, 96, 128 rows), of its range
-# (9 .. 192 rows) and of the decode kernels' (8 rows); then longer passes, which take every tile size and number of
-# slices along k of the 128-row kernels, with last row groups of 1, 9, 44, 57, 81 and 127 rows
-LENGTHS = [1, 8, 9, 16, 17, 31, 33, 48, 49, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 300, 385, 511, 777, 1025, 1465, 2001, 3001]
+# (9 .. 96 rows at d_model 4096, .. 192 in narrow models) and of the decode kernels' (8 rows); then longer passes, which take every tile
+# size, row group (80, 96, 112, 128 rows) and number of slices along k of the larger kernels, with last row groups of one row, of a
+# pair and a row, and of a whole group but one row
+LENGTHS = [1, 8, 9, 16, 17, 31, 33, 48, 49, 64, 65, 96, 97, 112, 113, 128, 129, 160, 161, 192, 193, 241, 256, 257, 289, 300, 337, 385, 401, 511, 561,
+           777, 1025, 1465, 2001, 3001]
 
 
 @pytest.fixture(scope="module", params=list(SHAPES))
