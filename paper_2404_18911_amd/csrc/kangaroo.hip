@@ -455,6 +455,10 @@ int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
 // produced the rows leaves them.  Else the 8-row-block kernels (gemm_prefill_body), with their layout and tile sums.
 inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= pf_stream_rows(x->c.d_model); }
 inline bool pf_pairs(const kg_ctx *x) { return x->kvt == 2; }
+// With the half-precision cache the prompt projections write keys and values into the cache themselves (KvOut) and the key rows of the
+// stacked q, k, v matrices are stored in rotation pairs: map_row() mode of those matrices, and Epi::k_pairs of their decode launches.
+inline int qkv_mode(const kg_ctx *x) { return x->bf && pf_pairs(x) ? qkv_rows(x->c.d_model, x->c.head_dim) : 0; }
+inline int qkv_pairs(const kg_ctx *x) { return x->bf && pf_pairs(x) ? x->c.head_dim : 0; }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
 {
@@ -536,9 +540,9 @@ int launch_reduce_rows(kg_ctx *x, int slices, int T, const Epi &e, size_t act_ou
     return check_launch(x, "prompt row sums");
 }
 
-// One projection of a short pass.  EPI_PLAIN / EPI_SWIGLU scale their rows by s_pscale (if ssq_in is set);
+// One projection of a short pass.  EPI_QKV / EPI_SWIGLU scale their rows by s_pscale (if ssq_in is set);
 // EPI_RESID leaves the rows' next scales there.
-int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T, const Epi &e, int act_out_K)
+int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T, const Epi &e, int act_out_K, const KvOut *kv)
 {
     const bool resid = e.kind == EPI_RESID;
     PfStreamArgs a;
@@ -547,6 +551,7 @@ int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, i
     a.KS = (K + 31) / 32; a.NT = N / 16;
     a.act = (const u32x4_t *)act; a.act_pair16 = 2 * act_bytes(K) / 16; a.T = T;
     a.act_out_blk = act_out_K ? act_bytes(act_out_K) : 0;
+    if (kv) a.kv = *kv;
     const StreamPlan p = pf_stream_plan(x->n_cus, a.NT, a.KS, T, resid);
     a.slices = p.slices; a.groups = p.groups; a.gx = p.gx;
     float *scale = at<float>(x->scr, x->s_pscale);
@@ -623,10 +628,10 @@ Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
 // Y[T][N] = X[T][K] . W^T with the epilogue e; in/out block strides follow the prompt buffers (activation tiles of K
 // features per block, d/16 tile sums per block)
 int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T, const Epi &e, bool ssq_in, bool ssq_out,
-                   int act_out_K)
+                   int act_out_K, const KvOut *kv = nullptr)
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
-    if (pf_streams(x, T)) return launch_stream_gemm(x, w_off, N, K, act, T, e, act_out_K);
+    if (pf_streams(x, T)) return launch_stream_gemm(x, w_off, N, K, act, T, e, act_out_K, kv);
     PfArgs a;
     memset(&a, 0, sizeof(a));
     a.W = at<const u32x4_t>(x->arena, w_off);
@@ -636,6 +641,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
     a.ssq_in_blk = ssq_in ? sq : 0; a.ssq_out_blk = ssq_out ? sq : 0;
     a.act_out_blk = act_out_K ? act_bytes(act_out_K) : 0;
     const int nb = (T + KG_ROWS - 1) / KG_ROWS;
+    if (kv) a.kv = *kv;
     if (pf_pairs(x)) {
         const bool resid = e.kind == EPI_RESID;
         const Pf2Plan p = pf2_plan(x->n_cus, a.NT, a.KS, T, resid);
@@ -680,18 +686,30 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
     void *actX = x->scr + x->s_pactX, *actA = x->scr + x->s_pactA, *actF = x->scr + x->s_pactF;
     float *x_mid = at<float>(x->scr, x->s_px1);
 
-    Epi e = epi_base(x, EPI_PLAIN, KG_ROWS, 3 * d);
-    e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv);
-    KGCHK(launch_pf_gemm(x, qkv_off, 3 * d, d, actX, T, e, true, false, 0));
+    Epi e;
+    AttnArgs a;
+    if (x->kvt == 2) {
+        // queries to s_pqkv, keys and values straight into the cache; the adapter's pass needs no queries
+        KvOut kv;
+        memset(&kv, 0, sizeof(kv));
+        kv.kv = (uint16_t *)x->kv; kv.page_table = at<const int>(x->scr, x->s_pt); kv.rope = at<const float2>(x->scr, x->s_rope);
+        kv.slot = slot; kv.n_slots = c.n_layers + 1; kv.H = c.n_heads; kv.log_hd = ilog2(c.head_dim); kv.logP = x->logP; kv.pos0 = pos0;
+        kv.d = d; kv.n0 = kv_only ? d : 0;
+        e = epi_base(x, EPI_QKV, KG_ROWS, 3 * d - kv.n0);
+        e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv);
+        KGCHK(launch_pf_gemm(x, qkv_off + packed_bytes(true, kv.n0, d), e.N, d, actX, T, e, true, false, 0, &kv));
+    } else {
+        e = epi_base(x, EPI_PLAIN, KG_ROWS, 3 * d);
+        e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv);
+        KGCHK(launch_pf_gemm(x, qkv_off, 3 * d, d, actX, T, e, true, false, 0));
 
-    // all rows' keys and values go to the cache first; then every 8-row block attends to the cache
-    AttnArgs a = attn_args(x, slot, pos0, T);
-    a.qkv = at<const float>(x->scr, x->s_pqkv);
-    a.opart = at<float>(x->scr, x->s_popart); a.mxs = at<float>(x->scr, x->s_pmxs); a.sms = at<float>(x->scr, x->s_psms);
-    a.cnt = at<int>(x->scr, x->s_pcnt);
-    a.act_out = actA; a.act_blk_bytes = act_bytes(d);
-    a.append_only = 1; a.append_all = 1;
-    {
+        // all rows' keys and values go to the cache first; then every 8-row block attends to the cache
+        a = attn_args(x, slot, pos0, T);
+        a.qkv = at<const float>(x->scr, x->s_pqkv);
+        a.opart = at<float>(x->scr, x->s_popart); a.mxs = at<float>(x->scr, x->s_pmxs); a.sms = at<float>(x->scr, x->s_psms);
+        a.cnt = at<int>(x->scr, x->s_pcnt);
+        a.act_out = actA; a.act_blk_bytes = act_bytes(d);
+        a.append_only = 1; a.append_all = 1;
         ProfScope ps(x, 1, 0.0);
         KGCHK(launch_attn_args(x, a, dim3(c.n_heads, 1, nb), KG_ROWS));
     }
@@ -791,7 +809,7 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     float *x_mid = with_ffn ? at<float>(x->scr, x->s_x1) : x_out;
 
     Epi e = epi_base(x, EPI_PLAIN, M, 3 * d);
-    e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_qkv);
+    e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
     KGCHK(launch_gemv(x, qkv_off, 3 * d, d, actX, e));
     KGCHK(launch_attn(x, slot, pos0, M, 0));
 
@@ -928,7 +946,7 @@ int run_adapter(kg_ctx *x, int frow, int M, int pos0, bool full)
     }
     if (!full) {
         Epi e = epi_base(x, EPI_PLAIN, M, 3 * c.d_model);
-        e.ssq_in = at<float>(x->scr, x->s_ssq0); e.out = at<float>(x->scr, x->s_qkv);
+        e.ssq_in = at<float>(x->scr, x->s_ssq0); e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
         KGCHK(launch_gemv(x, x->a_qkv, 3 * c.d_model, c.d_model, x->scr + x->s_actX, e));
         return launch_attn(x, c.n_layers, pos0, M, 1);
     }
@@ -1141,13 +1159,13 @@ int kg_load_tensor(kg_ctx *x, int kind, int layer, const void *src, size_t n_ele
     case KG_EMBED: rows = V; K = d; dst = x->embed; break;
     case KG_LM_HEAD: rows = V; K = d; dst = x->head; break;
     case KG_FINAL_NORM: is_gain = true; dst = x->gfinal; break;
-    case KG_WQ: case KG_WK: case KG_WV: rows = d; K = d; dst = x->lw[layer].qkv; row_off = (kind - KG_WQ) * d; break;
+    case KG_WQ: case KG_WK: case KG_WV: rows = d; K = d; dst = x->lw[layer].qkv; row_off = (kind - KG_WQ) * d; mode = qkv_mode(x); break;
     case KG_WO: rows = d; K = d; dst = x->lw[layer].wo; break;
     case KG_WG: case KG_WU: rows = f; K = d; dst = x->lw[layer].gu; mode = 1 + (kind - KG_WG); break;
     case KG_WD: rows = d; K = f; dst = x->lw[layer].wd; break;
     case KG_NORM1: is_gain = true; dst = x->lw[layer].g1; break;
     case KG_NORM2: is_gain = true; dst = x->lw[layer].g2; break;
-    case KG_A_WQ: case KG_A_WK: case KG_A_WV: rows = d; K = d; dst = x->a_qkv; row_off = (kind - KG_A_WQ) * d; break;
+    case KG_A_WQ: case KG_A_WK: case KG_A_WV: rows = d; K = d; dst = x->a_qkv; row_off = (kind - KG_A_WQ) * d; mode = qkv_mode(x); break;
     case KG_A_WO: rows = d; K = d; dst = x->a_wo; break;
     case KG_A_NORM_IN: is_gain = true; dst = x->a_gin; break;
     case KG_A_NORM_LAST: is_gain = true; dst = x->a_glast; break;
@@ -1627,7 +1645,7 @@ static std::vector<TrTensor> train_tensors(const kg_ctx *x)
         mat(d, d, x->a_w1, d, 0, 0);
         mat(d, d, x->a_w2, d, 0, 0);
     } else {
-        mat(3 * d, d, x->a_qkv, 3 * d, 0, 0);
+        mat(3 * d, d, x->a_qkv, 3 * d, 0, qkv_mode(x));
         mat(d, d, x->a_wo, d, 0, 0);
     }
     gain(x->a_gin);

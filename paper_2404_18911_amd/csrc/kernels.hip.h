@@ -23,7 +23,7 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 #define KG_ROWS 8
 
-enum { EPI_PLAIN = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_SILU = 4 };
+enum { EPI_PLAIN = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_SILU = 4, EPI_QKV = 5 };
 
 // What a projection kernel does with a finished 16-row tile y[16][8].
 struct Epi {
@@ -38,6 +38,7 @@ struct Epi {
     // EPI_PLAIN: out[(m + row_shift)][n] = y * scale, rows with m + row_shift < 0 are dropped
     float *out;
     int row_shift;
+    int k_pairs;        // head_dim where the key rows of a q, k, v projection are stored in rotation pairs (see map_row), else 0
     // EPI_HEAD: as EPI_PLAIN, plus per-tile statistics of z * inv_temp for the rows kept:
     // hstat[(row * N / 16 + tile) * 4 + {0,1,2}] = max, sum exp(. - max), arg-max index (as float bits):
     // the statistics of one row lie together, for the block that reduces them
@@ -182,6 +183,13 @@ __device__ __forceinline__ void store_act_pf(void *base, size_t blk_bytes, int b
     p[lo_off] = f2bf(v - bf2f(hi));
 }
 
+// Column of the q, k, v row that packed row n of the projection gives (e.k_pairs is a power of two; the second third holds the keys)
+__device__ __forceinline__ int plain_column(const Epi &e, int n)
+{
+    const int d = e.N / 3, w = (n - d) & (e.k_pairs - 1);
+    return (e.k_pairs && n >= d && n < 2 * d) ? n - w + (w >> 1) + (w & 1) * (e.k_pairs >> 1) : n;
+}
+
 template <bool BF>
 __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_ROWS], const float *sc,
                                          float (*sq)[KG_ROWS], float resv = 0.f, float gainv = 1.f,
@@ -192,7 +200,7 @@ __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_RO
             int row = t >> 3, m = t & 7;
             int mo = m + e.row_shift;
             float z = yt[row][m] * sc[m];
-            if (m < e.M && mo >= 0) e.out[(size_t)mo * e.N + rt * 16 + row] = z;
+            if (m < e.M && mo >= 0) e.out[(size_t)mo * e.N + plain_column(e, rt * 16 + row)] = z;
             sq[row][m] = z * e.inv_temp;
         }
         if (e.kind == EPI_HEAD) {
@@ -735,6 +743,18 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__
 #define PF_CBW 8
 #define PF_NB 3
 
+// Where the keys and values of a prompt pass's q, k, v projection go (EPI_QKV, half-precision cache): the epilogue rotates the keys, which
+// arrive in rotation pairs (map_row), and writes both to the rows' pages in the cache's own type; only the queries go to e.out.
+// (A launch of its own that read them back cost 4.8 us a layer at 45 rows, 7 at 256, 55 at 4096; the projection takes 0.6 .. 1 us longer.  Whole
+// prompts at the 7B shape: 45 tokens 4.13 -> 4.06 ms, 4096 tokens 95.2 -> 93.8; at 256 tokens, where the power limit takes back what the
+// shorter pause gives, 8.10 -> 8.09.)
+struct KvOut {
+    uint16_t *kv;           // pool: [phys page][slot][head][K|V][P][hd], half bit patterns
+    const int *page_table;
+    const float2 *rope;     // [max_seq][hd/2]
+    int slot, n_slots, H, log_hd, logP, pos0;
+    int d, n0;              // width of the model; packed row of the stacked projection at which this launch's weights start
+};
 struct PfArgs {
     const u32x4_t *W;       // weight tiles [NT][tile_pos(ks)][64]
     int KS, NT;
@@ -745,6 +765,7 @@ struct PfArgs {
     size_t act_out_blk;     // bytes per 8-row block of the output activation
     int gx, gy;             // row groups, tile groups (the grid holds 8 * ceil(gx * gy / 8) workgroups, see pf_work)
     float *part;            // gemm_prefill2_body: partial sums [slice = blockIdx.y][T][N] for pf_reduce_rows_kernel; null: the epilogue
+    KvOut kv;               // EPI_QKV
 };
 
 __device__ __forceinline__ Epi pf_block_epi(const Epi &e, const PfArgs &a, int b)
@@ -758,6 +779,46 @@ __device__ __forceinline__ Epi pf_block_epi(const Epi &e, const PfArgs &a, int b
     if (eb.act_out) eb.act_out = (char *)eb.act_out + (size_t)b * a.act_out_blk;
     if (eb.ssq_out) eb.ssq_out += (size_t)b * a.ssq_out_blk;
     return eb;
+}
+
+__device__ __forceinline__ float half_bits_to_f32(uint32_t low16) { return (float)__builtin_bit_cast(_Float16, (uint16_t)low16); }
+__device__ __forceinline__ uint16_t f32_to_half_bits(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
+
+// rotation of the pair (x0, x1) by the angle whose (cos, sin) is cs; written with explicit fused
+// operations so that every instantiation rounds alike
+__device__ __forceinline__ float rot_lo(float x0, float x1, float2 cs) { return fmaf(x0, cs.x, -__fmul_rn(x1, cs.y)); }
+__device__ __forceinline__ float rot_hi(float x0, float x1, float2 cs) { return fmaf(x1, cs.x, __fmul_rn(x0, cs.y)); }
+
+// position of row `row` of the pass inside its page's keys of head 0
+__device__ __forceinline__ uint16_t *kv_out_row(const KvOut &k, int row)
+{
+    const int pos = k.pos0 + row, page = k.page_table[pos >> k.logP];
+    return k.kv + (((size_t)page * k.n_slots + k.slot) * k.H << (k.logP + k.log_hd + 1)) + ((size_t)(pos & ((1 << k.logP) - 1)) << k.log_hd);
+}
+// four packed rows n .. n + 3 of the launch (n a multiple of 4), scaled, for one row of the pass
+__device__ __forceinline__ void store_qkv(const KvOut &k, float *out, uint16_t *kv_row, int row, int n, float y0, float y1, float y2, float y3)
+{
+    n += k.n0;
+    const int d = k.d, hd = 1 << k.log_hd;
+    if (n < d) {
+        *(float4 *)(out + (size_t)row * 3 * d + n) = make_float4(y0, y1, y2, y3);
+        return;
+    }
+    const bool key = n < 2 * d;
+    const int m = n - (key ? d : 2 * d), h = m >> k.log_hd, w = m & (hd - 1);
+    uint16_t *p = kv_row + ((size_t)h << (k.logP + k.log_hd + 1));
+    if (key) {
+        const int j = w >> 1;
+        const float4 cs = *(const float4 *)(k.rope + (size_t)(k.pos0 + row) * (hd >> 1) + j);      // (cos, sin) of pairs j, j + 1
+        const float a0 = rounded(y0), b0 = rounded(y1), a1 = rounded(y2), b1 = rounded(y3);
+        const float2 c0 = make_float2(cs.x, cs.y), c1 = make_float2(cs.z, cs.w);
+        *(uint32_t *)(p + j) = f32_to_half_bits(rounded(rot_lo(a0, b0, c0))) | ((uint32_t)f32_to_half_bits(rounded(rot_lo(a1, b1, c1))) << 16);
+        *(uint32_t *)(p + j + (hd >> 1)) = f32_to_half_bits(rounded(rot_hi(a0, b0, c0))) | ((uint32_t)f32_to_half_bits(rounded(rot_hi(a1, b1, c1))) << 16);
+    } else {
+        *(uint2 *)(p + ((size_t)1 << (k.logP + k.log_hd)) + w) =
+            make_uint2(f32_to_half_bits(rounded(y0)) | ((uint32_t)f32_to_half_bits(rounded(y1)) << 16),
+                       f32_to_half_bits(rounded(y2)) | ((uint32_t)f32_to_half_bits(rounded(y3)) << 16));
+    }
 }
 
 // (row group, group of weight tiles) of this workgroup.  Workgroups go to the 8 XCDs in turn; XCD x takes the x-th
@@ -1257,6 +1318,7 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
         const int lrow = (g0 + gb) * 16 + col, row = b0 * KG_ROWS + lrow;      // row in the group, in the pass
         const bool row_ok = row < a.T;
         const float sc = (e.kind != EPI_RESID && row_ok) ? scs[lrow >> 3][lrow & 7] : 1.f;
+        uint16_t *kv_row = e.kind == EPI_QKV && row_ok ? kv_out_row(a.kv, row) : nullptr;
 #pragma unroll
         for (int ta = 0; ta < WA; ta++) {
             const int rt = rt0 + ta, n0 = rt * 16 + 4 * g4;
@@ -1294,8 +1356,8 @@ __device__ __forceinline__ void gemm_prefill2_body(const PfArgs &a, const Epi &e
                     if (live && g4 == 0) e.ssq_out[(size_t)(row >> 3) * a.ssq_out_blk + (size_t)rt * KG_ROWS + (row & 7)] = sq;
                 }
             } else if (live) {
-                if (e.kind == EPI_PLAIN) {
-                    *(float4 *)(e.out + (size_t)row * e.N + n0) = make_float4(y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
+                if (e.kind == EPI_QKV) {
+                    store_qkv(a.kv, e.out, kv_row, row, n0, y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
                 } else {                          // EPI_SWIGLU: rows (2i, 2i+1) = (gate, up) of feature rt*8 + i
                     uint16_t hi[2], lo[2];
 #pragma unroll
@@ -1355,6 +1417,7 @@ struct PfStreamArgs {
     int slices, groups, gx; // k slices, groups of weight tiles, groups of 16 R rows
     float *part;            // partial sums [slice][T][N] for pf_reduce_rows_kernel; null: the epilogue (one slice)
     size_t act_out_blk;     // bytes per 8-row block of the output activation (SwiGLU)
+    KvOut kv;               // EPI_QKV
 };
 
 // Waves of a workgroup: 8, of 256 registers each, while those hold the accumulators and the operands of a step
@@ -1494,8 +1557,8 @@ __global__ __launch_bounds__(64 * pf_stream_waves(NTW, R), pf_stream_waves(NTW, 
                 continue;
             }
             const float sc = e.scale_in ? e.scale_in[row] : 1.f;
-            if (e.kind == EPI_PLAIN) {
-                *(float4 *)(e.out + (size_t)row * e.N + n0) = make_float4(y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
+            if (e.kind == EPI_QKV) {
+                store_qkv(a.kv, e.out, kv_out_row(a.kv, row), row, n0, y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc);
             } else {                          // EPI_SWIGLU: rows (2i, 2i+1) = (gate, up) of feature rt*8 + i
                 uint16_t hi[2], lo[2];
 #pragma unroll
@@ -1618,9 +1681,16 @@ __global__ __launch_bounds__(128) void pack_rows_kernel(const void *emb, Tok8 to
 
 // ---------------------------------------------------------------------------------------------
 // Weight re-tiling.  Destination row of source row r: mode 0: row_off + r; mode 1 (gate): 16*(r/8)
-// + 2*(r%8); mode 2 (up): the same + 1, so a tile holds 8 (gate, up) pairs.
+// + 2*(r%8); mode 2 (up): the same + 1, so a tile holds 8 (gate, up) pairs.  qkv_rows(d, head_dim): row_off + r of the stacked q, k, v
+// rows, with the keys of a head stored in rotation pairs (0, hd/2), (1, hd/2 + 1), ..: a lane of a prompt projection then holds
+// whole pairs, and its epilogue can rotate them and write the cache.
+__host__ __device__ __forceinline__ constexpr int qkv_rows(int d, int head_dim) { return (d << 8) | head_dim; }
 __device__ __forceinline__ int map_row(int r, int row_off, int mode)
 {
+    if (mode > 2) {
+        const int d = mode >> 8, hd = mode & 255, R = row_off + r, j = (R - d) & (hd - 1);
+        return (R >= d && R < 2 * d) ? R - j + 2 * (j & ((hd >> 1) - 1)) + (j >= (hd >> 1)) : R;
+    }
     return mode == 0 ? row_off + r : 16 * (r >> 3) + 2 * (r & 7) + (mode - 1);
 }
 
@@ -1700,8 +1770,6 @@ struct AttnArgs {
 // conditionally came out of the compiler with every second element undefined).
 struct kvhalf_t { uint16_t bits; };
 static_assert(sizeof(kvhalf_t) == 2, "two-byte cache element");
-__device__ __forceinline__ float half_bits_to_f32(uint32_t low16) { return (float)__builtin_bit_cast(_Float16, (uint16_t)low16); }
-__device__ __forceinline__ uint16_t f32_to_half_bits(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
 template <typename T> __device__ __forceinline__ float kv_ld(const T *p);
 template <> __device__ __forceinline__ float kv_ld<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float kv_ld<uint16_t>(const uint16_t *p) { return bf2f(*p); }
@@ -1834,10 +1902,6 @@ __device__ __forceinline__ float wave_sum_q4(float v)
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
-// rotation of the pair (x0, x1) by the angle whose (cos, sin) is cs; written with explicit fused
-// operations so that every instantiation rounds alike
-__device__ __forceinline__ float rot_lo(float x0, float x1, float2 cs) { return fmaf(x0, cs.x, -__fmul_rn(x1, cs.y)); }
-__device__ __forceinline__ float rot_hi(float x0, float x1, float2 cs) { return fmaf(x1, cs.x, __fmul_rn(x0, cs.y)); }
 
 // One (head, page) unit, 512 threads, MR >= number of rows (1, 2, 4 or 8: less code and fewer
 // registers for the common one- and two-row calls; a row's arithmetic is the same in all of them).
@@ -2138,8 +2202,8 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
 // One workgroup per head and block of 64 query rows (4 waves, two workgroups per compute unit) or of
 // 128 query rows (8 waves, a compute unit alone, two tiles of K and V in LDS: half the staging per row
 // and one barrier per tile; for passes whose blocks of 128 rows fill the device); a wave owns 16 rows.
-// The keys and values of all rows of this pass are already in the cache (appended by an earlier
-// launch), so the block walks the cache in tiles of 128 positions up to its own last row:
+// The keys and values of all rows of this pass are already in the cache (written by the q, k, v
+// projection), so the block walks the cache in tiles of 128 positions up to its own last row:
 //   S^T = K Q^T   per 16-position tile: A = keys from LDS (as stored: one position's 8 consecutive
 //         dimensions per lane), B = the rotated, scaled queries held in registers as half hi + lo
 //         parts (two MFMAs per step, fp32-grade scores); the result has a lane's query row in its
