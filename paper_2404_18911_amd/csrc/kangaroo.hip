@@ -39,6 +39,8 @@ struct LayerW {
     size_t qkv, wo, gu, wd, g1, g2; // byte offsets into the arena
 };
 
+constexpr int RES_ACCEPT = 2 * KG_ROWS, RES_WORDS = RES_ACCEPT + 2;
+
 struct Phase { enum { NONE = 0, READY = 1, DRAFTING = 2, VERIFIED = 3, PLAIN = 4 }; };
 
 // Workspace of the adapter's training step (byte offsets).  The parameter block, and likewise the
@@ -73,8 +75,8 @@ struct kg_ctx {
     int akind = 0;
     size_t kv_bytes, scratch_bytes;
     // scratch layout (byte offsets)
-    size_t s_x0, s_x1, s_F, s_qkv, s_actX, s_actA, s_actF, s_ssq0, s_ssq1, s_opart, s_mxs, s_sms, s_cnt,
-        s_dlog, s_tlog, s_tok, s_conf, s_pt, s_rope, s_invf, s_misc, s_hstat, s_dstat, s_tstat, s_acc;
+    size_t s_x0, s_x1, s_F, s_qkv, s_actX, s_actA, s_actF, s_ssq0, s_ssq1, s_actP, s_actD, s_ssqP, s_ssqD, s_opart, s_mxs, s_sms, s_cnt,
+        s_dlog, s_tlog, s_pt, s_rope, s_invf, s_misc, s_hstat, s_dstat, s_tstat;
     // prompt pass: device copy of the prompt and buffers for pf_rows rows at a time (bf16 weights)
     int pf_rows = 0;
     size_t s_ptok, s_px0, s_px1, s_pF, s_pqkv, s_pactX, s_pactA, s_pactF, s_pssq0, s_pssq1, s_popart, s_pmxs, s_psms,
@@ -82,13 +84,14 @@ struct kg_ctx {
     // bindings
     char *arena = nullptr, *kv = nullptr, *scr = nullptr;
     hipStream_t stream = nullptr;
-    hipEvent_t ev_fetch = nullptr;
     bool bound = false;
     std::vector<char> loaded; // per (kind, layer) flag
     std::vector<int> page_order;
-    // pinned host staging
-    int *h_tok = nullptr;
-    float *h_conf = nullptr;
+    // result words in pinned host memory (see post()): tokens and confidences of up to KG_ROWS rows, what accept_sample_kernel finds
+    unsigned long long *h_res = nullptr;
+    unsigned seq = 0;        // number of the launch whose results are awaited
+    int h_tok[KG_ROWS];
+    float h_conf[KG_ROWS];
     // sequence state (see kg_get_state)
     int phase = Phase::NONE;
     int base = 0, adapter_len = 0, lag = 0, pending = -1;
@@ -98,6 +101,7 @@ struct kg_ctx {
     int targets[KG_MAX_ROWS];
     int n_target_rows = 0;
     int plain_len = 0;
+    bool packed = true;      // s_actP / s_actD hold what the present gains make of the early features (false: packed again where they are read)
     int spec_shallow = -1;   // index j of an early feature f_j already computed ahead of the host's decision
     // algorithmic bytes (weights streamed + cached keys / values read) by what the launches belong to:
     // 0 = self-draft model (shallow layers + adapter + head of a draft step), 1 = shallow-only pass
@@ -203,14 +207,16 @@ void layout(kg_ctx *x)
     x->s_actF = take(act_bytes(f));
     x->s_ssq0 = take((size_t)(d / 16) * KG_ROWS * 4);
     x->s_ssq1 = take((size_t)(d / 16) * KG_ROWS * 4);
+    x->s_actP = take(act_bytes(d));          // early features as the adapter reads them, and as layer l does
+    x->s_actD = take(act_bytes(d));
+    x->s_ssqP = take((size_t)(d / 16) * KG_ROWS * 4);
+    x->s_ssqD = take((size_t)(d / 16) * KG_ROWS * 4);
     x->s_opart = take((size_t)c.n_heads * x->n_pages * KG_ROWS * c.head_dim * 4);
     x->s_mxs = take((size_t)c.n_heads * x->n_pages * KG_ROWS * 4);
     x->s_sms = take((size_t)c.n_heads * x->n_pages * KG_ROWS * 4);
     x->s_cnt = take((size_t)c.n_heads * 4);
     x->s_dlog = take((size_t)KG_ROWS * V * 4);
     x->s_tlog = take((size_t)KG_ROWS * V * 4);
-    x->s_tok = take(KG_ROWS * 8);            // tokens, then confidences: one 64-byte block, one copy to the host
-    x->s_conf = x->s_tok + KG_ROWS * 4;
     x->s_pt = take((size_t)x->n_pages * 4);
     x->s_rope = take((size_t)c.max_seq * (c.head_dim / 2) * 8);
     x->s_invf = take((size_t)(c.head_dim / 2) * 8);
@@ -218,7 +224,6 @@ void layout(kg_ctx *x)
     x->s_hstat = take((size_t)(V / 16) * KG_ROWS * 4 * 4);
     x->s_dstat = take(KG_ROWS * 2 * 4);
     x->s_tstat = take(KG_ROWS * 2 * 4);
-    x->s_acc = take(2 * 4);
     x->s_ptok = take((size_t)c.max_seq * 4);
     x->pf_rows = 0;
     if (x->bf) {
@@ -357,7 +362,10 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
     ProfScope ps(x, 0, (double)N * K * x->esz);
     x->acct[x->acct_phase] += (double)N * K * x->esz;
-    if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, e.M) : 1; ntw > 1)
+    if (x->bf && e.kind == EPI_FEATURE)
+        hipLaunchKernelGGL(gemv_bf16_feature_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream, at<const u32x4_t>(x->arena, w_off),
+                           (K + 31) / 32, e.M, (const u32x4_t *)act, N, e);
+    else if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, e.M) : 1; ntw > 1)
         launch_gemv_multi<FROM_ACT>(at<const u32x4_t>(x->arena, w_off), N, (K + 31) / 32, e.M, act, 0, e, ntw, x->stream);
     else if (x->bf)
         hipLaunchKernelGGL(gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream,
@@ -369,19 +377,19 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
 }
 
 int launch_pack_rows(kg_ctx *x, const int *tokens, const float *rows, int M, const float *gain, float *xout,
-                     void *act, float *ssq, const int *tok_dev = nullptr)
+                     void *act, float *ssq)
 {
     Tok8 tk;
     for (int i = 0; i < KG_ROWS; i++) tk.t[i] = (tokens && i < M) ? tokens[i] : 0;
     tk.vocab = x->c.vocab;
-    const void *emb = (tokens || tok_dev) ? (const void *)(x->arena + x->embed) : nullptr;
+    const void *emb = tokens ? (const void *)(x->arena + x->embed) : nullptr;
     const int d = x->c.d_model;
     ProfScope ps(x, 2, 0.0);
     if (x->bf)
-        hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(d / 16), dim3(128), 0, x->stream, emb, tk, tok_dev, rows, d, M,
+        hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(d / 16), dim3(128), 0, x->stream, emb, tk, (const int *)nullptr, rows, d, M,
                            gain, xout, act, ssq);
     else
-        hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(d / 16), dim3(128), 0, x->stream, emb, tk, tok_dev, rows, d, M,
+        hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(d / 16), dim3(128), 0, x->stream, emb, tk, (const int *)nullptr, rows, d, M,
                            gain, xout, act, ssq);
     return check_launch(x, "pack_rows");
 }
@@ -796,27 +804,49 @@ Epi epi_base(kg_ctx *x, int kind, int M, int N)
     return e;
 }
 
+// Where a block's last rows go besides x_out: the next projection's input x * gain with its tile sums of squares, from row `row` on; for the
+// early features the same for layer l (act2, ssq2, from row `row2` on) and a copy of the fp32 rows.
+struct RowsOut {
+    void *act; float *ssq; const float *gain; int row;
+    void *act2; float *ssq2; const float *gain2; int row2;
+    float *xout2;
+};
+RowsOut rows_out(kg_ctx *x, const float *gain)
+{
+    RowsOut o;
+    memset(&o, 0, sizeof(o));
+    o.act = gain ? x->scr + x->s_actX : nullptr; o.ssq = at<float>(x->scr, x->s_ssq0); o.gain = gain;
+    return o;
+}
+void set_rows_out(Epi &e, const RowsOut &o, int d)
+{
+    e.act_out = o.act; e.act_K = d; e.gain = o.gain; e.ssq_out = o.ssq; e.act_row = o.row;
+    if (!o.act2) return;
+    e.kind = EPI_FEATURE;
+    e.act2 = o.act2; e.ssq2 = o.ssq2; e.gain2 = o.gain2; e.row2 = o.row2; e.xout2 = o.xout2;
+}
+
 // Attention sub-layer + (optionally) feed-forward sub-layer of one block on M rows at pos0.
-// In:  actX = x_in * g_attn (packed), ssq0 = tile sums of squares of x_in, x_in fp32 rows.
-// Out: x rows in x_out; actX = x_out * next_gain if next_gain, ssq0 = tile sums of x_out.
+// In:  act_in = x_in * g_attn (packed), ssq_in = tile sums of squares of x_in, x_in fp32 rows.
+// Out: x rows in x_out and what `out` says.
 int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, size_t wd_off, const float *g2,
-              int M, int pos0, const float *x_in, float *x_out, const float *next_gain, bool with_ffn)
+              int M, int pos0, const void *act_in, const float *ssq_in, const float *x_in, float *x_out, const RowsOut &out, bool with_ffn)
 {
     const kg_config &c = x->c;
     const int d = c.d_model, f = c.d_ffn;
-    float *ssq0 = at<float>(x->scr, x->s_ssq0), *ssq1 = at<float>(x->scr, x->s_ssq1);
+    float *ssq1 = at<float>(x->scr, x->s_ssq1);
     void *actX = x->scr + x->s_actX, *actA = x->scr + x->s_actA, *actF = x->scr + x->s_actF;
     float *x_mid = with_ffn ? at<float>(x->scr, x->s_x1) : x_out;
 
     Epi e = epi_base(x, EPI_PLAIN, M, 3 * d);
-    e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
-    KGCHK(launch_gemv(x, qkv_off, 3 * d, d, actX, e));
+    e.ssq_in = ssq_in; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
+    KGCHK(launch_gemv(x, qkv_off, 3 * d, d, act_in, e));
     KGCHK(launch_attn(x, slot, pos0, M, 0));
 
     e = epi_base(x, EPI_RESID, M, d);
-    e.res = x_in; e.xout = x_mid; e.act_out = actX; e.act_K = d;
-    if (with_ffn) { e.gain = g2; e.ssq_out = ssq1; }
-    else { e.gain = next_gain; e.ssq_out = ssq0; if (!next_gain) e.act_out = nullptr; }
+    e.res = x_in; e.xout = x_mid;
+    if (with_ffn) { e.act_out = actX; e.act_K = d; e.gain = g2; e.ssq_out = ssq1; }
+    else set_rows_out(e, out, d);
     KGCHK(launch_gemv(x, wo_off, d, d, actA, e));
     if (!with_ffn) return KG_OK;
 
@@ -825,16 +855,16 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     KGCHK(launch_gemv(x, gu_off, 2 * f, d, actX, e));
 
     e = epi_base(x, EPI_RESID, M, d);
-    e.res = x_mid; e.xout = x_out; e.act_out = next_gain ? actX : nullptr; e.act_K = d; e.gain = next_gain;
-    e.ssq_out = ssq0;
+    e.res = x_mid; e.xout = x_out;
+    set_rows_out(e, out, d);
     KGCHK(launch_gemv(x, wd_off, d, f, actF, e));
     return KG_OK;
 }
 
-// Decoder blocks lo..hi-1.  x_first: fp32 rows feeding block lo (already packed into actX/ssq0
-// with norm1[lo]); the result rows land in x_last; final_gain prepares actX for what follows.
-int run_layers(kg_ctx *x, int lo, int hi, int M, int pos0, const float *x_first, float *x_last,
-               const float *final_gain)
+// Decoder blocks lo..hi-1.  x_first: fp32 rows feeding block lo (already packed into act_in / ssq_in
+// with norm1[lo]); the result rows land in x_last and where `out` says.
+int run_layers(kg_ctx *x, int lo, int hi, int M, int pos0, const void *act_in, const float *ssq_in, const float *x_first, float *x_last,
+               const RowsOut &out)
 {
     float *x0 = at<float>(x->scr, x->s_x0);
     const float *xin = x_first;
@@ -842,9 +872,9 @@ int run_layers(kg_ctx *x, int lo, int hi, int M, int pos0, const float *x_first,
         const LayerW &w = x->lw[i];
         bool last = (i == hi - 1);
         float *xout = last ? x_last : x0;
-        const float *ng = last ? final_gain : at<const float>(x->arena, x->lw[i + 1].g1);
-        KGCHK(run_block(x, i, w.qkv, w.wo, w.gu, w.wd, at<const float>(x->arena, w.g2), M, pos0, xin, xout, ng, true));
-        xin = xout;
+        const RowsOut o = last ? out : rows_out(x, at<const float>(x->arena, x->lw[i + 1].g1));
+        KGCHK(run_block(x, i, w.qkv, w.wo, w.gu, w.wd, at<const float>(x->arena, w.g2), M, pos0, act_in, ssq_in, xin, xout, o, true));
+        xin = xout; act_in = x->scr + x->s_actX; ssq_in = at<const float>(x->scr, x->s_ssq0);
     }
     return KG_OK;
 }
@@ -855,6 +885,13 @@ int run_layers(kg_ctx *x, int lo, int hi, int M, int pos0, const float *x_first,
 int run_head(kg_ctx *x, int M, int row_shift, float *logits, int n_out, float inv_temp, int mode = 0,
              const USrc *us = nullptr, int purpose = 0, float *stat = nullptr, bool draft = false)
 {
+    // a draft's token goes on into the shallow layers: its embedding is looked up where the token is found
+    EmbedOut emb;
+    memset(&emb, 0, sizeof(emb));
+    if (draft) {
+        emb.table = x->arena + x->embed; emb.bf = x->bf; emb.d = x->c.d_model; emb.gain = at<const float>(x->arena, x->lw[0].g1);
+        emb.xout = at<float>(x->scr, x->s_x0); emb.ssq = at<float>(x->scr, x->s_ssq0); emb.act = x->scr + x->s_actX;
+    }
     // the draft head is the adapter's own where its architecture has one (Table 2), else the shared LM head
     const size_t head_off = (draft && x->a_head) ? x->a_head : x->head;
     Epi e = epi_base(x, EPI_HEAD, M, x->c.vocab);
@@ -865,8 +902,8 @@ int run_head(kg_ctx *x, int M, int row_shift, float *logits, int n_out, float in
     USrc uu;
     if (us) uu = *us; else memset(&uu, 0, sizeof(uu));
     hipLaunchKernelGGL(head_final_kernel, dim3(n_out), dim3(1024), 0, x->stream, at<const float>(x->scr, x->s_hstat),
-                       x->c.vocab / 16, (const float *)logits, x->c.vocab, inv_temp, mode, uu, purpose, at<int>(x->scr, x->s_tok),
-                       at<float>(x->scr, x->s_conf), stat ? stat : at<float>(x->scr, x->s_tstat));
+                       x->c.vocab / 16, (const float *)logits, x->c.vocab, inv_temp, mode, uu, purpose, x->h_res, ++x->seq,
+                       stat ? stat : at<float>(x->scr, x->s_tstat), emb);
     return check_launch(x, "head_final");
 }
 
@@ -892,6 +929,11 @@ int usrc_row(kg_ctx *x, const kg_params *p, USrc &us, int row, int pos, int purp
     return KG_OK;
 }
 
+double now_s()
+{
+    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+
 // a token outside the vocabulary means the logits were not finite (the arg-max found no maximum)
 int check_tokens(kg_ctx *x, int n)
 {
@@ -901,26 +943,67 @@ int check_tokens(kg_ctx *x, int n)
     return KG_OK;
 }
 
-int fetch_results(kg_ctx *x, int n)
+// Waits until the words `first` .. first + n - 1 carry the number of the last launch that posts results.  poll: by looking at them, which
+// has the host at work again some 30 us before a stream synchronisation does (toy model, 32 tokens: 3.2 -> 2.8 ms a request; 7B,
+// 4000-token prompt, 150 tokens: 72.2 -> 70.8).  A wait of more than 20 ms (a long prompt, or a failed launch) goes on in
+// hipStreamSynchronize.  Steps whose caller will read logits next synchronise at once: the copy to pageable memory waits for the runtime to
+// have seen the stream's end, and behind a poll a 7B step with its logits took 30 us longer.
+int await_words(kg_ctx *x, int first, int n, bool poll)
+{
+    auto arrived = [&]() {
+        for (int i = 0; i < n; i++)
+            if ((unsigned)(__atomic_load_n(&x->h_res[first + i], __ATOMIC_ACQUIRE) >> 32) != x->seq) return false;
+        return true;
+    };
+    if (poll && !x->profiling) {
+        const double t0 = now_s();
+        while (!arrived() && now_s() - t0 < 0.02)
+            for (int i = 0; i < 32; i++) __builtin_ia32_pause();
+        if (arrived()) return KG_OK;
+    }
+    HIPCHK(x, hipStreamSynchronize(x->stream));
+    if (!arrived()) return fail(x, KG_EHIP, "a finished launch left no results");
+    return KG_OK;
+}
+
+int fetch_results(kg_ctx *x, int n, bool poll)
 {
     prof_flush(x);
-    HIPCHK(x, hipMemcpyAsync(x->h_tok, x->scr + x->s_tok, KG_ROWS * 8, hipMemcpyDeviceToHost, x->stream));
-    HIPCHK(x, hipStreamSynchronize(x->stream));
+    KGCHK(await_words(x, 0, n, poll));
+    KGCHK(await_words(x, KG_ROWS, n, poll));
     if (x->profiling) prof_collect(x);
+    for (int i = 0; i < n; i++) {
+        const uint32_t tok = (uint32_t)x->h_res[i], conf = (uint32_t)x->h_res[KG_ROWS + i];
+        memcpy(&x->h_tok[i], &tok, 4);
+        memcpy(&x->h_conf[i], &conf, 4);
+    }
     return check_tokens(x, n);
 }
 
 float *Frow(kg_ctx *x, int j) { return at<float>(x->scr, x->s_F) + (size_t)(j + 1) * x->c.d_model; } // f_j
 float *Flag(kg_ctx *x) { return at<float>(x->scr, x->s_F); }
 
-// shallow sub-network M^b[:l] on M tokens at pos0; early features go to rows f_j0..f_{j0+M-1}
-int run_shallow(kg_ctx *x, const int *tokens, int M, int pos0, int j0, const int *tok_dev = nullptr)
+const float *deep_gain(kg_ctx *x)
+{
+    return at<const float>(x->arena, x->c.exit_layer == x->c.n_layers ? x->gfinal : x->lw[x->c.exit_layer].g1);
+}
+
+// shallow sub-network M^b[:l] on M tokens at pos0 (tokens null: run_head has left the first activation of a draft's
+// token); early features go to rows f_j0..f_{j0+M-1}, packed for the adapter from row `arow` of s_actP on and for layer l from row j0
+// of s_actD on.  A single row that is not the second of a pair is kept in the lag slot as well: it may be the one the adapter
+// catches up on.
+int run_shallow(kg_ctx *x, const int *tokens, int M, int pos0, int j0, int arow)
 {
     const kg_config &c = x->c;
     float *x0 = at<float>(x->scr, x->s_x0);
-    KGCHK(launch_pack_rows(x, tokens, nullptr, M, at<const float>(x->arena, x->lw[0].g1), x0, x->scr + x->s_actX,
-                           at<float>(x->scr, x->s_ssq0), tok_dev));
-    return run_layers(x, 0, c.exit_layer, M, pos0, x0, Frow(x, j0), nullptr);
+    if (tokens)
+        KGCHK(launch_pack_rows(x, tokens, nullptr, M, at<const float>(x->arena, x->lw[0].g1), x0, x->scr + x->s_actX,
+                               at<float>(x->scr, x->s_ssq0)));
+    RowsOut o;
+    o.act = x->scr + x->s_actP; o.ssq = at<float>(x->scr, x->s_ssqP); o.gain = at<const float>(x->arena, x->a_gin); o.row = arow;
+    o.act2 = x->scr + x->s_actD; o.ssq2 = at<float>(x->scr, x->s_ssqD); o.gain2 = deep_gain(x); o.row2 = j0;
+    o.xout2 = M == 1 && arow == 0 ? Flag(x) : nullptr;
+    return run_layers(x, 0, c.exit_layer, M, pos0, x->scr + x->s_actX, at<const float>(x->scr, x->s_ssq0), x0, Frow(x, j0), o);
 }
 
 // adapter A on rows starting at F-buffer row `frow` (0 = lag slot), positions pos0..; when
@@ -930,30 +1013,31 @@ int run_adapter(kg_ctx *x, int frow, int M, int pos0, bool full)
     const kg_config &c = x->c;
     const int d = c.d_model;
     const float *rows = at<float>(x->scr, x->s_F) + (size_t)frow * c.d_model;
-    const float *glast = at<const float>(x->arena, x->a_glast);
+    const RowsOut out = rows_out(x, at<const float>(x->arena, x->a_glast));
+    void *act = x->scr + x->s_actP;
+    float *ssq = at<float>(x->scr, x->s_ssqP);
     if (x->akind == KG_ADAPTER_MLP && !full) return KG_OK;      // no cache to fill
-    KGCHK(launch_pack_rows(x, nullptr, rows, M, at<const float>(x->arena, x->a_gin), nullptr, x->scr + x->s_actX,
-                           at<float>(x->scr, x->s_ssq0)));
+    if (!x->packed) KGCHK(launch_pack_rows(x, nullptr, rows, M, at<const float>(x->arena, x->a_gin), nullptr, act, ssq));
     if (x->akind == KG_ADAPTER_MLP) {
         // h = f + W2 . silu(W1 . RMSNorm(f; g_in)), then the last norm is folded into the head's input
         Epi e = epi_base(x, EPI_SILU, M, d);
-        e.ssq_in = at<float>(x->scr, x->s_ssq0); e.act_out = x->scr + x->s_actA; e.act_K = d;
-        KGCHK(launch_gemv(x, x->a_w1, d, d, x->scr + x->s_actX, e));
+        e.ssq_in = ssq; e.act_out = x->scr + x->s_actA; e.act_K = d;
+        KGCHK(launch_gemv(x, x->a_w1, d, d, act, e));
         e = epi_base(x, EPI_RESID, M, d);
-        e.res = rows; e.xout = at<float>(x->scr, x->s_x1); e.act_out = x->scr + x->s_actX; e.act_K = d;
-        e.gain = glast; e.ssq_out = at<float>(x->scr, x->s_ssq0);
+        e.res = rows; e.xout = at<float>(x->scr, x->s_x1);
+        set_rows_out(e, out, d);
         return launch_gemv(x, x->a_w2, d, d, x->scr + x->s_actA, e);
     }
     if (!full) {
         Epi e = epi_base(x, EPI_PLAIN, M, 3 * c.d_model);
-        e.ssq_in = at<float>(x->scr, x->s_ssq0); e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
-        KGCHK(launch_gemv(x, x->a_qkv, 3 * c.d_model, c.d_model, x->scr + x->s_actX, e));
+        e.ssq_in = ssq; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
+        KGCHK(launch_gemv(x, x->a_qkv, 3 * c.d_model, c.d_model, act, e));
         return launch_attn(x, c.n_layers, pos0, M, 1);
     }
     if (x->akind == KG_ADAPTER_LAYER)     // one whole decoder block with the adapter's weights
         return run_block(x, c.n_layers, x->a_qkv, x->a_wo, x->a_gu, x->a_wd, at<const float>(x->arena, x->a_gpost), M,
-                         pos0, rows, at<float>(x->scr, x->s_x0), glast, true);
-    return run_block(x, c.n_layers, x->a_qkv, x->a_wo, 0, 0, nullptr, M, pos0, rows, at<float>(x->scr, x->s_x1), glast,
+                         pos0, act, ssq, rows, at<float>(x->scr, x->s_x0), out, true);
+    return run_block(x, c.n_layers, x->a_qkv, x->a_wo, 0, 0, nullptr, M, pos0, act, ssq, rows, at<float>(x->scr, x->s_x1), out,
                      false);
 }
 
@@ -965,9 +1049,10 @@ int run_deep(kg_ctx *x, int M, int pos0)
     const float *gf = at<const float>(x->arena, x->gfinal);
     if (c.exit_layer == c.n_layers)
         return launch_pack_rows(x, nullptr, Frow(x, 0), M, gf, nullptr, x->scr + x->s_actX, at<float>(x->scr, x->s_ssq0));
-    KGCHK(launch_pack_rows(x, nullptr, Frow(x, 0), M, at<const float>(x->arena, x->lw[c.exit_layer].g1), nullptr,
-                           x->scr + x->s_actX, at<float>(x->scr, x->s_ssq0)));
-    return run_layers(x, c.exit_layer, c.n_layers, M, pos0, Frow(x, 0), at<float>(x->scr, x->s_x0), gf);
+    void *act = x->scr + x->s_actD;
+    float *ssq = at<float>(x->scr, x->s_ssqD);
+    if (!x->packed) KGCHK(launch_pack_rows(x, nullptr, Frow(x, 0), M, deep_gain(x), nullptr, act, ssq));
+    return run_layers(x, c.exit_layer, c.n_layers, M, pos0, act, ssq, Frow(x, 0), at<float>(x->scr, x->s_x0), rows_out(x, gf));
 }
 
 int check_ready(kg_ctx *x)
@@ -1011,11 +1096,6 @@ int tensor_slot(const kg_ctx *x, int kind, int layer)
     if (kind <= KG_FINAL_NORM) return kind;
     if (kind <= KG_NORM2) return 3 + layer * 9 + (kind - KG_WQ);
     return 3 + x->c.n_layers * 9 + (kind - KG_A_WQ);
-}
-
-double now_s()
-{
-    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
 } // namespace
@@ -1118,12 +1198,12 @@ int kg_bind(kg_ctx *x, void *weights_dev, size_t weight_bytes, void *kv_dev, siz
         return fail(x, KG_EINVAL, "device buffers must be %zu-byte aligned", ALIGN);
     if (weight_bytes < x->arena_bytes || kv_bytes < x->kv_bytes || scratch_bytes < x->scratch_bytes)
         return fail(x, KG_ENOSPC, "buffers too small: need %zu/%zu/%zu bytes", x->arena_bytes, x->kv_bytes, x->scratch_bytes);
+    if (x->bound) HIPCHK(x, hipStreamSynchronize(x->stream));      // nothing under way uses the buffers given back
     x->arena = (char *)weights_dev; x->kv = (char *)kv_dev; x->scr = (char *)scratch_dev;
     x->stream = (hipStream_t)hip_stream;
-    if (!x->h_tok) {
-        HIPCHK(x, hipHostMalloc((void **)&x->h_tok, KG_ROWS * 8, hipHostMallocDefault));
-        x->h_conf = reinterpret_cast<float *>(x->h_tok + KG_ROWS);
-        HIPCHK(x, hipEventCreateWithFlags(&x->ev_fetch, hipEventDisableTiming));
+    if (!x->h_res) {
+        HIPCHK(x, hipHostMalloc((void **)&x->h_res, RES_WORDS * sizeof(*x->h_res), hipHostMallocMapped | hipHostMallocCoherent));
+        memset(x->h_res, 0, RES_WORDS * sizeof(*x->h_res));
     }
     x->bound = true;
     x->tr = nullptr;
@@ -1197,6 +1277,7 @@ int kg_load_tensor(kg_ctx *x, int kind, int layer, const void *src, size_t n_ele
     KGCHK(check_launch(x, "load_tensor"));
     HIPCHK(x, hipStreamSynchronize(x->stream));
     x->loaded[tensor_slot(x, kind, layer)] = 1;
+    x->packed = false;           // a sequence under way goes on with the new gains
     if (kind >= KG_A_WQ) x->tr = nullptr;   // the training master copies no longer match the adapter: bind again
     return KG_OK;
 }
@@ -1219,24 +1300,32 @@ int kg_set_page_order(kg_ctx *x, const int32_t *perm, int n)
     return KG_OK;
 }
 
-int kg_reset(kg_ctx *x)
+// a new sequence: host state, and the page counters in case a launch of the last one failed
+static int reset_sequence(kg_ctx *x)
 {
-    if (!x) return KG_EINVAL;
     x->phase = Phase::NONE;
     x->base = x->adapter_len = x->lag = 0;
     x->n_drafts = x->stopped = 0;
     x->pending = -1;
     x->spec_shallow = -1;
+    x->packed = true;
     if (x->bound) {
         HIPCHK(x, hipMemsetAsync(x->scr + x->s_cnt, 0, (size_t)x->c.n_heads * 4, x->stream));
         if (x->pf_rows > 0)
             HIPCHK(x, hipMemsetAsync(x->scr + x->s_pcnt, 0, (size_t)(x->pf_rows / KG_ROWS) * x->c.n_heads * 4, x->stream));
-        HIPCHK(x, hipStreamSynchronize(x->stream));
     }
     return KG_OK;
 }
 
-int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int32_t *first_token)
+int kg_reset(kg_ctx *x)
+{
+    if (!x) return KG_EINVAL;
+    KGCHK(reset_sequence(x));
+    if (x->bound) HIPCHK(x, hipStreamSynchronize(x->stream));
+    return KG_OK;
+}
+
+static int prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int32_t *first_token, bool poll)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1248,7 +1337,7 @@ int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int3
     USrc u_first;
     memset(&u_first, 0, sizeof(u_first));
     KGCHK(usrc_row(x, p, u_first, 0, n, 2));
-    KGCHK(kg_reset(x));
+    KGCHK(reset_sequence(x));
     x->acct_phase = 3;
     float inv_t = p->mode == 1 ? 1.f / p->temperature : 1.f;
     if (x->pf_rows > 0 && !(x->kvt == 2 && n <= KG_ROWS)) {
@@ -1270,13 +1359,13 @@ int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int3
     } else {
         for (int pos0 = 0; pos0 < n; pos0 += KG_ROWS) {
             int M = std::min(KG_ROWS, n - pos0);
-            KGCHK(run_shallow(x, prompt + pos0, M, pos0, 0));
+            KGCHK(run_shallow(x, prompt + pos0, M, pos0, 0, 0));
             KGCHK(run_adapter(x, 1, M, pos0, false));
             KGCHK(run_deep(x, M, pos0));
             if (pos0 + M == n) KGCHK(run_head(x, M, -(M - 1), at<float>(x->scr, x->s_tlog), 1, inv_t, p->mode, &u_first, 2));
         }
     }
-    KGCHK(fetch_results(x, 1));
+    KGCHK(fetch_results(x, 1, poll));
     x->base = n; x->adapter_len = n; x->lag = 0;
     x->n_drafts = 0; x->stopped = 0;
     x->n_target_rows = 1;
@@ -1285,6 +1374,11 @@ int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int3
     x->phase = Phase::READY;
     *first_token = x->pending;
     return KG_OK;
+}
+
+int kg_prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, int32_t *first_token)
+{
+    return prefill(x, p, prompt, n, first_token, false);
 }
 
 int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confidence, int *stop)
@@ -1303,11 +1397,12 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
     KGCHK(usrc_row(x, p, u_draft, 0, pos + 1, 0));
     // a run-ahead pass that becomes this step's shallow pass was booked as shallow-only: move it
     x->acct_phase = 0;
-    if (x->spec_shallow != j) KGCHK(run_shallow(x, &tok, 1, pos, j));
+    const bool pair = j == 0 && x->lag && x->akind != KG_ADAPTER_MLP;   // adapter catches up on [lagged f, f_0] (Figure 2)
+    if (x->spec_shallow != j) KGCHK(run_shallow(x, &tok, 1, pos, j, pair ? 1 : 0));
     else { x->acct[1] -= x->spec_cost; x->acct[0] += x->spec_cost; }
     x->spec_shallow = -1;
     int M = 1;
-    if (j == 0 && x->lag && x->akind != KG_ADAPTER_MLP) {   // adapter catches up on [lagged f, f_0] (Figure 2)
+    if (pair) {
         M = 2;
         KGCHK(run_adapter(x, 0, 2, pos - 1, true));
     } else {
@@ -1317,21 +1412,16 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
     float *dl = at<float>(x->scr, x->s_dlog) + (size_t)j * x->c.vocab;
     KGCHK(run_head(x, M, -(M - 1), dl, 1, inv_t, p->mode, &u_draft, 0, at<float>(x->scr, x->s_dstat) + 2 * j, true));
     // The draft token's early feature is needed whatever the host decides next (one more draft
-    // step, or verification): compute it now, reading the token from device memory, so that the
-    // GPU keeps working while the host waits for the token and its confidence.  The results are
-    // copied out first: the copy is ordered before these kernels on the stream.
-    HIPCHK(x, hipMemcpyAsync(x->h_tok, x->scr + x->s_tok, KG_ROWS * 8, hipMemcpyDeviceToHost, x->stream));
-    hipEvent_t ev = x->ev_fetch;
-    HIPCHK(x, hipEventRecord(ev, x->stream));
+    // step, or verification): compute it now, from the token that run_head has looked up, so that the
+    // GPU keeps working while the host waits for the token and its confidence.
     {
         x->acct_phase = 1;
         const double before = x->acct[1];
-        KGCHK(run_shallow(x, nullptr, 1, pos + 1, j + 1, at<const int>(x->scr, x->s_tok)));
+        KGCHK(run_shallow(x, nullptr, 1, pos + 1, j + 1, 0));
         x->spec_cost = x->acct[1] - before;
     }
     x->spec_shallow = j + 1;
-    HIPCHK(x, hipEventSynchronize(ev));
-    KGCHK(check_tokens(x, 1));
+    KGCHK(fetch_results(x, 1, true));
     x->lag = 0;
     x->adapter_len = pos + 1;
     x->drafts[j] = x->h_tok[0];
@@ -1355,13 +1445,13 @@ int kg_verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus
     if (x->base + k + 1 >= x->c.max_seq) return fail(x, KG_ENOSPC, "sequence would exceed max_seq");
     const int tok = x->drafts[k - 1];
     x->acct_phase = 1;
-    if (x->spec_shallow != k) KGCHK(run_shallow(x, &tok, 1, x->base + k, k));   // next early feature f_k; adapter not run
+    if (x->spec_shallow != k) KGCHK(run_shallow(x, &tok, 1, x->base + k, k, 0));   // next early feature f_k; adapter not run
     x->spec_shallow = -1;
     x->acct_phase = 2;
     KGCHK(run_deep(x, k + 1, x->base));
     float inv_t = p->mode == 1 ? 1.f / p->temperature : 1.f;
     KGCHK(run_head(x, k + 1, 0, at<float>(x->scr, x->s_tlog), k + 1, inv_t));
-    KGCHK(fetch_results(x, k + 1));
+    KGCHK(fetch_results(x, k + 1, true));
     for (int i = 0; i <= k; i++) { x->targets[i] = x->h_tok[i]; target_tokens[i] = x->h_tok[i]; }
     x->n_target_rows = k + 1;
     *k_plus_1 = k + 1;
@@ -1394,29 +1484,26 @@ int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
                                at<const float>(x->scr, x->s_dlog), at<const float>(x->scr, x->s_tstat),
                                at<const float>(x->scr, x->s_dstat), at<const float>(x->scr, x->s_hstat), x->c.vocab, k,
                                1.f / p->temperature, dr, us,
-                               at<int>(x->scr, x->s_acc));
+                               x->h_res + RES_ACCEPT, ++x->seq);
             KGCHK(check_launch(x, "accept_sample"));
         }
         prof_flush(x);
-        HIPCHK(x, hipMemcpyAsync(x->h_tok, x->scr + x->s_acc, 8, hipMemcpyDeviceToHost, x->stream));
-        HIPCHK(x, hipStreamSynchronize(x->stream));
+        KGCHK(await_words(x, RES_ACCEPT, 2, true));
         if (x->profiling) prof_collect(x);
-        n = x->h_tok[0];
+        n = (int)(uint32_t)x->h_res[RES_ACCEPT];
+        const int drawn = (int)(uint32_t)x->h_res[RES_ACCEPT + 1];
         if (n < 0 || n > k) return fail(x, KG_EHIP, "acceptance kernel returned %d accepted drafts of %d", n, k);
-        if (x->h_tok[1] < 0 || x->h_tok[1] >= x->c.vocab)
+        if (drawn < 0 || drawn >= x->c.vocab)
             return fail(x, KG_EHIP, "acceptance kernel drew no valid token (non-finite logits)");
         for (int i = 0; i < n; i++) emitted[i] = x->drafts[i];
-        emitted[n] = x->h_tok[1];
+        emitted[n] = drawn;
     }
     *n_emitted = n + 1;
     // rollback: caches are cut by length; the adapter saw f_0..f_{k-1} only
     const int old = x->base;
     x->base = old + n + 1;
     x->adapter_len = old + std::min(n + 1, k);
-    x->lag = (n == k);
-    if (x->lag) {
-        HIPCHK(x, hipMemcpyAsync(Flag(x), Frow(x, k), (size_t)x->c.d_model * 4, hipMemcpyDeviceToDevice, x->stream));
-    }
+    x->lag = (n == k);           // f_k, the last feature computed, stands in the lag slot already
     x->pending = emitted[n];
     x->plain_len = x->base;      // a plain step after this round continues the committed sequence
     x->n_drafts = 0; x->stopped = 0;
@@ -1434,7 +1521,7 @@ int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prom
     kg_stats s;
     memset(&s, 0, sizeof(s));
     int32_t tok;
-    KGCHK(kg_prefill(x, p, prompt, n_prompt, &tok));
+    KGCHK(prefill(x, p, prompt, n_prompt, &tok, true));
     const double a0[3] = {x->acct[0], x->acct[1], x->acct[2]};
     double t0 = now_s();
     int n = 0;
@@ -1465,7 +1552,7 @@ int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prom
     return KG_OK;
 }
 
-int kg_plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_token)
+static int plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_token, bool poll)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1479,18 +1566,24 @@ int kg_plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_to
     x->acct_phase = 2;
     KGCHK(launch_pack_rows(x, &tok, nullptr, 1, at<const float>(x->arena, x->lw[0].g1), x0, x->scr + x->s_actX,
                            at<float>(x->scr, x->s_ssq0)));
-    KGCHK(run_layers(x, 0, c.n_layers, 1, x->plain_len, x0, x0, at<const float>(x->arena, x->gfinal)));
+    KGCHK(run_layers(x, 0, c.n_layers, 1, x->plain_len, x->scr + x->s_actX, at<const float>(x->scr, x->s_ssq0), x0, x0,
+                     rows_out(x, at<const float>(x->arena, x->gfinal))));
     float inv_t = p->mode == 1 ? 1.f / p->temperature : 1.f;
     USrc u_next;
     memset(&u_next, 0, sizeof(u_next));
     KGCHK(usrc_row(x, p, u_next, 0, x->plain_len + 1, 2));
     KGCHK(run_head(x, 1, 0, at<float>(x->scr, x->s_tlog), 1, inv_t, p->mode, &u_next, 2));
-    KGCHK(fetch_results(x, 1));
+    KGCHK(fetch_results(x, 1, poll));
     x->plain_len++;
     x->n_target_rows = 1;
     x->phase = Phase::PLAIN;     // the adapter cache is no longer in step: draft calls are refused
     *next_token = x->h_tok[0];
     return KG_OK;
+}
+
+int kg_plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_token)
+{
+    return plain_step(x, p, token, next_token, false);
 }
 
 int kg_decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out,
@@ -1503,13 +1596,13 @@ int kg_decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_
     kg_stats s;
     memset(&s, 0, sizeof(s));
     int32_t tok;
-    KGCHK(kg_prefill(x, p, prompt, n_prompt, &tok));
+    KGCHK(prefill(x, p, prompt, n_prompt, &tok, true));
     const double a2 = x->acct[2];
     double t0 = now_s();
     int n = 0;
     out[n++] = tok;
     while (n < max_new) {
-        KGCHK(kg_plain_step(x, p, tok, &tok));
+        KGCHK(plain_step(x, p, tok, &tok, true));
         out[n++] = tok;
         s.plain_steps++;
     }
@@ -1609,9 +1702,9 @@ const char *kg_last_error(const kg_ctx *x) { return x ? x->err : "NULL context";
 void kg_destroy(kg_ctx *x)
 {
     if (!x) return;
-    if (x->h_tok) (void)hipHostFree(x->h_tok);
+    if (x->bound) (void)hipStreamSynchronize(x->stream);      // a run-ahead pass, or the end of a launch whose results are known, may be under way
+    if (x->h_res) (void)hipHostFree(x->h_res);
     for (hipEvent_t e : x->ev_pool) (void)hipEventDestroy(e);
-    if (x->ev_fetch) (void)hipEventDestroy(x->ev_fetch);
     delete x;
 }
 
@@ -1704,6 +1797,7 @@ int kg_train_workspace_bytes(const kg_ctx *x, int max_tokens, size_t *bytes)
 // master copy <-> the arena's form of one tensor (gains: fp32 in both; rounded to the storage type on the way back)
 static int train_sync_tensor(kg_ctx *x, const TrTensor &tt, float *master, bool to_arena)
 {
+    if (to_arena) x->packed = false;    // a sequence under way goes on with the new gains
     const size_t n = (size_t)tt.rows * tt.cols;
     const unsigned blocks = (unsigned)((n + 255) / 256);
     if (tt.rows == 1) {
@@ -1872,7 +1966,7 @@ static int train_frozen_forward(kg_ctx *x, const int32_t *tokens, int n)
     } else {
         for (int pos0 = 0; pos0 < n; pos0 += KG_ROWS) {
             const int M = std::min(KG_ROWS, n - pos0);
-            KGCHK(run_shallow(x, tokens + pos0, M, pos0, 0));
+            KGCHK(run_shallow(x, tokens + pos0, M, pos0, 0, 0));
             HIPCHK(x, hipMemcpyAsync(f(t.F) + (size_t)pos0 * d, Frow(x, 0), (size_t)M * d * 4, hipMemcpyDeviceToDevice, x->stream));
             KGCHK(run_deep(x, M, pos0));
             const float *xl = c.exit_layer == c.n_layers ? Frow(x, 0) : at<const float>(x->scr, x->s_x0);

@@ -23,7 +23,7 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 #define KG_ROWS 8
 
-enum { EPI_PLAIN = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_SILU = 4, EPI_QKV = 5 };
+enum { EPI_PLAIN = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_SILU = 4, EPI_QKV = 5, EPI_FEATURE = 6 };
 
 // What a projection kernel does with a finished 16-row tile y[16][8].
 struct Epi {
@@ -54,6 +54,12 @@ struct Epi {
     int act_K;
     const float *gain;
     float *ssq_out;
+    // EPI_FEATURE (early features, decode launches): as EPI_RESID with the rows of act_out and ssq_out from act_row on; and once more for
+    // layer l (act2 <- x * gain2 and ssq2 from row row2 on), and as fp32 rows (xout2, may be null)
+    int act_row, row2;
+    void *act2;
+    const float *gain2;
+    float *ssq2, *xout2;
 };
 
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -190,7 +196,9 @@ __device__ __forceinline__ int plain_column(const Epi &e, int n)
     return (e.k_pairs && n >= d && n < 2 * d) ? n - w + (w >> 1) + (w & 1) * (e.k_pairs >> 1) : n;
 }
 
-template <bool BF>
+// (EPI_FEATURE only where the kernel is compiled for it: in the one-projection kernel of every launch its arguments, loaded ahead of the
+// weights, cost 0.4 % of a decode forward.)
+template <bool BF, bool FEATURE = !BF>
 __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_ROWS], const float *sc,
                                          float (*sq)[KG_ROWS], float resv = 0.f, float gainv = 1.f,
                                          bool prefetched = false, int t = threadIdx.x)
@@ -242,6 +250,28 @@ __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_RO
                 for (int r = 0; r < 16; r++) s += sq[r][t];
                 e.ssq_out[(size_t)rt * KG_ROWS + t] = s;
             }
+        }
+    } else if (FEATURE && e.kind == EPI_FEATURE) {
+        if (t < 128) {
+            int row = t >> 3, m = t & 7;
+            float v = 0.f;
+            if (m < e.M) {
+                const int n = rt * 16 + row;
+                const size_t at = (size_t)m * e.N + n;
+                v = resv + yt[row][m];          // (operands fetched ahead by all kernels that have this epilogue)
+                e.xout[at] = v;
+                if (e.xout2) e.xout2[at] = v;
+                store_act<BF>(e.act_out, e.act_K, m + e.act_row, n, v * gainv);
+                store_act<BF>(e.act2, e.act_K, m + e.row2, n, v * e.gain2[n]);
+            }
+            sq[row][m] = v * v;
+        }
+        __syncthreads();
+        if (t < e.M) {
+            float s = 0.f;
+            for (int r = 0; r < 16; r++) s += sq[r][t];
+            e.ssq_out[(size_t)rt * KG_ROWS + t + e.act_row] = s;
+            e.ssq2[(size_t)rt * KG_ROWS + t + e.row2] = s;
         }
     } else if (e.kind == EPI_SILU) {
         if (t < 128) {
@@ -363,7 +393,7 @@ template <int SRC> struct BSource {
 
 #define GEMV_WAVES 8
 
-template <int SRC>
+template <int SRC, bool FEATURE = false>
 __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, int KS, int M, const void *__restrict__ act,
                                                const float *ssq_in, int nt_in, int N, const float *res, const float *gain,
                                                int K, const Epi &e)
@@ -457,7 +487,7 @@ __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, in
         yt[row][m] = v;
     }
     __syncthreads();
-    epilogue<true>(e, rt, yt, sc, sq, resv, gainv, true);
+    epilogue<true, FEATURE>(e, rt, yt, sc, sq, resv, gainv, true);
 }
 
 // Everything a wave needs before its first weight load is a leading scalar argument (a copy of the
@@ -470,6 +500,13 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
                                                                    const float *res, const float *gain, Epi e)
 {
     gemv_bf16_body<FROM_ACT>(W, KS, M, act, ssq_in, nt_in, N, res, gain, 0, e);
+}
+
+// the same for the projection that gives the early features (EPI_FEATURE)
+__global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_feature_kernel(const u32x4_t *__restrict__ W, int KS, int M,
+                                                                           const u32x4_t *__restrict__ act, int N, Epi e)
+{
+    gemv_bf16_body<FROM_ACT, true>(W, KS, M, act, nullptr, 0, N, e.res, e.gain, 0, e);
 }
 
 // the same product from plain rows x[M][K] (stand-alone product: no scale, no residual); y[m][n] fp32
@@ -686,7 +723,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__
     };
     load(sub);
     float resv = 0.f, gainv = 1.f;          // epilogue operands of thread (row, m)
-    if (e.kind == EPI_RESID && threadIdx.x < 128 && (int)(threadIdx.x & 7) < e.M) {
+    if ((e.kind == EPI_RESID || e.kind == EPI_FEATURE) && threadIdx.x < 128 && (int)(threadIdx.x & 7) < e.M) {
         const int n = rt * 16 + (threadIdx.x >> 3);
         resv = e.res[(size_t)(threadIdx.x & 7) * e.N + n];
         if (e.gain) gainv = e.gain[n];
@@ -2665,11 +2702,46 @@ __device__ int tile_inverse_cdf(const float *hs, int n_tiles, const float *z, fl
 // mode 1 additionally draws the token from softmax(z / T) with the row's uniform number (of the
 // given purpose: 0 a draft token, 2 a first / plain token).
 // stat_out[row] = (max of z/T, sum exp(z/T - max)).
-__global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, int n_tiles, const float *logits,
-                                                          int V, float inv_temp, int mode, USrc us, int purpose, int *tok_out,
-                                                          float *conf_out, float *stat_out)
+// A result word for the host, which polls for the sequence number in its upper half (pinned memory; one 8-byte store, so the
+// word is complete when its number is there).
+__device__ __forceinline__ void post(unsigned long long *slot, unsigned seq, uint32_t v)
 {
-    __shared__ float bm[16], bs[16];
+    __hip_atomic_store(slot, ((unsigned long long)seq << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// emb.table: row 0's token is looked up at once and becomes the first activation of the pass that follows, as pack_rows_kernel
+// makes it from a token in device memory: 1.5 us more here for a launch less (4.6 us).
+struct EmbedOut {
+    const void *table;      // [V][d], bfloat16 or fp32; null: no lookup
+    int bf, d;
+    const float *gain;
+    float *xout, *ssq;
+    void *act;
+};
+template <bool BF>
+__device__ __forceinline__ void embed_row(const EmbedOut &o, int tok, int V, float *sq)
+{
+    const int id = min(max(tok, 0), V - 1);
+    for (int n = threadIdx.x; n < o.d; n += 1024) {
+        const size_t idx = (size_t)id * o.d + n;
+        const float v = BF ? bf2f(((const uint16_t *)o.table)[idx]) : ((const float *)o.table)[idx];
+        o.xout[n] = v;
+        store_act<BF>(o.act, o.d, 0, n, v * o.gain[n]);
+        sq[n + (n >> 4)] = v * v;
+    }
+    __syncthreads();
+    for (int rt = threadIdx.x; rt < o.d >> 4; rt += 1024) {
+        float s = 0.f;
+        for (int r = 0; r < 16; r++) s += sq[17 * rt + r];
+        o.ssq[(size_t)rt * KG_ROWS] = s;
+    }
+}
+
+__global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, int n_tiles, const float *logits,
+                                                          int V, float inv_temp, int mode, USrc us, int purpose,
+                                                          unsigned long long *host, unsigned seq, float *stat_out, EmbedOut emb)
+{
+    __shared__ float bm[16], bs[16], sq[8192 + 512];      // d <= 8192; one float of padding per 16: embed_row's sums read without conflicts
     __shared__ int bi[16];
     __shared__ float fin[2];
     __shared__ int fin_i;
@@ -2706,16 +2778,24 @@ __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, in
             sum = a + b;
         }
         fin[0] = best; fin[1] = sum; fin_i = idx;
-        conf_out[m] = 1.f / sum;
+        post(host + KG_ROWS + m, seq, __float_as_uint(1.f / sum));
         stat_out[2 * m] = best;
         stat_out[2 * m + 1] = sum;
-        if (mode == 0) tok_out[m] = idx;
+        if (mode == 0) post(host + m, seq, (uint32_t)idx);
     }
-    if (mode == 0) return;
+    const bool look_up = emb.table && m == 0;
+    if (mode == 0 && !look_up) return;
     __syncthreads();
-    const int tok = tile_inverse_cdf(hstat + (size_t)m * n_tiles * 4, n_tiles, logits + (size_t)m * V, inv_temp, fin[0],
-                                     row_uniform(us, m, purpose, 0));
-    if (t == 0) tok_out[m] = tok < 0 ? fin_i : tok;
+    int tok = fin_i;
+    if (mode != 0) {
+        const int drawn = tile_inverse_cdf(hstat + (size_t)m * n_tiles * 4, n_tiles, logits + (size_t)m * V, inv_temp, fin[0],
+                                           row_uniform(us, m, purpose, 0));
+        if (drawn >= 0) tok = drawn;
+        if (t == 0) post(host + m, seq, (uint32_t)tok);
+    }
+    if (!look_up) return;
+    if (emb.bf) embed_row<true>(emb, tok, V, sq);
+    else embed_row<false>(emb, tok, V, sq);
 }
 
 // Speculative-sampling acceptance of one round (Section 3: the first rejected draft discards the
@@ -2728,7 +2808,7 @@ __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, in
 // out[0] = number of accepted drafts, out[1] = the redrawn / bonus token.
 __global__ __launch_bounds__(1024) void accept_sample_kernel(const float *zt, const float *zd, const float *tstat,
                                                              const float *dstat, const float *hstat_t, int V, int k,
-                                                             float inv_temp, I8 drafts, USrc us, int *out)
+                                                             float inv_temp, I8 drafts, USrc us, unsigned long long *host, unsigned seq)
 {
     __shared__ int n_acc;
     const int t = threadIdx.x;
@@ -2766,7 +2846,7 @@ __global__ __launch_bounds__(1024) void accept_sample_kernel(const float *zt, co
     }
     // all drafts kept (or an empty residual): the bonus token from p_n, through the target head's tile statistics
     if (tok < 0) tok = tile_inverse_cdf(hstat_t + (size_t)n * (V / 16) * 4, V / 16, zp, inv_temp, pm, row_uniform(us, n, 2, 1));
-    if (t == 0) { out[0] = n; out[1] = tok; }
+    if (t == 0) { post(host, seq, (uint32_t)n); post(host + 1, seq, (uint32_t)tok); }
 }
 
 // Streaming read of a buffer with no dependencies between the loads: the bandwidth that a weight

@@ -580,3 +580,39 @@ def test_seeded_sampling_is_sampling_from_the_seed_s_table(name, hs, temp):
                                              gpu_seed=seed)
     assert out[:40] == a[:40]
     kg.close()
+
+
+@pytest.mark.parametrize("name,exit_layer,adapter", [("toy", 1, 0), ("toy", 4, 0), ("toy_bf16", 2, 2), ("small_bf16", 2, 0), ("small_bf16", 6, 3)])
+def test_early_features_packed_by_the_shallow_pass_equal_rows_packed_again(name, exit_layer, adapter):
+    """The last shallow projection leaves the early features packed for the adapter (a lagged one beside the next round's first) and for layer
+    l; a tensor loaded in the middle of a sequence has every later read pack them again from the fp32 rows.  Same bits: tokens,
+    confidences, draft and target logits of every round, with drafts of every length and full and partial acceptance."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = dataclasses.replace(I.SHAPES[name], exit_layer=exit_layer, adapter=adapter)
+    W = I.gen_weights(shape, seed=3, alpha=0.05, head_scale=25.0)
+    prompt = I.gen_prompt(shape.vocab, 21)
+    p, _ = B.make_params(eta=0.5, gamma=6)
+    runs, lags = [], []
+    for again in (False, True):
+        kg = P.load_model(shape, W, 128, kv_page_tokens=16)
+        log = [kg.prefill(p, prompt)]
+        for _ in range(12):
+            stop = False
+            while not stop:
+                tok, conf, stop = kg.draft_step(p)
+                log += [tok, conf]
+                if again:
+                    kg.load_tensor(I.KIND_A_NORM_IN, -1, W[(I.KIND_A_NORM_IN, -1)])
+            n = kg.state()[3]
+            log += [kg.read_logits(0, i) for i in range(n)] + kg.verify(p)
+            log += [kg.read_logits(1, i) for i in range(n + 1)] + kg.accept(p)
+            lags.append(kg.state()[2])
+            if lags[-1]:
+                log.append(kg.read_feature(-1))
+        runs.append(log)
+        kg.close()
+    assert 1 in lags and (0 in lags or exit_layer == shape.n_layers), "full and (where drafts can be wrong) partial acceptance"
+    assert len(runs[0]) == len(runs[1])
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
