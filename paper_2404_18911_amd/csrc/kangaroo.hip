@@ -1797,7 +1797,6 @@ int kg_train_workspace_bytes(const kg_ctx *x, int max_tokens, size_t *bytes)
 // master copy <-> the arena's form of one tensor (gains: fp32 in both; rounded to the storage type on the way back)
 static int train_sync_tensor(kg_ctx *x, const TrTensor &tt, float *master, bool to_arena)
 {
-    if (to_arena) x->packed = false;    // a sequence under way goes on with the new gains
     const size_t n = (size_t)tt.rows * tt.cols;
     const unsigned blocks = (unsigned)((n + 255) / 256);
     if (tt.rows == 1) {
@@ -1807,10 +1806,7 @@ static int train_sync_tensor(kg_ctx *x, const TrTensor &tt, float *master, bool 
         else HIPCHK(x, hipMemcpyAsync(ar, master, n * 4, hipMemcpyDeviceToDevice, x->stream));
     } else if (x->bf) {
         const int KS = (tt.cols + 31) / 32;
-        if (to_arena)     // columns are a multiple of 8 for every tiled matrix (checked at load), master rows 16-byte aligned
-            hipLaunchKernelGGL(tr_pack_bf16_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, x->stream, (const float *)master, tt.rows, tt.cols, KS,
-                               tt.row_off, tt.mode, at<uint16_t>(x->arena, tt.arena_off));
-        else
+        if (!to_arena)          // (to the arena: tr_adamw_pack_kernel)
             hipLaunchKernelGGL(tr_unpack_bf16_kernel, dim3(blocks), dim3(256), 0, x->stream, at<const uint16_t>(x->arena, tt.arena_off),
                                tt.rows, tt.cols, KS, tt.row_off, tt.mode, master);
     } else {
@@ -1857,7 +1853,12 @@ static void launch_tr_gemm(TrGemm &g, int z, hipStream_t s)
 {
     g.gm = (g.M + TRG_M - 1) / TRG_M; g.gn = (g.N + TRG_N - 1) / TRG_N;
     g.swz = g.gn % 8 == 0 || g.gn >= 16;        // else columns of C would leave XCDs idle
-    const dim3 grid(g.swz ? 8 * g.gm * ((g.gn + 7) / 8) : g.gm * g.gn, 1, z);
+    int tiles = g.swz ? 8 * g.gm * ((g.gn + 7) / 8) : g.gm * g.gn;
+    if (g.causal) {
+        tiles = 0;
+        for (int m = 0; m < g.gm; m++) tiles += trg_causal_tiles(m, g.gn);
+    }
+    const dim3 grid(tiles, 1, z);
     const bool ka = g.sak == 1, kb = g.b_mode == 0 ? g.sbk == 1 : g.b_mode == 1, guard = !g.a_vec || (g.b_mode == 0 && !g.b_vec);
 #define TR_GEMM_LAUNCH(...) hipLaunchKernelGGL((tr_gemm_kernel<__VA_ARGS__>), grid, dim3(512), 0, s, g)
     if (g.b_mode) {             // against bf16 tiles: the callers' A are aligned rows
@@ -1877,6 +1878,7 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
                    long ldc, int M, int N, int K, int accumulate)
 {
     TrGemm g;
+    g.causal = 0;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = b_mode; g.b_KS = x->KSd;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
     g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
@@ -1903,9 +1905,10 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
 
 // One product per attention head in a single launch: head h reads A + h * bsa, B + h * bsb and writes C + h * bsc.
 static int tr_gemm_heads(kg_ctx *x, const float *A, long sam, long sak, long bsa, const float *B, long sbk, long sbn, long bsb,
-                         float *C, long ldc, long bsc, int M, int N, int K, int heads)
+                         float *C, long ldc, long bsc, int M, int N, int K, int heads, bool causal = false)
 {
     TrGemm g;
+    g.causal = causal;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = 0;
     g.batch = heads; g.bsa = bsa; g.bsb = bsb; g.bsc = bsc;
@@ -2052,7 +2055,7 @@ static int train_graph(kg_ctx *x, int n, double *loss)
     auto rms_bwd = [&](const float *in, const float *g, const float *r, const float *dy, float *dx, float *dg) {
         other();
         hipLaunchKernelGGL(tr_rmsnorm_bwd_kernel, dim3(n), dim3(256), 0, x->stream, in, g, r, dy, d, dx);
-        hipLaunchKernelGGL(tr_gain_grad_kernel, dim3((d + 63) / 64), dim3(1024), 0, x->stream, in, r, dy, n, d, dg, acc);
+        hipLaunchKernelGGL(tr_gain_grad_kernel, dim3((d + 15) / 16), dim3(1024), 0, x->stream, in, r, dy, n, d, dg, acc);
         return check_launch(x, "train_rmsnorm_bwd");
     };
     auto ew_blocks = [](size_t cnt) { return dim3((unsigned)((cnt + 255) / 256)); };
@@ -2078,7 +2081,8 @@ static int train_graph(kg_ctx *x, int n, double *loss)
             // causal attention, one product per head: S = Q.K^T, P = softmax(S / sqrt(hd)), O = P.V
             const float *Q = f(t.QKV), *K = f(t.QKV) + d, *Vv = f(t.QKV) + 2 * d;
             const long TT = (long)n * n;
-            KGCHK(tr_gemm_heads(x, Q, 3 * d, 1, hd, K, 1, 3 * d, hd, f(t.Pm), n, TT, n, n, hd, H));
+            // (1000 positions, without the tiles above the diagonal: 84 -> 72 us, and dP below 99 -> 76)
+            KGCHK(tr_gemm_heads(x, Q, 3 * d, 1, hd, K, 1, 3 * d, hd, f(t.Pm), n, TT, n, n, hd, H, true));
             other();
             hipLaunchKernelGGL(tr_softmax_causal_kernel, dim3(n, H), dim3(256), 0, x->stream, f(t.Pm), n, 1.f / sqrtf((float)hd));
             KGCHK(check_launch(x, "train_softmax"));
@@ -2146,7 +2150,7 @@ static int train_graph(kg_ctx *x, int n, double *loss)
             // dP = dO.V^T, dV = P^T.dO, dS = P (dP - rowsum(dP P)) / sqrt(hd), dQ = dS.K, dK = dS^T.Q, per head
             const float *Q = f(t.QKV), *K = f(t.QKV) + d, *Vv = f(t.QKV) + 2 * d;
             const long TT = (long)n * n;
-            KGCHK(tr_gemm_heads(x, f(t.dO), d, 1, hd, Vv, 1, 3 * d, hd, f(t.dS), n, TT, n, n, hd, H));
+            KGCHK(tr_gemm_heads(x, f(t.dO), d, 1, hd, Vv, 1, 3 * d, hd, f(t.dS), n, TT, n, n, hd, H, true));
             KGCHK(tr_gemm_heads(x, f(t.Pm), 1, n, TT, f(t.dO), d, 1, hd, f(t.dQKV) + 2 * d, 3 * d, hd, n, hd, n, H));
             other();
             hipLaunchKernelGGL(tr_dsoftmax_kernel, dim3(n, H), dim3(256), 0, x->stream, (const float *)f(t.Pm), f(t.dS), n,
@@ -2163,7 +2167,7 @@ static int train_graph(kg_ctx *x, int n, double *loss)
         KGCHK(tr_bwd(x, f(t.dQKV), P + o_a, f(t.dN), n, 3 * d, d, 0));              // dN = dQKV . Wqkv
     }
     other();
-    hipLaunchKernelGGL(tr_gain_grad_kernel, dim3((d + 63) / 64), dim3(1024), 0, x->stream, (const float *)f(t.F),
+    hipLaunchKernelGGL(tr_gain_grad_kernel, dim3((d + 15) / 16), dim3(1024), 0, x->stream, (const float *)f(t.F),
                        (const float *)f(t.rin), (const float *)f(t.dN), n, d, G + o_gin, acc);
     KGCHK(check_launch(x, "train_gain_grad"));
     // loss of this sequence (before any update), summed over positions in double on the host
@@ -2196,9 +2200,19 @@ int kg_train_apply(kg_ctx *x, const kg_train_params *hp)
     { ProfScope ps(x, 2, 0.0); }
     for (const TrTensor &tt : train_tensors(x)) {
         const size_t cnt = (size_t)tt.rows * tt.cols;
+        const float wd = tt.decay ? hp->weight_decay : 0.f;
+        if (x->bf && tt.rows > 1) {
+            // columns are a multiple of 8 for every tiled matrix (checked at load), master rows 16-byte aligned
+            const int KS = (tt.cols + 31) / 32;
+            hipLaunchKernelGGL(tr_adamw_pack_kernel, dim3((unsigned)((tt.rows + 15) / 16 * ((tt.cols + 127) / 128))), dim3(256), 0, x->stream, P + tt.off, (const float *)(G + tt.off),
+                               Mo + tt.off, Vo + tt.off, tt.rows, tt.cols, KS, hp->lr, hp->beta1, hp->beta2, hp->eps, wd, c1, c2, tt.row_off, tt.mode,
+                               at<uint16_t>(x->arena, tt.arena_off));
+            KGCHK(check_launch(x, "train_adamw"));
+            continue;
+        }
         hipLaunchKernelGGL(tr_adamw_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, x->stream, P + tt.off,
                            (const float *)(G + tt.off), Mo + tt.off, Vo + tt.off, cnt, hp->lr, hp->beta1, hp->beta2, hp->eps,
-                           tt.decay ? hp->weight_decay : 0.f, c1, c2);
+                           wd, c1, c2);
         KGCHK(check_launch(x, "train_adamw"));
         KGCHK(train_sync_tensor(x, tt, P + tt.off, true));
     }
@@ -2206,6 +2220,7 @@ int kg_train_apply(kg_ctx *x, const kg_train_params *hp)
     HIPCHK(x, hipStreamSynchronize(x->stream));
     if (x->profiling) prof_collect(x);
     x->tr_pending = 0;
+    x->packed = false;                  // a sequence under way goes on with the new gains
     x->phase = Phase::NONE;
     return KG_OK;
 }
@@ -2255,7 +2270,7 @@ int kg_op_gemm_f32(const float *A, long sam, long sak, const float *B, long sbk,
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
     g.k_chunk = (K + TRG_K - 1) / TRG_K * TRG_K; g.part = nullptr;
-    g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
+    g.batch = 1; g.bsa = g.bsb = g.bsc = 0; g.causal = 0;
     tr_gemm_vec_flags(g);
     launch_tr_gemm(g, 1, (hipStream_t)hip_stream);
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;

@@ -68,6 +68,7 @@ struct TrGemm {
     int batch;          // > 1: blockIdx.z is a batch index (one product per attention head), k is not split
     long bsa, bsb, bsc; // element offsets of A, B (b_mode 0) and C per batch index
     int gm, gn, swz;    // tiles of C; swz: see the tile order in the kernel
+    int causal;         // C[m][n] is needed for n <= m only: the launch holds the tiles that reach the diagonal (20 of 32 at 1000 positions)
 };
 
 __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
@@ -299,6 +300,13 @@ __device__ __forceinline__ void tr_gemm_store(const TrGemm &g, size_t boc, int m
         }
 }
 
+// tiles of row tm of C that hold an element with n <= m
+__host__ __device__ __forceinline__ int trg_causal_tiles(int tm, int gn)
+{
+    const int c = (tm * TRG_M + TRG_M - 1) / TRG_N + 1;
+    return c < gn ? c : gn;
+}
+
 // BP: bf16 parts of B (3: fp32 operand, 1: bf16 tiles); KA / KB: A / B contiguous along k (KB of tiles: b_mode 1);
 // GUARD: operands that cannot be fetched in aligned groups of four.
 template <int BP, bool KA, bool KB, bool GUARD>
@@ -310,7 +318,11 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
     // tile order: with swz the tiles of one column of C run one after another on one XCD (its L2 keeps that
     // part of B, usually the larger operand); used where the columns fill the XCDs
     int tm, tn;
-    if (g.swz) {
+    if (g.causal) {
+        tm = 0;
+        tn = blockIdx.x;
+        for (int c; tn >= (c = trg_causal_tiles(tm, g.gn)); tm++) tn -= c;
+    } else if (g.swz) {
         const int j = blockIdx.x >> 3;
         tm = j % g.gm;
         tn = (j / g.gm) * 8 + (blockIdx.x & 7);
@@ -528,23 +540,26 @@ __global__ __launch_bounds__(256) void tr_rmsnorm_bwd_kernel(const float *x, con
     for (int i = threadIdx.x; i < d; i += 256) dx[(size_t)row * d + i] = rr * dyr[i] * g[i] - xr[i] * r3 * s;
 }
 
-// dg[j] (+)= sum_t dy[t][j] * x[t][j] * r[t]; a block of 1024 threads handles 64 columns, its 16 groups of
-// 64 threads take every 16th row and their partial sums are added in group order
+// dg[j] (+)= sum_t dy[t][j] * x[t][j] * r[t]; a block of 1024 threads handles 16 columns (64 bytes of a row), its 64 groups of 16
+// threads take every 64th row, eight rows in flight, and their partial sums are added in group order.  (64 columns and 16 groups: 64
+// blocks for 4096 columns, a quarter of the device; 1000 rows 28 us a launch.)
 __global__ __launch_bounds__(1024) void tr_gain_grad_kernel(const float *x, const float *r, const float *dy, int T, int d, float *dg,
                                                             int accumulate)
 {
-    __shared__ float part[16][64];
-    const int c = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + c;
+    __shared__ float part[64][16];
+    const int c = threadIdx.x & 15, grp = threadIdx.x >> 4;
+    const int j = blockIdx.x * 16 + c;
     float s = 0.f;
-    if (j < d)
-        for (int t = grp; t < T; t += 16) s += dy[(size_t)t * d + j] * x[(size_t)t * d + j] * r[t];
+    if (j < d) {
+#pragma unroll 8
+        for (int t = grp; t < T; t += 64) s += dy[(size_t)t * d + j] * x[(size_t)t * d + j] * r[t];
+    }
     part[grp][c] = s;
     __syncthreads();
     if (grp == 0 && j < d) {
         float tot = 0.f;
 #pragma unroll
-        for (int g = 0; g < 16; g++) tot += part[g][c];
+        for (int g = 0; g < 64; g++) tot += part[g][c];
         dg[j] = accumulate ? dg[j] + tot : tot;
     }
 }
@@ -690,17 +705,22 @@ __global__ __launch_bounds__(1024) void tr_loss_kernel(const float *z, const flo
 }
 
 // AdamW with bias correction and decoupled weight decay; c1 = 1 - beta1^step, c2 = 1 - beta2^step
+__device__ __forceinline__ float tr_adamw(float w, float gi, float &m, float &v, float lr, float b1, float b2, float eps, float wd, float c1,
+                                          float c2)
+{
+    m = b1 * m + (1.f - b1) * gi;
+    v = b2 * v + (1.f - b2) * gi * gi;
+    return w * (1.f - lr * wd) - lr * (m / c1) / (sqrtf(v / c2) + eps);
+}
 __global__ void tr_adamw_kernel(float *w, const float *g, float *m, float *v, size_t n, float lr, float b1, float b2, float eps,
                                 float wd, float c1, float c2)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+    float mi = m[i], vi = v[i];
+    w[i] = tr_adamw(w[i], g[i], mi, vi, lr, b1, b2, eps, wd, c1, c2);
     m[i] = mi;
     v[i] = vi;
-    w[i] = w[i] * (1.f - lr * wd) - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 // dst[i] = src[i] rounded to bfloat16 (nearest even), kept as fp32: what a bf16 checkpoint would hold
@@ -720,20 +740,30 @@ __global__ void tr_unpack_bf16_kernel(const uint16_t *tiles, int rows, int K, in
     const int r = (int)(i / K), k = (int)(i % K);
     dst[i] = bf2f(tiles[packed_u16_index(map_row(r, row_off, mode), k, KS)]);
 }
-// one thread per 16-byte unit of a tile: 8 consecutive columns of one row
-__global__ void tr_pack_bf16_kernel(const float *src, int rows, int K, int KS, int row_off, int mode, uint16_t *tiles)
+// AdamW on a matrix of a bf16 model and its copy in the arena's tiles, in one pass over the master block, gradient and moments: 28 bytes a
+// number and 2 for the tiles.  A block takes 16 rows x 128 columns: 512 bytes of a row side by side on one side, whole tiles (where
+// rows keep their order) on the other.  q, k, v of a 7B adapter, 50 M numbers: 326 us (4.6 TB/s), against 252 + 116 us for AdamW and a launch
+// that read the master again; 373 with a wave per tile (128 bytes of a row), 332 with 8 rows x 256 columns.
+__global__ __launch_bounds__(256) void tr_adamw_pack_kernel(float *w, const float *g, float *m, float *v, int rows, int K, int KS, float lr, float b1,
+                                                           float b2, float eps, float wd, float c1, float c2, int row_off, int mode, uint16_t *tiles)
 {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int K8 = K >> 3;
-    if (i >= (size_t)rows * K8) return;
-    const int r = (int)(i / K8), k = (int)(i % K8) * 8;
-    const float4 a = *(const float4 *)(src + (size_t)r * K + k), b = *(const float4 *)(src + (size_t)r * K + k + 4);
-    u32x4_t v;
-    v[0] = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-    v[1] = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
-    v[2] = (uint32_t)f2bf(b.x) | ((uint32_t)f2bf(b.y) << 16);
-    v[3] = (uint32_t)f2bf(b.z) | ((uint32_t)f2bf(b.w) << 16);
-    *(u32x4_t *)(tiles + packed_u16_index(map_row(r, row_off, mode), k, KS)) = v;
+    const int kb = (K + 127) >> 7, r = (int)(blockIdx.x / kb) * 16 + (threadIdx.x >> 4), k = (int)(blockIdx.x % kb) * 128 + (threadIdx.x & 15) * 8;
+    if (r >= rows || k >= K) return;            // (K is a multiple of 8)
+    const size_t at = (size_t)r * K + k;
+    uint32_t o[4];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        float4 wv = *(const float4 *)(w + at + 4 * h), mv = *(const float4 *)(m + at + 4 * h), vv = *(const float4 *)(v + at + 4 * h);
+        const float4 gv = *(const float4 *)(g + at + 4 * h);
+        wv.x = tr_adamw(wv.x, gv.x, mv.x, vv.x, lr, b1, b2, eps, wd, c1, c2);
+        wv.y = tr_adamw(wv.y, gv.y, mv.y, vv.y, lr, b1, b2, eps, wd, c1, c2);
+        wv.z = tr_adamw(wv.z, gv.z, mv.z, vv.z, lr, b1, b2, eps, wd, c1, c2);
+        wv.w = tr_adamw(wv.w, gv.w, mv.w, vv.w, lr, b1, b2, eps, wd, c1, c2);
+        *(float4 *)(w + at + 4 * h) = wv; *(float4 *)(m + at + 4 * h) = mv; *(float4 *)(v + at + 4 * h) = vv;
+        o[2 * h] = (uint32_t)f2bf(wv.x) | ((uint32_t)f2bf(wv.y) << 16);
+        o[2 * h + 1] = (uint32_t)f2bf(wv.z) | ((uint32_t)f2bf(wv.w) << 16);
+    }
+    *(u32x4_t *)(tiles + packed_u16_index(map_row(r, row_off, mode), k, KS)) = u32x4_t{o[0], o[1], o[2], o[3]};
 }
 // the same for fp32 models; to_arena: master -> arena, else arena -> master
 __global__ void tr_copy_rows_f32_kernel(float *master, float *arena, int rows, int K, int row_off, int mode, int to_arena)
