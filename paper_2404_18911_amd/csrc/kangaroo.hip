@@ -318,15 +318,15 @@ void prof_collect(kg_ctx *x)   // call after prof_flush and a synchronisation of
 
 // ---- kernel launch helpers ---------------------------------------------------------------------
 
-void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &e, hipStream_t s)
+void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &e, hipStream_t s, const Feature &ft = Feature())
 {
     const dim3 grid(N / 16), block(256);
     if ((((uintptr_t)W | (uintptr_t)act) & 15) == 0) {
-        if (e.M <= 1) hipLaunchKernelGGL((gemv_f32_kernel<1, true>), grid, block, 0, s, W, K, act, e);
-        else if (e.M <= 2) hipLaunchKernelGGL((gemv_f32_kernel<2, true>), grid, block, 0, s, W, K, act, e);
-        else if (e.M <= 4) hipLaunchKernelGGL((gemv_f32_kernel<4, true>), grid, block, 0, s, W, K, act, e);
-        else hipLaunchKernelGGL((gemv_f32_kernel<8, true>), grid, block, 0, s, W, K, act, e);
-    } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e);
+        if (e.M <= 1) hipLaunchKernelGGL((gemv_f32_kernel<1, true>), grid, block, 0, s, W, K, act, e, ft);
+        else if (e.M <= 2) hipLaunchKernelGGL((gemv_f32_kernel<2, true>), grid, block, 0, s, W, K, act, e, ft);
+        else if (e.M <= 4) hipLaunchKernelGGL((gemv_f32_kernel<4, true>), grid, block, 0, s, W, K, act, e, ft);
+        else hipLaunchKernelGGL((gemv_f32_kernel<8, true>), grid, block, 0, s, W, K, act, e, ft);
+    } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e, ft);
 }
 
 // Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, whose time grows with M, else
@@ -357,14 +357,14 @@ void launch_gemv_multi(const u32x4_t *W, int N, int KS, int M, const void *act, 
     }
 }
 
-int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Epi &e)
+int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Epi &e, const Feature &ft = Feature())
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
     ProfScope ps(x, 0, (double)N * K * x->esz);
     x->acct[x->acct_phase] += (double)N * K * x->esz;
     if (x->bf && e.kind == EPI_FEATURE)
         hipLaunchKernelGGL(gemv_bf16_feature_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream, at<const u32x4_t>(x->arena, w_off),
-                           (K + 31) / 32, e.M, (const u32x4_t *)act, N, e);
+                           (K + 31) / 32, e.M, (const u32x4_t *)act, N, e, ft);
     else if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, e.M) : 1; ntw > 1)
         launch_gemv_multi<FROM_ACT>(at<const u32x4_t>(x->arena, w_off), N, (K + 31) / 32, e.M, act, 0, e, ntw, x->stream);
     else if (x->bf)
@@ -372,7 +372,7 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
                            at<const u32x4_t>(x->arena, w_off), (K + 31) / 32, e.M, (const u32x4_t *)act, e.ssq_in, e.nt_in,
                            e.N, e.kind == EPI_RESID ? e.res : nullptr, e.gain, e);
     else
-        launch_gemv_f32(at<const float>(x->arena, w_off), N, K, (const float *)act, e, x->stream);
+        launch_gemv_f32(at<const float>(x->arena, w_off), N, K, (const float *)act, e, x->stream, ft);
     return check_launch(x, "gemv");
 }
 
@@ -804,12 +804,11 @@ Epi epi_base(kg_ctx *x, int kind, int M, int N)
     return e;
 }
 
-// Where a block's last rows go besides x_out: the next projection's input x * gain with its tile sums of squares, from row `row` on; for the
-// early features the same for layer l (act2, ssq2, from row `row2` on) and a copy of the fp32 rows.
+// Where a block's last rows go besides x_out: the next projection's input x * gain with its tile sums of squares; for the early
+// features what Feature says.
 struct RowsOut {
-    void *act; float *ssq; const float *gain; int row;
-    void *act2; float *ssq2; const float *gain2; int row2;
-    float *xout2;
+    void *act; float *ssq; const float *gain;
+    bool feature; Feature ft;
 };
 RowsOut rows_out(kg_ctx *x, const float *gain)
 {
@@ -820,10 +819,8 @@ RowsOut rows_out(kg_ctx *x, const float *gain)
 }
 void set_rows_out(Epi &e, const RowsOut &o, int d)
 {
-    e.act_out = o.act; e.act_K = d; e.gain = o.gain; e.ssq_out = o.ssq; e.act_row = o.row;
-    if (!o.act2) return;
-    e.kind = EPI_FEATURE;
-    e.act2 = o.act2; e.ssq2 = o.ssq2; e.gain2 = o.gain2; e.row2 = o.row2; e.xout2 = o.xout2;
+    e.act_out = o.act; e.act_K = d; e.gain = o.gain; e.ssq_out = o.ssq;
+    if (o.feature) e.kind = EPI_FEATURE;
 }
 
 // Attention sub-layer + (optionally) feed-forward sub-layer of one block on M rows at pos0.
@@ -847,7 +844,7 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     e.res = x_in; e.xout = x_mid;
     if (with_ffn) { e.act_out = actX; e.act_K = d; e.gain = g2; e.ssq_out = ssq1; }
     else set_rows_out(e, out, d);
-    KGCHK(launch_gemv(x, wo_off, d, d, actA, e));
+    KGCHK(launch_gemv(x, wo_off, d, d, actA, e, out.ft));
     if (!with_ffn) return KG_OK;
 
     e = epi_base(x, EPI_SWIGLU, M, 2 * f);
@@ -857,7 +854,7 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     e = epi_base(x, EPI_RESID, M, d);
     e.res = x_mid; e.xout = x_out;
     set_rows_out(e, out, d);
-    KGCHK(launch_gemv(x, wd_off, d, f, actF, e));
+    KGCHK(launch_gemv(x, wd_off, d, f, actF, e, out.ft));
     return KG_OK;
 }
 
@@ -1000,9 +997,10 @@ int run_shallow(kg_ctx *x, const int *tokens, int M, int pos0, int j0, int arow)
         KGCHK(launch_pack_rows(x, tokens, nullptr, M, at<const float>(x->arena, x->lw[0].g1), x0, x->scr + x->s_actX,
                                at<float>(x->scr, x->s_ssq0)));
     RowsOut o;
-    o.act = x->scr + x->s_actP; o.ssq = at<float>(x->scr, x->s_ssqP); o.gain = at<const float>(x->arena, x->a_gin); o.row = arow;
-    o.act2 = x->scr + x->s_actD; o.ssq2 = at<float>(x->scr, x->s_ssqD); o.gain2 = deep_gain(x); o.row2 = j0;
-    o.xout2 = M == 1 && arow == 0 ? Flag(x) : nullptr;
+    o.act = x->scr + x->s_actP; o.ssq = at<float>(x->scr, x->s_ssqP); o.gain = at<const float>(x->arena, x->a_gin);
+    o.feature = true; o.ft.act_row = arow;
+    o.ft.act2 = x->scr + x->s_actD; o.ft.ssq2 = at<float>(x->scr, x->s_ssqD); o.ft.gain2 = deep_gain(x); o.ft.row2 = j0;
+    o.ft.xout2 = M == 1 && arow == 0 ? Flag(x) : nullptr;
     return run_layers(x, 0, c.exit_layer, M, pos0, x->scr + x->s_actX, at<const float>(x->scr, x->s_ssq0), x0, Frow(x, j0), o);
 }
 

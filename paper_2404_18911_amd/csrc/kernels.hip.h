@@ -54,8 +54,12 @@ struct Epi {
     int act_K;
     const float *gain;
     float *ssq_out;
-    // EPI_FEATURE (early features, decode launches): as EPI_RESID with the rows of act_out and ssq_out from act_row on; and once more for
-    // layer l (act2 <- x * gain2 and ssq2 from row row2 on), and as fp32 rows (xout2, may be null)
+};
+
+// EPI_FEATURE (early features, decode launches): as EPI_RESID with the rows of act_out and ssq_out from act_row on; and once more for
+// layer l (act2 <- x * gain2 and ssq2 from row row2 on), and as fp32 rows (xout2, may be null).  An argument of the kernels that have this
+// epilogue only: 48 more bytes in every projection's arguments cost 0.6 % of a 26 us launch.
+struct Feature {
     int act_row, row2;
     void *act2;
     const float *gain2;
@@ -192,23 +196,27 @@ __device__ __forceinline__ void store_act_pf(void *base, size_t blk_bytes, int b
 // Column of the q, k, v row that packed row n of the projection gives (e.k_pairs is a power of two; the second third holds the keys)
 __device__ __forceinline__ int plain_column(const Epi &e, int n)
 {
-    const int d = e.N / 3, w = (n - d) & (e.k_pairs - 1);
-    return (e.k_pairs && n >= d && n < 2 * d) ? n - w + (w >> 1) + (w & 1) * (e.k_pairs >> 1) : n;
+    if (e.k_pairs) {
+        const int d = e.N / 3, w = (n - d) & (e.k_pairs - 1);
+        if (n >= d && n < 2 * d) n += (w >> 1) + (w & 1) * (e.k_pairs >> 1) - w;
+    }
+    return n;
 }
 
 // (EPI_FEATURE only where the kernel is compiled for it: in the one-projection kernel of every launch its arguments, loaded ahead of the
 // weights, cost 0.4 % of a decode forward.)
-template <bool BF, bool FEATURE = !BF>
+// PAIRS: the rows may be those of a q, k, v projection with key rows in pairs (not in the stand-alone product).
+template <bool BF, bool FEATURE = !BF, bool PAIRS = BF>
 __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_ROWS], const float *sc,
                                          float (*sq)[KG_ROWS], float resv = 0.f, float gainv = 1.f,
-                                         bool prefetched = false, int t = threadIdx.x)
+                                         bool prefetched = false, int t = threadIdx.x, const Feature *ft = nullptr)
 {
     if (e.kind == EPI_PLAIN || e.kind == EPI_HEAD) {
         if (t < 128) {
             int row = t >> 3, m = t & 7;
             int mo = m + e.row_shift;
             float z = yt[row][m] * sc[m];
-            if (m < e.M && mo >= 0) e.out[(size_t)mo * e.N + plain_column(e, rt * 16 + row)] = z;
+            if (m < e.M && mo >= 0) e.out[(size_t)mo * e.N + (PAIRS ? plain_column(e, rt * 16 + row) : rt * 16 + row)] = z;
             sq[row][m] = z * e.inv_temp;
         }
         if (e.kind == EPI_HEAD) {
@@ -260,9 +268,9 @@ __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_RO
                 const size_t at = (size_t)m * e.N + n;
                 v = resv + yt[row][m];          // (operands fetched ahead by all kernels that have this epilogue)
                 e.xout[at] = v;
-                if (e.xout2) e.xout2[at] = v;
-                store_act<BF>(e.act_out, e.act_K, m + e.act_row, n, v * gainv);
-                store_act<BF>(e.act2, e.act_K, m + e.row2, n, v * e.gain2[n]);
+                if (ft->xout2) ft->xout2[at] = v;
+                store_act<BF>(e.act_out, e.act_K, m + ft->act_row, n, v * gainv);
+                store_act<BF>(ft->act2, e.act_K, m + ft->row2, n, v * ft->gain2[n]);
             }
             sq[row][m] = v * v;
         }
@@ -270,8 +278,8 @@ __device__ __forceinline__ void epilogue(const Epi &e, int rt, float (*yt)[KG_RO
         if (t < e.M) {
             float s = 0.f;
             for (int r = 0; r < 16; r++) s += sq[r][t];
-            e.ssq_out[(size_t)rt * KG_ROWS + t + e.act_row] = s;
-            e.ssq2[(size_t)rt * KG_ROWS + t + e.row2] = s;
+            e.ssq_out[(size_t)rt * KG_ROWS + t + ft->act_row] = s;
+            ft->ssq2[(size_t)rt * KG_ROWS + t + ft->row2] = s;
         }
     } else if (e.kind == EPI_SILU) {
         if (t < 128) {
@@ -396,7 +404,7 @@ template <int SRC> struct BSource {
 template <int SRC, bool FEATURE = false>
 __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, int KS, int M, const void *__restrict__ act,
                                                const float *ssq_in, int nt_in, int N, const float *res, const float *gain,
-                                               int K, const Epi &e)
+                                               int K, const Epi &e, const Feature *ft = nullptr)
 {
     __shared__ float part[GEMV_WAVES][16][KG_ROWS];
     __shared__ float yt[16][KG_ROWS];
@@ -487,7 +495,7 @@ __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, in
         yt[row][m] = v;
     }
     __syncthreads();
-    epilogue<true, FEATURE>(e, rt, yt, sc, sq, resv, gainv, true);
+    epilogue<true, FEATURE, SRC == FROM_ACT>(e, rt, yt, sc, sq, resv, gainv, true, threadIdx.x, ft);
 }
 
 // Everything a wave needs before its first weight load is a leading scalar argument (a copy of the
@@ -504,9 +512,9 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
 
 // the same for the projection that gives the early features (EPI_FEATURE)
 __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_feature_kernel(const u32x4_t *__restrict__ W, int KS, int M,
-                                                                           const u32x4_t *__restrict__ act, int N, Epi e)
+                                                                           const u32x4_t *__restrict__ act, int N, Epi e, Feature ft)
 {
-    gemv_bf16_body<FROM_ACT, true>(W, KS, M, act, nullptr, 0, N, e.res, e.gain, 0, e);
+    gemv_bf16_body<FROM_ACT, true>(W, KS, M, act, nullptr, 0, N, e.res, e.gain, 0, e, &ft);
 }
 
 // the same product from plain rows x[M][K] (stand-alone product: no scale, no residual); y[m][n] fp32
@@ -611,7 +619,7 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_multi_kernel(const u3
 #pragma unroll
     for (int t0 = 0; t0 < NTW; t0 += 4) {
         const int t = t0 + (threadIdx.x >> 7);                              // 128 threads per tile (none where there is no tile)
-        epilogue<true>(e, rt0 + t, yt[t], sc, sq[t], 0.f, 1.f, false, t < ntw ? (int)(threadIdx.x & 127) : 1 << 20);
+        epilogue<true, false, SRC == FROM_ACT>(e, rt0 + t, yt[t], sc, sq[t], 0.f, 1.f, false, t < ntw ? (int)(threadIdx.x & 127) : 1 << 20);
     }
 }
 
@@ -691,7 +699,7 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_valu_kernel(cons
 // VEC: weights and activations are 16-byte aligned (a caller of the stand-alone product may pass others).
 template <int MR, bool VEC>
 __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__ W, int K,
-                                                       const float *__restrict__ act, Epi e)
+                                                       const float *__restrict__ act, Epi e, Feature ft)
 {
     constexpr int U = MR <= 4 ? 4 : 2;      // groups of 4 k per thread in flight
     __shared__ float yt[16][KG_ROWS];
@@ -751,7 +759,7 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__
         if (sub == 0) yt[row][m] = v;
     }
     __syncthreads();
-    epilogue<false>(e, rt, yt, sc, sq, resv, gainv, true);
+    epilogue<false>(e, rt, yt, sc, sq, resv, gainv, true, threadIdx.x, &ft);
 }
 
 // ---------------------------------------------------------------------------------------------
