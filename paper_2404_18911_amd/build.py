@@ -9,6 +9,7 @@ _ROOT = os.path.dirname(_HERE)
 LIB = os.path.join(_HERE, "libkangaroo.so")
 SOURCES = [os.path.join(_HERE, "csrc", "kangaroo.hip")]
 HEADERS = [os.path.join(_HERE, "csrc", "kernels.hip.h"), os.path.join(_HERE, "csrc", "train.hip.h"),
+           os.path.join(_HERE, "csrc", "prompt_plan.h"),
            os.path.join(_ROOT, "include", "kangaroo.h")]
 
 

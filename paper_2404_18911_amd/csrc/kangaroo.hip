@@ -2,6 +2,7 @@
 // it carves the caller's arena / KV pool / scratch, launches the kernels of kernels.hip.h on the
 // caller's stream, and runs the control flow of the draft-and-verify round (Section 3, Figure 2).
 #include "kernels.hip.h"
+#include "prompt_plan.h"
 #include "train.hip.h"
 
 #include <chrono>
@@ -31,8 +32,6 @@ constexpr int PF_ROWS_MAX = 1024, PF_ROWS_MAX_HALF = 4096;
 // layers: 96 rows 1.24 / 1.32, 112 rows 1.42 / 1.40; d_model 3072, 6 layers: 100 rows 0.90 / 0.86, 192 rows 1.14 / 0.99; 2560: 0.77 / 0.74,
 // 0.88 / 0.82; 2048: 0.64 / 0.64, 0.71 / 0.71; 1280: 0.48 / 0.50, 0.52 / 0.56; 768: 0.39 / 0.43, 0.42 / 0.46.
 inline int pf_stream_rows(int d_model) { return d_model <= 2048 ? 192 : 96; }
-// Projections cut along k write at most PF_SLICES partial sums per output, PF_PART_ROWS rows of them in all.
-constexpr int PF_SLICES = 8, PF_PART_ROWS = 4096;
 inline size_t up(size_t x, size_t a = ALIGN) { return (x + a - 1) / a * a; }
 
 struct LayerW {
@@ -585,53 +584,10 @@ int launch_stream_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, i
 
 // ---- longer passes: projections in workgroups of 80 .. 128 rows (gemm_prefill2_body) ----
 
-// The kernel's variants: weight tiles and pairs of 8-row blocks of a workgroup, and microseconds per k-step of a workgroup where
-// all compute units have one (s with 8 pairs; a share f of it does not depend on the pairs: 0.29 us with 5 pairs and 0.41 with 8 at 8
-// tiles, 0.39 / 0.54 at 12, 0.47 / 0.68 at 16, 1.09 / 1.69 at 32).
-struct Pf2Variant { void (*kernel)(PfArgs, Epi); int ntw, pairs; double step_us; };
-#define PF2_V(t, p, s, f) {gemm_prefill2_kernel_t##t##_p##p, t, p, s * (f + (1.0 - f) * p / 8)}
-#define PF2_VS(t, s, f) PF2_V(t, 5, s, f), PF2_V(t, 6, s, f), PF2_V(t, 7, s, f), PF2_V(t, 8, s, f)
-const Pf2Variant pf2_variants[] = {PF2_V(6, 8, 0.38, 0.2), PF2_VS(8, 0.46, 0.216), PF2_VS(12, 0.63, 0.152), PF2_VS(16, 0.775, 0.149),
-                                   PF2_VS(32, 1.465, 0.1)};
-#undef PF2_VS
-#undef PF2_V
-
-// Which variant, in how many slices along k (`split` allowed: EPI_RESID).  A workgroup fills a compute unit, so a
-// launch takes whole rounds of them; a partly filled last round runs at a higher clock (0.75 of a round when nearly
-// empty).  Partial sums are written at 5 TB/s and added by pf_reduce_rows_kernel (4 us + what it moves at 6 TB/s, against
-// 5 us for the scales of rows that are finished in place).  The model is within a tenth of the measured launches (us,
-// real passes): 7B shape, 256 rows: q,k,v 6 tiles 54, 8 tiles 59, 12 tiles 71; gate+up 12 tiles 81, 16 tiles 89; down_proj
-// 16 tiles in 7 slices 45, 8 tiles in 4 slices 48, 8 tiles uncut 138; 1024 rows: gate+up 16 tiles 288, 12 tiles 313, 32
-// tiles 359; down_proj 16 tiles in 2 slices 138, 8 tiles uncut 163; 4096 rows: q,k,v 32 tiles 607, 16 tiles 660;
-// gate+up 16 tiles 1133, 32 tiles 1152.  Passes that long run at the card's power limit, where the tile that moves
-// fewer bytes per multiplication also leaves the other launches a higher clock: 32 tiles are entered 3 % cheaper than
-// they measure alone (4096 rows, whole pass: 94.5 ms with 32 tiles for gate+up, 96.9 ms with 16; 3000 rows, where 32
-// tiles need a fifth round for the last 8 workgroups: 76.4 against 74.6 ms).
-//   Groups of 80, 96 or 112 rows where they fit the pass's rows or the rounds better than groups of 128: rows multiplied for nothing
-// cost as much as the others, in time and in power (these launches run at 1.6 .. 1.9 GHz on random data, at 2.4 GHz on zeros).  us,
-// 128 rows at their best / the group picked: 7B, 300 rows: q,k,v 78 / 57 (12 tiles, 80 rows), gate+up 156 / 132 (12, 80), down_proj 60 / 51
-// (16, 80, 4 slices); 400 rows: 87 / 68, 194 / 151, 71 / 62; 777 rows: q,k,v 184 / 144 (32, 80); 13B, 777 rows: 275 / 245 (32, 112),
-// gate+up 443 / 401 (16, 112), o_proj 92 / 79 (12, 96).  They have to be 4 % ahead: nearer than that the fit does not rank them
-// (7B, 512 rows, whole pass: 2.69 ms with 128 rows, 2.75 where it took 32 tiles x 112 rows for gate+up as 2 % ahead).
-struct Pf2Plan { int variant, slices; };
-Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
-{
-    const int pairs = (T + 15) / 16;
-    Pf2Plan best = {0, 1};
-    double best_cost = -1.0;
-    for (int v = 0; v < (int)(sizeof(pf2_variants) / sizeof(pf2_variants[0])); v++)
-        for (int S = 1; S <= (split ? PF_SLICES : 1); S++) {
-            if (S > 1 && (S * T > PF_PART_ROWS || KS < 8 * S || pf2_variants[v].ntw == 32)) break;
-            const Pf2Variant &pv = pf2_variants[v];
-            const int gx = (pairs + pv.pairs - 1) / pv.pairs;
-            const double wgs = (double)gx * ((NT + pv.ntw - 1) / pv.ntw) * S, whole = std::floor(wgs / n_cus), rest = wgs / n_cus - whole;
-            const double rounds = whole + (rest > 0 ? 0.75 + 0.25 * rest : 0.0), bytes = (double)T * NT * 64;
-            const double step = pv.step_us * (pv.pairs < 8 ? 1.04 : 1.0);
-            const double cost = rounds * ((double)KS / S * step + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
-            if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {v, S}; }
-        }
-    return best;
-}
+// in the order of pf2_variants
+#define PF2_K(t, p, s, f) gemm_prefill2_kernel_t##t##_p##p,
+void (*const pf2_kernels[])(PfArgs, Epi) = {PF2_VARIANTS(PF2_K)};
+#undef PF2_K
 
 // Y[T][N] = X[T][K] . W^T with the epilogue e; in/out block strides follow the prompt buffers (activation tiles of K
 // features per block, d/16 tile sums per block)
@@ -661,7 +617,7 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
         e2.scale_in = ssq_in ? at<float>(x->scr, x->s_pscale) : nullptr;
         {
             ProfScope ps(x, 3, 2.0 * T * (double)N * K);
-            hipLaunchKernelGGL(v.kernel, dim3(8 * ((a.gx * a.gy + 7) / 8), p.slices), dim3(768), 0, x->stream, a, e2);
+            hipLaunchKernelGGL(pf2_kernels[p.variant], dim3(8 * ((a.gx * a.gy + 7) / 8), p.slices), dim3(768), 0, x->stream, a, e2);
             KGCHK(check_launch(x, "prompt projection"));
         }
         if (p.slices > 1) return launch_reduce_rows(x, p.slices, T, e, a.act_out_blk);

@@ -1,0 +1,53 @@
+"""How long prompt passes are cut into workgroups (csrc/prompt_plan.h), on the CPU: the header is host arithmetic, compiled here
+with g++ and asked for every projection of a range of widths and pass lengths."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+PART_ROWS, SLICES, CUS_PER_XCD = 4096, 8, 32
+
+
+@pytest.fixture(scope="module")
+def picks(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path_factory.mktemp("plan") / "plan")
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2404_18911_amd", "csrc"),
+                          os.path.join(HERE, "native", "prompt_plan_driver.cpp"), "-o", exe], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    asked = []
+    for d in list(range(512, 8193, 256)):
+        f = d * 43 // 16 // 16 * 16
+        for T in list(range(97, 1100, 13)) + [1200, 1465, 2001, 3000, 4096]:
+            asked += [(3 * d // 16, d // 32, T, 0), (2 * f // 16, d // 32, T, 0), (d // 16, d // 32, T, 1), (d // 16, (f + 31) // 32, T, 1)]
+    out = subprocess.run([exe], input="\n".join("%d %d %d %d" % a for a in asked), capture_output=True, text=True, timeout=120).stdout
+    rows = [tuple(map(int, l.split())) for l in out.splitlines()]
+    assert [r[:4] for r in rows] == asked
+    return rows
+
+
+def test_picked_slices_fit_the_buffers_and_the_projection(picks):
+    for NT, KS, T, split, tiles, pairs, S in picks:
+        assert tiles in (6, 8, 12, 16, 32) and 5 <= pairs <= 8 and (tiles > 6 or pairs == 8)
+        assert 1 <= S <= (SLICES if split else 1)
+        if S > 1:
+            assert S * T <= PART_ROWS and KS >= 8 * S and tiles < 32
+
+
+def test_no_slicing_leaves_an_xcd_with_a_few_workgroups_more_than_whole_rounds(picks):
+    """A slice's workgroups are dealt out to the 8 XCDs in equal shares (the larger share decides), so S slices put S * ceil(w / 8)
+    workgroups on one XCD.  A plan that counts compute units of the whole device instead took such launches for one round."""
+    cut = 0
+    for NT, KS, T, split, tiles, pairs, S in picks:
+        if S == 1:
+            continue
+        cut += 1
+        w = -(-((T + 15) // 16) // pairs) * -(-NT // tiles)
+        on_one = S * -(-w // 8)
+        rest = on_one % CUS_PER_XCD
+        assert on_one < CUS_PER_XCD or rest == 0 or rest >= CUS_PER_XCD // 4, (NT, KS, T, tiles, pairs, S, on_one)
+    assert cut > 1000
