@@ -462,10 +462,11 @@ int launch_rms_scale(kg_ctx *x, const float *ssq, int T);
 // produced the rows leaves them.  Else the 8-row-block kernels (gemm_prefill_body), with their layout and tile sums.
 inline bool pf_streams(const kg_ctx *x, int T) { return x->kvt == 2 && T <= pf_stream_rows(x->c.d_model); }
 inline bool pf_pairs(const kg_ctx *x) { return x->kvt == 2; }
-// With the half-precision cache the prompt projections write keys and values into the cache themselves (KvOut) and the key rows of the
-// stacked q, k, v matrices are stored in rotation pairs: map_row() mode of those matrices, and Epi::k_pairs of their decode launches.
-inline int qkv_mode(const kg_ctx *x) { return x->bf && pf_pairs(x) ? qkv_rows(x->c.d_model, x->c.head_dim) : 0; }
-inline int qkv_pairs(const kg_ctx *x) { return x->bf && pf_pairs(x) ? x->c.head_dim : 0; }
+// The key rows of the stacked q, k, v matrices of a bf16 model are stored in rotation pairs, with every cache type (contexts of one model may
+// be bound to one arena): map_row() mode of those matrices, and Epi::k_pairs of the launches that write them as plain rows.  With the
+// half-precision cache the prompt projections write keys and values into the cache themselves (KvOut).
+inline int qkv_mode(const kg_ctx *x) { return x->bf ? qkv_rows(x->c.d_model, x->c.head_dim) : 0; }
+inline int qkv_pairs(const kg_ctx *x) { return x->bf ? x->c.head_dim : 0; }
 
 int launch_pf_pack(kg_ctx *x, const int *tok_dev, const float *rows, int T, const float *gain, float *xout)
 {
@@ -664,7 +665,7 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
         KGCHK(launch_pf_gemm(x, qkv_off + packed_bytes(true, kv.n0, d), e.N, d, actX, T, e, true, false, 0, &kv));
     } else {
         e = epi_base(x, EPI_PLAIN, KG_ROWS, 3 * d);
-        e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv);
+        e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv); e.k_pairs = qkv_pairs(x);
         KGCHK(launch_pf_gemm(x, qkv_off, 3 * d, d, actX, T, e, true, false, 0));
 
         // all rows' keys and values go to the cache first; then every 8-row block attends to the cache

@@ -1125,6 +1125,9 @@ __device__ __forceinline__ void gemm_prefill_body(const PfArgs &a, const Epi &e)
                 }
             }
         } else {
+            // a tile of a q, k, v projection's key rows (a tile holds nothing else then): two rotation pairs a lane
+            const bool keys = e.k_pairs && __builtin_amdgcn_readfirstlane(rt) >= e.N / 48 && __builtin_amdgcn_readfirstlane(rt) < 2 * (e.N / 48);
+            const int c0 = keys ? plain_column(e, n0) : n0;
 #pragma unroll
             for (int cb = 0; cb < CBW; cb++) {
                 if (cb >= nbw) break;
@@ -1132,8 +1135,12 @@ __device__ __forceinline__ void gemm_prefill_body(const PfArgs &a, const Epi &e)
                 if (!(okl && col < eb.M)) continue;
                 const float sc = scs[cb][col];
                 if (eb.kind == EPI_PLAIN) {
-                    *(float4 *)(eb.out + (size_t)col * eb.N + n0) =
-                        make_float4(tot[tw][cb][0] * sc, tot[tw][cb][1] * sc, tot[tw][cb][2] * sc, tot[tw][cb][3] * sc);
+                    float *o = eb.out + (size_t)col * eb.N + c0;
+                    const float y[4] = {tot[tw][cb][0] * sc, tot[tw][cb][1] * sc, tot[tw][cb][2] * sc, tot[tw][cb][3] * sc};
+                    if (keys) {
+                        *(float2 *)o = make_float2(y[0], y[2]);
+                        *(float2 *)(o + (e.k_pairs >> 1)) = make_float2(y[1], y[3]);
+                    } else *(float4 *)o = make_float4(y[0], y[1], y[2], y[3]);
                 } else {                          // EPI_SWIGLU: rows (2i, 2i+1) = (gate, up) of feature rt*8 + i
                     uint16_t hi[2], lo[2];
 #pragma unroll
