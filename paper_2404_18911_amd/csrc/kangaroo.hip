@@ -101,6 +101,7 @@ struct kg_ctx {
     int n_target_rows = 0;
     int plain_len = 0;
     bool packed = true;      // s_actP / s_actD hold what the present gains make of the early features (false: packed again where they are read)
+    int lag_row = -1;        // index k of the early feature f_k of this round that stands in the lag slot too; -1: the slot is as the last round left it
     int spec_shallow = -1;   // index j of an early feature f_j already computed ahead of the host's decision
     // algorithmic bytes (weights streamed + cached keys / values read) by what the launches belong to:
     // 0 = self-draft model (shallow layers + adapter + head of a draft step), 1 = shallow-only pass
@@ -944,8 +945,8 @@ const float *deep_gain(kg_ctx *x)
 
 // shallow sub-network M^b[:l] on M tokens at pos0 (tokens null: run_head has left the first activation of a draft's
 // token); early features go to rows f_j0..f_{j0+M-1}, packed for the adapter from row `arow` of s_actP on and for layer l from row j0
-// of s_actD on.  A single row that is not the second of a pair is kept in the lag slot as well: it may be the one the adapter
-// catches up on.
+// of s_actD on.  A single row is kept in the lag slot as well, since it may be the one the adapter catches up on; not while a lagged
+// feature waits there for a draft step to succeed.
 int run_shallow(kg_ctx *x, const int *tokens, int M, int pos0, int j0, int arow)
 {
     const kg_config &c = x->c;
@@ -957,7 +958,9 @@ int run_shallow(kg_ctx *x, const int *tokens, int M, int pos0, int j0, int arow)
     o.act = x->scr + x->s_actP; o.ssq = at<float>(x->scr, x->s_ssqP); o.gain = at<const float>(x->arena, x->a_gin);
     o.feature = true; o.ft.act_row = arow;
     o.ft.act2 = x->scr + x->s_actD; o.ft.ssq2 = at<float>(x->scr, x->s_ssqD); o.ft.gain2 = deep_gain(x); o.ft.row2 = j0;
-    o.ft.xout2 = M == 1 && arow == 0 ? Flag(x) : nullptr;
+    const bool keep = M == 1 && !x->lag;
+    o.ft.xout2 = keep ? Flag(x) : nullptr;
+    if (keep) x->lag_row = j0;
     return run_layers(x, 0, c.exit_layer, M, pos0, x->scr + x->s_actX, at<const float>(x->scr, x->s_ssq0), x0, Frow(x, j0), o);
 }
 
@@ -1263,6 +1266,7 @@ static int reset_sequence(kg_ctx *x)
     x->n_drafts = x->stopped = 0;
     x->pending = -1;
     x->spec_shallow = -1;
+    x->lag_row = -1;
     x->packed = true;
     if (x->bound) {
         HIPCHK(x, hipMemsetAsync(x->scr + x->s_cnt, 0, (size_t)x->c.n_heads * 4, x->stream));
@@ -1369,6 +1373,8 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
     // The draft token's early feature is needed whatever the host decides next (one more draft
     // step, or verification): compute it now, from the token that run_head has looked up, so that the
     // GPU keeps working while the host waits for the token and its confidence.
+    const bool packed = x->packed;
+    if (pair) x->packed = false;        // row 0 of s_actP becomes the run-ahead pass's: a step repeated after an error packs the pair again
     {
         x->acct_phase = 1;
         const double before = x->acct[1];
@@ -1377,6 +1383,7 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
     }
     x->spec_shallow = j + 1;
     KGCHK(fetch_results(x, 1, true));
+    x->packed = packed;
     x->lag = 0;
     x->adapter_len = pos + 1;
     x->drafts[j] = x->h_tok[0];
@@ -1453,12 +1460,16 @@ int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
         for (int i = 0; i < n; i++) emitted[i] = x->drafts[i];
         emitted[n] = drawn;
     }
+    // f_k, the last feature computed, stands in the lag slot already, but for a round of one draft after a lagged round
+    if (n == k && x->lag_row != k)
+        HIPCHK(x, hipMemcpyAsync(Flag(x), Frow(x, k), (size_t)x->c.d_model * 4, hipMemcpyDeviceToDevice, x->stream));
+    x->lag_row = -1;
     *n_emitted = n + 1;
     // rollback: caches are cut by length; the adapter saw f_0..f_{k-1} only
     const int old = x->base;
     x->base = old + n + 1;
     x->adapter_len = old + std::min(n + 1, k);
-    x->lag = (n == k);           // f_k, the last feature computed, stands in the lag slot already
+    x->lag = (n == k);
     x->pending = emitted[n];
     x->plain_len = x->base;      // a plain step after this round continues the committed sequence
     x->n_drafts = 0; x->stopped = 0;

@@ -616,3 +616,56 @@ def test_early_features_packed_by_the_shallow_pass_equal_rows_packed_again(name,
     assert len(runs[0]) == len(runs[1])
     for a, b in zip(*runs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("gamma", [1, 6])
+@pytest.mark.parametrize("name,adapter", [("toy", 0), ("toy_bf16", 2), ("small_bf16", 0), ("small_bf16", 3)])
+def test_a_draft_step_repeated_after_an_error_still_has_the_lagged_feature(name, adapter, gamma):
+    """A draft step whose logits are not finite fails and leaves the sequence as it was, the lagged feature included, so the same step
+    with a corrected tensor gives what it gives without the failure: tokens, confidences, logits, and the adapter's keys and values of the
+    two positions it catches up on, bit for bit.  And after every round the lagged feature is that round's f_k, with drafts of one
+    token (after a lagged round too) and of several."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = dataclasses.replace(I.SHAPES[name], adapter=adapter)
+    W = I.gen_weights(shape, seed=3, alpha=0.05, head_scale=25.0)
+    prompt = I.gen_prompt(shape.vocab, 21)
+    p, _ = B.make_params(eta=0.5, gamma=gamma)
+    good = W[(I.KIND_A_NORM_LAST, -1)]
+    bad = good.copy()
+    bad[5] = 0x7FC0 if bad.dtype == np.uint16 else np.nan
+    runs, failed = [], 0
+    for fail in (False, True):
+        kg = P.load_model(shape, W, 128, kv_page_tokens=16)
+        log = [kg.prefill(p, prompt)]
+        lagged = 0
+        for _ in range(10):
+            base, _, lag, _ = kg.state()
+            if fail and lag:
+                before = kg.read_feature(-1)
+                kg.load_tensor(I.KIND_A_NORM_LAST, -1, bad)
+                with pytest.raises(B.KangarooError) as e:
+                    kg.draft_step(p)
+                assert e.value.code == B.KG_EHIP and kg.state() == (base, base - 1, 1, 0)
+                np.testing.assert_array_equal(kg.read_feature(-1), before)
+                failed += 1
+                kg.load_tensor(I.KIND_A_NORM_LAST, -1, good)
+            stop = False
+            while not stop:
+                tok, conf, stop = kg.draft_step(p)
+                log += [tok, conf]
+            k = kg.state()[3]
+            if adapter != 3:
+                log += [a for pos in range(base - lag, base + k) for a in kg.read_kv(shape.n_layers, pos)]
+            log += [kg.read_logits(0, i) for i in range(k)] + kg.verify(p)
+            fk = kg.read_feature(k)
+            log += [kg.read_logits(1, i) for i in range(k + 1)] + kg.accept(p)
+            if kg.state()[2]:
+                lagged += 1
+                np.testing.assert_array_equal(kg.read_feature(-1), fk)
+        assert lagged >= 2
+        runs.append(log)
+        kg.close()
+    assert failed >= 1 and len(runs[0]) == len(runs[1])
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
