@@ -898,11 +898,12 @@ int check_tokens(kg_ctx *x, int n)
     return KG_OK;
 }
 
-// Waits until the words `first` .. first + n - 1 carry the number of the last launch that posts results.  poll: by looking at them, which
-// has the host at work again some 30 us before a stream synchronisation does (toy model, 32 tokens: 3.2 -> 2.8 ms a request; 7B,
-// 4000-token prompt, 150 tokens: 72.2 -> 70.8).  A wait of more than 20 ms (a long prompt, or a failed launch) goes on in
-// hipStreamSynchronize.  Steps whose caller will read logits next synchronise at once: the copy to pageable memory waits for the runtime to
-// have seen the stream's end, and behind a poll a 7B step with its logits took 30 us longer.
+// Waits until the words `first` .. first + n - 1 carry the number of the last launch that posts results.  poll (draft steps and whole
+// requests, whose next launch follows at once): by looking at them, which has the host at work again some 30 us before a stream
+// synchronisation does (toy model, 32 tokens: 3.2 -> 2.8 ms a request; 7B, 4000-token prompt, 150 tokens: 72.2 -> 70.8).  A wait of more than
+// 20 ms (a long prompt, or a failed launch) goes on in hipStreamSynchronize.  The other stepwise calls synchronise at once: after them the
+// stream is idle, so their caller may use the buffers on other streams, and a logits row read next comes sooner (the copy to pageable
+// memory waits until the runtime has seen the stream's end; 7B width, 4 layers, 8 rounds with the verified rows' logits: 8.62 -> 8.41 ms).
 int await_words(kg_ctx *x, int first, int n, bool poll)
 {
     auto arrived = [&]() {
@@ -910,7 +911,7 @@ int await_words(kg_ctx *x, int first, int n, bool poll)
             if ((unsigned)(__atomic_load_n(&x->h_res[first + i], __ATOMIC_ACQUIRE) >> 32) != x->seq) return false;
         return true;
     };
-    if (poll && !x->profiling) {
+    if (poll) {
         const double t0 = now_s();
         while (!arrived() && now_s() - t0 < 0.02)
             for (int i = 0; i < 32; i++) __builtin_ia32_pause();
@@ -921,18 +922,24 @@ int await_words(kg_ctx *x, int first, int n, bool poll)
     return KG_OK;
 }
 
-int fetch_results(kg_ctx *x, int n, bool poll)
+int take_results(kg_ctx *x, int n, bool poll)
 {
-    prof_flush(x);
     KGCHK(await_words(x, 0, n, poll));
     KGCHK(await_words(x, KG_ROWS, n, poll));
-    if (x->profiling) prof_collect(x);
     for (int i = 0; i < n; i++) {
         const uint32_t tok = (uint32_t)x->h_res[i], conf = (uint32_t)x->h_res[KG_ROWS + i];
         memcpy(&x->h_tok[i], &tok, 4);
         memcpy(&x->h_conf[i], &conf, 4);
     }
     return check_tokens(x, n);
+}
+
+int fetch_results(kg_ctx *x, int n, bool poll)
+{
+    prof_flush(x);
+    const int rc = take_results(x, n, poll && !x->profiling);
+    if (x->profiling) prof_collect(x);
+    return rc;
 }
 
 float *Frow(kg_ctx *x, int j) { return at<float>(x->scr, x->s_F) + (size_t)(j + 1) * x->c.d_model; } // f_j
@@ -1382,7 +1389,7 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
         x->spec_cost = x->acct[1] - before;
     }
     x->spec_shallow = j + 1;
-    KGCHK(fetch_results(x, 1, true));
+    KGCHK(take_results(x, 1, true));     // (the run-ahead pass keeps the stream busy: waiting for an event ahead of it is no better, 7.90 ms for 7.85)
     x->packed = packed;
     x->lag = 0;
     x->adapter_len = pos + 1;
@@ -1397,7 +1404,7 @@ int kg_draft_step(kg_ctx *x, const kg_params *p, int32_t *token, float *confiden
     return KG_OK;
 }
 
-int kg_verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus_1)
+static int verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus_1, bool poll)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1413,7 +1420,7 @@ int kg_verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus
     KGCHK(run_deep(x, k + 1, x->base));
     float inv_t = p->mode == 1 ? 1.f / p->temperature : 1.f;
     KGCHK(run_head(x, k + 1, 0, at<float>(x->scr, x->s_tlog), k + 1, inv_t));
-    KGCHK(fetch_results(x, k + 1, true));
+    KGCHK(fetch_results(x, k + 1, poll));
     for (int i = 0; i <= k; i++) { x->targets[i] = x->h_tok[i]; target_tokens[i] = x->h_tok[i]; }
     x->n_target_rows = k + 1;
     *k_plus_1 = k + 1;
@@ -1421,7 +1428,12 @@ int kg_verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus
     return KG_OK;
 }
 
-int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
+int kg_verify(kg_ctx *x, const kg_params *p, int32_t *target_tokens, int *k_plus_1)
+{
+    return verify(x, p, target_tokens, k_plus_1, false);
+}
+
+static int accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted, bool poll)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1450,7 +1462,7 @@ int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
             KGCHK(check_launch(x, "accept_sample"));
         }
         prof_flush(x);
-        KGCHK(await_words(x, RES_ACCEPT, 2, true));
+        KGCHK(await_words(x, RES_ACCEPT, 2, poll && !x->profiling));
         if (x->profiling) prof_collect(x);
         n = (int)(uint32_t)x->h_res[RES_ACCEPT];
         const int drawn = (int)(uint32_t)x->h_res[RES_ACCEPT + 1];
@@ -1477,8 +1489,22 @@ int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
     return KG_OK;
 }
 
-int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out,
-                int *n_out, kg_stats *st)
+int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
+{
+    return accept(x, p, emitted, n_emitted, false);
+}
+
+// A request's steps poll; its call returns with the stream idle (the last launch may not have retired when its results are there, and
+// after an error a run-ahead pass may be under way).  seq: the context's launch number before the request, the same if nothing was launched.
+static int end_request(kg_ctx *x, unsigned seq, int rc)
+{
+    if (!x || x->seq == seq) return rc;
+    const hipError_t e = hipStreamSynchronize(x->stream);
+    if (rc == KG_OK && e != hipSuccess) return fail(x, KG_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+    return rc;
+}
+
+static int generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out, int *n_out, kg_stats *st)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1500,8 +1526,8 @@ int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prom
         double tb = now_s();
         int32_t tg[KG_MAX_ROWS], em[KG_MAX_ROWS];
         int kp1 = 0, ne = 0;
-        KGCHK(kg_verify(x, p, tg, &kp1));
-        KGCHK(kg_accept(x, p, em, &ne));
+        KGCHK(verify(x, p, tg, &kp1, true));
+        KGCHK(accept(x, p, em, &ne, true));
         double tc = now_s();
         s.t_draft_s += tb - ta; s.t_verify_s += tc - tb;
         s.rounds++; s.verify_calls++; s.drafted += kp1 - 1; s.accepted += ne - 1;
@@ -1516,6 +1542,13 @@ int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prom
     *n_out = n;
     if (st) *st = s;
     return KG_OK;
+}
+
+int kg_generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out,
+                int *n_out, kg_stats *st)
+{
+    const unsigned seq = x ? x->seq : 0;
+    return end_request(x, seq, generate(x, p, prompt, n_prompt, max_new, out, n_out, st));
 }
 
 static int plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_token, bool poll)
@@ -1552,8 +1585,7 @@ int kg_plain_step(kg_ctx *x, const kg_params *p, int32_t token, int32_t *next_to
     return plain_step(x, p, token, next_token, false);
 }
 
-int kg_decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out,
-                    int *n_out, kg_stats *st)
+static int decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out, int *n_out, kg_stats *st)
 {
     KGCHK(check_ready(x));
     KGCHK(check_params(x, p));
@@ -1578,6 +1610,13 @@ int kg_decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_
     *n_out = n;
     if (st) *st = s;
     return KG_OK;
+}
+
+int kg_decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_prompt, int max_new, int32_t *out,
+                    int *n_out, kg_stats *st)
+{
+    const unsigned seq = x ? x->seq : 0;
+    return end_request(x, seq, decode_plain(x, p, prompt, n_prompt, max_new, out, n_out, st));
 }
 
 int kg_read_logits(kg_ctx *x, int which, int row, float *host_out)

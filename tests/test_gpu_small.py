@@ -669,3 +669,50 @@ def test_a_draft_step_repeated_after_an_error_still_has_the_lagged_feature(name,
     assert failed >= 1 and len(runs[0]) == len(runs[1])
     for a, b in zip(*runs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("name", ["toy", "small_bf16"])
+def test_calls_return_with_the_stream_idle(name):
+    """After every call but a draft step nothing of the context is under way on its stream (a caller may use the buffers on another
+    stream, or read logits, which waits for the stream's end); a draft step waits for its own results and not for the pass it runs
+    ahead, also with profiling on, whose times are collected by the calls that wait for the stream."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = I.SHAPES[name]
+    kg = P.load_model(shape, I.gen_weights(shape, seed=3, alpha=0.05, head_scale=25.0), 160, kv_page_tokens=16)
+    prompt = I.gen_prompt(shape.vocab, 21)
+    busy = []
+
+    def idle(what):
+        if not kg.stream.query():
+            busy.append(what)
+        kg.stream.synchronize()
+    for mode in (0, 1):
+        p, _ = B.make_params(mode=mode, eta=0.5, gamma=4, seed=7)
+        for _ in range(5):
+            tok = kg.prefill(p, prompt)
+            idle("prefill")
+            for _ in range(4):
+                stop = False
+                while not stop:
+                    _, _, stop = kg.draft_step(p)
+                kg.verify(p)
+                idle("verify")
+                kg.accept(p)
+                if mode == 1:                  # (a greedy accept launches nothing it would wait for)
+                    idle("accept")
+            kg.plain_step(p, tok)
+            idle("plain_step")
+            kg.generate(p, prompt, 20)
+            idle("generate")
+            kg.decode_plain(p, prompt, 10)
+            idle("decode_plain")
+    assert not busy, sorted(set(busy))
+    kg.set_profiling(True)
+    kg.prefill(p, prompt)
+    before = list(kg.get_profile().launches)
+    kg.draft_step(p)
+    assert list(kg.get_profile().launches) == before and sum(before) > 0
+    kg.verify(p)
+    assert sum(kg.get_profile().launches) > sum(before)
+    kg.close()
