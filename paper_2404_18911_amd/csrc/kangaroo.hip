@@ -1163,11 +1163,11 @@ int kg_bind(kg_ctx *x, void *weights_dev, size_t weight_bytes, void *kv_dev, siz
         return fail(x, KG_EINVAL, "device buffers must be %zu-byte aligned", ALIGN);
     if (weight_bytes < x->arena_bytes || kv_bytes < x->kv_bytes || scratch_bytes < x->scratch_bytes)
         return fail(x, KG_ENOSPC, "buffers too small: need %zu/%zu/%zu bytes", x->arena_bytes, x->kv_bytes, x->scratch_bytes);
-    if (x->bound) HIPCHK(x, hipStreamSynchronize(x->stream));      // nothing under way uses the buffers given back
+    // (the stream of an earlier binding is the caller's and may be gone: it is not touched)
     x->arena = (char *)weights_dev; x->kv = (char *)kv_dev; x->scr = (char *)scratch_dev;
     x->stream = (hipStream_t)hip_stream;
     if (!x->h_res) {
-        HIPCHK(x, hipHostMalloc((void **)&x->h_res, RES_WORDS * sizeof(*x->h_res), hipHostMallocMapped | hipHostMallocCoherent));
+        HIPCHK(x, hipHostMalloc((void **)&x->h_res, RES_WORDS * sizeof(*x->h_res), hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable));
         memset(x->h_res, 0, RES_WORDS * sizeof(*x->h_res));
     }
     x->bound = true;
@@ -1707,7 +1707,7 @@ const char *kg_last_error(const kg_ctx *x) { return x ? x->err : "NULL context";
 void kg_destroy(kg_ctx *x)
 {
     if (!x) return;
-    if (x->bound) (void)hipStreamSynchronize(x->stream);      // a run-ahead pass, or the end of a launch whose results are known, may be under way
+    // the stream may be gone; a run-ahead pass still under way on it posts no result words
     if (x->h_res) (void)hipHostFree(x->h_res);
     for (hipEvent_t e : x->ev_pool) (void)hipEventDestroy(e);
     delete x;

@@ -716,3 +716,37 @@ def test_calls_return_with_the_stream_idle(name):
     kg.verify(p)
     assert sum(kg.get_profile().launches) > sum(before)
     kg.close()
+
+
+def test_a_context_outlives_the_stream_of_its_binding():
+    """The stream is the caller's: a context may be bound to another one, or destroyed, after the stream of its last binding is gone."""
+    import ctypes
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = I.SHAPES["small_bf16"]
+    W = I.gen_weights(shape, seed=3, alpha=0.05, head_scale=25.0)
+    prompt = I.gen_prompt(shape.vocab, 21)
+    p, _ = B.make_params(eta=0.5, gamma=4)
+    kg = P.load_model(shape, W, 96, kv_page_tokens=16)
+    want = kg.generate(p, prompt, 30)[0]
+    kg.L.hipStreamCreate.argtypes = [ctypes.POINTER(ctypes.c_void_p)]           # (found through the library's own dependencies)
+    kg.L.hipStreamDestroy.argtypes = [ctypes.c_void_p]
+
+    def bind(stream):
+        kg._chk(kg.L.kg_bind(kg.h, kg.arena.data_ptr(), kg.weight_bytes, kg.kv.data_ptr(), kg.kv_bytes, kg.scratch.data_ptr(),
+                             kg.scratch_bytes, stream))
+        kg.load_weights((k, l, W[(k, l)]) for k, l, _, _ in I.tensor_list(shape))
+    for _ in range(3):
+        s = ctypes.c_void_p()
+        assert kg.L.hipStreamCreate(ctypes.byref(s)) == 0
+        bind(s)
+        assert kg.generate(p, prompt, 30)[0] == want
+        assert kg.L.hipStreamDestroy(s) == 0
+    bind(kg.stream.cuda_stream)
+    assert kg.generate(p, prompt, 30)[0] == want
+    s = ctypes.c_void_p()
+    assert kg.L.hipStreamCreate(ctypes.byref(s)) == 0
+    bind(s)
+    assert kg.generate(p, prompt, 30)[0] == want
+    assert kg.L.hipStreamDestroy(s) == 0
+    kg.close()
