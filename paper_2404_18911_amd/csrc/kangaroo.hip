@@ -835,7 +835,7 @@ int run_layers(kg_ctx *x, int lo, int hi, int M, int pos0, const void *act_in, c
 }
 
 // LM head on the rows packed in actX (+ssq0): logits rows (m + row_shift) of `logits`, then
-// arg-max and top-1 probability of rows 0..n_out-1 into the device tok/conf arrays.
+// arg-max and top-1 probability of rows 0..n_out-1 into the result words.
 // u: per-row uniform numbers for sampling (mode 1), stat: where the rows' (max, sum exp) go.
 int run_head(kg_ctx *x, int M, int row_shift, float *logits, int n_out, float inv_temp, int mode = 0,
              const USrc *us = nullptr, int purpose = 0, float *stat = nullptr, bool draft = false)
@@ -2225,7 +2225,6 @@ int kg_train_apply(kg_ctx *x, const kg_train_params *hp)
     HIPCHK(x, hipStreamSynchronize(x->stream));
     if (x->profiling) prof_collect(x);
     x->tr_pending = 0;
-    x->packed = false;                  // a sequence under way goes on with the new gains
     x->phase = Phase::NONE;
     return KG_OK;
 }

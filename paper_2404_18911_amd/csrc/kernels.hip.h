@@ -58,7 +58,8 @@ struct Epi {
 
 // EPI_FEATURE (early features, decode launches): as EPI_RESID with the rows of act_out and ssq_out from act_row on; and once more for
 // layer l (act2 <- x * gain2 and ssq2 from row row2 on), and as fp32 rows (xout2, may be null).  An argument of the kernels that have this
-// epilogue only: 48 more bytes in every projection's arguments cost 0.6 % of a 26 us launch.
+// epilogue only: 40 more bytes in every bf16 projection's arguments cost 0.6 % of a 26 us launch.  (gemv_f32_kernel has it for all its
+// launches: stand-alone fp32 products of 256 x 256 to 2048 x 1024 take what they took without it, 4 .. 11 us within 2 %.)
 struct Feature {
     int act_row, row2;
     void *act2;
@@ -1212,7 +1213,7 @@ __global__ __launch_bounds__(512) void pf_rms_scale_kernel(const float *ssq, int
 // few operands from LDS per multiplication; all reads of a k-step are issued together, the hi halves are
 // multiplied into every accumulator before the lo halves, and the operands of k-step ks + 1 are read under the
 // second half of step ks (two register sets).  Without PIPE (32 tiles, whose 128 accumulator registers leave no
-// room for a second set) a wave owns 4 weight tiles x all 8 pairs.
+// room for a second set) a wave owns 4 weight tiles x all pairs of the group.
 // AW x (8 / AW) multiplying waves; a wave owns WA weight tiles x its share of the workgroup's NP pairs of 8-row blocks; NB
 // stage buffers
 template <int AW, int WA, int NP, int NB, bool PIPE>
@@ -2712,12 +2713,7 @@ __device__ int tile_inverse_cdf(const float *hs, int n_tiles, const float *z, fl
     return found;
 }
 
-// Final reduction of the per-tile LM-head statistics for one row per block: arg-max (lowest index
-// among equal maxima) and top-1 probability of softmax(z / T) = 1 / sum exp((z - max) / T).
-// mode 1 additionally draws the token from softmax(z / T) with the row's uniform number (of the
-// given purpose: 0 a draft token, 2 a first / plain token).
-// stat_out[row] = (max of z/T, sum exp(z/T - max)).
-// A result word for the host, which polls for the sequence number in its upper half (pinned memory; one 8-byte store, so the
+// A result word for the host, which knows it by the launch number in its upper half (pinned memory; one 8-byte store, so the
 // word is complete when its number is there).
 __device__ __forceinline__ void post(unsigned long long *slot, unsigned seq, uint32_t v)
 {
@@ -2752,6 +2748,12 @@ __device__ __forceinline__ void embed_row(const EmbedOut &o, int tok, int V, flo
     }
 }
 
+// Final reduction of the per-tile LM-head statistics for one row per block: arg-max (lowest index
+// among equal maxima) and top-1 probability of softmax(z / T) = 1 / sum exp((z - max) / T).
+// mode 1 additionally draws the token from softmax(z / T) with the row's uniform number (of the
+// given purpose: 0 a draft token, 2 a first / plain token).
+// stat_out[row] = (max of z/T, sum exp(z/T - max)).
+// host[row], host[KG_ROWS + row]: the result words with the row's token and the bits of its top-1 probability.
 __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, int n_tiles, const float *logits,
                                                           int V, float inv_temp, int mode, USrc us, int purpose,
                                                           unsigned long long *host, unsigned seq, float *stat_out, EmbedOut emb)
@@ -2820,7 +2822,7 @@ __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, in
 // Row i decides the token at us.pos[i]; its acceptance number has purpose 1 (us.u0), its redraw /
 // bonus number purpose 2 (us.u1).
 // zt: target logits [k+1][V], zd: draft logits [k][V]; tstat/dstat: (max, sum exp) per row of z/T.
-// out[0] = number of accepted drafts, out[1] = the redrawn / bonus token.
+// host[0], host[1]: the result words with the number of accepted drafts and the redrawn / bonus token.
 __global__ __launch_bounds__(1024) void accept_sample_kernel(const float *zt, const float *zd, const float *tstat,
                                                              const float *dstat, const float *hstat_t, int V, int k,
                                                              float inv_temp, I8 drafts, USrc us, unsigned long long *host, unsigned seq)
