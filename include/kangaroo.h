@@ -156,9 +156,9 @@ int kg_workspace_bytes(const kg_ctx *ctx, size_t *weight_bytes, size_t *kv_bytes
 /* Bind caller-owned device memory (256-byte aligned, at least the sizes above; all BORROWED until
  * kg_destroy or the next kg_bind) and the HIP stream (a hipStream_t, may be NULL for the default stream)
  * every kernel of this context is launched on.  Clears scratch and resets the sequence.  A call returns
- * with the context's work on the stream done; only kg_draft_step (its next shallow pass), kg_accept (one row's copy),
- * the kg_op_* calls and calls that fail may leave some under way: after those, memory is given back in the
- * stream's order or once it is synchronised.  kg_destroy and a later kg_bind do not touch the stream of the earlier
+ * with the context's work on the stream done; only kg_draft_step (its next shallow pass), the kg_op_* calls and
+ * calls that fail may leave some under way: after those, memory is given back in the stream's order or once it is
+ * synchronised.  kg_destroy and a later kg_bind do not touch the stream of the earlier
  * binding: it may have been destroyed by then. */
 int kg_bind(kg_ctx *ctx, void *weights_dev, size_t weight_bytes, void *kv_dev, size_t kv_bytes,
             void *scratch_dev, size_t scratch_bytes, void *hip_stream);

@@ -898,8 +898,8 @@ int check_tokens(kg_ctx *x, int n)
     return KG_OK;
 }
 
-// Waits until the words `first` .. first + n - 1 carry the number of the last launch that posts results.  poll (draft steps and whole
-// requests, whose next launch follows at once): by looking at them, which has the host at work again some 30 us before a stream
+// Waits until the words `first` .. first + n - 1 carry the number of the last launch that posts results.  poll (draft steps and the steps of
+// whole requests, whose next launch follows at once): by looking at them, which has the host at work again some 30 us before a stream
 // synchronisation does (toy model, 32 tokens: 3.2 -> 2.8 ms a request; 7B, 4000-token prompt, 150 tokens: 72.2 -> 70.8).  A wait of more than
 // 20 ms (a long prompt, or a failed launch) goes on in hipStreamSynchronize.  The other stepwise calls synchronise at once: after them the
 // stream is idle, so their caller may use the buffers on other streams, and a logits row read next comes sooner (the copy to pageable
@@ -1473,8 +1473,10 @@ static int accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitte
         emitted[n] = drawn;
     }
     // f_k, the last feature computed, stands in the lag slot already, but for a round of one draft after a lagged round
-    if (n == k && x->lag_row != k)
+    if (n == k && x->lag_row != k) {
         HIPCHK(x, hipMemcpyAsync(Flag(x), Frow(x, k), (size_t)x->c.d_model * 4, hipMemcpyDeviceToDevice, x->stream));
+        if (!poll) HIPCHK(x, hipStreamSynchronize(x->stream));
+    }
     x->lag_row = -1;
     *n_emitted = n + 1;
     // rollback: caches are cut by length; the adapter saw f_0..f_{k-1} only
@@ -1494,13 +1496,12 @@ int kg_accept(kg_ctx *x, const kg_params *p, int32_t *emitted, int *n_emitted)
     return accept(x, p, emitted, n_emitted, false);
 }
 
-// A request's steps poll; its call returns with the stream idle (the last launch may not have retired when its results are there, and
-// after an error a run-ahead pass may be under way).  seq: the context's launch number before the request, the same if nothing was launched.
+// A request's steps poll, but for those that may be its last: its call returns with the stream idle.  (Polling there too and synchronising
+// once more at the end: toy model, 32 tokens and the last logits 2.54 -> 2.62 ms.)  After an error launches may be under way: seq is the
+// context's launch number before the request, the same if nothing was launched.
 static int end_request(kg_ctx *x, unsigned seq, int rc)
 {
-    if (!x || x->seq == seq) return rc;
-    const hipError_t e = hipStreamSynchronize(x->stream);
-    if (rc == KG_OK && e != hipSuccess) return fail(x, KG_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+    if (rc != KG_OK && x && x->seq != seq) (void)hipStreamSynchronize(x->stream);
     return rc;
 }
 
@@ -1513,7 +1514,7 @@ static int generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_
     kg_stats s;
     memset(&s, 0, sizeof(s));
     int32_t tok;
-    KGCHK(prefill(x, p, prompt, n_prompt, &tok, true));
+    KGCHK(prefill(x, p, prompt, n_prompt, &tok, max_new > 1));
     const double a0[3] = {x->acct[0], x->acct[1], x->acct[2]};
     double t0 = now_s();
     int n = 0;
@@ -1526,8 +1527,9 @@ static int generate(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n_
         double tb = now_s();
         int32_t tg[KG_MAX_ROWS], em[KG_MAX_ROWS];
         int kp1 = 0, ne = 0;
-        KGCHK(verify(x, p, tg, &kp1, true));
-        KGCHK(accept(x, p, em, &ne, true));
+        const bool more = n + x->n_drafts + 1 < max_new;       // another round follows whatever is accepted
+        KGCHK(verify(x, p, tg, &kp1, more || p->mode == 1));
+        KGCHK(accept(x, p, em, &ne, more));
         double tc = now_s();
         s.t_draft_s += tb - ta; s.t_verify_s += tc - tb;
         s.rounds++; s.verify_calls++; s.drafted += kp1 - 1; s.accepted += ne - 1;
@@ -1594,13 +1596,13 @@ static int decode_plain(kg_ctx *x, const kg_params *p, const int32_t *prompt, in
     kg_stats s;
     memset(&s, 0, sizeof(s));
     int32_t tok;
-    KGCHK(prefill(x, p, prompt, n_prompt, &tok, true));
+    KGCHK(prefill(x, p, prompt, n_prompt, &tok, max_new > 1));
     const double a2 = x->acct[2];
     double t0 = now_s();
     int n = 0;
     out[n++] = tok;
     while (n < max_new) {
-        KGCHK(plain_step(x, p, tok, &tok, true));
+        KGCHK(plain_step(x, p, tok, &tok, n + 1 < max_new));
         out[n++] = tok;
         s.plain_steps++;
     }

@@ -688,8 +688,8 @@ def test_calls_return_with_the_stream_idle(name):
             busy.append(what)
         kg.stream.synchronize()
     for mode in (0, 1):
-        p, _ = B.make_params(mode=mode, eta=0.5, gamma=4, seed=7)
-        for _ in range(5):
+        for rep in range(5):
+            p, _ = B.make_params(mode=mode, eta=0.5, gamma=1 if rep == 4 else 4, seed=7)
             tok = kg.prefill(p, prompt)
             idle("prefill")
             for _ in range(4):
@@ -699,14 +699,15 @@ def test_calls_return_with_the_stream_idle(name):
                 kg.verify(p)
                 idle("verify")
                 kg.accept(p)
-                if mode == 1:                  # (a greedy accept launches nothing it would wait for)
-                    idle("accept")
+                idle("accept")
             kg.plain_step(p, tok)
             idle("plain_step")
-            kg.generate(p, prompt, 20)
-            idle("generate")
-            kg.decode_plain(p, prompt, 10)
-            idle("decode_plain")
+            for new in (1, 2, 3, 9, 20):
+                kg.generate(p, prompt, new)
+                idle("generate")
+            for new in (1, 10):
+                kg.decode_plain(p, prompt, new)
+                idle("decode_plain")
     assert not busy, sorted(set(busy))
     kg.set_profiling(True)
     kg.prefill(p, prompt)
