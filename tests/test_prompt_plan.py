@@ -12,22 +12,35 @@ PART_ROWS, SLICES, CUS_PER_XCD = 4096, 8, 32
 
 
 @pytest.fixture(scope="module")
-def picks(tmp_path_factory):
+def plan(tmp_path_factory):
+    """What the plan picks for a list of (weight tiles, k-steps, rows, may be cut): those, then tiles, pairs and slices."""
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     exe = str(tmp_path_factory.mktemp("plan") / "plan")
     res = subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2404_18911_amd", "csrc"),
                           os.path.join(HERE, "native", "prompt_plan_driver.cpp"), "-o", exe], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
+
+    def ask(asked):
+        out = subprocess.run([exe], input="\n".join("%d %d %d %d" % a for a in asked), capture_output=True, text=True, timeout=120).stdout
+        rows = [tuple(map(int, l.split())) for l in out.splitlines()]
+        assert [r[:4] for r in rows] == asked
+        return rows
+    return ask
+
+
+def _projections(d, f, T):
+    return [(3 * d // 16, d // 32, T, 0), (2 * f // 16, d // 32, T, 0), (d // 16, d // 32, T, 1), (d // 16, (f + 31) // 32, T, 1)]
+
+
+@pytest.fixture(scope="module")
+def picks(plan):
     asked = []
     for d in list(range(512, 8193, 256)):
         f = d * 43 // 16 // 16 * 16
         for T in list(range(97, 1100, 13)) + [1200, 1465, 2001, 3000, 4096]:
-            asked += [(3 * d // 16, d // 32, T, 0), (2 * f // 16, d // 32, T, 0), (d // 16, d // 32, T, 1), (d // 16, (f + 31) // 32, T, 1)]
-    out = subprocess.run([exe], input="\n".join("%d %d %d %d" % a for a in asked), capture_output=True, text=True, timeout=120).stdout
-    rows = [tuple(map(int, l.split())) for l in out.splitlines()]
-    assert [r[:4] for r in rows] == asked
-    return rows
+            asked += _projections(d, f, T)
+    return plan(asked)
 
 
 def test_picked_slices_fit_the_buffers_and_the_projection(picks):
@@ -51,3 +64,16 @@ def test_no_slicing_leaves_an_xcd_with_a_few_workgroups_more_than_whole_rounds(p
         rest = on_one % CUS_PER_XCD
         assert on_one < CUS_PER_XCD or rest == 0 or rest >= CUS_PER_XCD // 4, (NT, KS, T, tiles, pairs, S, on_one)
     assert cut > 1000
+
+
+def test_the_gpu_prompt_tests_reach_every_variant_and_number_of_slices(plan):
+    """The passes of tests/test_gpu_prompt_kernels.py run every tile size with every number of pairs, and every number of slices."""
+    from tests.test_gpu_prompt_kernels import LENGTHS, SHAPES
+    asked = []
+    for s in SHAPES.values():
+        for T in LENGTHS:
+            if T > (192 if s.d_model <= 2048 else 96):          # shorter ones are weight streams
+                asked += _projections(s.d_model, s.d_ffn, T)
+    rows = plan(asked)
+    assert {r[4:6] for r in rows} == {(6, 8)} | {(t, p) for t in (8, 12, 16, 32) for p in (5, 6, 7, 8)}
+    assert {r[6] for r in rows} == set(range(1, SLICES + 1))
