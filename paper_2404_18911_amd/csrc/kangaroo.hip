@@ -643,8 +643,10 @@ int launch_pf_gemm(kg_ctx *x, size_t w_off, int N, int K, const void *act, int T
 // One decoder block (or the adapter's key/value projection when kv_only) on T prompt rows at pos0.
 // In: pactX = x_in * g_attn, pssq0 = tile sums of x_in.  Out: x rows in x_out, pactX = x_out *
 // next_gain, pssq0 = tile sums of x_out.  Every row's arithmetic is that of the one-token kernels.
+// kv_only: keys and values of all rows go to the cache and nothing else is done; with the half-precision cache the queries are not computed
+// then unless `queries` is set (they are left in pqkv).
 int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, size_t wd_off, const float *g2, int T,
-             int pos0, const float *x_in, float *x_out, const float *next_gain, bool kv_only)
+             int pos0, const float *x_in, float *x_out, const float *next_gain, bool kv_only, bool queries = false)
 {
     const kg_config &c = x->c;
     const int d = c.d_model, f = c.d_ffn, nb = (T + KG_ROWS - 1) / KG_ROWS;
@@ -655,12 +657,12 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
     Epi e;
     AttnArgs a;
     if (x->kvt == 2) {
-        // queries to s_pqkv, keys and values straight into the cache; the adapter's pass needs no queries
+        // queries to s_pqkv, keys and values straight into the cache
         KvOut kv;
         memset(&kv, 0, sizeof(kv));
         kv.kv = (uint16_t *)x->kv; kv.page_table = at<const int>(x->scr, x->s_pt); kv.rope = at<const float2>(x->scr, x->s_rope);
         kv.slot = slot; kv.n_slots = c.n_layers + 1; kv.H = c.n_heads; kv.log_hd = ilog2(c.head_dim); kv.logP = x->logP; kv.pos0 = pos0;
-        kv.d = d; kv.n0 = kv_only ? d : 0;
+        kv.d = d; kv.n0 = kv_only && !queries ? d : 0;
         e = epi_base(x, EPI_QKV, KG_ROWS, 3 * d - kv.n0);
         e.ssq_in = ssq0; e.out = at<float>(x->scr, x->s_pqkv);
         KGCHK(launch_pf_gemm(x, qkv_off + packed_bytes(true, kv.n0, d), e.N, d, actX, T, e, true, false, 0, &kv));
@@ -727,30 +729,6 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
     return KG_OK;
 }
 
-// Full model M^b and the adapter's cache on prompt rows pos0..pos0+T-1 (token ids in the device
-// copy of the prompt).  Returns the device rows holding the last layer's output.
-int pf_rows_pass(kg_ctx *x, int pos0, int T, const float **x_last)
-{
-    const kg_config &c = x->c;
-    const int L = c.n_layers, l = c.exit_layer;
-    float *x0 = at<float>(x->scr, x->s_px0), *F = at<float>(x->scr, x->s_pF);
-    KGCHK(launch_pf_pack(x, at<const int>(x->scr, x->s_ptok) + pos0, nullptr, T, at<const float>(x->arena, x->lw[0].g1), x0));
-    const float *xin = x0;
-    for (int i = 0; i < L; i++) {
-        const LayerW &w = x->lw[i];
-        float *xout = (i == l - 1) ? F : x0;           // early features of all rows (Section 3.1)
-        const float *ng = (i == L - 1) ? nullptr : at<const float>(x->arena, x->lw[i + 1].g1);
-        KGCHK(pf_block(x, i, w.qkv, w.wo, w.gu, w.wd, at<const float>(x->arena, w.g2), T, pos0, xin, xout, ng, false));
-        xin = xout;
-    }
-    *x_last = xin;
-    // adapter: keys and values of every prompt position (its attention output is not needed here);
-    // the adapter made of two linear maps keeps no cache
-    if (x->akind == KG_ADAPTER_MLP) return KG_OK;
-    KGCHK(launch_pf_pack(x, nullptr, F, T, at<const float>(x->arena, x->a_gin), nullptr));
-    return pf_block(x, L, x->a_qkv, 0, 0, 0, nullptr, T, pos0, nullptr, nullptr, nullptr, true);
-}
-
 Epi epi_base(kg_ctx *x, int kind, int M, int N)
 {
     Epi e;
@@ -781,11 +759,10 @@ void set_rows_out(Epi &e, const RowsOut &o, int d)
     if (o.feature) e.kind = EPI_FEATURE;
 }
 
-// Attention sub-layer + (optionally) feed-forward sub-layer of one block on M rows at pos0.
-// In:  act_in = x_in * g_attn (packed), ssq_in = tile sums of squares of x_in, x_in fp32 rows.
+// What follows the attention of a block on M rows (its output in actA): output projection and, with_ffn, the feed-forward sub-layer.
 // Out: x rows in x_out and what `out` says.
-int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, size_t wd_off, const float *g2,
-              int M, int pos0, const void *act_in, const float *ssq_in, const float *x_in, float *x_out, const RowsOut &out, bool with_ffn)
+int run_block_rest(kg_ctx *x, size_t wo_off, size_t gu_off, size_t wd_off, const float *g2, int M, const float *x_in, float *x_out,
+                   const RowsOut &out, bool with_ffn)
 {
     const kg_config &c = x->c;
     const int d = c.d_model, f = c.d_ffn;
@@ -793,12 +770,7 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     void *actX = x->scr + x->s_actX, *actA = x->scr + x->s_actA, *actF = x->scr + x->s_actF;
     float *x_mid = with_ffn ? at<float>(x->scr, x->s_x1) : x_out;
 
-    Epi e = epi_base(x, EPI_PLAIN, M, 3 * d);
-    e.ssq_in = ssq_in; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
-    KGCHK(launch_gemv(x, qkv_off, 3 * d, d, act_in, e));
-    KGCHK(launch_attn(x, slot, pos0, M, 0));
-
-    e = epi_base(x, EPI_RESID, M, d);
+    Epi e = epi_base(x, EPI_RESID, M, d);
     e.res = x_in; e.xout = x_mid;
     if (with_ffn) { e.act_out = actX; e.act_K = d; e.gain = g2; e.ssq_out = ssq1; }
     else set_rows_out(e, out, d);
@@ -814,6 +786,90 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
     set_rows_out(e, out, d);
     KGCHK(launch_gemv(x, wd_off, d, f, actF, e, out.ft));
     return KG_OK;
+}
+
+// Attention sub-layer + (optionally) feed-forward sub-layer of one block on M rows at pos0.
+// In:  act_in = x_in * g_attn (packed), ssq_in = tile sums of squares of x_in, x_in fp32 rows.
+// Out: x rows in x_out and what `out` says.
+int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, size_t wd_off, const float *g2,
+              int M, int pos0, const void *act_in, const float *ssq_in, const float *x_in, float *x_out, const RowsOut &out, bool with_ffn)
+{
+    const int d = x->c.d_model;
+    Epi e = epi_base(x, EPI_PLAIN, M, 3 * d);
+    e.ssq_in = ssq_in; e.out = at<float>(x->scr, x->s_qkv); e.k_pairs = qkv_pairs(x);
+    KGCHK(launch_gemv(x, qkv_off, 3 * d, d, act_in, e));
+    KGCHK(launch_attn(x, slot, pos0, M, 0));
+    return run_block_rest(x, wo_off, gu_off, wd_off, g2, M, x_in, x_out, out, with_ffn);
+}
+
+// Rows of a prompt pass that the caller wants the last layer's output of.  Only keys and values of the others are read again.
+enum class PfRows { NONE, LAST, ALL };
+
+// Passes of more rows compute the query of their last row by itself (11 us for one row's input and one projection).
+// Queries of all rows in the last layer / the last one: 7B width, 256 rows: 58 / 38 + 11 us; 13B width, 777 rows: 245 / 165 + 12.
+constexpr int PF_LAST_QUERY = 384;
+
+// The last layer of a pass of which only the last row goes on: keys and values of all rows, then that row through the decode kernels,
+// whose arithmetic these are.  Leaves its input of the LM head in actX / ssq0.  (At T rows all kernels behind the q, k, v projection do
+// 1 / T of the work: a pass through L layers saves most of 3 / 4 of one.)
+int pf_last_row(kg_ctx *x, int slot, const LayerW &w, int T, int pos0, const float *x_in)
+{
+    const kg_config &c = x->c;
+    const int d = c.d_model;
+    const float *row_in = x_in + (size_t)(T - 1) * d;
+    const bool own_query = pf_pairs(x) && T > PF_LAST_QUERY;
+    KGCHK(pf_block(x, slot, w.qkv, w.wo, w.gu, w.wd, nullptr, T, pos0, x_in, nullptr, nullptr, true, !own_query));
+    const float *q = at<const float>(x->scr, x->s_pqkv) + (size_t)(T - 1) * 3 * d;
+    if (own_query) {
+        float *ssq = at<float>(x->scr, x->s_ssq1);
+        KGCHK(launch_pack_rows(x, nullptr, row_in, 1, at<const float>(x->arena, w.g1), nullptr, x->scr + x->s_actX, ssq));
+        Epi e = epi_base(x, EPI_PLAIN, 1, d);       // the first d of the stacked q, k, v rows
+        e.ssq_in = ssq; e.out = at<float>(x->scr, x->s_qkv);
+        KGCHK(launch_gemv(x, w.qkv, d, d, x->scr + x->s_actX, e));
+        q = e.out;
+    }
+    AttnArgs a = attn_args(x, slot, pos0 + T - 1, 1);
+    a.qkv = q; a.preappended = 1;
+    {
+        ProfScope ps(x, 1, (double)(pos0 + T) * 2 * d * x->kvesz);
+        KGCHK(launch_attn_args(x, a, dim3(c.n_heads, a.S), 1));
+    }
+    return run_block_rest(x, w.wo, w.gu, w.wd, at<const float>(x->arena, w.g2), 1, row_in, at<float>(x->scr, x->s_x0),
+                          rows_out(x, at<const float>(x->arena, x->gfinal)), true);
+}
+
+// Full model M^b and the adapter's cache on prompt rows pos0..pos0+T-1 (token ids in the device
+// copy of the prompt).  want = ALL: *x_last is set to the device rows holding the last layer's output; LAST: the last row is left in
+// actX / ssq0, ready for the LM head.
+int pf_rows_pass(kg_ctx *x, int pos0, int T, PfRows want, const float **x_last)
+{
+    const kg_config &c = x->c;
+    const int L = c.n_layers, l = c.exit_layer;
+    float *x0 = at<float>(x->scr, x->s_px0), *F = at<float>(x->scr, x->s_pF);
+    KGCHK(launch_pf_pack(x, at<const int>(x->scr, x->s_ptok) + pos0, nullptr, T, at<const float>(x->arena, x->lw[0].g1), x0));
+    const float *xin = x0;
+    const int full = want == PfRows::ALL || l == L ? L : L - 1;     // (the adapter reads all rows of layer l's output)
+    for (int i = 0; i < full; i++) {
+        const LayerW &w = x->lw[i];
+        float *xout = (i == l - 1) ? F : x0;           // early features of all rows (Section 3.1)
+        const float *ng = (i == L - 1) ? nullptr : at<const float>(x->arena, x->lw[i + 1].g1);
+        KGCHK(pf_block(x, i, w.qkv, w.wo, w.gu, w.wd, at<const float>(x->arena, w.g2), T, pos0, xin, xout, ng, false));
+        xin = xout;
+    }
+    if (full < L) {
+        const LayerW &w = x->lw[L - 1];
+        if (want == PfRows::LAST) KGCHK(pf_last_row(x, L - 1, w, T, pos0, xin));
+        else KGCHK(pf_block(x, L - 1, w.qkv, w.wo, w.gu, w.wd, nullptr, T, pos0, xin, nullptr, nullptr, true));
+    } else if (want == PfRows::LAST) {
+        KGCHK(launch_pack_rows(x, nullptr, xin + (size_t)(T - 1) * c.d_model, 1, at<const float>(x->arena, x->gfinal), nullptr,
+                               x->scr + x->s_actX, at<float>(x->scr, x->s_ssq0)));
+    }
+    if (x_last) *x_last = xin;
+    // adapter: keys and values of every prompt position (its attention output is not needed here);
+    // the adapter made of two linear maps keeps no cache
+    if (x->akind == KG_ADAPTER_MLP) return KG_OK;
+    KGCHK(launch_pf_pack(x, nullptr, F, T, at<const float>(x->arena, x->a_gin), nullptr));
+    return pf_block(x, L, x->a_qkv, 0, 0, 0, nullptr, T, pos0, nullptr, nullptr, nullptr, true);
 }
 
 // Decoder blocks lo..hi-1.  x_first: fp32 rows feeding block lo (already packed into act_in / ssq_in
@@ -1313,14 +1369,10 @@ static int prefill(kg_ctx *x, const kg_params *p, const int32_t *prompt, int n, 
         HIPCHK(x, hipMemcpyAsync(x->scr + x->s_ptok, prompt, (size_t)n * 4, hipMemcpyHostToDevice, x->stream));
         for (int pos0 = 0; pos0 < n; pos0 += x->pf_rows) {
             const int T = std::min(x->pf_rows, n - pos0);
-            const float *x_last = nullptr;
-            KGCHK(pf_rows_pass(x, pos0, T, &x_last));
-            if (pos0 + T == n) {
-                // target distribution of the first new token: final norm + LM head on the last row
-                KGCHK(launch_pack_rows(x, nullptr, x_last + (size_t)(T - 1) * c.d_model, 1, at<const float>(x->arena, x->gfinal),
-                                       nullptr, x->scr + x->s_actX, at<float>(x->scr, x->s_ssq0)));
-                KGCHK(run_head(x, 1, 0, at<float>(x->scr, x->s_tlog), 1, inv_t, p->mode, &u_first, 2));
-            }
+            const bool last = pos0 + T == n;
+            KGCHK(pf_rows_pass(x, pos0, T, last ? PfRows::LAST : PfRows::NONE, nullptr));
+            // target distribution of the first new token: final norm (folded) + LM head on the last row
+            if (last) KGCHK(run_head(x, 1, 0, at<float>(x->scr, x->s_tlog), 1, inv_t, p->mode, &u_first, 2));
         }
     } else {
         for (int pos0 = 0; pos0 < n; pos0 += KG_ROWS) {
@@ -1969,7 +2021,7 @@ static int train_frozen_forward(kg_ctx *x, const int32_t *tokens, int n)
         for (int pos0 = 0; pos0 < n; pos0 += x->pf_rows) {
             const int T = std::min(x->pf_rows, n - pos0);
             const float *x_last = nullptr;
-            KGCHK(pf_rows_pass(x, pos0, T, &x_last));
+            KGCHK(pf_rows_pass(x, pos0, T, PfRows::ALL, &x_last));
             HIPCHK(x, hipMemcpyAsync(f(t.F) + (size_t)pos0 * d, x->scr + x->s_pF, (size_t)T * d * 4, hipMemcpyDeviceToDevice, x->stream));
             HIPCHK(x, hipMemcpyAsync(f(t.X) + (size_t)pos0 * d, x_last, (size_t)T * d * 4, hipMemcpyDeviceToDevice, x->stream));
         }
