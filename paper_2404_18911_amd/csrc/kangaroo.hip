@@ -694,15 +694,16 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
         pa.act_out = actA; pa.act_blk_bytes = act_bytes(d);
         pa.act_pair = pf_pairs(x) ? 1 : 0;
         ProfScope ps(x, 1, 0.0);
-        // workgroups of 128 rows (8 waves, a compute unit each) where those alone fill the device, else of 64 rows
-        if ((size_t)c.n_heads * ((T + 127) / 128) >= (size_t)x->n_cus) {
+        // Workgroups of 128 rows where those alone give most compute units one, else of 32 rows (us, 32 / 128 rows; 32 heads: 400 rows
+        // 18 / 22, 512 rows 22 / 22, 640 rows 29 / 25, 1024 rows 46 / 34; 40 heads: 256 rows 15 / 17, 512 rows 27 / 24).
+        if ((size_t)c.n_heads * ((T + 127) / 128) * 8 >= (size_t)x->n_cus * 5) {
             const dim3 grid(c.n_heads, (T + 127) / 128);
-            if (c.head_dim == 128) hipLaunchKernelGGL((pf_attn_kernel<128, 8>), grid, dim3(512), 0, x->stream, pa);
-            else hipLaunchKernelGGL((pf_attn_kernel<64, 8>), grid, dim3(512), 0, x->stream, pa);
+            if (c.head_dim == 128) hipLaunchKernelGGL(pf_attn_kernel<128>, grid, dim3(256), 0, x->stream, pa);
+            else hipLaunchKernelGGL(pf_attn_kernel<64>, grid, dim3(256), 0, x->stream, pa);
         } else {
-            const dim3 grid(c.n_heads, (T + 63) / 64);
-            if (c.head_dim == 128) hipLaunchKernelGGL((pf_attn_kernel<128, 4>), grid, dim3(256), 0, x->stream, pa);
-            else hipLaunchKernelGGL((pf_attn_kernel<64, 4>), grid, dim3(256), 0, x->stream, pa);
+            const dim3 grid(c.n_heads, (T + 31) / 32);
+            if (c.head_dim == 128) hipLaunchKernelGGL(pf_attn_short_kernel<128>, grid, dim3(256), 0, x->stream, pa);
+            else hipLaunchKernelGGL(pf_attn_short_kernel<64>, grid, dim3(256), 0, x->stream, pa);
         }
         KGCHK(check_launch(x, "prompt attention"));
     } else {

@@ -2251,27 +2251,27 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
 }
 
 // ---------------------------------------------------------------------------------------------
-// Attention of the prompt rows (prefill) on the matrix units, for a half-precision KV cache.
-// One workgroup per head and block of 64 query rows (4 waves, two workgroups per compute unit) or of
-// 128 query rows (8 waves, a compute unit alone, two tiles of K and V in LDS: half the staging per row
-// and one barrier per tile; for passes whose blocks of 128 rows fill the device); a wave owns 16 rows.
-// The keys and values of all rows of this pass are already in the cache (written by the q, k, v
-// projection), so the block walks the cache in tiles of 128 positions up to its own last row:
-//   S^T = K Q^T   per 16-position tile: A = keys from LDS (as stored: one position's 8 consecutive
-//         dimensions per lane), B = the rotated, scaled queries held in registers as half hi + lo
-//         parts (two MFMAs per step, fp32-grade scores); the result has a lane's query row in its
-//         column and four positions in its registers;
-//   row softmax   running maximum and sum per query row (flash-attention recurrence), reductions
-//         over a lane's own registers and two lane exchanges;
-//   O = P V       A = the probabilities straight from the score registers, rounded to half (the
-//         contraction index may be enumerated in any order as long as both operands agree: k-slot
-//         j of lane group g is position 32 u + 16 (j / 4) + 4 g + j % 4), B = V^T from LDS, where the
-//         values were transposed on the way in and laid out in exactly that order.
-// Rows are masked causally; rows beyond the pass are computed and dropped.  The output goes to the
-// activation tiles of the output projection (hi + lo bf16 parts per 8-row block), like the decode
-// kernel's.  Numerically the rows differ from the decode kernel's in the order of the sums and in
-// the half-precision probabilities (relative 2^-12), far inside the logit tolerance.
+// Attention of the prompt rows (prefill) on the matrix units, for a half-precision KV cache.  The keys and values of all rows
+// of this pass are already in the cache (written by the q, k, v projection).  A wave owns 32 query rows and walks the cache:
+//   S^T = K Q^T   A = 32 keys (as stored: one position's 8 consecutive dimensions per lane), B = the rotated, scaled queries held
+//         in registers as half hi + lo parts (two MFMAs per step, fp32-grade scores); a lane gets one query row (its column) and
+//         positions 8 (r / 4) + 4 (lane / 32) + r % 4 in its 16 registers;
+//   row softmax   running maximum and sum per query row (flash-attention recurrence) in powers of two (the queries carry log2 e): over a
+//         lane's own registers and the lane 32 away, nothing else, since
+//   O^T = V^T P   B = the probabilities straight from the score registers, rounded to half (the contraction index may be enumerated
+//         in any order as long as both operands agree), A = V^T, which ds_read_b64_tr_b16 gathers from values stored as they are (per 16
+//         lanes 4 positions x 16 dimensions, transposed), leaves a query's outputs in the same column: rescaling needs no lane exchange.
+// Rows are masked causally; rows beyond the pass are computed and dropped.  The output goes to the activation tiles of the
+// output projection (hi + lo bf16 parts per 8-row block), like the decode kernel's.  Numerically the rows differ from the decode
+// kernel's in the order of the sums and in the half-precision probabilities (relative 2^-12), far inside the logit tolerance.
+//   32 x 32 tiles, because what bounds 16 x 16 ones is the way of K and V out of LDS (512 KB per 128 rows and 128 positions, 4096
+// cycles, against 3072 of matrix instructions per SIMD; here 256 KB).  us per launch, 32 heads of 128: 16 x 16 tiles with values transposed
+// on the way into LDS / here: 45 rows 10.1 / 6.9, 256 rows 15.0 / 12.4, 777 rows 32.7 / 29.6, 1024 rows 38 / 34, 2048 rows 84 / 71,
+// 4096 rows 287 / 208 (0.66 PFLOP/s, hi and lo counted; matrix units busy half the time, the vector units with exponentials and sums the rest).
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 struct PfAttnArgs {
     const float *qkv;        // [T][3d] rows of this pass: q | k | v, RMS-scaled projections, not rotated
@@ -2285,220 +2285,364 @@ struct PfAttnArgs {
     int act_pair;            // layout of act_out (pf_act_ptr)
 };
 
-template <int HD, int NW>     // NW waves: 16 NW query rows per workgroup
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void pf_attn_kernel(const PfAttnArgs a)
+// A lane's query (column lane % 32 of the wave's rows from row0 on): rotated, scaled by log2 e / sqrt(hd), split into half hi + lo, in
+// B-operand order: step ks holds dimensions 16 ks + 8 (lane / 32) .. + 7.
+template <int HD>
+__device__ __forceinline__ void pf_attn_queries(const PfAttnArgs &a, int h, int row0, int lane, f16x8_t (&qhi)[HD / 16], f16x8_t (&qlo)[HD / 16])
 {
-    constexpr int NT = 64 * NW, ROWS = 16 * NW;
-    constexpr int NBUF = NW == 8 ? 2 : 1;       // tiles of K and V^T in LDS (two workgroups of 4 waves share a compute unit instead)
-    constexpr int CH = 16 * HD / NT;            // 16-byte chunks of a K tile (and of a V tile) per thread
-    constexpr int VSTEP = NT / 128;             // chunk index step of a thread's V chunks
-    constexpr int KS = HD / 32;                 // contraction steps of Q.K^T
-    constexpr int DT = HD / 16;                 // 16-wide tiles of the head dimension
-    constexpr int HH = HD / 2;
-    constexpr int KROW = HD + 8;                // halves per key row in LDS (16 bytes of padding: conflict-free 16-byte reads)
-    constexpr int VROW = 128 + 8;               // halves per dimension row of V^T in LDS
-    __shared__ __align__(16) uint16_t Ks[NBUF][128 * KROW];
-    __shared__ __align__(16) uint16_t Vt[NBUF][HD * VROW];
+    constexpr int HH = HD / 2, KH = HD / 32;        // steps ks and ks + KH hold the two halves of the same rotation pairs
+    const int row = min(row0 + (lane & 31), a.T - 1), g = lane >> 5;
+    const float *q = a.qkv + (size_t)row * 3 * a.d + h * HD;
+    const float2 *rp = a.rope + (size_t)(a.pos0 + row) * HH;
+    const float qscale = 1.44269504088896341f * rsqrtf((float)HD);
+    float4 x0[KH][2], x1[KH][2], cs[KH][4];
+#pragma unroll
+    for (int ks = 0; ks < KH; ks++) {
+        const int i0 = 16 * ks + 8 * g;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            x0[ks][j] = *(const float4 *)(q + i0 + 4 * j);
+            x1[ks][j] = *(const float4 *)(q + i0 + HH + 4 * j);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) cs[ks][j] = *(const float4 *)(rp + i0 + 2 * j);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KH; ks++) {
+        const float xa[8] = {x0[ks][0].x, x0[ks][0].y, x0[ks][0].z, x0[ks][0].w, x0[ks][1].x, x0[ks][1].y, x0[ks][1].z, x0[ks][1].w};
+        const float xb[8] = {x1[ks][0].x, x1[ks][0].y, x1[ks][0].z, x1[ks][0].w, x1[ks][1].x, x1[ks][1].y, x1[ks][1].z, x1[ks][1].w};
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const float4 c4 = cs[ks][e >> 1];
+            const float2 c = (e & 1) ? make_float2(c4.z, c4.w) : make_float2(c4.x, c4.y);
+            const float va = rounded(rot_lo(xa[e], xb[e], c) * qscale), vb = rounded(rot_hi(xa[e], xb[e], c) * qscale);
+            const _Float16 ha = (_Float16)va, hb = (_Float16)vb;
+            qhi[ks][e] = ha; qlo[ks][e] = (_Float16)(va - (float)ha);
+            qhi[ks + KH][e] = hb; qlo[ks + KH][e] = (_Float16)(vb - (float)hb);
+        }
+    }
+}
+
+__device__ __forceinline__ f32x16_t f32x16_zero()
+{
+    return f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+}
+
+// the larger of a lane's value and that of the lane 32 away; their sum
+__device__ __forceinline__ float pair_max(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float pair_sum(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, and their sum.  m_run follows
+// the running maximum with a lag: only where a row's has grown by more than 8 is it moved and what was summed so far (o, l_run)
+// multiplied by the difference; probabilities up to 2^8 are as exact in half precision as those up to 1.  A row that has seen no position
+// yet has m_run = -inf and sums 0.
+template <int NS, int DT>
+__device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[2 * NS], float &m_run, float &l_run, f32x16_t (&o)[DT])
+{
+    float mx = s[0][0];
+#pragma unroll
+    for (int i = 0; i < NS; i++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) mx = fmaxf(mx, s[i][r]);
+    mx = pair_max(mx);
+    if (__any(mx > m_run + 8.f)) {
+        const float m_new = fmaxf(m_run, mx);
+        const float scale = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));     // 0 for the first positions a row sees
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) o[dt] *= scale;
+        l_run *= scale;
+        m_run = m_new;
+    }
+    const float m_ref = m_run == -INFINITY ? 0.f : m_run;
+    float sum[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NS; i++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const float v = __builtin_amdgcn_exp2f(s[i][r] - m_ref);        // 0 for a masked score
+            sum[r & 1] += v;
+            p[2 * i + (r >> 3)][r & 7] = (_Float16)v;
+        }
+    l_run += sum[0] + sum[1];
+}
+
+// Values in LDS as [position][HD] halves, the 32-byte pieces of a row permuted so that four rows of one piece lie in different banks.
+template <int HD> __device__ __forceinline__ int pf_v_piece(int pos, int piece) { return piece ^ (HD == 128 ? pos & 7 : pos & 3); }
+
+// a lane's 8 values of V^T for dimension 32 dt + lane % 32: positions 16 u + 4 (lane / 32) + {0 .. 3, 8 .. 11} of the 16-position step u
+template <int HD>
+__device__ __forceinline__ f16x8_t pf_v_operand(const uint16_t *v, int u, int dt, int lane)
+{
+    const int i = lane & 15, p0 = 16 * u + 4 * (lane >> 5) + (i >> 2);
+    f16x4_t part[2];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        const uint16_t *p = v + (p0 + 8 * e) * HD + pf_v_piece<HD>(p0 + 8 * e, 2 * dt + ((lane >> 4) & 1)) * 16 + (i & 3) * 4;
+        part[e] = __builtin_bit_cast(f16x4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
+    }
+    return __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// 4 consecutive output dimensions k .. k + 3 of a row of the pass
+__device__ __forceinline__ void pf_attn_store(const PfAttnArgs &a, int row, int k, const float (&v)[4])
+{
+    uint16_t hi[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const float x = rounded(v[i]);
+        hi[i] = f2bf(x);
+        lo[i] = f2bf(x - bf2f(hi[i]));
+    }
+    int lo_off;
+    uint16_t *p = pf_act_ptr(a.act_out, a.act_blk_bytes, row >> 3, row & 7, k, a.act_pair, lo_off);
+    *(uint2 *)p = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+    *(uint2 *)(p + lo_off) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+}
+
+// 16 bytes per lane straight from memory into LDS: from base + off (or addr) of each lane to `lds` (a byte address, uniform in the
+// wave) + 16 lane.  In assembly because the compiler, which cannot tell the buffers of a ring apart, would wait for all such loads before
+// any read of LDS; it does not count these: whoever reads what they bring waits for them himself (lds_loads_landed, then a barrier).
+__device__ __forceinline__ void lds_load16(const void *base, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_load16(const void *addr, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_loads_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
+
+// Longer passes: one workgroup per (head, 128 rows), 4 waves of 32 rows, two workgroups per compute unit (one multiplies while the other
+// is at its softmax or its barrier).  Tiles of 64 positions of K and V, two of each in LDS; the next tile comes straight into LDS under
+// this one's work (4096 rows: 208 us; through registers, keys under the scores and values under P.V, 223; with two heads at a time on an XCD
+// instead of the late row blocks of all its heads first, 245).
+template <int HD>
+__global__ __launch_bounds__(256, 2) void pf_attn_kernel(const PfAttnArgs a)
+{
+    constexpr int KS = HD / 16, DT = HD / 32;
+    constexpr int CPR = HD / 8, RPL = 64 / CPR; // 16-byte chunks per row; rows a wave's load covers
+    constexpr int CH = 16 / RPL;                // loads per wave of a K tile (and of a V tile)
+    constexpr int KM = CPR - 1;                 // the chunks of a key row are permuted by the low bits of its position (no bank conflicts)
+    __shared__ __align__(16) uint16_t Ks[2][64 * HD];
+    __shared__ __align__(16) uint16_t Vs[2][64 * HD];
     __shared__ int pages[128];                  // the page table (a context has at most 128 pages)
     const int h = blockIdx.x, t = threadIdx.x;
     const int rb = (int)gridDim.y - 1 - (int)blockIdx.y;        // late row blocks (most tiles) are scheduled first
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    const int q16 = lane & 15, g = lane >> 4;
-    const int P = 1 << a.logP, d = a.d;
-    const int row = rb * ROWS + wave * 16 + q16;                  // the query row this lane's column stands for
-    const int qpos = a.pos0 + row;
-    const int last_pos = a.pos0 + min(a.T, rb * ROWS + ROWS) - 1;   // last position any row of the block attends to
-    const int n_tiles = (last_pos >> 7) + 1;
-    const int wave_last = a.pos0 + min(a.T - 1, rb * ROWS + wave * 16 + 15);
+    const int P = 1 << a.logP;
+    const int row0 = rb * 128 + wave * 32;                        // the wave's first row
+    const int row = row0 + (lane & 31), qpos = a.pos0 + row;
+    const int last_pos = a.pos0 + min(a.T, rb * 128 + 128) - 1;     // last position any row of the block attends to
+    const int n_tiles = (last_pos >> 6) + 1;
+    const int wave_first = a.pos0 + row0, wave_last = a.pos0 + min(a.T, row0 + 32) - 1;
     const size_t unit = (size_t)2 * P * HD;
+    const size_t page_stride = (size_t)a.n_slots * a.H * unit;              // elements per physical page
+    const kvhalf_t *kv_head = a.kv + ((size_t)a.slot * a.H + h) * unit;     // this layer's and head's keys in physical page 0
     if (t <= (last_pos >> a.logP) && t < 128) pages[t] = a.page_table[t];
     __syncthreads();
 
-    // keys as stored: thread -> (position, 8 dimensions); values: thread -> (8 dimensions, position =
-    // lane-consecutive).  A tile's loads are issued one tile ahead, into registers, and stay in flight
-    // under the multiplications of the tile before.
-    u32x4_t kreg[CH], vreg[CH];
-    const size_t page_stride = (size_t)a.n_slots * a.H * unit;              // elements per physical page
-    const kvhalf_t *kv_head = a.kv + ((size_t)a.slot * a.H + h) * unit;     // this layer's and head's keys in physical page 0
-    auto load_tile = [&](int tile0) {       // (positions beyond the block's reach repeat the last one: finite, and masked below)
+    // a lane's part of a wave's load: row (of RPL), place in the row, and the chunks of a key row and of a value row that belong there
+    const int lrow = RPL * wave + lane / CPR, place = lane % CPR;
+    const int kc = place ^ (lrow & KM), vc = 2 * pf_v_piece<HD>(lrow, place >> 1) + (place & 1);
+    const uint32_t koff = (lrow * HD + 8 * kc) * 2, voff = (lrow * HD + 8 * vc) * 2;
+    const uint32_t lds_k = lds_address(&Ks[0][0]) + 1024 * wave, lds_v = lds_address(&Vs[0][0]) + 1024 * wave;
+    auto load_tile = [&](int tile0, int b) {
+        if (a.logP >= 6 && tile0 + 63 <= last_pos) {        // 64 rows of one page
+            const kvhalf_t *src = kv_head + (size_t)__builtin_amdgcn_readfirstlane(pages[tile0 >> a.logP]) * page_stride + (size_t)(tile0 & (P - 1)) * HD;
 #pragma unroll
-        for (int i = 0; i < CH; i++) {
-            const int pc = t + NT * i, pos = pc / (HD / 8), dq = pc % (HD / 8);
-            const int ap = min(tile0 + pos, last_pos);
-            kreg[i] = *(const u32x4_t *)(kv_head + (size_t)pages[ap >> a.logP] * page_stride + ((ap & (P - 1)) * HD + 8 * dq));
-        }
-        {
-            const int ap = min(tile0 + (t & 127), last_pos);                // one position per thread, CH chunks of it
-            const kvhalf_t *Vp = kv_head + (size_t)pages[ap >> a.logP] * page_stride + ((P + (ap & (P - 1))) * HD + 8 * (t >> 7));
+            for (int i = 0; i < CH; i++) lds_load16(src + 4 * RPL * HD * i, koff, lds_k + 128 * HD * b + 4096 * i);
 #pragma unroll
-            for (int i = 0; i < CH; i++) vreg[i] = *(const u32x4_t *)(Vp + 8 * VSTEP * i);
+            for (int i = 0; i < CH; i++) lds_load16(src + (size_t)P * HD + 4 * RPL * HD * i, voff, lds_v + 128 * HD * b + 4096 * i);
+        } else {                                            // (positions beyond the block's reach repeat the last one: finite, and masked below)
+#pragma unroll
+            for (int i = 0; i < CH; i++) {
+                const int ap = min(tile0 + lrow + 4 * RPL * i, last_pos);
+                const kvhalf_t *src = kv_head + (size_t)pages[ap >> a.logP] * page_stride + (ap & (P - 1)) * HD;
+                lds_load16(src + 8 * kc, lds_k + 128 * HD * b + 4096 * i);
+                lds_load16(src + (size_t)P * HD + 8 * vc, lds_v + 128 * HD * b + 4096 * i);
+            }
         }
     };
-    load_tile(0);                               // under the preparation of the queries
-
-    // queries: rotate, scale, split into half hi + lo, in B-operand order (8 consecutive dimensions per lane and step)
+    load_tile(0, 0);
     f16x8_t qhi[KS], qlo[KS];
-    {
-        const float *q = a.qkv + (size_t)min(row, a.T - 1) * 3 * d + h * HD;
-        const float2 *rp = a.rope + (size_t)min(qpos, a.pos0 + a.T - 1) * HH;
-        const float qscale = rsqrtf((float)HD);
-        // all loads first (8 consecutive dimensions: 16-byte loads), then the arithmetic
-        float4 x0v[KS][2], x1v[KS][2], csv[KS][4];
+    pf_attn_queries<HD>(a, h, row0, lane, qhi, qlo);
+    f32x16_t o[DT];
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            const int i0 = (32 * ks + 8 * g) % HH;
+    for (int dt = 0; dt < DT; dt++) o[dt] = f32x16_zero();
+    float m_run = -INFINITY, l_run = 0.f;       // running maximum of the row (same in its two lanes), this lane's share of the sum
+    lds_loads_landed();
+    __syncthreads();
+    for (int kt = 0; kt < n_tiles; kt++) {
+        const int tile0 = kt << 6, b = kt & 1;
+        if (kt + 1 < n_tiles) load_tile(tile0 + 64, b ^ 1);     // no wave reads the other buffers any more: their tile was finished before the last barrier
+        if (tile0 <= wave_last) {               // else nothing of this tile is visible to the wave's rows
+            f32x16_t s[2] = {f32x16_zero(), f32x16_zero()};
+            // a step's keys are read under the step before
+            auto keys = [&](int ks, int i) {
+                const int pos = 32 * i + (lane & 31);
+                return __builtin_bit_cast(f16x8_t, *(const u32x4_t *)&Ks[b][pos * HD + 8 * ((2 * ks + (lane >> 5)) ^ (pos & KM))]);
+            };
+            f16x8_t kk[2][2] = {{keys(0, 0), keys(0, 1)}};
 #pragma unroll
-            for (int j = 0; j < 2; j++) {
-                x0v[ks][j] = *(const float4 *)(q + i0 + 4 * j);
-                x1v[ks][j] = *(const float4 *)(q + i0 + HH + 4 * j);
+            for (int ks = 0; ks < KS; ks++) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (ks + 1 < KS) { kk[(ks + 1) & 1][0] = keys(ks + 1, 0); kk[(ks + 1) & 1][1] = keys(ks + 1, 1); }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2; i++) s[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kk[ks & 1][i], qhi[ks], s[i], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 2; i++) s[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kk[ks & 1][i], qlo[ks], s[i], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            // causal mask (only a tile that reaches beyond the wave's first row needs it).  Every row sees position 0, so its maximum is
+            // finite from the first tile on; rows beyond the pass are computed like the others (on the last row's queries) and dropped.
+            if (tile0 + 63 > wave_first) {
 #pragma unroll
-            for (int j = 0; j < 4; j++) csv[ks][j] = *(const float4 *)(rp + i0 + 2 * j);
-        }
+                for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            const float x0a[8] = {x0v[ks][0].x, x0v[ks][0].y, x0v[ks][0].z, x0v[ks][0].w, x0v[ks][1].x, x0v[ks][1].y, x0v[ks][1].z, x0v[ks][1].w};
-            const float x1a[8] = {x1v[ks][0].x, x1v[ks][0].y, x1v[ks][0].z, x1v[ks][0].w, x1v[ks][1].x, x1v[ks][1].y, x1v[ks][1].z, x1v[ks][1].w};
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const int dim = 32 * ks + 8 * g + e;
-                const float4 c4 = csv[ks][e >> 1];
-                const float2 cs = (e & 1) ? make_float2(c4.z, c4.w) : make_float2(c4.x, c4.y);
-                const float v = rounded((dim < HH ? rot_lo(x0a[e], x1a[e], cs) : rot_hi(x0a[e], x1a[e], cs)) * qscale);
-                const _Float16 hi = (_Float16)v;
-                qhi[ks][e] = hi;
-                qlo[ks][e] = (_Float16)(v - (float)hi);
+                    for (int r = 0; r < 16; r++)
+                        s[i][r] = tile0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) <= qpos ? s[i][r] : -INFINITY;
             }
+            f16x8_t p[4];
+            pf_attn_softmax<2, DT>(s, p, m_run, l_run, o);
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int dt = 0; dt < DT; dt++)
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(pf_v_operand<HD>(Vs[b], u, dt, lane), p[u], o[dt], 0, 0, 0);
         }
-    }
-    f32x4_t o[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; dt++) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;       // running maximum of the row (same in its four lanes), this lane's share of the sum
-
-    // column of position pos inside a dimension row of V^T: [u = pos / 32][g = (pos % 16) / 4][j = 4 ((pos / 16) % 2) + pos % 4]
-    uint16_t *vt_lane;
-    uint32_t vt_sel;
-    {
-        const int pos = t & 127, odd = pos & 1;
-        const int col = (pos >> 5) * 32 + ((pos & 15) >> 2) * 8 + ((pos >> 4) & 1) * 4 + (pos & 3);
-        vt_lane = &Vt[0][(8 * (t >> 7) + odd) * VROW + (col & ~1)];
-        vt_sel = odd ? 0x03020706u : 0x05040100u;   // (hi of other, hi of mine) : (lo of mine, lo of other)
-    }
-    const int wave_first = a.pos0 + rb * ROWS + wave * 16;        // position of the wave's first row
-    // tile in registers -> LDS buffer bf: keys as stored; values transposed: a 32-bit word of the thread holds
-    // dimensions (2 j, 2 j + 1) of its position; with the neighbouring lane's word (position ^ 1) the even lane
-    // forms the pair of positions of dimension 2 j and the odd lane that of dimension 2 j + 1: one byte
-    // permutation and one 32-bit LDS write per word
-    auto write_tile = [&](int bf) {
-#pragma unroll
-        for (int i = 0; i < CH; i++) {
-            const int pc = t + NT * i, pos = pc / (HD / 8), dq = pc % (HD / 8);
-            *(u32x4_t *)&Ks[bf][pos * KROW + 8 * dq] = kreg[i];
-        }
-#pragma unroll
-        for (int i = 0; i < CH; i++) {
-#pragma unroll
-            for (int w = 0; w < 4; w++) {
-                const uint32_t mine = vreg[i][w];
-                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // lane ^ 1
-                *(uint32_t *)(vt_lane + bf * (HD * VROW) + (8 * VSTEP * i + 2 * w) * VROW) = __builtin_amdgcn_perm(other, mine, vt_sel);
-            }
-        }
-    };
-    // One tile in LDS: barrier, write, barrier, then the next tile's loads fly under this tile's multiplications.
-    // Two tiles in LDS: the next tile is written into the other buffer after this tile's multiplications (no wave
-    // reads that buffer any more: its tile was finished before the last barrier), one barrier per tile.
-    if (NBUF == 2) {
-        write_tile(0);
+        lds_loads_landed();
         __syncthreads();
     }
-    for (int kt = 0; kt < n_tiles; kt++) {
-        const int tile0 = kt << 7, bf = NBUF == 2 ? (kt & 1) : 0;
-        const bool more = kt + 1 < n_tiles;
-        if (NBUF == 1) {
-            __syncthreads();                    // the previous tile has been consumed
-            write_tile(0);
-            __syncthreads();
+    // normalise and store: lane holds dimensions 32 dt + 8 (r / 4) + 4 (lane / 32) + r % 4 of its row
+    const float l = pair_sum(l_run), inv = l > 0.f ? 1.f / l : 0.f;
+    if (row < a.T) {
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+            for (int rr = 0; rr < 4; rr++) {
+                const float v[4] = {o[dt][4 * rr] * inv, o[dt][4 * rr + 1] * inv, o[dt][4 * rr + 2] * inv, o[dt][4 * rr + 3] * inv};
+                pf_attn_store(a, row, h * HD + 32 * dt + 8 * rr + 4 * (lane >> 5), v);
+            }
+    }
+}
+
+// Short passes, whose blocks of 128 rows would leave compute units idle: one workgroup per (head, 32 rows); its 4 waves take the tiles of 32
+// positions in turn, keys straight from memory in operand order, values through a piece of LDS of their own, with no barrier before
+// their sums are added.
+template <int HD>
+__global__ __launch_bounds__(256, 2) void pf_attn_short_kernel(const PfAttnArgs a)
+{
+    constexpr int KS = HD / 16, DT = HD / 32, NW = 4;
+    constexpr int CPR = HD / 8, CH = 32 * CPR / 64;     // 16-byte chunks per row of values; per lane of a tile
+    constexpr int NG = 4 * DT;                          // groups of 4 output registers of a lane
+    __shared__ __align__(16) float part[NW][NG][64][4]; // a wave's values (32 x HD halves), then its sums
+    __shared__ float mw[NW][32], lw[NW][32];
+    __shared__ int pages[128];
+    const int h = blockIdx.x, t = threadIdx.x;
+    const int row0 = 32 * ((int)gridDim.y - 1 - (int)blockIdx.y);
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, q = lane & 31, g = lane >> 5;
+    const int P = 1 << a.logP;
+    const int row = row0 + q, qpos = a.pos0 + row;
+    const int last_pos = a.pos0 + min(a.T, row0 + 32) - 1, n_tiles = (last_pos >> 5) + 1;
+    const size_t unit = (size_t)2 * P * HD;
+    const size_t page_stride = (size_t)a.n_slots * a.H * unit;
+    const kvhalf_t *kv_head = a.kv + ((size_t)a.slot * a.H + h) * unit;
+    if (t <= (last_pos >> a.logP) && t < 128) pages[t] = a.page_table[t];
+    __syncthreads();
+    uint16_t *vs = (uint16_t *)&part[wave][0][0][0];
+
+    u32x4_t kreg[KS], vreg[CH];
+    auto load_tile = [&](int tile0) {       // (positions beyond the block's reach repeat the last one: finite, and masked below)
+        const int kp = min(tile0 + q, last_pos);
+        const kvhalf_t *Kp = kv_head + (size_t)pages[kp >> a.logP] * page_stride + (kp & (P - 1)) * HD;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) kreg[ks] = *(const u32x4_t *)(Kp + 16 * ks + 8 * g);
+#pragma unroll
+        for (int i = 0; i < CH; i++) {
+            const int c = lane + 64 * i, vp = min(tile0 + c / CPR, last_pos);
+            vreg[i] = *(const u32x4_t *)(kv_head + (size_t)pages[vp >> a.logP] * page_stride + ((P + (vp & (P - 1))) * HD + 8 * (c % CPR)));
         }
-        if (more) load_tile(tile0 + 128);
-        if (tile0 <= wave_last) {               // else nothing of this tile is visible to the wave's rows (uniform in the wave)
-            // scores of 128 positions x 16 query rows
-            f32x4_t s[8];
+    };
+    f32x16_t o[DT];
 #pragma unroll
-            for (int pt = 0; pt < 8; pt++) {
-                s[pt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int dt = 0; dt < DT; dt++) o[dt] = f32x16_zero();
+    float m_run = -INFINITY, l_run = 0.f;
+    if (wave < n_tiles) {
+        load_tile(32 * wave);
+        f16x8_t qhi[KS], qlo[KS];
+        pf_attn_queries<HD>(a, h, row0, lane, qhi, qlo);
+        for (int kt = wave; kt < n_tiles; kt += NW) {
+            const int tile0 = 32 * kt;
+            __builtin_amdgcn_wave_barrier();        // (a wave's accesses to LDS take effect in program order)
 #pragma unroll
-                for (int ks = 0; ks < KS; ks++) {
-                    const f16x8_t kk = __builtin_bit_cast(f16x8_t, *(const u32x4_t *)&Ks[bf][(16 * pt + q16) * KROW + 32 * ks + 8 * g]);
-                    s[pt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk, qhi[ks], s[pt], 0, 0, 0);
-                    s[pt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk, qlo[ks], s[pt], 0, 0, 0);
-                }
+            for (int i = 0; i < CH; i++) {
+                const int c = lane + 64 * i, pos = c / CPR, dq = c % CPR;
+                *(u32x4_t *)&vs[pos * HD + 16 * pf_v_piece<HD>(pos, dq >> 1) + 8 * (dq & 1)] = vreg[i];
             }
-            // causal mask (only a tile that reaches beyond the wave's first row needs it), tile maximum of the row.
-            // Every row sees position 0, so its maximum is finite from the first tile on; rows beyond the pass are
-            // computed like the others (on the last row's queries) and dropped.
-            if (tile0 + 127 > wave_first) {
+            __builtin_amdgcn_wave_barrier();
+            f32x16_t s[1] = {f32x16_zero()};
 #pragma unroll
-                for (int pt = 0; pt < 8; pt++)
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        s[pt][r] = (tile0 + 16 * pt + 4 * g + r <= qpos) ? s[pt][r] : -INFINITY;
+            for (int ks = 0; ks < KS; ks++) {
+                s[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kreg[ks]), qhi[ks], s[0], 0, 0, 0);
+                s[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, kreg[ks]), qlo[ks], s[0], 0, 0, 0);
             }
-            float mx = -INFINITY;
+            if (kt + NW < n_tiles) load_tile(tile0 + 32 * NW);
+            if (tile0 + 31 > a.pos0 + row0) {
 #pragma unroll
-            for (int pt = 0; pt < 8; pt++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) mx = fmaxf(mx, s[pt][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m_run, mx);
-            const float scale = __expf(m_run - m_new);              // 0 in the first tile (m_run = -inf)
-            float psum = 0.f;
-            f16x8_t pa[4];
-#pragma unroll
-            for (int pt = 0; pt < 8; pt++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const float p = __expf(s[pt][r] - m_new);       // 0 for a masked score
-                    psum += p;
-                    pa[pt >> 1][4 * (pt & 1) + r] = (_Float16)p;
-                }
-            l_run = l_run * scale + psum;
-            m_run = m_new;
-            // rescale the output rows 4 g + r by the factor of their query row, then add P.V
-            float sc[4];
-#pragma unroll
-            for (int r = 0; r < 4; r++) sc[r] = __shfl(scale, 4 * g + r);
-#pragma unroll
-            for (int dt = 0; dt < DT; dt++) {
-#pragma unroll
-                for (int r = 0; r < 4; r++) o[dt][r] *= sc[r];
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const f16x8_t vv = __builtin_bit_cast(f16x8_t, *(const u32x4_t *)&Vt[bf][(16 * dt + q16) * VROW + 32 * u + 8 * g]);
-                    o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[u], vv, o[dt], 0, 0, 0);
-                }
+                for (int r = 0; r < 16; r++) s[0][r] = tile0 + 8 * (r >> 2) + 4 * g + (r & 3) <= qpos ? s[0][r] : -INFINITY;
             }
-        }
-        if (NBUF == 2) {
-            if (more) write_tile(bf ^ 1);
-            __syncthreads();
+            f16x8_t p[2];
+            pf_attn_softmax<1, DT>(s, p, m_run, l_run, o);
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+#pragma unroll
+                for (int dt = 0; dt < DT; dt++)
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(pf_v_operand<HD>(vs, u, dt, lane), p[u], o[dt], 0, 0, 0);
         }
     }
-    // normalise and store: lane holds dimension 16 dt + q16 of query rows 4 g + r
-    float l = l_run + __shfl_xor(l_run, 16);
-    l += __shfl_xor(l, 32);
+    // Merge: the waves' sums weighted by 2^(maximum of the wave - maximum of all), added in wave order; wave w finishes the w-th
+    // quarter of the registers.
+    l_run = pair_sum(l_run);
+    if (g == 0) { mw[wave][q] = m_run; lw[wave][q] = l_run; }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < NG; j++)
+        *(float4 *)part[wave][j][lane] = make_float4(o[j >> 2][4 * (j & 3)], o[j >> 2][4 * (j & 3) + 1], o[j >> 2][4 * (j & 3) + 2], o[j >> 2][4 * (j & 3) + 3]);
+    __syncthreads();
+    if (row >= a.T) return;
+    const int nw = min(NW, n_tiles);
+    float mx = -INFINITY, l = 0.f, wt[NW];
+#pragma unroll
+    for (int w = 0; w < NW; w++) mx = fmaxf(mx, mw[w][q]);      // finite: every row sees position 0
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        wt[w] = __builtin_amdgcn_exp2f(mw[w][q] - mx);
+        l = fmaf(wt[w], lw[w][q], l);
+    }
     const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-        const float ir = __shfl(inv, 4 * g + r);
-        const int orow = rb * ROWS + wave * 16 + 4 * g + r;
-        if (orow < a.T) {
+    for (int jj = 0; jj < NG / NW; jj++) {
+        const int j = wave * (NG / NW) + jj;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int dt = 0; dt < DT; dt++)
-                store_act_pf(a.act_out, a.act_blk_bytes, orow >> 3, orow & 7, h * HD + 16 * dt + q16, o[dt][r] * ir, a.act_pair);
-        }
+        for (int w = 0; w < NW; w++)
+            if (w < nw) {
+                const float4 y = *(const float4 *)part[w][j][lane];
+                v[0] = fmaf(wt[w], y.x, v[0]); v[1] = fmaf(wt[w], y.y, v[1]); v[2] = fmaf(wt[w], y.z, v[2]); v[3] = fmaf(wt[w], y.w, v[3]);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] *= inv;
+        pf_attn_store(a, row, h * HD + 32 * (j >> 2) + 8 * (j & 3) + 4 * g, v);
     }
 }
 

@@ -7,7 +7,6 @@
 // from their bf16 tiles as they are.  Included by kangaroo.hip after kernels.hip.h.
 #pragma once
 
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------------------------
 // C[M][N] (+)= sum_k A(m, k) * B(k, n), fp32, any strides.
