@@ -333,13 +333,13 @@ void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &
 // gemv_multi_kernel, whose time hardly does.  Measured (us, stand-alone product over weights that no cache holds; gemv_bf16_body with
 // 5, 6, 7, 8 rows / gemv_multi_kernel):
 //   tiles   4096 features                    5120 features                    11008 features
-//   2       13.5 14.0 14.7 15.2 / 16.2       16.7 17.3 18.0 18.9 / 17.0       32.0 33.2 34.7 36.4 / 32.1
-//   3       18.2 18.9 19.9 20.6 / 17.9       22.1 23.4 24.9 26.0 / 22.1       44.4 46.4 48.7 51.4 / 45.8
-//   4       23.0 24.0 24.9 26.5 / 25.0       28.2 29.7 31.4 33.0 / 28.3       57.7 60.5 63.6 67.0 / 57.3
-//   5       28.0 29.1 30.4 32.3 / 28.6       34.4 36.1 38.0 40.4 / 34.7       71.1 74.4 78.2 82.7 / 69.1
-//   6       32.8 34.2 35.6 37.4 / 34.2       40.6 42.6 44.9 47.7 / 40.4       84.5 88.2 92.9 97.9 / 86.0
-//   7       37.9 39.3 40.9 43.3 / 38.7       46.7 49.2 51.6 54.7 / 46.5       97.9 102  108  113  / 96.3
-//   8       42.6 44.4 46.1 48.6 / 46.1       52.8 55.5 58.3 62.0 / 52.4       111  116  122  129  / 110
+//   2       13.2 13.6 14.2 14.7 / 18.6       15.8 16.4 17.3 18.2 / 15.5       30.9 32.0 33.5 35.3 / 29.8
+//   3       18.0 18.7 19.5 20.3 / 18.0       22.0 22.9 24.2 25.3 / 21.8       44.0 45.9 48.3 50.8 / 46.3
+//   4       22.8 23.7 24.7 26.0 / 25.5       28.1 29.3 31.0 32.6 / 27.8       57.7 60.1 63.1 66.6 / 56.3
+//   5       27.5 28.7 30.0 31.6 / 28.3       34.3 35.8 37.9 39.8 / 34.7       71.0 74.0 77.9 82.3 / 69.0
+//   6       32.2 33.7 35.3 37.1 / 35.5       40.5 42.4 44.8 47.1 / 40.2       84.2 88.0 92.5 97.7 / 86.2
+//   7       37.0 38.8 40.5 42.6 / 38.5       46.7 48.8 51.7 54.5 / 46.9       97.9 102  108  114  / 97.0
+//   8       41.6 43.5 45.7 48.1 / 46.3       52.8 55.4 58.7 61.8 / 53.7       111  116  122  129  / 113
 // So from 6 rows on with 3 to 7 tiles, with 4 tiles from 7; not with 2, nor with 8 (6 and 7 rows of 4096 features).
 inline int gemv_tiles(int n_cus, int N, int M)
 {

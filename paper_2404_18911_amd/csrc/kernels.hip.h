@@ -117,15 +117,29 @@ __device__ __forceinline__ int b_slot(int lane) { return (((lane & 7) * 2 + ((la
 // Wave w of an 8-wave block serves batch row w.  The partials (at most 8 per lane: d <= 8192) are
 // fetched by scale_fetch at kernel start so that their latency hides behind the weight stream;
 // scale_finish reduces them.  Result valid after the next __syncthreads().
+// Loads of which some lanes want nothing go through a buffer whose bounds the others respect (a lane out of bounds gets 0 and moves no
+// bytes): a masked load is a branch around it, after which the compiler no longer knows how many loads are in flight and waits for
+// more of them than are needed, in a weight stream for the very chunk it has just asked for.  us per launch in a 7B request, masked
+// activation loads and sums of squares / here: q,k,v 17.2 / 16.7, o_proj 8.0 / 7.6, gate+up 28.8 / 28.3, LM head 40.1 / 38.8; seven
+// rows: q,k,v 18.9 / 18.4, gate+up 32.6 / 32.3.  Stand-alone, 4096 x 4096, one row 7.31 / 6.76; 13840 x 5136, 7 rows 26.3 / 24.5.
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t buffer_of(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+#define BUFFER_NONE 0x80000000u     // a byte offset no buffer here reaches
+
 struct ScaleRegs { float v[8]; };
 __device__ __forceinline__ void scale_fetch(const float *ssq_in, int M, int nt_in, ScaleRegs &r)
 {
-    int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < 8; j++) {
-        int i = lane + 64 * j;
-        r.v[j] = (ssq_in && wave < M && i < nt_in) ? ssq_in[(size_t)i * KG_ROWS + wave] : 0.f;
-    }
+    for (int j = 0; j < 8; j++) r.v[j] = 0.f;
+    if (!ssq_in || wave >= M) return;
+    const buffer_t b = buffer_of(ssq_in, (uint32_t)nt_in * KG_ROWS * 4);
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+        r.v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (lane + 64 * j) * KG_ROWS * 4 + wave * 4, 0, 0));
 }
 __device__ __forceinline__ void scale_finish(const Epi &e, const ScaleRegs &r, float *sc)
 {
@@ -135,7 +149,7 @@ __device__ __forceinline__ void scale_finish(const Epi &e, const ScaleRegs &r, f
         if (e.ssq_in) {
             s = 0.f;
 #pragma unroll
-            for (int j = 0; j < 8; j++) s += r.v[j];
+            for (int j = 0; j < 8; j++) s += rounded(r.v[j]);       // (or the compiler adds, and waits, where the loads are)
             for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
             s = rsqrtf(fmaf(s, e.inv_d, e.eps));
         }
@@ -348,8 +362,9 @@ template <int SRC> struct BRaw { float v[4]; };
 template <> struct BRaw<FROM_ACT> { u32x4_t v; };
 
 template <int SRC> struct BSource {
-    const u32x4_t *tiles;       // FROM_ACT: this lane's slot of k-step 0
-    const float *row;           // else this lane's row at its four k of k-step 0
+    buffer_t buf;
+    uint32_t off;               // this lane's 16 bytes of k-step 0 (its slot, or its row at its four k); BUFFER_NONE: the column stands for no row
+    const float *row;           // FROM_ROWS_UNALIGNED: the same as an address
     int k, K;                   // first of the pair's 8 k, features
     bool on, lo;                // the lane's column stands for a live row; for the lo part of it
     __device__ __forceinline__ BSource(const void *act, int M, int lane, int K_)
@@ -358,19 +373,25 @@ template <int SRC> struct BSource {
         lo = (lane & 8) != 0;
         k = (lane >> 4) * 8;
         K = K_;
-        tiles = (const u32x4_t *)act + b_slot(lane);
+        buf = buffer_of(act, 0x7FFFFFFFu);
+        const uint32_t at = (uint32_t)(lane & 7) * K_ + k + (lo ? 4 : 0);
+        off = !on ? BUFFER_NONE : SRC == FROM_ACT ? 16 * b_slot(lane) : 4 * at;
         row = (const float *)act + (size_t)(lane & 7) * K_ + k + (lo ? 4 : 0);
     }
     __device__ __forceinline__ BRaw<SRC> load(int ks) const
     {
         BRaw<SRC> r;
         if constexpr (SRC == FROM_ACT) {
-            r.v = on ? tiles[ks * 64] : u32x4_t{0u, 0u, 0u, 0u};
+            r.v = __builtin_amdgcn_raw_buffer_load_b128(buf, off, ks * 1024, 0);
+        } else if constexpr (SRC == FROM_ROWS) {
+            // (K is a multiple of 16: the last k-step may be half empty)
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(buf, k + 32 * ks + 8 <= K ? off : BUFFER_NONE, ks * 128, 0);
+#pragma unroll
+            for (int i = 0; i < 4; i++) r.v[i] = __uint_as_float(v[i]);
         } else {
-            const bool in = on && k + 32 * ks + 8 <= K;             // (K is a multiple of 16: the last k-step may be half empty)
             const float *p = row + 32 * ks;
             float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (in) a = SRC == FROM_ROWS ? *(const float4 *)p : make_float4(p[0], p[1], p[2], p[3]);
+            if (on && k + 32 * ks + 8 <= K) a = make_float4(p[0], p[1], p[2], p[3]);
             r.v[0] = a.x; r.v[1] = a.y; r.v[2] = a.z; r.v[3] = a.w;
         }
         return r;
@@ -452,33 +473,51 @@ __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, in
 #pragma unroll
         for (int u = 0; u < U; u++) mma(A[u], Bv[u]);
     };
-    int n = q;
-    {
-        // chunks of 4 tiles, double-buffered: the loads of chunk i+1 are in flight while chunk i is
-        // multiplied, so a wave never drains its memory pipe between chunks
+    // chunks of 4 tiles, double-buffered: the loads of chunk i+1 are in flight while chunk i is
+    // multiplied, so a wave never drains its memory pipe between chunks.  LONG: some waves have a long range (KS is no multiple of 8),
+    // with its own load in front; a copy of its own, for with that condition the compiler waits for all loads in every turn of the loop.
+#define GEMV_FENCE __builtin_amdgcn_sched_barrier(0)        // (nor is a load moved below a multiplication)
+    auto stream = [&](auto has_long) {
+        constexpr bool LONG = decltype(has_long)::value;
         u32x4_t a0[4], a1[4];
         BRaw<SRC> b0[4], b1[4];
-        u32x4_t ax = {0u, 0u, 0u, 0u};                     // first tile of a long range (k-step ks0)
-        BRaw<SRC> bx;
-        if (long_range) {
-            ax = __builtin_nontemporal_load(wbase + (size_t)(ks0 - wave * q) * 64);
-            bx = bsrc.load(ks0);
+        int n = q & 3, rem = q >> 2;
+        if constexpr (LONG) {
+            u32x4_t ax = {0u, 0u, 0u, 0u};                 // first tile of a long range (k-step ks0)
+            BRaw<SRC> bx;
+            if (long_range) {
+                ax = __builtin_nontemporal_load(wbase + (size_t)(ks0 - wave * q) * 64);
+                bx = bsrc.load(ks0);
+            }
+            if (rem) load(a0, b0, 4);
+            if (long_range) mma(ax, bx);
+        } else if (rem) {
+            load(a0, b0, 4);
         }
-        int rem = n >> 2;
-        n &= 3;
-        if (rem) load(a0, b0, 4);
-        if (long_range) mma(ax, bx);
-        while (rem >= 2) {
+        for (; rem > 2; rem -= 2) {
             load(a1, b1, 4);
+            GEMV_FENCE;
             mul(a0, b0, 4);
-            if (rem > 2) load(a0, b0, 4);
+            GEMV_FENCE;
+            load(a0, b0, 4);
+            GEMV_FENCE;
             mul(a1, b1, 4);
-            rem -= 2;
+            GEMV_FENCE;
         }
-        if (rem == 1) mul(a0, b0, 4);
+        if (rem == 2) {
+            load(a1, b1, 4);
+            GEMV_FENCE;
+            mul(a0, b0, 4);
+            mul(a1, b1, 4);
+        } else if (rem == 1) {
+            mul(a0, b0, 4);
+        }
         if (n >= 2) { load(a0, b0, 2); mul(a0, b0, 2); n -= 2; }
         if (n >= 1) { load(a0, b0, 1); mul(a0, b0, 1); }
-    }
+    };
+#undef GEMV_FENCE
+    if (n_long) stream(std::true_type{});
+    else stream(std::false_type{});
     scale_finish(e, sr, sc);
     // D layout: lane holds column (lane & 15) and tile rows 4*(lane >> 4) + r.  Columns m and m+8
     // are the hi and lo parts of batch row m: fold them.
@@ -530,7 +569,7 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 4) void gemv_bf16_rows_kernel(cons
 
 // Projections of several rows with more weight tiles than compute units: one workgroup per compute unit and NTW tiles per
 // workgroup.  gemv_bf16_kernel fetches the activations of a k-step through the L1 once per weight tile (M / 8 of the
-// weights' bytes, and they come after them: gate+up of the 7B shape takes 29.3 us with one row and 36.5 us with eight);
+// weights' bytes, and they come after them: gate+up of the 7B shape takes 28 us with one row and 36 us with eight);
 // here they serve NTW tiles.  Every tile's sums run over the same k in the same order as there: the results are
 // the same bits for any number of rows.  The tiles are shared out evenly (no group has more than NTW).
 // D k-steps of loads are in flight per wave.  (Two tiles per workgroup in gemv_bf16_body instead, 16 waves a compute
@@ -576,29 +615,42 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_multi_kernel(const u3
 #pragma unroll
         for (int t = 0; t < NTW; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[s][t]), b, acc[t], 0, 0, 0);
     };
+    // fewer than 2 D steps are left, the first D of them loaded or on their way
+    auto finish = [&](int i) {
 #pragma unroll
-    for (int s = 0; s < D; s++)
-        if (s < n) load(s, s);
-    int i = 0;
-    for (; i + 2 * D <= n; i += D) {
+        for (int s = 0; s < D; s++)
+            if (i + s < n) {
+                mul(s);
+                if (i + s + D < n) load(s, i + s + D);
+            }
+#pragma unroll
+        for (int s = 0; s < D; s++)
+            if (i + D + s < n) mul(s);
+    };
+    // (two ways apart from the start: after loads that may not have been issued the compiler waits for all of them in every turn)
+    if (n >= 2 * D) {
 #pragma unroll
         for (int s = 0; s < D; s++) {
-            mul(s);
-            load(s, i + s + D);
+            load(s, s);
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    // fewer than 2 D steps are left, the first D of them loaded or on their way
+        int i = 0;
+        for (; i + 2 * D <= n; i += D) {
 #pragma unroll
-    for (int s = 0; s < D; s++)
-        if (i + s < n) {
-            mul(s);
-            if (i + s + D < n) load(s, i + s + D);
+            for (int s = 0; s < D; s++) {
+                __builtin_amdgcn_sched_barrier(0);
+                mul(s);
+                load(s, i + s + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    i += D;
+        finish(i);
+    } else {
 #pragma unroll
-    for (int s = 0; s < D; s++)
-        if (i + s < n) mul(s);
+        for (int s = 0; s < D; s++)
+            if (s < n) load(s, s);
+        finish(0);
+    }
     scale_finish(e, sr, sc);
     // fold the hi and lo columns, add the waves' sums in wave order (as gemv_bf16_body)
 #pragma unroll
