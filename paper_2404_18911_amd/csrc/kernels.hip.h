@@ -127,6 +127,13 @@ __device__ __forceinline__ buffer_t buffer_of(const void *p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }
+// a pointer that is the same in all lanes, where the compiler cannot tell
+template <typename T> __device__ __forceinline__ T *uniform(T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (T *)(((uint64_t)hi << 32) | lo);
+}
 #define BUFFER_NONE 0x80000000u     // a byte offset no buffer here reaches
 
 struct ScaleRegs { float v[8]; };
@@ -1888,13 +1895,13 @@ template <> __device__ __forceinline__ void kv_st<float>(float *p, float v) { *p
 template <> __device__ __forceinline__ void kv_st<uint16_t>(uint16_t *p, float v) { *p = f2bf(v); }
 template <> __device__ __forceinline__ void kv_st<kvhalf_t>(kvhalf_t *p, float v) { p->bits = f32_to_half_bits(v); }
 
-template <typename T, int N8> struct KvVec;           // N8 groups of 8 cache elements, loaded as 16-byte pieces
+template <typename T, int N8> struct KvVec;           // N8 groups of 8 cache elements, loaded as 16-byte pieces (byte offset in a buffer)
 template <int N8> struct KvVec<uint16_t, N8> {
     u32x4_t r[N8];
-    __device__ __forceinline__ void load(const uint16_t *p)
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off)
     {
 #pragma unroll
-        for (int i = 0; i < N8; i++) r[i] = *(const u32x4_t *)(p + 8 * i);
+        for (int i = 0; i < N8; i++) r[i] = __builtin_amdgcn_raw_buffer_load_b128(b, off + 16 * i, 0, 0);
     }
     __device__ __forceinline__ float get(int i) const
     {
@@ -1904,10 +1911,10 @@ template <int N8> struct KvVec<uint16_t, N8> {
 };
 template <int N8> struct KvVec<kvhalf_t, N8> {
     u32x4_t r[N8];
-    __device__ __forceinline__ void load(const kvhalf_t *p)
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off)
     {
 #pragma unroll
-        for (int i = 0; i < N8; i++) r[i] = *(const u32x4_t *)(p + 8 * i);
+        for (int i = 0; i < N8; i++) r[i] = __builtin_amdgcn_raw_buffer_load_b128(b, off + 16 * i, 0, 0);
     }
     __device__ __forceinline__ float get(int i) const
     {
@@ -1916,57 +1923,54 @@ template <int N8> struct KvVec<kvhalf_t, N8> {
     }
 };
 template <int N8> struct KvVec<float, N8> {
-    float4 r[2 * N8];
-    __device__ __forceinline__ void load(const float *p)
+    u32x4_t r[2 * N8];
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off)
     {
 #pragma unroll
-        for (int i = 0; i < 2 * N8; i++) r[i] = *(const float4 *)(p + 4 * i);
+        for (int i = 0; i < 2 * N8; i++) r[i] = __builtin_amdgcn_raw_buffer_load_b128(b, off + 16 * i, 0, 0);
     }
-    __device__ __forceinline__ float get(int i) const
-    {
-        const float4 &v = r[i >> 2];
-        return (i & 3) == 0 ? v.x : (i & 3) == 1 ? v.y : (i & 3) == 2 ? v.z : v.w;
-    }
+    __device__ __forceinline__ float get(int i) const { return __uint_as_float(r[i >> 2][i & 3]); }
 };
 
 // E consecutive cache elements owned by one lane in the P.V pass (E = head_dim / 64)
 template <typename T, int E> struct KvLane;
 template <> struct KvLane<uint16_t, 2> {
     uint32_t r;
-    __device__ __forceinline__ void load(const uint16_t *p) { r = *(const uint32_t *)p; }
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0); }
     __device__ __forceinline__ float get(int e) const { return __uint_as_float(e ? (r & 0xFFFF0000u) : (r << 16)); }
 };
 template <> struct KvLane<uint16_t, 1> {
     uint16_t r;
-    __device__ __forceinline__ void load(const uint16_t *p) { r = *p; }
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b16(b, off, 0, 0); }
     __device__ __forceinline__ float get(int) const { return bf2f(r); }
 };
 template <> struct KvLane<kvhalf_t, 2> {
     uint32_t r;
-    __device__ __forceinline__ void load(const kvhalf_t *p) { r = *(const uint32_t *)p; }
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0); }
     __device__ __forceinline__ float get(int e) const { return half_bits_to_f32(e ? (r >> 16) : (r & 0xFFFFu)); }
 };
 template <> struct KvLane<kvhalf_t, 1> {
     uint32_t r;
-    __device__ __forceinline__ void load(const kvhalf_t *p) { r = p->bits; }
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b16(b, off, 0, 0); }
     __device__ __forceinline__ float get(int) const { return half_bits_to_f32(r); }
 };
 template <> struct KvLane<float, 2> {
-    float2 r;
-    __device__ __forceinline__ void load(const float *p) { r = *(const float2 *)p; }
-    __device__ __forceinline__ float get(int e) const { return e ? r.y : r.x; }
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    u32x2_t r;
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0); }
+    __device__ __forceinline__ float get(int e) const { return __uint_as_float(r[e]); }
 };
 template <> struct KvLane<float, 1> {
-    float r;
-    __device__ __forceinline__ void load(const float *p) { r = *p; }
-    __device__ __forceinline__ float get(int) const { return r; }
+    uint32_t r;
+    __device__ __forceinline__ void load(buffer_t b, uint32_t off) { r = __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0); }
+    __device__ __forceinline__ float get(int) const { return __uint_as_float(r); }
 };
 
 // physical page of logical page s: the first 16 come from the argument block through a chain of
 // selects on constant indices
 __device__ __forceinline__ int attn_page(const AttnArgs &a, int s)
 {
-    if (s >= 16) return a.page_table[s];
+    if (s >= 16) return ((const __attribute__((address_space(4))) int *)a.page_table)[s];       // (a scalar load: nothing writes the table here)
     int p = a.pages[0];
 #pragma unroll
     for (int i = 1; i < 16; i++) p = (s == i) ? a.pages[i] : p;
@@ -2047,29 +2051,30 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
     T *const Vp = Kp + (size_t)P * HD;
     void *const act_out = (char *)a.act_out + (size_t)zb * a.act_blk_bytes;
 
-    // this call's rows (thread = row rm, rotation pair rj): issued first, they come from the L2
+    // All loads first, without a condition per lane or position (see buffer_of): this call's rows (thread = row rm, rotation pair rj),
+    // which come from the L2 and are waited for alone, then the rows cached by earlier calls: score lane (position pl, quarter sub); P.V lane owns
+    // EPL elements.  (With the cached rows requested under conditions the compiler waited for this call's before it
+    // asked for any: 7B shape, one row and two pages 6.4 -> 5.6 us, two rows and one page 5.5 -> 5.1.)
     const bool has_row = t < M * HH;
     const int rm = t / HH, rj = t % HH, rpos = pos0 + rm;
     const bool row_here = has_row && !a.preappended && (a.append_all || (rpos >= p_begin && rpos < p_begin + P));
-    float2 cs = make_float2(1.f, 0.f);
-    float q0 = 0.f, q1 = 0.f, k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
-    if (has_row) {
-        const float *q = qkv + (size_t)rm * 3 * d;
-        cs = a.rope[(size_t)rpos * HH + rj];
-        q0 = q[rj]; q1 = q[rj + HH];
-        if (row_here) { k0 = q[d + rj]; k1 = q[d + rj + HH]; v0 = q[2 * d + rj]; v1 = q[2 * d + rj + HH]; }
-    }
-    // rows cached by earlier calls: score lane (position pl, quarter sub); P.V lane owns EPL elements
+    const int rq = min(rm, M - 1);
+    const float *q = qkv + (size_t)rq * 3 * d;
+    const float2 cs = a.rope[(size_t)(pos0 + rq) * HH + rj];
+    float q0 = q[rj], q1 = q[rj + HH];
+    const float k0 = q[d + rj], k1 = q[d + rj + HH], v0 = q[2 * d + rj], v1 = q[2 * d + rj + HH];      // (of no use if !row_here)
     const int pl = t >> 2, sub = t & 3;
-    const bool k_old = pl < n_old;
     KvVec<T, EL / 8> kreg;
     KvLane<T, EPL> vreg[16];
-    if (!a.append_only) {
-        if (k_old) kreg.load(Kp + (size_t)pl * HD + sub * EL);
+    {
+        const uint32_t cached = a.append_only ? 0 : __builtin_amdgcn_readfirstlane(n_old) * HD * sizeof(T);
+        const buffer_t kb = buffer_of(uniform(Kp), cached), vb = buffer_of(uniform(Vp), cached);
+        kreg.load(kb, (pl * HD + sub * EL) * sizeof(T));
 #pragma unroll
-        for (int i = 0; i < 16; i++)
-            if (wave * 16 + i < n_old) vreg[i].load(Vp + (size_t)(wave * 16 + i) * HD + EPL * lane);
+        for (int i = 0; i < 16; i++) vreg[i].load(vb, ((wave * 16 + i) * HD + EPL * lane) * sizeof(T));
     }
+    __builtin_amdgcn_sched_barrier(0);
+    q0 = rounded(q0); q1 = rounded(q1);         // (the rotation is not begun, and its operands not waited for, above)
     if (!has_row && t < MR * HH) { qs[rm][rj] = 0.f; qs[rm][rj + HH] = 0.f; }   // unused rows of the instantiation
     if (has_row) {
         const float qscale = rsqrtf((float)HD);
@@ -2096,7 +2101,7 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
     if (a.append_only) return;
     __syncthreads();
     // positions written by this call are taken from LDS (the very values the cache now holds)
-    const bool k_new = !k_old && pl < n_valid;
+    const bool k_new = pl >= n_old && pl < n_valid;
     const int mk = p_begin + pl - pos0;
 
     // scores and wave-local softmax
@@ -2105,26 +2110,28 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
     float pr[MR], dot[MR];
 #pragma unroll
     for (int m = 0; m < MR; m++) dot[m] = 0.f;
+    const bool cached_here = wave * 16 < __builtin_amdgcn_readfirstlane(n_old);      // does the wave have a cached position?
+    if (cached_here)
+#pragma unroll
+    for (int i4 = 0; i4 < EL; i4 += 4) {        // (zeros where no position is cached)
+        const float kf0 = kreg.get(i4), kf1 = kreg.get(i4 + 1), kf2 = kreg.get(i4 + 2), kf3 = kreg.get(i4 + 3);
+#pragma unroll
+        for (int m = 0; m < MR; m++) {
+            const float4 qv = *(const float4 *)&qs[m][sub * EL + i4];
+            dot[m] = fmaf(kf0, qv.x, dot[m]);
+            dot[m] = fmaf(kf1, qv.y, dot[m]);
+            dot[m] = fmaf(kf2, qv.z, dot[m]);
+            dot[m] = fmaf(kf3, qv.w, dot[m]);
+        }
+    }
     if (k_new) {
 #pragma unroll
         for (int m = 0; m < MR; m++)
             if (m < M) {
+                dot[m] = 0.f;
 #pragma unroll
                 for (int i = 0; i < EL; i++) dot[m] = fmaf(kn[mk][sub * EL + i], qs[m][sub * EL + i], dot[m]);
             }
-    } else if (k_old) {
-#pragma unroll
-        for (int i4 = 0; i4 < EL; i4 += 4) {
-            const float kf0 = kreg.get(i4), kf1 = kreg.get(i4 + 1), kf2 = kreg.get(i4 + 2), kf3 = kreg.get(i4 + 3);
-#pragma unroll
-            for (int m = 0; m < MR; m++) {
-                const float4 qv = *(const float4 *)&qs[m][sub * EL + i4];
-                dot[m] = fmaf(kf0, qv.x, dot[m]);
-                dot[m] = fmaf(kf1, qv.y, dot[m]);
-                dot[m] = fmaf(kf2, qv.z, dot[m]);
-                dot[m] = fmaf(kf3, qv.w, dot[m]);
-            }
-        }
     }
 #pragma unroll
     for (int m = 0; m < MR; m++) {
@@ -2157,8 +2164,11 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         }
         __builtin_amdgcn_wave_barrier();
     }
+    // probability of row m at the wave's position i (rows beyond M carry 0 and are not stored)
+    auto prob = [&](int m, int i) { return MR >= 4 ? pw[wave][m][i] : __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[m]), 4 * i)); };
+    if (cached_here)
 #pragma unroll
-    for (int i4 = 0; i4 < 16; i4 += 4) {
+    for (int i4 = 0; i4 < 16; i4 += 4) {        // cached positions (the values of others are zeros here)
         float4 p4[MR];
         if (MR >= 4) {
 #pragma unroll
@@ -2166,30 +2176,23 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         }
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            const int i = i4 + j;
-            const int pv = wave * 16 + i;
-            if (pv < n_valid) {                                  // uniform in the wave
-                float vv[EPL];
-                if (pv >= n_old) {
+            float vv[EPL];
 #pragma unroll
-                    for (int e = 0; e < EPL; e++) vv[e] = vn[p_begin + pv - pos0][EPL * lane + e];
-                } else {
+            for (int e = 0; e < EPL; e++) vv[e] = vreg[i4 + j].get(e);
 #pragma unroll
-                    for (int e = 0; e < EPL; e++) vv[e] = vreg[i].get(e);
-                }
+            for (int m = 0; m < MR; m++) {
+                const float p = MR < 4 ? prob(m, i4 + j) : j == 0 ? p4[m].x : j == 1 ? p4[m].y : j == 2 ? p4[m].z : p4[m].w;
 #pragma unroll
-                for (int m = 0; m < MR; m++) {
-                    if (MR >= 4) {          // rows beyond M carry probability 0 and are not stored
-                        const float p = j == 0 ? p4[m].x : j == 1 ? p4[m].y : j == 2 ? p4[m].z : p4[m].w;
-#pragma unroll
-                        for (int e = 0; e < EPL; e++) acc[m][e] = fmaf(p, vv[e], acc[m][e]);
-                    } else if (m < M) {
-                        const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[m]), 4 * i));
-#pragma unroll
-                        for (int e = 0; e < EPL; e++) acc[m][e] = fmaf(p, vv[e], acc[m][e]);
-                    }
-                }
+                for (int e = 0; e < EPL; e++) acc[m][e] = fmaf(p, vv[e], acc[m][e]);
             }
+        }
+    }
+    for (int pv = max(n_old, wave * 16); pv < min(n_valid, wave * 16 + 16); pv++) {        // this call's (uniform in the wave)
+#pragma unroll
+        for (int m = 0; m < MR; m++) {
+            const float p = prob(m, pv - wave * 16);
+#pragma unroll
+            for (int e = 0; e < EPL; e++) acc[m][e] = fmaf(p, vn[p_begin + pv - pos0][EPL * lane + e], acc[m][e]);
         }
     }
 #pragma unroll
@@ -2277,27 +2280,73 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         if (t == 0) __hip_atomic_store(&a.cnt[hz], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    // page weights exp(max_page - max_all), through LDS so that the page loop has independent loads
-    float (*wgt)[MR] = (float (*)[MR]) & ow[0][0][0];    // [page][row], S <= 128 <= 8 * HD
-    for (int m = wave; m < M; m += 8) {
-        float gm = -INFINITY;
-        for (int ss = lane; ss < S; ss += 64) gm = fmaxf(gm, ld_dev(&a.mxs[(hb + ss) * KG_ROWS + m]));
+    // Many pages: four groups of HD threads take every fourth page, MB rows and 8 pages of loads in flight; the first of them fly while wave m
+    // works out the page weights exp(max_page - max_all) and the sum of row m, which go through LDS, as do the groups' sums (added in
+    // group order).  (One group and weights read twice, 8 loads at a time: a launch
+    // of one row at 4000 positions 18.0 us, of eight 31; here 16.2 and 29.6.)
+    constexpr int G = 4, MB = MR < 2 ? 1 : HD == 64 ? 2 : MR < 4 ? 2 : 4;
+    float (*gsum)[MR][HD] = ow;                             // [group - 1][row][element]
+    float (*wgt)[MR] = (float (*)[MR]) & ow[3][0][0];       // [page][row], S <= 128 <= 5 * HD
+    float *denl = &sw[0][0];
+    const int e = t % HD, grp = __builtin_amdgcn_readfirstlane(t / HD);
+    float ov[MB][8], num[MR];
+    auto load = [&](int m0, int j0) {
+#pragma unroll
+        for (int r = 0; r < MB; r++)
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const int ss = min(grp + G * (j0 + j), S - 1), m = min(m0 + r, M - 1);
+                ov[r][j] = ld_dev(&a.opart[((hb + ss) * KG_ROWS + m) * HD + e]);
+            }
+    };
+    if (grp < G) load(0, 0);
+    if (wave < M) {
+        const int s0 = min(lane, S - 1), s1 = min(lane + 64, S - 1);
+        const float x0 = ld_dev(&a.mxs[(hb + s0) * KG_ROWS + wave]), x1 = ld_dev(&a.mxs[(hb + s1) * KG_ROWS + wave]);
+        const float d0 = ld_dev(&a.sms[(hb + s0) * KG_ROWS + wave]), d1 = ld_dev(&a.sms[(hb + s1) * KG_ROWS + wave]);
+        float gm = fmaxf(x0, x1);
         for (int o = 32; o >= 1; o >>= 1) gm = fmaxf(gm, __shfl_xor(gm, o));
-        for (int ss = lane; ss < S; ss += 64) {
-            const float mxv = ld_dev(&a.mxs[(hb + ss) * KG_ROWS + m]);
-            wgt[ss][m] = (mxv == -INFINITY) ? 0.f : __expf(mxv - gm);
-        }
+        const float w0 = lane < S && x0 != -INFINITY ? __expf(x0 - gm) : 0.f, w1 = lane + 64 < S && x1 != -INFINITY ? __expf(x1 - gm) : 0.f;
+        if (lane < S) wgt[lane][wave] = w0;
+        if (lane + 64 < S) wgt[lane + 64][wave] = w1;
+        float den = fmaf(w1, d1, w0 * d0);
+        for (int o = 32; o >= 1; o >>= 1) den += __shfl_xor(den, o);
+        if (lane == 0) denl[wave] = den;
     }
     __syncthreads();
-    for (int i = t; i < M * HD; i += 512) {
-        const int m = i / HD, e = i % HD;
-        float num = 0.f, den = 0.f;
-        for (int ss = 0; ss < S; ss++) {
-            const float w = wgt[ss][m];
-            num = fmaf(w, ld_dev(&a.opart[((hb + ss) * KG_ROWS + m) * HD + e]), num);
-            den = fmaf(w, ld_dev(&a.sms[(hb + ss) * KG_ROWS + m]), den);
+    const int J = (S + G - 1) / G;
+#pragma unroll
+    for (int m0 = 0; m0 < MR; m0 += MB) {
+        if (m0 >= M || grp >= G) break;
+#pragma unroll
+        for (int r = 0; r < MB; r++) num[m0 + r] = 0.f;
+        for (int j0 = 0; j0 < J; j0 += 8) {
+            if (m0 || j0) load(m0, j0);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const int ss = grp + G * (j0 + j);
+                if (ss < S) {
+#pragma unroll
+                    for (int r = 0; r < MB; r++) num[m0 + r] = fmaf(wgt[ss][min(m0 + r, M - 1)], ov[r][j], num[m0 + r]);
+                }
+            }
         }
-        store_act<BF>(act_out, d, m, h * HD + e, num / den);
+    }
+    if (grp > 0 && grp < G) {
+#pragma unroll
+        for (int m = 0; m < MR; m++)
+            if (m < M) gsum[grp - 1][m][e] = num[m];
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int m = 0; m < MR; m++)
+            if (m < M) {
+                float v = num[m];
+#pragma unroll
+                for (int g = 1; g < G; g++) v += gsum[g - 1][m][e];
+                store_act<BF>(act_out, d, m, h * HD + e, v / denl[m]);
+            }
     }
     if (t == 0) __hip_atomic_store(&a.cnt[hz], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
