@@ -320,13 +320,9 @@ void prof_collect(kg_ctx *x)   // call after prof_flush and a synchronisation of
 
 void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &e, hipStream_t s, const Feature &ft = Feature())
 {
-    const dim3 grid(N / 16), block(256);
-    if ((((uintptr_t)W | (uintptr_t)act) & 15) == 0) {
-        if (e.M <= 1) hipLaunchKernelGGL((gemv_f32_kernel<1, true>), grid, block, 0, s, W, K, act, e, ft);
-        else if (e.M <= 2) hipLaunchKernelGGL((gemv_f32_kernel<2, true>), grid, block, 0, s, W, K, act, e, ft);
-        else if (e.M <= 4) hipLaunchKernelGGL((gemv_f32_kernel<4, true>), grid, block, 0, s, W, K, act, e, ft);
-        else hipLaunchKernelGGL((gemv_f32_kernel<8, true>), grid, block, 0, s, W, K, act, e, ft);
-    } else hipLaunchKernelGGL((gemv_f32_kernel<8, false>), grid, block, 0, s, W, K, act, e, ft);
+    if (e.M == 1) hipLaunchKernelGGL(gemv_f32_row_kernel, dim3(N / 16), dim3(256), 0, s, W, K, act, e, ft);
+    else if (e.M <= 4) hipLaunchKernelGGL(gemv_f32_kernel<1>, dim3(N / 16), dim3(512), 0, s, W, K, act, e, ft);
+    else hipLaunchKernelGGL(gemv_f32_kernel<2>, dim3(N / 16), dim3(512), 0, s, W, K, act, e, ft);
 }
 
 // Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, whose time grows with M, else

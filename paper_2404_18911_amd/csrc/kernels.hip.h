@@ -59,7 +59,7 @@ struct Epi {
 // EPI_FEATURE (early features, decode launches): as EPI_RESID with the rows of act_out and ssq_out from act_row on; and once more for
 // layer l (act2 <- x * gain2 and ssq2 from row row2 on), and as fp32 rows (xout2, may be null).  An argument of the kernels that have this
 // epilogue only: 40 more bytes in every bf16 projection's arguments cost 0.6 % of a 26 us launch.  (gemv_f32_kernel has it for all its
-// launches: stand-alone fp32 products of 256 x 256 to 2048 x 1024 take what they took without it, 4 .. 11 us within 2 %.)
+// launches: stand-alone fp32 products of 256 x 256 to 2048 x 1024 took what they took without it, within 2 %.)
 struct Feature {
     int act_row, row2;
     void *act2;
@@ -161,28 +161,6 @@ __device__ __forceinline__ void scale_finish(const Epi &e, const ScaleRegs &r, f
             s = rsqrtf(fmaf(s, e.inv_d, e.eps));
         }
         if (lane == 0) sc[wave] = s;
-    }
-}
-// for blocks with fewer than 8 waves
-__device__ __forceinline__ void compute_scale(const Epi &e, float *sc)
-{
-    int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int m = wave; m < e.M; m += (int)(blockDim.x >> 6)) {
-        float s = 1.f;
-        if (e.ssq_in) {
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                int i = lane + 64 * j;
-                v[j] = i < e.nt_in ? e.ssq_in[(size_t)i * KG_ROWS + m] : 0.f;
-            }
-            s = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; j++) s += v[j];
-            for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-            s = rsqrtf(fmaf(s, e.inv_d, e.eps));
-        }
-        if (lane == 0) sc[m] = s;
     }
 }
 
@@ -750,76 +728,245 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_valu_kernel(cons
     }
 }
 
-// Projection, fp32 weights (row-major [N][K]) and fp32 activations [8][K], K a multiple of 4: 16 threads per weight
-// row, each taking every 16th group of 4 consecutive k.  The models this serves are small (the float32
-// configuration: K of 256 and 688, 16 .. 86 workgroups), so a launch is a chain of memory latencies: the
-// groups of a chunk, the row sums of the scale and the epilogue's operands are requested together before
-// any is used (4.1 us per launch at the float32 configuration; 15.5 us when a thread took one k at a time).
-// MR >= rows (1, 2, 4 or 8); a row's sum runs over the same k in the same order in every instantiation.
-// VEC: weights and activations are 16-byte aligned (a caller of the stand-alone product may pass others).
-template <int MR, bool VEC>
-__global__ __launch_bounds__(256) void gemv_f32_kernel(const float *__restrict__ W, int K,
-                                                       const float *__restrict__ act, Epi e, Feature ft)
+// Lane exchanges of reductions as data-parallel-primitive moves (no trip through the
+// LDS crossbar as __shfl_xor takes).  All 64 lanes must be active.  quad_x1 / quad_x2: the value of
+// lane ^ 1 / lane ^ 2.  half_mirror / row_mirror: the value of the mirrored lane inside a group of
+// 8 / 16 lanes; where the value is already uniform over groups of 4 / 8 lanes that is the value
+// lane ^ 4 / lane ^ 8 holds, so a butterfly built from them gives every lane the bits the xor
+// butterfly gives.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
 {
-    constexpr int U = MR <= 4 ? 4 : 2;      // groups of 4 k per thread in flight
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float quad_x1(float v) { return dpp_move<0xB1>(v); }       // quad_perm [1,0,3,2]
+__device__ __forceinline__ float quad_x2(float v) { return dpp_move<0x4E>(v); }       // quad_perm [2,3,0,1]
+__device__ __forceinline__ float half_mirror(float v) { return dpp_move<0x141>(v); }
+__device__ __forceinline__ float row_mirror(float v) { return dpp_move<0x140>(v); }
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// v of the lanes with bit 32 (16, 8, 4) of their number clear and w of the others, each added to that of the lane that far away
+__device__ __forceinline__ float fold32(float v, float w)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(w), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float v, float w)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(w), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold8(float v, float w, int lane)
+{
+    const bool hi = lane & 8;
+    const float keep = hi ? w : v, give = hi ? v : w;
+    return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xF, 0xF, false));      // row_ror:8
+}
+__device__ __forceinline__ float fold4(float v, float w, int lane)
+{
+    const bool hi = lane & 4;
+    const float keep = hi ? w : v;
+    const int give = __float_as_int(hi ? v : w);
+    int other = __builtin_amdgcn_update_dpp(0, give, 0x104, 0xF, 0x5, false);           // row_shl:4 into lanes with bit 4 clear
+    other = __builtin_amdgcn_update_dpp(other, give, 0x114, 0xF, 0xA, false);           // row_shr:4 into the others
+    return keep + __int_as_float(other);
+}
+
+// Projection, fp32 weights (row-major [N][K]) and fp32 activations [8][K], K a multiple of 4: one workgroup (8 waves) per 16 weight
+// rows, wave (rh, kp) takes rows 8 rh .. 8 rh + 7 and every fourth step of 64 k.  Lane (b, i) = (lane / 4, lane % 4) loads 4 consecutive k
+// from 4 b on of weight rows i and 4 + i and of activation rows i (and 4 + i, MC = 2), for v_mfma_f32_4x4x1_16b_f32: one fused
+// multiply-add per k slot b, weight row and activation row; the slots are added by lane exchanges at the end, each leaving half the
+// sums in a lane.  (Of the fp32 matrix instructions the one that wastes least on few rows: v_mfma_f32_16x16x4_f32 does 16 columns, and one
+// row of 512 x 8192 took 20.9 us with it.)
+// The models this serves are small (the float32 configuration: K of 256 and 688, 16 .. 86 workgroups), so a launch is a chain of latencies:
+// the row sums of the scale, the operands of the first D steps and those of the epilogue are requested together before any is used, and
+// the scale is reduced while the others are on their way.  us per launch in a request of that configuration, one, two and eight rows: 4.4, 4.8
+// and 8.1 with 16 threads to a weight row on the vector units and all loads masked; 3.4 (the kernel below), 3.6 and 4.3 here.
+// A row's arithmetic does not depend on the others or on their number.  Rows of weights and activations need not be 16-byte aligned.
+template <int MC>
+__global__ __launch_bounds__(512) void gemv_f32_kernel(const float *__restrict__ W, int K, const float *__restrict__ act, Epi e, Feature ft)
+{
+    constexpr int D = 4;                    // steps in flight
+    typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+    __shared__ float red[4][16][KG_ROWS];
+    __shared__ float sq[16][KG_ROWS];
+    __shared__ float sc[KG_ROWS];
+    const int rt = blockIdx.x, t = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, i4 = lane & 3, slot = lane >> 2;
+    const int rh = wave & 1, kp = wave >> 1;
+    const int S = (K + 63) >> 6, n = kp < S ? (S - kp + 3) >> 2 : 0;       // steps, the last one perhaps short; this wave's
+    ScaleRegs sr;
+    scale_fetch(e.ssq_in, e.M, e.nt_in, sr);
+    const float *wr = W + (size_t)(rt * 16 + rh * 8 + i4) * K;
+    const buffer_t xb = buffer_of(act, 0x7FFFFFFFu);
+    f32x4_t w[D][2];
+    u32x4_t x[D][MC];
+    auto load = [&](int s, int i) {         // (no lane is masked, see buffer_of; k beyond the last repeats it in the weights, and is 0 in the rows)
+        const int k = 64 * (kp + 4 * i) + 4 * slot, kw = min(k, K - 4);
+#pragma unroll
+        for (int r = 0; r < 2; r++) w[s][r] = *(const f32x4u_t *)(wr + (size_t)4 * r * K + kw);
+#pragma unroll
+        for (int c = 0; c < MC; c++)
+            x[s][c] = __builtin_amdgcn_raw_buffer_load_b128(xb, k < K && 4 * c + i4 < e.M ? 4u * ((4 * c + i4) * K + k) : BUFFER_NONE, 0, 0);
+    };
+    f32x4_t acc[2][MC];                     // [rows 4 r ..][activation rows 4 c ..][row]
+#pragma unroll
+    for (int r = 0; r < 2; r++)
+#pragma unroll
+        for (int c = 0; c < MC; c++) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](int s, int i) {
+        const int k = 64 * (kp + 4 * i);
+        if (k + 64 > K && k + 4 * slot >= K) w[s][0] = w[s][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};      // (0 x infinity)
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int r = 0; r < 2; r++)
+#pragma unroll
+                for (int c = 0; c < MC; c++)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[s][r][j], __uint_as_float(x[s][c][j]), acc[r][c], 0, 0, 0);
+    };
+    float resv = 0.f, gainv = 1.f;          // epilogue operands of thread (row, m)
+    auto operands = [&]() {
+        if ((e.kind == EPI_RESID || e.kind == EPI_FEATURE) && t < 128 && (t & 7) < e.M) {
+            const int nn = rt * 16 + (t >> 3);
+            resv = e.res[(size_t)(t & 7) * e.N + nn];
+            if (e.gain) gainv = e.gain[nn];
+        }
+        scale_finish(e, sr, sc);
+    };
+    if (n >= D) {
+#pragma unroll
+        for (int s = 0; s < D; s++) {
+            load(s, s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        operands();
+        int i = 0;
+        for (; i + 2 * D <= n; i += D) {
+#pragma unroll
+            for (int s = 0; s < D; s++) {
+                mul(s, i + s);
+                load(s, i + s + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < D; s++) {
+            mul(s, i + s);
+            if (i + s + D < n) load(s, i + s + D);
+        }
+#pragma unroll
+        for (int s = 0; s < D; s++)
+            if (i + s + D < n) mul(s, i + s + D);
+    } else {
+#pragma unroll
+        for (int s = 0; s < D - 1; s++)
+            if (s < n) load(s, s);
+        operands();
+#pragma unroll
+        for (int s = 0; s < D - 1; s++)
+            if (s < n) mul(s, s);
+    }
+    // lane (b, i): 4 weight rows (registers) x activation row i of k slot b.  After the folds lane bits 32, 16, 8 say which of the 8
+    // weight rows it holds the sum of and bit 4 (MC = 2) which four activation rows.
+    float v[MC];
+#pragma unroll
+    for (int c = 0; c < MC; c++) {
+        float y[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) y[q] = fold32(acc[0][c][q], acc[1][c][q]);
+        v[c] = fold8(fold16(y[0], y[2]), fold16(y[1], y[3]), lane);
+    }
+    const float sum = fold4(v[0], v[MC - 1], lane);
+    const int row = 8 * rh + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1), m = i4 + (lane & 4);
+    red[kp][row][m] = sum;                  // (MC = 1: the same number twice, the second of no use)
+    __syncthreads();
+    if (t < 128) red[0][t >> 3][t & 7] = (red[0][t >> 3][t & 7] + red[1][t >> 3][t & 7]) + (red[2][t >> 3][t & 7] + red[3][t >> 3][t & 7]);
+    __syncthreads();
+    epilogue<false>(e, rt, red[0], sc, sq, resv, gainv, true, t, &ft);
+}
+
+// The same sums of one row on the vector units (a k slot's products one after another, slots and quarters of the steps in the order
+// above): 16 consecutive lanes read 256 bytes of a weight row, where the matrix instruction's operand has neighbouring lanes in four rows.
+// us, one row, matrix / vector: 2048 x 1024 4.18 / 3.78, 512 x 8192 17.6 / 9.9, 256 x 688 3.37 / 3.37; from two rows on the matrix form is as
+// fast or faster at the sizes of small models (2048 x 1024, two rows, 4.37 against 4.75 with two rows on the vector units).
+__global__ __launch_bounds__(256) void gemv_f32_row_kernel(const float *__restrict__ W, int K, const float *__restrict__ act, Epi e, Feature ft)
+{
+    constexpr int D = 8;                    // steps of 64 k in flight
+    typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
     __shared__ float yt[16][KG_ROWS];
     __shared__ float sq[16][KG_ROWS];
     __shared__ float sc[KG_ROWS];
-    const int rt = blockIdx.x;
-    const int row = threadIdx.x >> 4, sub = threadIdx.x & 15;
+    const int rt = blockIdx.x, t = threadIdx.x, row = t >> 4, slot = t & 15;
+    const int S = (K + 63) >> 6;
+    ScaleRegs sr;
+    scale_fetch(e.ssq_in, 1, e.nt_in, sr);
     const float *wr = W + (size_t)(rt * 16 + row) * K;
-    const int G = K >> 2;
-    auto ld = [](const float *p) {
-        if (VEC) return *(const float4 *)p;
-        return make_float4(p[0], p[1], p[2], p[3]);
+    f32x4_t w[D], x[D];
+    auto load = [&](int s, int i) {
+        const int k = min(64 * i + 4 * slot, K - 4);
+        w[s] = *(const f32x4u_t *)(wr + k);
+        x[s] = *(const f32x4u_t *)(act + k);
     };
-    float4 w[U], x[U][MR];
-    auto load = [&](int g0) {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};    // steps i % 4
+    auto mul = [&](int s, int i) {
+        if (64 * i + 64 > K && 64 * i + 4 * slot >= K) w[s] = x[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int g = g0 + 16 * u;
-            w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int j = 0; j < 4; j++) acc[s & 3] = fmaf(w[s][j], x[s][j], acc[s & 3]);
+    };
+    float resv = 0.f, gainv = 1.f;          // epilogue operands of thread (row, 0)
+    auto operands = [&]() {
+        if ((e.kind == EPI_RESID || e.kind == EPI_FEATURE) && t < 128 && (t & 7) == 0) {
+            const int nn = rt * 16 + (t >> 3);
+            resv = e.res[nn];
+            if (e.gain) gainv = e.gain[nn];
+        }
+        scale_finish(e, sr, sc);
+    };
+    if (S >= D) {
 #pragma unroll
-            for (int m = 0; m < MR; m++) x[u][m] = w[u];
-            if (g < G) {
-                w[u] = ld(wr + 4 * g);
+        for (int s = 0; s < D; s++) {
+            load(s, s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        operands();
+        int i = 0;
+        for (; i + 2 * D <= S; i += D) {
 #pragma unroll
-                for (int m = 0; m < MR; m++)
-                    if (m < e.M) x[u][m] = ld(act + (size_t)m * K + 4 * g);
+            for (int s = 0; s < D; s++) {
+                mul(s, i + s);
+                load(s, i + s + D);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-    };
-    load(sub);
-    float resv = 0.f, gainv = 1.f;          // epilogue operands of thread (row, m)
-    if ((e.kind == EPI_RESID || e.kind == EPI_FEATURE) && threadIdx.x < 128 && (int)(threadIdx.x & 7) < e.M) {
-        const int n = rt * 16 + (threadIdx.x >> 3);
-        resv = e.res[(size_t)(threadIdx.x & 7) * e.N + n];
-        if (e.gain) gainv = e.gain[n];
-    }
-    compute_scale(e, sc);
-    float acc[MR];
 #pragma unroll
-    for (int m = 0; m < MR; m++) acc[m] = 0.f;
-    for (int g0 = sub; g0 < G; g0 += 16 * U) {
-        if (g0 != sub) load(g0);
+        for (int s = 0; s < D; s++) {
+            mul(s, i + s);
+            if (i + s + D < S) load(s, i + s + D);
+        }
 #pragma unroll
-        for (int u = 0; u < U; u++)
+        for (int s = 0; s < D; s++)
+            if (i + s + D < S) mul(s, i + s + D);
+    } else {
 #pragma unroll
-            for (int m = 0; m < MR; m++) {
-                acc[m] = fmaf(w[u].x, x[u][m].x, acc[m]);
-                acc[m] = fmaf(w[u].y, x[u][m].y, acc[m]);
-                acc[m] = fmaf(w[u].z, x[u][m].z, acc[m]);
-                acc[m] = fmaf(w[u].w, x[u][m].w, acc[m]);
-            }
+        for (int s = 0; s < D - 1; s++)
+            if (s < S) load(s, s);
+        operands();
+#pragma unroll
+        for (int s = 0; s < D - 1; s++)
+            if (s < S) mul(s, s);
     }
 #pragma unroll
-    for (int m = 0; m < MR; m++) {
-        float v = acc[m];
-        for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-        if (sub == 0) yt[row][m] = v;
+    for (int j = 0; j < 4; j++) {
+        acc[j] += dpp_move<0x128>(acc[j]);                              // lane ^ 8 (row_ror:8)
+        acc[j] = fold4(acc[j], acc[j], t);
+        acc[j] += quad_x2(acc[j]);
+        acc[j] += quad_x1(acc[j]);
     }
+    if (slot == 0) yt[row][0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     __syncthreads();
-    epilogue<false>(e, rt, yt, sc, sq, resv, gainv, true, threadIdx.x, &ft);
+    epilogue<false>(e, rt, yt, sc, sq, resv, gainv, true, t, &ft);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1977,24 +2124,6 @@ __device__ __forceinline__ int attn_page(const AttnArgs &a, int s)
     return p;
 }
 
-// Lane exchanges of the softmax reductions as data-parallel-primitive moves (no trip through the
-// LDS crossbar as __shfl_xor takes).  All 64 lanes must be active.  quad_x1 / quad_x2: the value of
-// lane ^ 1 / lane ^ 2.  half_mirror / row_mirror: the value of the mirrored lane inside a group of
-// 8 / 16 lanes; where the value is already uniform over groups of 4 / 8 lanes that is the value
-// lane ^ 4 / lane ^ 8 holds, so a butterfly built from them gives every lane the bits the xor
-// butterfly gives.
-template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float quad_x1(float v) { return dpp_move<0xB1>(v); }       // quad_perm [1,0,3,2]
-__device__ __forceinline__ float quad_x2(float v) { return dpp_move<0x4E>(v); }       // quad_perm [2,3,0,1]
-__device__ __forceinline__ float half_mirror(float v) { return dpp_move<0x141>(v); }
-__device__ __forceinline__ float row_mirror(float v) { return dpp_move<0x140>(v); }
-__device__ __forceinline__ float lane_value(float v, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
 // max / sum over the wave of a value that is uniform over groups of 4 lanes, in the order of the
 // xor butterfly over offsets 4, 8, 16, 32 (the last two levels combine the four 16-lane rows as
 // (r0 . r1) . (r2 . r3), which is what every lane of that butterfly ends with)

@@ -66,3 +66,29 @@ def test_a_row_of_linear_does_not_depend_on_the_others(N, K):
     ref = x.double() @ w.double().T
     bound = (x.abs().double() @ w.abs().double().T) * 2.0 ** -15 + 1e-7
     assert bool(((one.double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("N,K", [(16, 16), (48, 64), (64, 80), (256, 256), (256, 688), (2048, 1024), (64, 8192)])
+def test_a_row_of_an_fp32_product_does_not_depend_on_the_others(N, K):
+    """One row goes through the vector units, 2 .. 4 and 5 .. 8 rows through the matrix units: the same bits, also of numbers whose products are
+    subnormal or near the top of the range (fewer steps than waves, a last step of 16 k, every number of steps per wave below its ring)."""
+    import torch
+    from paper_2404_18911_amd import binding as B
+    L = B.lib()
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    s = torch.cuda.current_stream().cuda_stream
+    w = torch.randn(N, K, generator=g, device="cuda") * 0.05
+    work = torch.empty(L.kg_op_work_bytes(K), dtype=torch.uint8, device="cuda")
+
+    def linear(rows):
+        y = torch.full((rows.shape[0], N), float("nan"), device="cuda")
+        assert L.kg_op_linear(0, w.data_ptr(), N, K, rows.data_ptr(), rows.shape[0], y.data_ptr(), work.data_ptr(), s) == B.KG_OK
+        return y
+    for scale in (1.0, 1e-38, 1e30):
+        x = torch.randn(8, K, generator=g, device="cuda") * scale
+        one = torch.cat([linear(x[m:m + 1]) for m in range(8)])
+        for M in range(2, 9):
+            assert torch.equal(linear(x[:M]), one[:M]), (scale, M)
+        ref = x.double() @ w.double().T
+        bound = (x.abs().double() @ w.abs().double().T) * (K + 8) * 2.0 ** -24 + K * 1.5e-45       # K + 8 roundings of a sum, and of subnormal products
+        assert bool(((one.double() - ref).abs() <= bound).all()), scale
