@@ -2133,6 +2133,31 @@ __device__ __forceinline__ float wave_max_q4(float v)
     v = fmaxf(v, row_mirror(v));
     return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
+// values of 16 lanes (a row), of the whole wave; every lane gets the result
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, quad_x1(v));
+    v = fmaxf(v, quad_x2(v));
+    v = fmaxf(v, half_mirror(v));
+    return fmaxf(v, row_mirror(v));
+}
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += quad_x1(v);
+    v += quad_x2(v);
+    v += half_mirror(v);
+    return v + row_mirror(v);
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = row_max(v);
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v = row_sum(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
 __device__ __forceinline__ float wave_sum_q4(float v)
 {
     v += half_mirror(v);
@@ -3017,25 +3042,45 @@ __device__ int block_inverse_cdf(const float *za, const float *zb, F w, int V, f
     return lastpos;
 }
 
-// Block-wide inverse-CDF draw from softmax(z / T) through the LM head's per-tile statistics (1024
-// threads): tile i (16 consecutive tokens) weighs s_i exp(m_i - mx), so the tile that holds u * total is
-// found from n_tiles numbers, and only its 16 logits are looked at.  Walks ascending token indices;
+// The LM head's statistics of a row's tiles (16 consecutive tokens each), tile i at hs[4 i] = (max of z / T, sum exp(z / T - max), index of
+// the max), shared out over 1024 threads in ascending stretches.  Up to 8 tiles of a thread are kept in registers, all requested
+// together (vocabularies of up to 131072 tokens); those of a longer stretch are read again each time.
+struct TileStats {
+    const float *hs;
+    int i0, n;              // this thread's tiles
+    float4 v[8];
+    __device__ __forceinline__ TileStats(const float *hs_, int n_tiles)
+    {
+        hs = hs_;
+        const int chunk = (n_tiles + 1023) >> 10, t = threadIdx.x;
+        i0 = min(n_tiles, t * chunk);
+        n = min(n_tiles, i0 + chunk) - i0;
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            if (k < chunk) v[k] = *(const float4 *)(hs + (size_t)min(i0 + k, n_tiles - 1) * 4);
+    }
+    template <class F> __device__ __forceinline__ void each(F f) const      // f(statistics, tile)
+    {
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            if (k < n) f(v[k], i0 + k);
+        for (int k = 8; k < n; k++) f(*(const float4 *)(hs + (size_t)(i0 + k) * 4), i0 + k);
+    }
+};
+// weight of a tile under the row's maximum mx of z / T
+__device__ __forceinline__ float tile_weight(const float4 &h, float mx) { return h.x == -INFINITY ? 0.f : h.y * __expf(h.x - mx); }
+
+// Block-wide inverse-CDF draw from softmax(z / T) through the tile statistics (1024 threads): the tile that holds u * total is
+// found from the tiles' weights, and only its 16 logits are looked at.  Walks ascending token indices;
 // sums in double.  Returns -1 when the total is not positive.  All threads must call it; all get the result.
-// hs: statistics of the row, tile i at hs[4 i] = (max of z / T, sum exp(z / T - max), ..).
-__device__ int tile_inverse_cdf(const float *hs, int n_tiles, const float *z, float inv_temp, float mx, float u)
+__device__ int tile_inverse_cdf(const TileStats &ts, const float *z, float inv_temp, float mx, float u)
 {
     __shared__ double wsum[16];
     __shared__ int cand[16];
     __shared__ int found;
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int chunk = (n_tiles + 1023) >> 10;
-    const int i0 = min(n_tiles, t * chunk), i1 = min(n_tiles, i0 + chunk);
-    auto weight = [&](int i) {
-        const float2 ms = *(const float2 *)(hs + (size_t)i * 4);
-        return (double)(ms.y * __expf(ms.x - mx));
-    };
     double local = 0.0;
-    for (int i = i0; i < i1; i++) local += weight(i);
+    ts.each([&](const float4 &h, int) { local += (double)tile_weight(h, mx); });
     double incl = local;                                   // inclusive scan inside the wave
     for (int o = 1; o < 64; o <<= 1) {
         double v = __shfl_up(incl, o);
@@ -3053,29 +3098,37 @@ __device__ int tile_inverse_cdf(const float *hs, int n_tiles, const float *z, fl
     const double thr = (double)u * total;                  // u < 1: below the total
     const double excl = base + incl - local;
     // the stretch that holds the threshold: the last one that starts at or below it
-    const unsigned long long starts_below = __ballot(i0 < i1 && excl <= thr);
+    const unsigned long long starts_below = __ballot(ts.n > 0 && excl <= thr);
     if (lane == 0) cand[wave] = starts_below ? wave * 64 + 63 - __builtin_clzll(starts_below) : -1;
     __syncthreads();
     int owner = -1;
     for (int k = 0; k < 16; k++) owner = max(owner, cand[k]);
     if (t == owner) {
-        double acc = excl;
+        double acc = excl, last = 0.0;
         int tile = -1;
-        for (int i = i0; i < i1; i++) {
-            const double wt = weight(i);
-            if (wt > 0.0) {
-                if (tile >= 0) acc += weight(tile);        // pass the tile before: the threshold lies beyond it
-                tile = i;
-                if (acc + wt > thr) break;
-            }
-        }
+        bool hit = false;
+        ts.each([&](const float4 &h, int i) {
+            const double wt = (double)tile_weight(h, mx);
+            if (hit || !(wt > 0.0)) return;
+            acc += last;                                   // pass the tile before: the threshold lies beyond it
+            last = wt;
+            tile = i;
+            hit = acc + wt > thr;
+        });
         // (a stretch whose sums fall short of the threshold by rounding ends at its last tile with weight)
         if (tile >= 0) {
             // inside the tile the 16 weights are recomputed; if their sum misses the tile's own by rounding,
             // the tile's last token with weight is the draw
+            float zv[16];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const float4 q = *(const float4 *)(z + tile * 16 + 4 * j);
+                zv[4 * j] = q.x; zv[4 * j + 1] = q.y; zv[4 * j + 2] = q.z; zv[4 * j + 3] = q.w;
+            }
             int f = -1, lastw = -1;
+#pragma unroll
             for (int j = 0; j < 16; j++) {
-                const float wj = __expf(z[tile * 16 + j] * inv_temp - mx);
+                const float wj = __expf(zv[j] * inv_temp - mx);
                 acc += (double)wj;
                 if (wj > 0.f) lastw = tile * 16 + j;
                 if (f < 0 && acc > thr) f = tile * 16 + j;
@@ -3095,8 +3148,7 @@ __device__ __forceinline__ void post(unsigned long long *slot, unsigned seq, uin
 }
 
 // emb.table: row 0's token is looked up at once and becomes the first activation of the pass that follows, as pack_rows_kernel
-// makes it from a token in device memory: 0.5 us more here at 256 features and 3.3 .. 3.6 at 4096 (arg-max 5.2 -> 8.5 us, draw 8.9 -> 12.6), for a
-// launch less (2.7 and 4.6 us) and the gap before it.
+// makes it from a token in device memory: 1 us more here at 4096 features, for a launch less (2.7 and 4.6 us) and the gap before it.
 struct EmbedOut {
     const void *table;      // [V][d], bfloat16 or fp32; null: no lookup
     int bf, d;
@@ -3104,16 +3156,48 @@ struct EmbedOut {
     float *xout, *ssq;
     void *act;
 };
+// gain: this thread's features 4 t .. 4 t + 3 and those 4096 further on
 template <bool BF>
-__device__ __forceinline__ void embed_row(const EmbedOut &o, int tok, int V, float *sq)
+__device__ __forceinline__ void embed_row(const EmbedOut &o, int tok, int V, const float4 (&gain)[2], float *sq)
 {
     const int id = min(max(tok, 0), V - 1);
-    for (int n = threadIdx.x; n < o.d; n += 1024) {
+    float v[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; j++) {               // d <= 8192
+        const int n = 4 * threadIdx.x + 4096 * j;
+        if (n >= o.d) continue;
         const size_t idx = (size_t)id * o.d + n;
-        const float v = BF ? bf2f(((const uint16_t *)o.table)[idx]) : ((const float *)o.table)[idx];
-        o.xout[n] = v;
-        store_act<BF>(o.act, o.d, 0, n, v * o.gain[n]);
-        sq[n + (n >> 4)] = v * v;
+        if (BF) {
+            const uint2 q = *(const uint2 *)((const uint16_t *)o.table + idx);
+            v[j][0] = __uint_as_float(q.x << 16); v[j][1] = __uint_as_float(q.x & 0xFFFF0000u);
+            v[j][2] = __uint_as_float(q.y << 16); v[j][3] = __uint_as_float(q.y & 0xFFFF0000u);
+        } else {
+            const float4 q = *(const float4 *)((const float *)o.table + idx);
+            v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+        const int n = 4 * threadIdx.x + 4096 * j;
+        if (n >= o.d) continue;
+        *(float4 *)(o.xout + n) = make_float4(v[j][0], v[j][1], v[j][2], v[j][3]);
+        const float g[4] = {gain[j].x, gain[j].y, gain[j].z, gain[j].w};
+        if (BF) {                               // as store_act, four features at a time
+            uint16_t hi[4], lo[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float x = rounded(v[j][i] * g[i]);
+                hi[i] = f2bf(x);
+                lo[i] = f2bf(x - bf2f(hi[i]));
+            }
+            uint16_t *p = (uint16_t *)o.act + (size_t)(n >> 5) * 512 + ((n >> 3) & 3) * 8 + (n & 7);
+            *(uint2 *)p = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+            *(uint2 *)(p + 32) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+        } else {
+            *(float4 *)((float *)o.act + n) = make_float4(v[j][0] * g[0], v[j][1] * g[1], v[j][2] * g[2], v[j][3] * g[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) sq[n + i + (n >> 4)] = v[j][i] * v[j][i];
     }
     __syncthreads();
     for (int rt = threadIdx.x; rt < o.d >> 4; rt += 1024) {
@@ -3129,65 +3213,59 @@ __device__ __forceinline__ void embed_row(const EmbedOut &o, int tok, int V, flo
 // given purpose: 0 a draft token, 2 a first / plain token).
 // stat_out[row] = (max of z/T, sum exp(z/T - max)).
 // host[row], host[KG_ROWS + row]: the result words with the row's token and the bits of its top-1 probability.
+// One workgroup that waits: every load that does not depend on another is issued at the start, the statistics are read once, the
+// maximum is found before any sum is taken (no rescaling on the way), and the last step over 16 waves is taken by 16 lanes.  us at
+// 32000 tokens, statistics read twice, both reductions pairwise with the last step by one thread, the look-up feature by feature / here:
+// seven verification rows 5.9 / 4.0, a draft with its look-up 8.4 / 5.0, with a draw 12.6 / 7.9; 1024 tokens 4.8 / 3.3.
 __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, int n_tiles, const float *logits,
                                                           int V, float inv_temp, int mode, USrc us, int purpose,
                                                           unsigned long long *host, unsigned seq, float *stat_out, EmbedOut emb)
 {
+    constexpr int NONE = 0x7FFFFFFF;
     __shared__ float bm[16], bs[16], sq[8192 + 512];      // d <= 8192; one float of padding per 16: embed_row's sums read without conflicts
     __shared__ int bi[16];
-    __shared__ float fin[2];
-    __shared__ int fin_i;
     const int m = blockIdx.x, t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    float best = -INFINITY, sum = 0.f;
-    int idx = 0x7FFFFFFF;
-    for (int i = t; i < n_tiles; i += 1024) {
-        const float4 hs = *(const float4 *)(hstat + ((size_t)m * n_tiles + i) * 4);
-        float mx = hs.x, sm = hs.y;
-        int id = __float_as_int(hs.z);
-        if (mx > best) { sum = sum * __expf(best - mx) + sm; best = mx; idx = id; }
-        else { sum += sm * __expf(mx - best); if (mx == best && id < idx) idx = id; }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-        float om = __shfl_xor(best, o), os = __shfl_xor(sum, o);
-        int oi = __shfl_xor(idx, o);
-        float nm = fmaxf(best, om);
-        float a = (best == -INFINITY) ? 0.f : sum * __expf(best - nm);
-        float b = (om == -INFINITY) ? 0.f : os * __expf(om - nm);
-        if (om > best || (om == best && oi < idx)) idx = oi;
-        best = nm;
-        sum = a + b;
-    }
-    if (lane == 0) { bm[wave] = best; bs[wave] = sum; bi[wave] = idx; }
-    __syncthreads();
-    if (t == 0) {
-        best = bm[0]; sum = bs[0]; idx = bi[0];
-        for (int w = 1; w < 16; w++) {
-            float nm = fmaxf(best, bm[w]);
-            float a = (best == -INFINITY) ? 0.f : sum * __expf(best - nm);
-            float b = (bm[w] == -INFINITY) ? 0.f : bs[w] * __expf(bm[w] - nm);
-            if (bm[w] > best || (bm[w] == best && bi[w] < idx)) idx = bi[w];
-            best = nm;
-            sum = a + b;
-        }
-        fin[0] = best; fin[1] = sum; fin_i = idx;
-        post(host + KG_ROWS + m, seq, __float_as_uint(1.f / sum));
-        stat_out[2 * m] = best;
-        stat_out[2 * m + 1] = sum;
-        if (mode == 0) post(host + m, seq, (uint32_t)idx);
-    }
+    const TileStats ts(hstat + (size_t)m * n_tiles * 4, n_tiles);
     const bool look_up = emb.table && m == 0;
-    if (mode == 0 && !look_up) return;
+    float4 gain[2];
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+        if (look_up && 4 * t + 4096 * j < emb.d) gain[j] = *(const float4 *)(emb.gain + 4 * t + 4096 * j);
+    const float u = mode != 0 ? row_uniform(us, m, purpose, 0) : 0.f;
+    float best = -INFINITY;
+    int idx = NONE;
+    ts.each([&](const float4 &h, int) {
+        if (h.x > best) { best = h.x; idx = __float_as_int(h.z); }
+    });
+    // stretches, waves and lanes ascend, so the first of equal maxima has the lowest index
+    const float wm = wave_max(best);
+    const unsigned long long have = __ballot(best == wm && idx != NONE);
+    const int wi = have ? __builtin_amdgcn_readlane(idx, __builtin_ctzll(have)) : NONE;
+    if (lane == 0) { bm[wave] = wm; bi[wave] = wi; }
     __syncthreads();
-    int tok = fin_i;
+    const float wv = bm[lane & 15], mx = row_max(wv);
+    const unsigned have16 = (unsigned)__ballot(wv == mx && bi[lane & 15] != NONE) & 0xFFFFu;
+    int tok = have16 ? bi[__builtin_ctz(have16)] : NONE;
+    float part = 0.f;
+    ts.each([&](const float4 &h, int) { part += tile_weight(h, mx); });
+    part = wave_sum(part);
+    if (lane == 0) bs[wave] = part;
     if (mode != 0) {
-        const int drawn = tile_inverse_cdf(hstat + (size_t)m * n_tiles * 4, n_tiles, logits + (size_t)m * V, inv_temp, fin[0],
-                                           row_uniform(us, m, purpose, 0));
+        const int drawn = tile_inverse_cdf(ts, logits + (size_t)m * V, inv_temp, mx, u);
         if (drawn >= 0) tok = drawn;
-        if (t == 0) post(host + m, seq, (uint32_t)tok);
+    } else {
+        __syncthreads();
+    }
+    const float sum = row_sum(bs[lane & 15]);
+    if (t == 0) {
+        post(host + KG_ROWS + m, seq, __float_as_uint(1.f / sum));
+        post(host + m, seq, (uint32_t)tok);
+        stat_out[2 * m] = mx;
+        stat_out[2 * m + 1] = sum;
     }
     if (!look_up) return;
-    if (emb.bf) embed_row<true>(emb, tok, V, sq);
-    else embed_row<false>(emb, tok, V, sq);
+    if (emb.bf) embed_row<true>(emb, tok, V, gain, sq);
+    else embed_row<false>(emb, tok, V, gain, sq);
 }
 
 // Speculative-sampling acceptance of one round (Section 3: the first rejected draft discards the
@@ -3237,7 +3315,7 @@ __global__ __launch_bounds__(1024) void accept_sample_kernel(const float *zt, co
         __syncthreads();
     }
     // all drafts kept (or an empty residual): the bonus token from p_n, through the target head's tile statistics
-    if (tok < 0) tok = tile_inverse_cdf(hstat_t + (size_t)n * (V / 16) * 4, V / 16, zp, inv_temp, pm, row_uniform(us, n, 2, 1));
+    if (tok < 0) tok = tile_inverse_cdf(TileStats(hstat_t + (size_t)n * (V / 16) * 4, V / 16), zp, inv_temp, pm, row_uniform(us, n, 2, 1));
     if (t == 0) { post(host, seq, (uint32_t)n); post(host + 1, seq, (uint32_t)tok); }
 }
 

@@ -31,3 +31,41 @@ def test_verification_rows_through_the_head_equal_decoded_rows(vocab):
             np.testing.assert_array_equal(rows[r], one)
             assert tokens[r] == int(np.argmax(one))
     kg.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("vocab", [16, 1024, 16384, 16400, 131072, 131088, 147472])
+def test_choices_draws_and_confidences_follow_the_logits(vocab, dtype):
+    """From one weight tile to more than eight per thread of the final reduction (which keeps eight in registers): the arg-max, the token that
+    a uniform number draws and the confidence against the row's logits in 64 bits.  A draw may fall to a neighbour where the number lies within
+    1e-5 of a boundary (float32 tile sums of 16 exponentials: 2^-20)."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = I.ModelShape("vocab", 2, 64, 1, 64, 64, vocab, 1, dtype)
+    W = I.gen_weights(shape, seed=9, alpha=1.0, head_scale=8.0)
+    kg = P.load_model(shape, W, 48, kv_page_tokens=16)
+    prompt = [int(t) for t in I.gen_prompt(vocab, 10, seed=3)]
+
+    def parts(z):
+        w = np.exp(z.astype(np.float64) - z.max())
+        return np.cumsum(w), w.sum()
+
+    def drawn(z, u, tok):
+        c, total = parts(z)
+        assert (c[tok - 1] if tok else 0.0) - 1e-5 * total <= u * total <= c[tok] + 1e-5 * total, (u, tok)
+    greedy, _ = B.make_params(eta=0.0)
+    tok = kg.prefill(greedy, prompt)
+    assert tok == int(np.argmax(kg.read_logits(1, 0)))
+    for i in range(3):
+        t, conf, _ = kg.draft_step(greedy)
+        z = kg.read_logits(0, i)
+        assert t == int(np.argmax(z))
+        assert abs(conf * parts(z)[1] - 1.0) <= 1e-5
+    for u in (0.0, 0.03, 0.5, 0.97, float(np.float32(1.0 - 2.0 ** -24))):
+        table = np.full((48, 3), u, dtype=np.float32)
+        p, keep = B.make_params(mode=1, temperature=1.0, eta=0.0, uniforms=table)
+        tok = kg.prefill(p, prompt)
+        drawn(kg.read_logits(1, 0), u, tok)
+        t, _, _ = kg.draft_step(p)
+        drawn(kg.read_logits(0, 0), u, t)
+    kg.close()
