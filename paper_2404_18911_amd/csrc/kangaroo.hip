@@ -1904,29 +1904,41 @@ static void tr_gemm_vec_flags(TrGemm &g)
     }
 }
 
-// tiles of C, their order, and the launch; z = slices of k or batch members
-static void launch_tr_gemm(TrGemm &g, int z, hipStream_t s)
+// tiles of C, their order, and the launch; z = slices of k.  small: tiles of 64 x 128, one product per batch member
+static void launch_tr_gemm(TrGemm &g, int z, hipStream_t s, bool small = false)
 {
-    g.gm = (g.M + TRG_M - 1) / TRG_M; g.gn = (g.N + TRG_N - 1) / TRG_N;
-    g.swz = g.gn % 8 == 0 || g.gn >= 16;        // else columns of C would leave XCDs idle
+    const int tm = small ? TRG_SM : TRG_M, tn = small ? TRG_SN : TRG_N;
+    g.gm = (g.M + tm - 1) / tm; g.gn = (g.N + tn - 1) / tn;
+    g.swz = !small && (g.gn % 8 == 0 || g.gn >= 16);        // else columns of C would leave XCDs idle
     int tiles = g.swz ? 8 * g.gm * ((g.gn + 7) / 8) : g.gm * g.gn;
     if (g.causal) {
         tiles = 0;
-        for (int m = 0; m < g.gm; m++) tiles += trg_causal_tiles(m, g.gn);
+        for (int m = 0; m < g.gm; m++) tiles += trg_causal_tiles(m, g.gn, tm, tn);
     }
-    const dim3 grid(tiles, 1, z);
+    const dim3 grid(small ? tiles * g.batch : tiles, 1, z);
     const bool ka = g.sak == 1, kb = g.b_mode == 0 ? g.sbk == 1 : g.b_mode == 1, guard = !g.a_vec || (g.b_mode == 0 && !g.b_vec);
 #define TR_GEMM_LAUNCH(...) hipLaunchKernelGGL((tr_gemm_kernel<__VA_ARGS__>), grid, dim3(512), 0, s, g)
+#define TR_GEMM_FORMS(LAUNCH, ...) \
+    if (guard) { \
+        if (ka) { if (kb) LAUNCH(__VA_ARGS__ true, true, true); else LAUNCH(__VA_ARGS__ true, false, true); } \
+        else { if (kb) LAUNCH(__VA_ARGS__ false, true, true); else LAUNCH(__VA_ARGS__ false, false, true); } \
+    } else { \
+        if (ka) { if (kb) LAUNCH(__VA_ARGS__ true, true, false); else LAUNCH(__VA_ARGS__ true, false, false); } \
+        else { if (kb) LAUNCH(__VA_ARGS__ false, true, false); else LAUNCH(__VA_ARGS__ false, false, false); } \
+    }
+#define TR_SMALL_LAUNCH(...) hipLaunchKernelGGL((tr_gemm_small_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g)
+#define TR_GEMM3_LAUNCH(...) TR_GEMM_LAUNCH(3, __VA_ARGS__)
     if (g.b_mode) {             // against bf16 tiles: the callers' A are aligned rows
         if (kb) TR_GEMM_LAUNCH(1, true, true, false);
         else TR_GEMM_LAUNCH(1, true, false, false);
-    } else if (guard) {
-        if (ka) { if (kb) TR_GEMM_LAUNCH(3, true, true, true); else TR_GEMM_LAUNCH(3, true, false, true); }
-        else { if (kb) TR_GEMM_LAUNCH(3, false, true, true); else TR_GEMM_LAUNCH(3, false, false, true); }
+    } else if (small) {
+        TR_GEMM_FORMS(TR_SMALL_LAUNCH)
     } else {
-        if (ka) { if (kb) TR_GEMM_LAUNCH(3, true, true, false); else TR_GEMM_LAUNCH(3, true, false, false); }
-        else { if (kb) TR_GEMM_LAUNCH(3, false, true, false); else TR_GEMM_LAUNCH(3, false, false, false); }
+        TR_GEMM_FORMS(TR_GEMM3_LAUNCH)
     }
+#undef TR_GEMM3_LAUNCH
+#undef TR_SMALL_LAUNCH
+#undef TR_GEMM_FORMS
 #undef TR_GEMM_LAUNCH
 }
 
@@ -1934,7 +1946,7 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
                    long ldc, int M, int N, int K, int accumulate)
 {
     TrGemm g;
-    g.causal = 0;
+    g.causal = g.k_tri = 0;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = b_mode; g.b_KS = x->KSd;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
     g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
@@ -1961,18 +1973,17 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
 
 // One product per attention head in a single launch: head h reads A + h * bsa, B + h * bsb and writes C + h * bsc.
 static int tr_gemm_heads(kg_ctx *x, const float *A, long sam, long sak, long bsa, const float *B, long sbk, long sbn, long bsb,
-                         float *C, long ldc, long bsc, int M, int N, int K, int heads, bool causal = false)
+                         float *C, long ldc, long bsc, int M, int N, int K, int heads, bool causal, int k_tri)
 {
     TrGemm g;
-    g.causal = causal;
+    g.causal = causal; g.k_tri = k_tri;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = 0;
     g.batch = heads; g.bsa = bsa; g.bsb = bsb; g.bsc = bsc;
     g.k_chunk = (K + TRG_K - 1) / TRG_K * TRG_K; g.part = nullptr;
     tr_gemm_vec_flags(g);
-    if (heads == 1) { g.batch = 1; }
     ProfScope ps(x, 4, 2.0 * M * (double)N * K * heads);
-    launch_tr_gemm(g, heads, x->stream);
+    launch_tr_gemm(g, 1, x->stream, true);
     return check_launch(x, "train_gemm_heads");
 }
 
@@ -2137,12 +2148,12 @@ static int train_graph(kg_ctx *x, int n, double *loss)
             // causal attention, one product per head: S = Q.K^T, P = softmax(S / sqrt(hd)), O = P.V
             const float *Q = f(t.QKV), *K = f(t.QKV) + d, *Vv = f(t.QKV) + 2 * d;
             const long TT = (long)n * n;
-            // (1000 positions, without the tiles above the diagonal: 84 -> 72 us, and dP below 99 -> 76)
-            KGCHK(tr_gemm_heads(x, Q, 3 * d, 1, hd, K, 1, 3 * d, hd, f(t.Pm), n, TT, n, n, hd, H, true));
+            // (1000 positions, without the tiles above the diagonal and in tiles of 64 x 128: 84 -> 62 us, and dP below 99 -> 65)
+            KGCHK(tr_gemm_heads(x, Q, 3 * d, 1, hd, K, 1, 3 * d, hd, f(t.Pm), n, TT, n, n, hd, H, true, 0));
             other();
             hipLaunchKernelGGL(tr_softmax_causal_kernel, dim3(n, H), dim3(256), 0, x->stream, f(t.Pm), n, 1.f / sqrtf((float)hd));
             KGCHK(check_launch(x, "train_softmax"));
-            KGCHK(tr_gemm_heads(x, f(t.Pm), n, 1, TT, Vv, 3 * d, 1, hd, f(t.O), d, hd, n, hd, n, H));
+            KGCHK(tr_gemm_heads(x, f(t.Pm), n, 1, TT, Vv, 3 * d, 1, hd, f(t.O), d, hd, n, hd, n, H, false, 1));
         }
         KGCHK(tr_fwd(x, f(t.O), P + o_b, f(t.H), n, d, d, 1));
         if (kind == KG_ADAPTER_LAYER) {
@@ -2206,14 +2217,14 @@ static int train_graph(kg_ctx *x, int n, double *loss)
             // dP = dO.V^T, dV = P^T.dO, dS = P (dP - rowsum(dP P)) / sqrt(hd), dQ = dS.K, dK = dS^T.Q, per head
             const float *Q = f(t.QKV), *K = f(t.QKV) + d, *Vv = f(t.QKV) + 2 * d;
             const long TT = (long)n * n;
-            KGCHK(tr_gemm_heads(x, f(t.dO), d, 1, hd, Vv, 1, 3 * d, hd, f(t.dS), n, TT, n, n, hd, H, true));
-            KGCHK(tr_gemm_heads(x, f(t.Pm), 1, n, TT, f(t.dO), d, 1, hd, f(t.dQKV) + 2 * d, 3 * d, hd, n, hd, n, H));
+            KGCHK(tr_gemm_heads(x, f(t.dO), d, 1, hd, Vv, 1, 3 * d, hd, f(t.dS), n, TT, n, n, hd, H, true, 0));
+            KGCHK(tr_gemm_heads(x, f(t.Pm), 1, n, TT, f(t.dO), d, 1, hd, f(t.dQKV) + 2 * d, 3 * d, hd, n, hd, n, H, false, 2));
             other();
             hipLaunchKernelGGL(tr_dsoftmax_kernel, dim3(n, H), dim3(256), 0, x->stream, (const float *)f(t.Pm), f(t.dS), n,
                                1.f / sqrtf((float)hd));
             KGCHK(check_launch(x, "train_dsoftmax"));
-            KGCHK(tr_gemm_heads(x, f(t.dS), n, 1, TT, K, 3 * d, 1, hd, f(t.dQKV), 3 * d, hd, n, hd, n, H));
-            KGCHK(tr_gemm_heads(x, f(t.dS), 1, n, TT, Q, 3 * d, 1, hd, f(t.dQKV) + d, 3 * d, hd, n, hd, n, H));
+            KGCHK(tr_gemm_heads(x, f(t.dS), n, 1, TT, K, 3 * d, 1, hd, f(t.dQKV), 3 * d, hd, n, hd, n, H, false, 1));
+            KGCHK(tr_gemm_heads(x, f(t.dS), 1, n, TT, Q, 3 * d, 1, hd, f(t.dQKV) + d, 3 * d, hd, n, hd, n, H, false, 2));
         }
         other();
         hipLaunchKernelGGL(tr_rope_kernel, dim3((unsigned)((nrope + 255) / 256)), dim3(256), 0, x->stream, f(t.dQKV), n, d, hd,
@@ -2325,7 +2336,7 @@ int kg_op_gemm_f32(const float *A, long sam, long sak, const float *B, long sbk,
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn; g.b_mode = 0; g.b_KS = 0;
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
     g.k_chunk = (K + TRG_K - 1) / TRG_K * TRG_K; g.part = nullptr;
-    g.batch = 1; g.bsa = g.bsb = g.bsc = 0; g.causal = 0;
+    g.batch = 1; g.bsa = g.bsb = g.bsc = 0; g.causal = g.k_tri = 0;
     tr_gemm_vec_flags(g);
     launch_tr_gemm(g, 1, (hipStream_t)hip_stream);
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;

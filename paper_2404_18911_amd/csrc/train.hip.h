@@ -68,6 +68,7 @@ struct TrGemm {
     long bsa, bsb, bsc; // element offsets of A, B (b_mode 0) and C per batch index
     int gm, gn, swz;    // tiles of C; swz: see the tile order in the kernel
     int causal;         // C[m][n] is needed for n <= m only: the launch holds the tiles that reach the diagonal (20 of 32 at 1000 positions)
+    int k_tri;          // 1: A(m, k) is zero for k > m, k beyond a tile's last row is left out; 2: for k < m, k before its first row
 };
 
 __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
@@ -76,8 +77,10 @@ __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
 }
 
 #define TRG_K 32            // k per step
-#define TRG_M 128           // tile of C
+#define TRG_M 128           // tile of C, 8 waves
 #define TRG_N 256
+#define TRG_SM 64           // the smaller tile, 4 waves
+#define TRG_SN 128
 #define TRG_SCALE 0x1p24f   // of the fp32 operands before they are split
 
 // Where the 8 numbers k = 8 c .. 8 c + 7 of row r lie in a plane (in elements): rows of 64 bytes, the rows of a 4 x 4
@@ -104,12 +107,13 @@ __device__ __forceinline__ void tr_split2(float a, float b, uint32_t (&o)[3])
     }
 }
 
-// One fp32 operand of a ROWS x 32 block (rows m or n, k): the ROWS / 16 numbers each of 512 threads fetches and how
-// it stores them.  KC (contiguous along k): 8 consecutive k of one row (ROWS = 128) or two rows (256).
-// Else 4 consecutive rows x 2 (ROWS = 128) or 4 consecutive k, transposed on the way to LDS.
-template <int ROWS, bool KC>
+// One fp32 operand of a ROWS x 32 block (rows m or n, k): the 8 or 16 numbers each of NTH threads fetches and how
+// it stores them.  KC (contiguous along k): 8 consecutive k of one row or of two.
+// Else 4 consecutive rows x 2 or 4 consecutive k, transposed on the way to LDS.
+template <int ROWS, bool KC, int NTH>
 struct TrOperand {
-    static constexpr int NV = ROWS / 16, NK = ROWS / 64;     // numbers per thread; k per thread when transposing
+    static constexpr int NV = ROWS * TRG_K / NTH, NK = NV / 4;     // numbers per thread; k per thread when transposing
+    static_assert(NV == 8 || NV == 16, "numbers per thread");
     static constexpr int KT = TRG_K / NK;                    // threads along k when transposing
     const float *p;         // element (row0, k) of the block that is fetched next
     long s_row, s_k;
@@ -121,7 +125,7 @@ struct TrOperand {
         p = p_; s_row = s_row_; s_k = s_k_; rows = rows_;
         if constexpr (KC) {
 #pragma unroll
-            for (int i = 0; i < NV / 8; i++) q[i] = p + (size_t)min(trg_item_row((t >> 2) + 128 * i), rows - 1) * s_row + (size_t)(t & 3) * 8;
+            for (int i = 0; i < NV / 8; i++) q[i] = p + (size_t)min(trg_item_row((t >> 2) + NTH / 4 * i), rows - 1) * s_row + (size_t)(t & 3) * 8;
         } else {
             const int r = (t / KT) * 4;
             q[0] = p + (r < rows ? r : 0) + (size_t)(t % KT) * NK * s_k;
@@ -156,7 +160,7 @@ struct TrOperand {
             const int kq = (t & 3) * 8;
 #pragma unroll
             for (int i = 0; i < NV / 8; i++) {
-                const int r = trg_item_row((t >> 2) + 128 * i);
+                const int r = trg_item_row((t >> 2) + NTH / 4 * i);
                 const float *e = p + (size_t)r * s_row + kq;
 #pragma unroll
                 for (int j = 0; j < 8; j++) v[8 * i + j] = (r < rows && k0 + kq + j < k_hi) ? e[j] : 0.f;
@@ -183,7 +187,7 @@ struct TrOperand {
         if constexpr (KC) {
 #pragma unroll
             for (int i = 0; i < NV / 8; i++) {
-                const int at = trg_at(trg_item_row((t >> 2) + 128 * i), t & 3);
+                const int at = trg_at(trg_item_row((t >> 2) + NTH / 4 * i), t & 3);
                 u32x4_t o[3];
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
@@ -218,31 +222,34 @@ __device__ __forceinline__ float tr_gemm_b(const TrGemm &g, size_t bob, int k, i
     return bf2f(((const uint16_t *)g.B)[g.b_mode == 1 ? packed_u16_index(n, k, g.b_KS) : packed_u16_index(k, n, g.b_KS)]);
 }
 
-__device__ __forceinline__ void tr_zero(f32x16_t (&c)[2][2])
+template <int MI>
+__device__ __forceinline__ void tr_zero(f32x16_t (&c)[MI][2])
 {
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+    for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int r = 0; r < 16; r++) c[i][j][r] = 0.f;
 }
 
-// A wave's 64 x 64 of C at (m0, n0) by the fp32 matrix instruction (32x32x2), operands straight from memory: what the
+// A wave's 32 MI x 64 of C at (m0, n0) by the fp32 matrix instruction (32x32x2), operands straight from memory: what the
 // products are by definition, for any fp32 numbers.  Of eight k a lane takes four consecutive ones of its row and
 // of its column, lanes 0..31 the first four.
+template <int MI>
 __device__ __forceinline__ void tr_gemm_plain(const TrGemm &g, size_t boa, size_t bob, int m0, int n0, int k_lo, int k_hi, int lane,
-                                              f32x16_t (&acc)[2][2])
+                                              f32x16_t (&acc)[MI][2])
 {
     tr_zero(acc);
     if (m0 >= g.M || n0 >= g.N) return;
     const int fr = lane & 31, fc = lane >> 5;
-    const float *pa[2], *pb[2];
+    const float *pa[MI], *pb[2];
     int n[2];
+#pragma unroll
+    for (int i = 0; i < MI; i++) pa[i] = (const float *)g.A + boa + (size_t)min(m0 + 32 * i + fr, g.M - 1) * g.sam;
 #pragma unroll
     for (int i = 0; i < 2; i++) {                       // rows and columns beyond the last repeat it: they are not stored
         n[i] = min(n0 + 32 * i + fr, g.N - 1);
-        pa[i] = (const float *)g.A + boa + (size_t)min(m0 + 32 * i + fr, g.M - 1) * g.sam;
         pb[i] = (const float *)g.B + bob + (size_t)n[i] * g.sbn;
     }
     const bool va = g.a_vec && g.sak == 1, vb = g.b_vec && g.sbk == 1;
@@ -257,9 +264,9 @@ __device__ __forceinline__ void tr_gemm_plain(const TrGemm &g, size_t boa, size_
     };
     for (int k0 = k_lo; k0 < k_hi; k0 += 8) {
         const int k = k0 + 4 * fc;
-        float a[2][4], b[2][4];
+        float a[MI][4], b[2][4];
 #pragma unroll
-        for (int i = 0; i < 2; i++) load(a[i], pa[i], k, g.sak, va);
+        for (int i = 0; i < MI; i++) load(a[i], pa[i], k, g.sak, va);
 #pragma unroll
         for (int i = 0; i < 2; i++) {
             if (g.b_mode == 0) load(b[i], pb[i], k, g.sbk, vb);
@@ -270,17 +277,18 @@ __device__ __forceinline__ void tr_gemm_plain(const TrGemm &g, size_t boa, size_
 #pragma unroll
         for (int q = 0; q < 4; q++)
 #pragma unroll
-            for (int i = 0; i < 2; i++)
+            for (int i = 0; i < MI; i++)
 #pragma unroll
                 for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
     }
 }
 
 // accumulator register r of lane l: row 8 * (r / 4) + 4 * (l / 32) + r % 4, column l % 32
-__device__ __forceinline__ void tr_gemm_store(const TrGemm &g, size_t boc, int m0, int n0, bool split, int lane, const f32x16_t (&acc)[2][2])
+template <int MI>
+__device__ __forceinline__ void tr_gemm_store(const TrGemm &g, size_t boc, int m0, int n0, bool split, int lane, const f32x16_t (&acc)[MI][2])
 {
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+    for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < 2; j++) {
             const int n = n0 + 32 * j + (lane & 31);
@@ -300,45 +308,50 @@ __device__ __forceinline__ void tr_gemm_store(const TrGemm &g, size_t boc, int m
 }
 
 // tiles of row tm of C that hold an element with n <= m
-__host__ __device__ __forceinline__ int trg_causal_tiles(int tm, int gn)
+__host__ __device__ __forceinline__ int trg_causal_tiles(int tm, int gn, int tile_m, int tile_n)
 {
-    const int c = (tm * TRG_M + TRG_M - 1) / TRG_N + 1;
+    const int c = (tm * tile_m + tile_m - 1) / tile_n + 1;
     return c < gn ? c : gn;
 }
 
 // BP: bf16 parts of B (3: fp32 operand, 1: bf16 tiles); KA / KB: A / B contiguous along k (KB of tiles: b_mode 1);
-// GUARD: operands that cannot be fetched in aligned groups of four.
-template <int BP, bool KA, bool KB, bool GUARD>
+// GUARD: operands that cannot be fetched in aligned groups of four.  SMALL: tiles of 64 x 128 by 4 waves, two workgroups per compute unit.
+// (for the per-head products of the attention, 64 or 128 columns wide: a 128 x 256 tile is half empty there and one launch of 256 tiles takes
+// as long as its longest sum.  1000 positions, 32 heads of 128: P.V, dS.K 102 -> 55 us, P^T.dO, dS^T.Q 110 -> 62, with the k beyond the
+// diagonal left out; Q.K^T, dO.V^T 74 -> 62.)
+template <int BP, bool KA, bool KB, bool GUARD, bool SMALL>
 __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][3][TRG_M * TRG_K];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BP][TRG_N * TRG_K];
+    constexpr int TM = SMALL ? TRG_SM : TRG_M, TN = SMALL ? TRG_SN : TRG_N, NTH = SMALL ? 256 : 512, MI = TM / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][3][TM * TRG_K];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BP][TN * TRG_K];
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     // tile order: with swz the tiles of one column of C run one after another on one XCD (its L2 keeps that
     // part of B, usually the larger operand); used where the columns fill the XCDs
     int tm, tn;
-    if (g.causal) {
+    const int member = SMALL ? blockIdx.x % g.batch : 0, tile = SMALL ? blockIdx.x / g.batch : blockIdx.x;
+    if (SMALL && g.causal) {
         tm = 0;
-        tn = blockIdx.x;
-        for (int c; tn >= (c = trg_causal_tiles(tm, g.gn)); tm++) tn -= c;
-    } else if (g.swz) {
-        const int j = blockIdx.x >> 3;
+        tn = tile;
+        for (int c; tn >= (c = trg_causal_tiles(tm, g.gn, TM, TN)); tm++) tn -= c;
+    } else if (!SMALL && g.swz) {
+        const int j = tile >> 3;
         tm = j % g.gm;
-        tn = (j / g.gm) * 8 + (blockIdx.x & 7);
+        tn = (j / g.gm) * 8 + (tile & 7);
         if (tn >= g.gn) return;
     } else {
-        tm = blockIdx.x / g.gn;
-        tn = blockIdx.x % g.gn;
+        tm = tile / g.gn;
+        tn = tile % g.gn;
     }
-    const int m0 = tm * TRG_M, n0 = tn * TRG_N;
-    const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
-    const bool batched = g.batch > 1;
-    const bool split = !batched && gridDim.z > 1;
-    const int k_lo = batched ? 0 : blockIdx.z * g.k_chunk, k_hi = batched ? g.K : min(g.K, k_lo + g.k_chunk);
-    const size_t boa = batched ? (size_t)blockIdx.z * g.bsa : 0, bob = batched ? (size_t)blockIdx.z * g.bsb : 0,
-                 boc = batched ? (size_t)blockIdx.z * g.bsc : 0;
-    TrOperand<TRG_M, KA> oa;
-    TrOperand<TRG_N, KB> ob;
+    if (SMALL && g.k_tri == 1) tm = g.gm - 1 - tm;      // the longest sums first
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int wm = (wave & 1) * (TM / 2), wn = (wave >> 1) * 64;
+    const bool split = !SMALL && gridDim.z > 1;
+    const int k_lo = split ? blockIdx.z * g.k_chunk : SMALL && g.k_tri == 2 ? m0 : 0,
+              k_hi = split ? min(g.K, k_lo + g.k_chunk) : SMALL && g.k_tri == 1 ? min(g.K, m0 + TM) : g.K;
+    const size_t boa = (size_t)member * g.bsa, bob = (size_t)member * g.bsb, boc = (size_t)member * g.bsc;
+    TrOperand<TM, KA, NTH> oa;
+    TrOperand<TN, KB, NTH> ob;
     oa.init((const float *)g.A + boa + (size_t)m0 * g.sam + (size_t)k_lo * g.sak, g.sam, g.sak, g.M - m0, t);
     if constexpr (BP == 3) ob.init((const float *)g.B + bob + (size_t)n0 * g.sbn + (size_t)k_lo * g.sbk, g.sbn, g.sbk, g.N - n0, t);
     // numbers a thread has fetched: two sets, so that a fetch has more than a whole step to arrive
@@ -402,7 +415,7 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
         if constexpr (BP == 3) ob.stash(w.b, Bs[buf], t);
         else stash_tiles(w, Bs[buf][0]);
     };
-    f32x16_t acc[2][2], rest[2][2];                     // sums of the products of first parts, and of all others
+    f32x16_t acc[MI][2], rest[MI][2];                   // sums of the products of first parts, and of all others
     tr_zero(acc);
     tr_zero(rest);
     const int fr = lane & 31, fc = lane >> 5;           // operand layout of the 32x32x16 instruction: row, which 8 k
@@ -413,7 +426,7 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
 #pragma unroll
             for (int q = 0; q < BP; q++) b[j][q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&Bs[buf][q][trg_at(wn + 32 * j + fr, 2 * kk + fc)]);
 #pragma unroll
-        for (int i = 0; i < 2; i++) {
+        for (int i = 0; i < MI; i++) {
 #pragma unroll
             for (int q = 0; q < 3; q++) a[q] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t *)&As[buf][q][trg_at(wm + 32 * i + fr, 2 * kk + fc)]);
 #pragma unroll
@@ -457,7 +470,7 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
     // a number that is not finite once scaled and split leaves its whole row or column of sums without a finite value
     bool odd = false;
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+    for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -472,9 +485,11 @@ __device__ __forceinline__ void tr_gemm_body(const TrGemm &g)
     }
     tr_gemm_store(g, boc, m0 + wm, n0 + wn, split, lane, acc);
 }
-// (a bound of 256 registers: 8 waves fill a compute unit, whose LDS one workgroup takes anyway)
+// (a bound of 256 registers: 8 waves fill a compute unit, whose LDS one workgroup or two of the small ones take anyway)
 template <int BP, bool KA, bool KB, bool GUARD>
-__global__ __launch_bounds__(512, 2) void tr_gemm_kernel(const TrGemm g) { tr_gemm_body<BP, KA, KB, GUARD>(g); }
+__global__ __launch_bounds__(512, 2) void tr_gemm_kernel(const TrGemm g) { tr_gemm_body<BP, KA, KB, GUARD, false>(g); }
+template <bool KA, bool KB, bool GUARD>
+__global__ __launch_bounds__(256, 2) void tr_gemm_small_kernel(const TrGemm g) { tr_gemm_body<3, KA, KB, GUARD, true>(g); }
 
 // C[m][n] (+)= part[0][m][n] + part[1][m][n] + ... in slice order
 __global__ void tr_gemm_reduce_kernel(const float *part, int S, int M, int N, float *C, long ldc, int accumulate)
@@ -588,7 +603,7 @@ __global__ void tr_rope_kernel(float *qkv, int T, int d, int hd, const float2 *t
 // S = Q.K^T, P = causal softmax(S / sqrt(hd)), O = P.V forward; dP = dO.V^T, dV = P^T.dO,
 // dS = P (dP - rowsum(dP P)) / sqrt(hd), dQ = dS.K, dK = dS^T.Q backward.  The two kernels below are
 // the row-wise pieces; both work in place on [H][T][T], one block per (row i, head h), and leave
-// exact zeros above the diagonal.
+// exact zeros above the diagonal as far as the products read (to the end of the tile of TRG_SM rows and columns on the diagonal).
 __global__ __launch_bounds__(256) void tr_softmax_causal_kernel(float *P, int T, float scale)
 {
     __shared__ float red[4];
@@ -610,10 +625,11 @@ __global__ __launch_bounds__(256) void tr_softmax_causal_kernel(float *P, int T,
         sum += v[c];
     }
     sum = tr_block_sum(sum, red);
+    const int end = min(T, (i / TRG_SM + 1) * TRG_SM);
 #pragma unroll
     for (int c = 0; c < TR_T_MAX / 256; c++) {
         const int j = t + 256 * c;
-        if (j < T) row[j] = v[c] / sum;
+        if (j < end) row[j] = v[c] / sum;
     }
 }
 
@@ -634,10 +650,11 @@ __global__ __launch_bounds__(256) void tr_dsoftmax_kernel(const float *P, float 
         D += p[c] * g[c];
     }
     D = tr_block_sum(D, red);
+    const int end = min(T, (i / TRG_SM + 1) * TRG_SM);
 #pragma unroll
     for (int c = 0; c < TR_T_MAX / 256; c++) {
         const int j = t + 256 * c;
-        if (j < T) drow[j] = p[c] * (g[c] - D) * scale;
+        if (j < end) drow[j] = p[c] * (g[c] - D) * scale;
     }
 }
 

@@ -122,6 +122,14 @@ def test_training_step_follows_the_oracle(name, n, hs, kind):
     kg.close()
 
 
+@pytest.mark.parametrize("name,n", [("toy", 63), ("toy", 64), ("toy", 65), ("toy_bf16", 96), ("toy", 127), ("toy_bf16", 128), ("toy", 129),
+                                    ("small_bf16", 64), ("small_bf16", 192), ("small_bf16", 193)])
+def test_attention_products_at_the_edges_of_their_tiles(name, n):
+    """The per-head products leave out what the causal mask makes zero, in tiles of 64 rows: one position less than, as many as and one
+    more than a tile, loads in aligned groups of four and not, heads of 64 and of 128."""
+    test_training_step_follows_the_oracle(name, n, 1.0, 0)
+
+
 def test_training_lowers_the_loss_and_keeps_decoding_lossless():
     """Ten steps on one sequence: Eq. 3 goes down monotonically at a small step size, and greedy
     Kangaroo with the trained adapter still emits exactly the plain stream."""
