@@ -1766,7 +1766,6 @@ void kg_destroy(kg_ctx *x)
 
 // ---- adapter training (Eq. 3, AdamW) --------------------------------------------------------------
 
-constexpr int TR_SPLIT_MAX = 8;
 
 // One trainable tensor: where it sits in a parameter-sized block (float offset), its shape, whether
 // AdamW decays it, and where and how the decode calls keep it in the arena.
@@ -1951,11 +1950,9 @@ static int tr_gemm(kg_ctx *x, const void *A, long sam, long sak, const void *B, 
     g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
     g.batch = 1; g.bsa = g.bsb = g.bsc = 0;
     tr_gemm_vec_flags(g);
-    // few output tiles and a long k: slice k so that the launch has enough workgroups to fill the chip
-    const int tiles = ((N + TRG_N - 1) / TRG_N) * ((M + TRG_M - 1) / TRG_M);
-    int S = 1;
-    while (S < TR_SPLIT_MAX && tiles * S < x->n_cus && K / (2 * S) >= 256 && (size_t)2 * S * M * N <= x->tl.part_floats) S *= 2;
-    g.k_chunk = ((K + S - 1) / S + TRG_K - 1) / TRG_K * TRG_K;
+    const TrSlices cut = tr_slices(x->n_cus, M, N, K, b_mode != 0, x->tl.part_floats);
+    const int S = cut.slices;
+    g.k_chunk = cut.chunk;
     g.part = at<float>(x->tr, x->tl.part);
     {
         ProfScope ps(x, 4, 2.0 * M * (double)N * K);

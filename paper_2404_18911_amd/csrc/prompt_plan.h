@@ -1,6 +1,8 @@
-// How a long prompt pass is cut into workgroups (gemm_prefill2_body): plain host arithmetic, no device code.
+// How a long prompt pass (gemm_prefill2_body) and a training contraction (tr_gemm_body) are cut into workgroups: plain host arithmetic, no
+// device code.
 #pragma once
 #include <cmath>
+#include <cstddef>
 
 // Projections cut along k write at most PF_SLICES partial sums per output, PF_PART_ROWS rows of them in all.
 constexpr int PF_SLICES = 8, PF_PART_ROWS = 4096;
@@ -59,5 +61,29 @@ inline Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
             const double cost = rounds * ((double)KS / S * step + 4.0) + (S > 1 ? S * bytes / 5e6 + (S + 3) * bytes / 6e6 + 4.0 : split ? 5.0 : 0.0);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = {v, S}; }
         }
+    return best;
+}
+
+constexpr int TRG_K = 32, TRG_M = 128, TRG_N = 256;     // k per step and tile of C of tr_gemm_kernel
+constexpr int TR_SPLIT_MAX = 8;
+
+// Into how many slices of `chunk` numbers k a training contraction of M x N x K is cut: whole rounds of workgroups of one tile each (6 us
+// apart from their steps of 32 k: 1.9 us a step with all compute units at work, 1.4 against bf16 tiles), partial sums written and added at
+// 4.5 TB/s by a launch of 4 us.  So few tiles are cut to fill the device, and a launch whose last round is half empty to halve the rounds
+// (1000 x 12288 x 4096, 384 tiles on 256 compute units: 690 us -> 554 and 35 for the sums).  No slice is empty.
+struct TrSlices { int slices, chunk; };
+inline TrSlices tr_slices(int n_cus, int M, int N, int K, bool tiles16, size_t part_floats)
+{
+    const int tiles = ((N + TRG_N - 1) / TRG_N) * ((M + TRG_M - 1) / TRG_M);
+    TrSlices best = {1, 0};
+    double best_us = -1.0;
+    for (int S = 1; S <= TR_SPLIT_MAX; S++) {
+        if (S > 1 && (K / S < 128 || (size_t)S * M * N > part_floats)) break;
+        const int chunk = ((K + S - 1) / S + TRG_K - 1) / TRG_K * TRG_K;
+        if (S > 1 && (S - 1) * chunk >= K) continue;
+        const int rounds = (tiles * S + n_cus - 1) / n_cus;
+        const double us = rounds * (chunk / TRG_K * (tiles16 ? 1.4 : 1.9) + 6.0) + (S > 1 ? 4.0 + (S + 1) * (double)M * N * 4 / 4.5e6 : 0.0);
+        if (best_us < 0 || us < best_us) { best_us = us; best = {S, chunk}; }
+    }
     return best;
 }

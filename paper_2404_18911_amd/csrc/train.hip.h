@@ -76,9 +76,7 @@ __device__ __forceinline__ size_t packed_u16_index(int row, int col, int KS)
     return ((((size_t)(row >> 4) * KS + tile_pos(col >> 5, KS)) * 64 + ((col >> 3) & 3) * 16 + (row & 15)) << 3) + (col & 7);
 }
 
-#define TRG_K 32            // k per step
-#define TRG_M 128           // tile of C, 8 waves
-#define TRG_N 256
+// k per step TRG_K; tile of C, 8 waves, TRG_M x TRG_N (prompt_plan.h)
 #define TRG_SM 64           // the smaller tile, 4 waves
 #define TRG_SN 128
 #define TRG_SCALE 0x1p24f   // of the fp32 operands before they are split

@@ -130,6 +130,13 @@ def test_attention_products_at_the_edges_of_their_tiles(name, n):
     test_training_step_follows_the_oracle(name, n, 1.0, 0)
 
 
+@pytest.mark.parametrize("name,n,d,ff", [("toy", 19, 384, 1008), ("toy_bf16", 300, 640, 912)])
+def test_contractions_in_any_number_of_slices(monkeypatch, name, n, d, ff):
+    """Widths that are cut along k in 2, 3, 5, 6 and 7 slices, the last one shorter than the others."""
+    monkeypatch.setitem(I.SHAPES, "sliced", dataclasses.replace(I.SHAPES[name], d_model=d, n_heads=d // 64, d_ffn=ff))
+    test_training_step_follows_the_oracle("sliced", n, 1.0, 2)
+
+
 def test_training_lowers_the_loss_and_keeps_decoding_lossless():
     """Ten steps on one sequence: Eq. 3 goes down monotonically at a small step size, and greedy
     Kangaroo with the trained adapter still emits exactly the plain stream."""

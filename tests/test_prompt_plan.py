@@ -1,5 +1,5 @@
-"""How long prompt passes are cut into workgroups (csrc/prompt_plan.h), on the CPU: the header is host arithmetic, compiled here
-with g++ and asked for every projection of a range of widths and pass lengths."""
+"""How long prompt passes and the training step's contractions are cut into workgroups (csrc/prompt_plan.h), on the CPU: the header is host
+arithmetic, compiled here with g++ and asked for every projection of a range of widths and pass lengths."""
 import os
 import shutil
 import subprocess
@@ -21,10 +21,10 @@ def plan(tmp_path_factory):
                           os.path.join(HERE, "native", "prompt_plan_driver.cpp"), "-o", exe], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
 
-    def ask(asked):
-        out = subprocess.run([exe], input="\n".join("%d %d %d %d" % a for a in asked), capture_output=True, text=True, timeout=120).stdout
+    def ask(asked, *mode):
+        out = subprocess.run([exe, *mode], input="\n".join(" ".join(map(str, a)) for a in asked), capture_output=True, text=True, timeout=120).stdout
         rows = [tuple(map(int, l.split())) for l in out.splitlines()]
-        assert [r[:4] for r in rows] == asked
+        assert [r[:len(a)] for r, a in zip(rows, asked)] == asked and len(rows) == len(asked)
         return rows
     return ask
 
@@ -77,3 +77,21 @@ def test_the_gpu_prompt_tests_reach_every_variant_and_number_of_slices(plan):
     rows = plan(asked)
     assert {r[4:6] for r in rows} == {(6, 8)} | {(t, p) for t in (8, 12, 16, 32) for p in (5, 6, 7, 8)}
     assert {r[6] for r in rows} == set(range(1, SLICES + 1))
+
+
+def test_slices_of_a_training_contraction_hold_every_k_once(plan):
+    """None empty, none beyond the partial sums' buffer, each a whole number of steps but the last, and no launch cut that fills its rounds."""
+    asked = []
+    for d in (64, 384, 640, 1024, 4096, 5120, 6656):
+        f, V = d * 43 // 16 // 16 * 16, 32000
+        for T in (1, 33, 129, 256, 300, 777, 1000, 1400, 2048):
+            part = SLICES * min(T, 256) * 3 * d
+            asked += [(T, n, k, t16, part) for t16 in (0, 1) for n, k in ((3 * d, d), (d, 3 * d), (d, d), (f, d), (d, f), (V, d), (d, V))]
+            asked += [(n, k, T, 0, part) for n, k in ((3 * d, d), (d, d), (f, d), (d, f), (V, d))]
+    seen = set()
+    for M, N, K, t16, part, S, chunk in plan(asked, "train"):
+        seen.add(S)
+        assert 1 <= S <= SLICES and chunk % 32 == 0 and (S - 1) * chunk < K <= S * chunk
+        assert S == 1 or (S * M * N <= part and K // S >= 128)
+        assert S == 1 or (-(-M // 128) * -(-N // 256)) % 256 != 0
+    assert seen == set(range(1, SLICES + 1))
