@@ -51,7 +51,7 @@
 // A contraction with few output tiles and a long k is split over blockIdx.z: slice z handles k in
 // [z * k_chunk, (z + 1) * k_chunk) and writes its own partial [M][N] at part + z * M * N; a second
 // kernel adds the slices in order (no atomics: the result does not depend on scheduling).
-// With batch > 1 the launch holds one product per blockIdx.z instead (the per-head products of the
+// With batch > 1 (tr_gemm_small_kernel) the launch holds one product per blockIdx.x % batch (the per-head products of the
 // attention: operands and result advance by bsa / bsb / bsc elements per head).
 struct TrGemm {
     const void *A; long sam, sak;

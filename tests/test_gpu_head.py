@@ -1,4 +1,4 @@
-"""The LM head over verification rows where several weight tiles share a workgroup (6 rows and more, vocabularies of 3 to 7
+"""The LM head over verification rows where several weight tiles share a workgroup (6 rows and more, vocabularies of 3 to 8
 tiles per compute unit): the logits and choices of one-token decoding, bit for bit."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ from paper_2404_18911_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab", [8208, 12288, 16384, 16400, 24576, 28672])
+@pytest.mark.parametrize("vocab", [8208, 12288, 16384, 16400, 24576, 28672, 32000])
 def test_verification_rows_through_the_head_equal_decoded_rows(vocab):
     from paper_2404_18911_amd import binding as B
     from tests import parity as P
