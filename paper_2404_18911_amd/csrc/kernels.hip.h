@@ -1997,8 +1997,8 @@ __global__ void rope_table_kernel(float2 *tab, int max_seq, int half, const doub
 // grid = (heads, pages in use, blocks of 8 rows); block = 512.  A block handles one head and one
 // page of P positions: it rotates q (and k), appends the new k/v rows that fall in its page,
 // computes scores, a page-local softmax and P.V, and stores an unnormalised partial.  The last
-// block to finish for a head merges the partials in page order (so results do not depend on
-// arrival order, nor on how many rows or trailing pages the launch had).
+// block to finish for a head merges the partials in an order fixed by the page numbers (so results do not
+// depend on arrival order, nor on how many rows or trailing pages the launch had).
 // The argument block is only read (never indexed dynamically, never modified): it then stays in
 // scalar registers instead of being copied to private memory.
 struct AttnArgs {
@@ -2392,11 +2392,11 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         }
     }
     if (single) return;
-    // The last block of this head merges the pages in order.  The partials are exchanged with
-    // device-scope relaxed atomic stores / loads (write-through, cache-bypassing accesses); every
-    // wave waits for its stores to be acknowledged before the block bumps the head's counter.  A
-    // device-scope fence would write back and invalidate the whole L2 and costs several
-    // microseconds here.
+    // The last block of this head merges the pages, every fourth one and then the four sums, the weights' sum as a tree over the
+    // pages: in one order however many pages the launch covers, since those of its last row may be more than the earlier rows have (pages
+    // a row does not reach add zeros).  The partials are exchanged with device-scope relaxed atomic stores / loads (write-through,
+    // cache-bypassing accesses); every wave waits for its stores to be acknowledged before the block bumps the head's counter.  A
+    // device-scope fence would write back and invalidate the whole L2 and costs several microseconds here.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (t == 0) {
@@ -2420,21 +2420,22 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
             float gm = -INFINITY;
 #pragma unroll
             for (int ss = 0; ss < 8; ss++) gm = fmaxf(gm, mv[ss]);
-            float num = 0.f, den = 0.f;
+            float num[4] = {0.f, 0.f, 0.f, 0.f}, dp[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ss = 0; ss < 8; ss++) {
                 if (ss < S) {
                     const float w = (mv[ss] == -INFINITY) ? 0.f : __expf(mv[ss] - gm);
-                    num = fmaf(w, ov[ss], num);
-                    den = fmaf(w, sv[ss], den);
+                    num[ss & 3] = fmaf(w, ov[ss], num[ss & 3]);
+                    dp[ss] = fmaf(w, sv[ss], 0.f);      // (a product that no addition is fused with)
                 }
             }
-            store_act<BF>(act_out, d, m, h * HD + e, num / den);
+            const float den = ((dp[0] + dp[4]) + (dp[2] + dp[6])) + ((dp[1] + dp[5]) + (dp[3] + dp[7]));
+            store_act<BF>(act_out, d, m, h * HD + e, (((num[0] + num[1]) + num[2]) + num[3]) / den);
         }
         if (t == 0) __hip_atomic_store(&a.cnt[hz], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    // Many pages: four groups of HD threads take every fourth page, MB rows and 8 pages of loads in flight; the first of them fly while wave m
+    // Many pages: four groups of HD threads take every fourth page, as above, MB rows and 8 pages of loads in flight; the first of them fly while wave m
     // works out the page weights exp(max_page - max_all) and the sum of row m, which go through LDS, as do the groups' sums (added in
     // group order).  (One group and weights read twice, 8 loads at a time: a launch
     // of one row at 4000 positions 18.0 us, of eight 31; here 16.2 and 29.6.)
