@@ -2435,21 +2435,21 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         if (t == 0) __hip_atomic_store(&a.cnt[hz], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    // Many pages: four groups of HD threads take every fourth page, as above, MB rows and 8 pages of loads in flight; the first of them fly while wave m
-    // works out the page weights exp(max_page - max_all) and the sum of row m, which go through LDS, as do the groups' sums (added in
-    // group order).  (One group and weights read twice, 8 loads at a time: a launch
-    // of one row at 4000 positions 18.0 us, of eight 31; here 16.2 and 29.6.)
-    constexpr int G = 4, MB = MR < 2 ? 1 : HD == 64 ? 2 : MR < 4 ? 2 : 4;
+    // Many pages: four groups of HD threads take every fourth page, as above, MB rows and JB pages of loads in flight; the first of them fly
+    // while wave m works out the page weights exp(max_page - max_all) and the sum of row m, which go through LDS, as do the groups' sums (added
+    // in group order).  (One group and weights read twice, 8 loads at a time: a launch of one row at 4000 positions 17.7 us, of seven 30.2; here
+    // 16.1 and 28.2.  Seven rows, four of them and 8 pages at a time: 20.2 us at 9 pages, 21.0 at 16, half of the loads of no use; here 19.2 and 20.0.)
+    constexpr int G = 4, MB = MR < 2 ? 1 : MR < 4 ? 2 : HD == 128 ? MR : MR / 2, JB = MR < 8 ? 8 : 4;
     float (*gsum)[MR][HD] = ow;                             // [group - 1][row][element]
     float (*wgt)[MR] = (float (*)[MR]) & ow[3][0][0];       // [page][row], S <= 128 <= 5 * HD
     float *denl = &sw[0][0];
     const int e = t % HD, grp = __builtin_amdgcn_readfirstlane(t / HD);
-    float ov[MB][8], num[MR];
+    float ov[MB][JB], num[MR];
     auto load = [&](int m0, int j0) {
 #pragma unroll
         for (int r = 0; r < MB; r++)
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
+            for (int j = 0; j < JB; j++) {
                 const int ss = min(grp + G * (j0 + j), S - 1), m = min(m0 + r, M - 1);
                 ov[r][j] = ld_dev(&a.opart[((hb + ss) * KG_ROWS + m) * HD + e]);
             }
@@ -2475,10 +2475,10 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
         if (m0 >= M || grp >= G) break;
 #pragma unroll
         for (int r = 0; r < MB; r++) num[m0 + r] = 0.f;
-        for (int j0 = 0; j0 < J; j0 += 8) {
+        for (int j0 = 0; j0 < J; j0 += JB) {
             if (m0 || j0) load(m0, j0);
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
+            for (int j = 0; j < JB; j++) {
                 const int ss = grp + G * (j0 + j);
                 if (ss < S) {
 #pragma unroll
