@@ -2597,9 +2597,10 @@ __device__ __forceinline__ float pair_sum(float v)
 }
 
 // Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, and their sum.  m_run follows
-// the running maximum with a lag: only where a row's has grown by more than 8 is it moved and what was summed so far (o, l_run)
-// multiplied by the difference; probabilities up to 2^8 are as exact in half precision as those up to 1.  A row that has seen no position
-// yet has m_run = -inf and sums 0.
+// the running maximum with a lag, as in FlashAttention-4's conditional rescaling: only where a row's has grown by more than 8 is it moved
+// and what was summed so far (o, l_run) multiplied by the difference; probabilities up to 2^8 are as exact in half precision as those up
+// to 1.  Each row decides for itself, so that its bits depend on what it sees alone.  A row that has seen no position yet has m_run = -inf
+// and sums 0.
 template <int NS, int DT>
 __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[2 * NS], float &m_run, float &l_run, f32x16_t (&o)[DT])
 {
@@ -2609,8 +2610,9 @@ __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[
 #pragma unroll
         for (int r = 0; r < 16; r++) mx = fmaxf(mx, s[i][r]);
     mx = pair_max(mx);
-    if (__any(mx > m_run + 8.f)) {
-        const float m_new = fmaxf(m_run, mx);
+    const bool grown = mx > m_run + 8.f;
+    if (__any(grown)) {
+        const float m_new = grown ? mx : m_run;         // (where it stays, scale is 1, or 0 times the zeros of a row without a position)
         const float scale = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));     // 0 for the first positions a row sees
 #pragma unroll
         for (int dt = 0; dt < DT; dt++) o[dt] *= scale;

@@ -46,3 +46,37 @@ def test_every_page_size(name, page):
 def test_a_second_pass_behind_4096_positions():
     _compare(SHAPES["few"], 128, [4097, 4111, 4160, 4161])
     _compare(SHAPES["narrow"], 64, [4096, 4096 + 385, 4096 + 449])
+
+
+def _scaled(bits, by):
+    return I.f32_to_bf16_bits(I.bf16_bits_to_f32(bits) * by)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_a_row_does_not_depend_on_later_ones(hd):
+    """Two prompts that differ in the last token leave the same bits in both layers' caches at every earlier position (what a row sees
+    decides where the reference of its probabilities lies, not what its neighbours see).  Queries 64 times as large as usual: scores spread so far
+    that a late row's maximum often leaves the others' behind."""
+    import torch
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = I.ModelShape("apart", 2, 40 * hd, 40, hd, 640, 1024, 2)
+    W = I.gen_weights(shape, seed=31, alpha=1.0)
+    for i in range(2):
+        W[(I.KIND_WQ, i)] = _scaled(W[(I.KIND_WQ, i)], 64.0)
+    prompt = [int(t) for t in I.gen_prompt(shape.vocab, 700, seed=32)]
+    page = 128
+    kg = P.load_model(shape, W, 720, kv_page_tokens=page)
+    p, _ = B.make_params()
+
+    def caches(tokens):
+        kg.kv.zero_()
+        kg.prefill(p, tokens)
+        n = 6 * 3 * 40 * 2 * page * hd
+        pool = kg.kv.view(torch.int16)[:n].view(6, 3, 40, 2, page, hd)[:, :2].permute(0, 4, 1, 2, 3, 5).reshape(6 * page, -1)
+        return pool[:len(tokens) - 1].clone()
+    for n in (33, 63, 160, 300, 640, 700):
+        want = caches(prompt[:n])
+        for last in (1, 500, 1000):
+            assert torch.equal(caches(prompt[:n - 1] + [last]), want), (n, last)
+    kg.close()
