@@ -2512,7 +2512,7 @@ __global__ __launch_bounds__(512, (sizeof(T) == 2 ? 6 : 1)) void attn_kernel(con
 //   S^T = K Q^T   A = 32 keys (as stored: one position's 8 consecutive dimensions per lane), B = the rotated, scaled queries held
 //         in registers as half hi + lo parts (two MFMAs per step, fp32-grade scores); a lane gets one query row (its column) and
 //         positions 8 (r / 4) + 4 (lane / 32) + r % 4 in its 16 registers;
-//   row softmax   running maximum and sum per query row (flash-attention recurrence) in powers of two (the queries carry log2 e): over a
+//   row softmax   running maximum and sum per query row (flash-attention recurrence) in powers of two: over a
 //         lane's own registers and the lane 32 away, nothing else, since
 //   O^T = V^T P   B = the probabilities straight from the score registers, rounded to half (the contraction index may be enumerated
 //         in any order as long as both operands agree), A = V^T, which ds_read_b64_tr_b16 gathers from values stored as they are (per 16
@@ -2541,7 +2541,7 @@ struct PfAttnArgs {
     int act_pair;            // layout of act_out (pf_act_ptr)
 };
 
-// A lane's query (column lane % 32 of the wave's rows from row0 on): rotated, scaled by log2 e / sqrt(hd), split into half hi + lo, in
+// A lane's query (column lane % 32 of the wave's rows from row0 on): rotated, scaled by 1 / sqrt(hd), split into half hi + lo, in
 // B-operand order: step ks holds dimensions 16 ks + 8 (lane / 32) .. + 7.
 template <int HD>
 __device__ __forceinline__ void pf_attn_queries(const PfAttnArgs &a, int h, int row0, int lane, f16x8_t (&qhi)[HD / 16], f16x8_t (&qlo)[HD / 16])
@@ -2550,7 +2550,7 @@ __device__ __forceinline__ void pf_attn_queries(const PfAttnArgs &a, int h, int 
     const int row = min(row0 + (lane & 31), a.T - 1), g = lane >> 5;
     const float *q = a.qkv + (size_t)row * 3 * a.d + h * HD;
     const float2 *rp = a.rope + (size_t)(a.pos0 + row) * HH;
-    const float qscale = 1.44269504088896341f * rsqrtf((float)HD);
+    const float qscale = rsqrtf((float)HD);
     float4 x0[KH][2], x1[KH][2], cs[KH][4];
 #pragma unroll
     for (int ks = 0; ks < KH; ks++) {
@@ -2596,7 +2596,8 @@ __device__ __forceinline__ float pair_sum(float v)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, and their sum.  m_run follows
+// Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, and their sum.  (The factor log2 e
+// of the exponent comes with the subtraction, as one fused multiply-add: in the queries it would take a third of the half range from them.)  m_run follows
 // the running maximum with a lag, as in FlashAttention-4's conditional rescaling: only where a row's has grown by more than 8 is it moved
 // and what was summed so far (o, l_run) multiplied by the difference; probabilities up to 2^8 are as exact in half precision as those up
 // to 1.  Each row decides for itself, so that its bits depend on what it sees alone.  A row that has seen no position yet has m_run = -inf
@@ -2609,7 +2610,8 @@ __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[
     for (int i = 0; i < NS; i++)
 #pragma unroll
         for (int r = 0; r < 16; r++) mx = fmaxf(mx, s[i][r]);
-    mx = pair_max(mx);
+    constexpr float LOG2E = 1.44269504088896341f;
+    mx = pair_max(mx) * LOG2E;
     const bool grown = mx > m_run + 8.f;
     if (__any(grown)) {
         const float m_new = grown ? mx : m_run;         // (where it stays, scale is 1, or 0 times the zeros of a row without a position)
@@ -2625,7 +2627,7 @@ __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[
     for (int i = 0; i < NS; i++)
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-            const float v = __builtin_amdgcn_exp2f(s[i][r] - m_ref);        // 0 for a masked score
+            const float v = __builtin_amdgcn_exp2f(fmaf(s[i][r], LOG2E, -m_ref));        // 0 for a masked score
             sum[r & 1] += v;
             p[2 * i + (r >> 3)][r & 7] = (_Float16)v;
         }

@@ -80,3 +80,34 @@ def test_a_row_does_not_depend_on_later_ones(hd):
         for last in (1, 500, 1000):
             assert torch.equal(caches(prompt[:n - 1] + [last]), want), (n, last)
     kg.close()
+
+
+@pytest.mark.parametrize("name", ["narrow", "wide"])
+def test_queries_up_to_the_half_precision_range(name):
+    """Scaled queries of 55 thousand, which a half holds (and 1.44 times as much it does not): every embedding is a row of signs, so that the
+    normalised input is too, and a head's queries are one of its features times a number, at the first rotation pair's first component."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = SHAPES[name]
+    d, hd = shape.d_model, shape.head_dim
+    W = I.gen_weights(shape, seed=41, alpha=1.0)
+    W[(I.KIND_EMBED, -1)] = I.f32_to_bf16_bits(np.where(np.random.default_rng(42).random((shape.vocab, d)) < 0.5, -1.0, 1.0).astype(np.float32))
+    wq = np.zeros((d, d), dtype=np.float32)
+    for h in range(shape.n_heads):
+        wq[h * hd, 7 * h] = 55000.0 * np.sqrt(hd)
+    W[(I.KIND_WQ, 0)] = I.f32_to_bf16_bits(wq)
+    prompt = [int(t) for t in I.gen_prompt(shape.vocab, 600, seed=43)]
+    kg = P.load_model(shape, W, 616)
+    p, _ = B.make_params()
+    lengths, want = (9, 40, 200, 600), {}
+    kg.prefill(p, prompt[:1])
+    for i in range(1, max(lengths)):
+        kg.plain_step(p, prompt[i])
+        if i + 1 in lengths:
+            want[i + 1] = kg.read_logits(1, 0)
+    for n in lengths:
+        kg.prefill(p, prompt[:n])
+        z = kg.read_logits(1, 0)
+        assert np.isfinite(z).all(), n
+        np.testing.assert_allclose(z, want[n], rtol=0, atol=2e-3 * max(1.0, float(np.std(want[n]))), err_msg=str(n))
+    kg.close()
