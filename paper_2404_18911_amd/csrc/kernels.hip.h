@@ -2596,12 +2596,13 @@ __device__ __forceinline__ float pair_sum(float v)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, and their sum.  (The factor log2 e
-// of the exponent comes with the subtraction, as one fused multiply-add: in the queries it would take a third of the half range from them.)  m_run follows
-// the running maximum with a lag, as in FlashAttention-4's conditional rescaling: only where a row's has grown by more than 8 is it moved
-// and what was summed so far (o, l_run) multiplied by the difference; probabilities up to 2^8 are as exact in half precision as those up
-// to 1.  Each row decides for itself, so that its bits depend on what it sees alone.  A row that has seen no position yet has m_run = -inf
-// and sums 0.
+// Probabilities of NS x 32 scores per query row (s is the lane's: positions as above) relative to 2^m_run, m_run the row's running maximum,
+// and their sum.  (The factor log2 e of the exponent comes with the subtraction, as one fused multiply-add: in the queries it would take a
+// third of the half range from them.)  Where a row's maximum has grown, what was summed so far (o, l_run) is multiplied by the difference; no
+// other row of the wave shows in a row's bits.  A row that has seen no position yet has m_run = -inf and sums 0.
+//   m_run is the maximum itself: a row's largest probability is then 1 and exact in half precision.  Following it with a lag of 8 (FlashAttention-4's
+// conditional rescaling) saves nothing here (4096 rows of the 7B width, 4 layers: 9.53 ms with, 9.53 without) and costs precision: error of the
+// attention output against 64 bits, 1000 rows, 1.5e-4 with, 1.1e-4 without, and with scores 16 times as large 8.5e-5 and 2.3e-5.
 template <int NS, int DT>
 __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[2 * NS], float &m_run, float &l_run, f32x16_t (&o)[DT])
 {
@@ -2612,9 +2613,8 @@ __device__ __forceinline__ void pf_attn_softmax(f32x16_t (&s)[NS], f16x8_t (&p)[
         for (int r = 0; r < 16; r++) mx = fmaxf(mx, s[i][r]);
     constexpr float LOG2E = 1.44269504088896341f;
     mx = pair_max(mx) * LOG2E;
-    const bool grown = mx > m_run + 8.f;
-    if (__any(grown)) {
-        const float m_new = grown ? mx : m_run;         // (where it stays, scale is 1, or 0 times the zeros of a row without a position)
+    if (__any(mx > m_run)) {
+        const float m_new = fmaxf(m_run, mx);           // (where it stays, scale is 1, or 0 times the zeros of a row without a position)
         const float scale = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));     // 0 for the first positions a row sees
 #pragma unroll
         for (int dt = 0; dt < DT; dt++) o[dt] *= scale;

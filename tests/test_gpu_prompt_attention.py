@@ -111,3 +111,37 @@ def test_queries_up_to_the_half_precision_range(name):
         assert np.isfinite(z).all(), n
         np.testing.assert_allclose(z, want[n], rtol=0, atol=2e-3 * max(1.0, float(np.std(want[n]))), err_msg=str(n))
     kg.close()
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_the_largest_probability_is_exact(hd):
+    """Rows that see one position at about 149 times the weight of another one, read by the same wave many positions earlier, and nothing else: where both
+    values are 1 the output is 1 but for the half-precision rounding of the smaller probability (0.0067 x 2^-12) and the two bfloat16 parts
+    of the output (2^-17), together below 2^-16.  (The larger one, rounded relative to the smaller: 2.5e-4.)  Workgroups of 32 and of 128 rows."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    d = 40 * hd
+    # (a base of the rotation so large that the pair used here does not turn)
+    shape = I.ModelShape("exact", 2, d, 40, hd, 640, 1024, 1, rope_theta=1e12)
+    W = I.gen_weights(shape, seed=51, alpha=1.0)
+    rng = np.random.default_rng(52)
+    # features of a token: 1, the signs that mark tokens 0 and 1, random signs: the normalised input is the same
+    embed = np.where(rng.random((shape.vocab, d)) < 0.5, -1.0, 1.0).astype(np.float32)
+    embed[:, 0], embed[:, 1:3] = 1.0, -1.0
+    embed[0, 1] = embed[1, 2] = 1.0
+    wq, wk = np.zeros((d, d), dtype=np.float32), np.zeros((d, d), dtype=np.float32)
+    at = np.arange(40) * hd + hd // 2 - 1
+    wq[at, 0] = np.sqrt(hd)
+    wk[at, 1], wk[at, 2] = 24.0, 26.5           # keys -2.5, 2.5 and -50.5 of tokens 0, 1 and others
+    for kind, a in ((I.KIND_EMBED, embed), (I.KIND_WQ, wq), (I.KIND_WK, wk), (I.KIND_WV, np.eye(d, dtype=np.float32)),
+                    (I.KIND_WO, np.eye(d, dtype=np.float32)), (I.KIND_WD, np.zeros((d, 640), dtype=np.float32))):
+        W[(kind, -1 if kind == I.KIND_EMBED else 0)] = I.f32_to_bf16_bits(a)
+    kg = P.load_model(shape, W, 720)
+    kg.train_bind(704)
+    for n in (200, 700):
+        tokens = [0] + [int(t) for t in rng.integers(2, 1024, n - 1)]
+        tokens[140] = 1                         # (in the fifth tile of 32: the same wave's as the first)
+        F, _ = kg.train_features(tokens)
+        out = (F.cpu().numpy() - embed[tokens])[140:, (embed[0] == 1.0) & (embed[1] == 1.0)]
+        assert out.shape[1] > 200 and np.abs(out - 1.0).max() <= 2.0 ** -16, np.abs(out - 1.0).max()
+    kg.close()
