@@ -3072,7 +3072,7 @@ struct TileStats {
         for (int k = 8; k < n; k++) f(*(const float4 *)(hs + (size_t)(i0 + k) * 4), i0 + k);
     }
 };
-// weight of a tile under the row's maximum mx of z / T
+// weight of a tile under the row's maximum mx of z / T (none for one of -infinity, whose own sum is not a number)
 __device__ __forceinline__ float tile_weight(const float4 &h, float mx) { return h.x == -INFINITY ? 0.f : h.y * __expf(h.x - mx); }
 
 // Block-wide inverse-CDF draw from softmax(z / T) through the tile statistics (1024 threads): the tile that holds u * total is
@@ -3240,7 +3240,7 @@ __global__ __launch_bounds__(1024) void head_final_kernel(const float *hstat, in
     float best = -INFINITY;
     int idx = NONE;
     ts.each([&](const float4 &h, int) {
-        if (h.x > best) { best = h.x; idx = __float_as_int(h.z); }
+        if (h.x > best || (h.x == best && idx == NONE)) { best = h.x; idx = __float_as_int(h.z); }      // (a row of -infinity has a first token too)
     });
     // stretches, waves and lanes ascend, so the first of equal maxima has the lowest index
     const float wm = wave_max(best);

@@ -69,3 +69,37 @@ def test_choices_draws_and_confidences_follow_the_logits(vocab, dtype):
         t, _, _ = kg.draft_step(p)
         drawn(kg.read_logits(0, 0), u, t)
     kg.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lowest", [False, True])
+def test_logits_of_minus_infinity(dtype, lowest):
+    """Rows whose logits all overflow to minus infinity choose the lowest token, as an arg-max with ties does (their sum of weights is 0);
+    with one finite logit among them that one, with all the probability."""
+    from paper_2404_18911_amd import binding as B
+    from tests import parity as P
+    shape = I.ModelShape("minus", 1, 64, 1, 64, 64, 1040, 1, dtype)
+    W = I.gen_weights(shape, seed=9, alpha=1.0)
+    store = (lambda a: a) if dtype == "f32" else I.f32_to_bf16_bits
+    # the residual stream is the embedding (8 in its first feature once normalised), and the head reads that feature only
+    embed, head = np.zeros((1040, 64), dtype=np.float32), np.zeros((1040, 64), dtype=np.float32)
+    embed[:, 0] = 1.0
+    head[:, 0] = -3e38
+    if lowest:
+        head[700, 0] = -3.0
+    W[(I.KIND_EMBED, -1)], W[(I.KIND_LM_HEAD, -1)] = store(embed), store(head)
+    for k in (I.KIND_WO, I.KIND_WD):
+        W[(k, 0)] = np.zeros_like(W[(k, 0)])
+    W[(I.KIND_A_WO, -1)] = np.zeros_like(W[(I.KIND_A_WO, -1)])
+    kg = P.load_model(shape, W, 48, kv_page_tokens=16)
+    want = 700 if lowest else 0
+    for mode in (0, 1):
+        p, keep = B.make_params(mode=mode, temperature=1.0, eta=0.0, uniforms=np.full((48, 3), 0.5, dtype=np.float32))
+        assert kg.prefill(p, [3, 4, 5]) == want
+        z = kg.read_logits(1, 0)
+        assert np.isneginf(np.delete(z, 700)).all() and np.isneginf(z[700]) != lowest
+        t, conf, _ = kg.draft_step(p)
+        assert t == want and conf == (1.0 if lowest else np.inf)
+        kg.prefill(p, [3, 4, 5])
+        assert kg.plain_step(p, want) == want
+    kg.close()
