@@ -612,8 +612,9 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_multi_kernel(const u3
         for (int s = 0; s < D; s++)
             if (i + D + s < n) mul(s);
     };
-    // (two ways apart from the start: after loads that may not have been issued the compiler waits for all of them in every turn)
-    if (n >= 2 * D) {
+    // (two ways apart from the start: after loads that may not have been issued the compiler waits for all of them in every turn.  us with
+    // 7 rows, 2048 and 2560 features, that way from 2 D steps on / here: 3 tiles 11.2 and 13.9 / 10.6 and 12.7, 5 tiles 16.8 and 20.1 / 16.2 and 19.1)
+    if (n >= D) {
 #pragma unroll
         for (int s = 0; s < D; s++) {
             load(s, s);
