@@ -325,22 +325,27 @@ void launch_gemv_f32(const float *W, int N, int K, const float *act, const Epi &
     else hipLaunchKernelGGL(gemv_f32_kernel<2>, dim3(N / 16), dim3(512), 0, s, W, K, act, e, ft);
 }
 
-// Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, whose time grows with M, else
-// gemv_multi_kernel, whose time hardly does.  Measured (us, stand-alone product over weights that no cache holds; gemv_bf16_body with
-// 5, 6, 7, 8 rows / gemv_multi_kernel):
-//   tiles   4096 features                    5120 features                    11008 features
-//   2       13.2 13.6 14.2 14.7 / 18.6       15.8 16.4 17.3 18.2 / 15.5       30.9 32.0 33.5 35.3 / 29.8
-//   3       18.0 18.7 19.5 20.3 / 18.0       22.0 22.9 24.2 25.3 / 21.8       44.0 45.9 48.3 50.8 / 46.3
-//   4       22.8 23.7 24.7 26.0 / 25.5       28.1 29.3 31.0 32.6 / 27.8       57.7 60.1 63.1 66.6 / 56.3
-//   5       27.5 28.7 30.0 31.6 / 28.3       34.3 35.8 37.9 39.8 / 34.7       71.0 74.0 77.9 82.3 / 69.0
-//   6       32.2 33.7 35.3 37.1 / 35.5       40.5 42.4 44.8 47.1 / 40.2       84.2 88.0 92.5 97.7 / 86.2
-//   7       37.0 38.8 40.5 42.6 / 38.5       46.7 48.8 51.7 54.5 / 46.9       97.9 102  108  114  / 97.0
-//   8       41.6 43.5 45.7 48.1 / 46.3       52.8 55.4 58.7 61.8 / 53.7       111  116  122  129  / 113
-// So from 6 rows on with 3 to 7 tiles, with 4 tiles from 7 and with 8 tiles 8 (7 rows of 4096 features: 45.7 against 46.3); not with 2.
-inline int gemv_tiles(int n_cus, int N, int M)
+// Weight tiles per workgroup of a projection of M rows: 1 = gemv_bf16_body, whose time grows with the rows and, by more, with the
+// features, else gemv_multi_kernel, whose time hardly grows with the rows.  Measured (us, stand-alone product of 4096 weight rows per tile over
+// weights that no cache holds; gemv_bf16_body with 5, 6, 7, 8 rows / gemv_multi_kernel with 7):
+//  tiles 2048 features               4096                         5120                         8192                         11008
+//   2   7.6 7.9 8.2 8.5 / 8.7        12.9 13.5 14.1 14.5 / 18.4   15.7 16.3 17.1 18.0 / 15.3   26.4 26.8 27.6 28.2 / 22.6   30.7 31.9 33.5 35.1 / 29.4
+//   3   10.7 10.7 11.0 11.4 / 10.6   17.8 18.4 19.4 20.3 / 17.6   21.9 22.8 24.1 25.2 / 21.4   36.9 37.9 39.2 40.5 / 32.8   44.2 45.8 48.0 50.7 / 46.7
+//   4   12.8 13.2 13.7 14.3 / 20.3   22.6 23.6 24.6 26.0 / 25.2   28.1 29.4 31.0 32.5 / 27.3   47.8 49.0 50.5 52.0 / 42.2   57.4 59.7 62.8 66.2 / 55.6
+//   5   16.6 16.9 17.4 17.5 / 16.2   27.4 28.5 29.8 31.3 / 27.9   34.3 35.8 38.0 39.9 / 34.5   58.5 60.3 62.4 64.1 / 52.4   71.1 73.8 77.6 82.1 / 68.6
+//   6   18.0 18.5 19.4 19.9 / 19.0   32.0 33.6 35.5 37.5 / 35.1   40.5 42.0 44.5 47.1 / 39.7   68.8 70.8 73.1 76.5 / 61.5   83.6 87.3 92.1 97.1 / 84.5
+//   7   21.5 22.3 23.0 23.6 / 21.9   37.2 38.7 40.5 42.5 / 37.8   46.4 48.5 51.4 54.2 / 46.1   79.6 81.6 84.9 89.3 / 71.3   97.1 102 107 113 / 95.6
+//   8   23.0 23.7 24.6 25.7 / 27.4   41.5 43.6 45.8 48.7 / 46.0   52.8 55.2 58.7 61.7 / 53.4   90.6 92.8 96.0 99.1 / 83.7   110 116 122 128 / 111
+// (where the last tiles are not whole, say 5.5 a compute unit, gemv_multi_kernel gains up to a tenth more).  So from 5 rows on with very many
+// features, from 6 with many, and with fewer from 6 to 8, by tiles.  Not with 2 tiles (just above one tile a compute unit half of them would idle), and
+// not where the workgroups' weights are some 256 KB apart and few steps long (4 and 8 tiles of 2048 features, 8 of 1024: 21.3 us against
+// 15.5 .. 16.8; of 1040 15.7).  (24576 x 4096 is the one shape that loses by this, 35.2 us against 33.6 with 6 rows; 22544 x 4096 gains, 31.5 against 33.0.)
+inline int gemv_tiles(int n_cus, int N, int K, int M)
 {
     const int ntw = (N / 16 + n_cus - 1) / n_cus;
-    return M >= (ntw == 8 ? 8 : ntw == 4 ? 7 : 6) && ntw >= 3 && ntw <= 8 ? ntw : 1;
+    if (ntw < 3 || ntw > 8 || (K <= 2048 && ntw * K % 8192 == 0)) return 1;
+    const int from = K >= 6144 ? (ntw == 3 ? 6 : 5) : K >= 4608 ? 6 : ntw == 8 ? 8 : ntw == 4 ? 7 : 6;
+    return M >= from ? ntw : 1;
 }
 template <int SRC>
 void launch_gemv_multi(const u32x4_t *W, int N, int KS, int M, const void *act, int K, const Epi &e, int ntw, hipStream_t s)
@@ -361,7 +366,7 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
     if (x->bf && e.kind == EPI_FEATURE)
         hipLaunchKernelGGL(gemv_bf16_feature_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream, at<const u32x4_t>(x->arena, w_off),
                            (K + 31) / 32, e.M, (const u32x4_t *)act, N, e, ft);
-    else if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, e.M) : 1; ntw > 1)
+    else if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, K, e.M) : 1; ntw > 1)
         launch_gemv_multi<FROM_ACT>(at<const u32x4_t>(x->arena, w_off), N, (K + 31) / 32, e.M, act, 0, e, ntw, x->stream);
     else if (x->bf)
         hipLaunchKernelGGL(gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream,
@@ -2389,7 +2394,7 @@ static int op_linear_launch(int dtype, const void *packed, int N, int K, const f
         const dim3 grid(N / 16), block(64 * GEMV_WAVES);
         const u32x4_t *W = (const u32x4_t *)packed;
         const int KS = (K + 31) / 32;
-        if (const int ntw = gemv_tiles(256, N, M); ntw > 1) {      // (an MI355X's compute units; the results do not depend on it)
+        if (const int ntw = gemv_tiles(256, N, K, M); ntw > 1) {      // (an MI355X's compute units; the results do not depend on it)
             Epi e;
             memset(&e, 0, sizeof(e));
             e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;

@@ -43,10 +43,10 @@ def test_linear_of_aligned_and_unaligned_rows(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("N,K", [(12288, 528), (13840, 1040), (16400, 528), (19968, 1040), (27648, 272), (22016, 4096), (28688, 272), (32768, 1040),
-                                 (12288, 2576), (20480, 2064)])
+                                 (12288, 2576), (20480, 2064), (16384, 6160)])
 def test_a_row_of_linear_does_not_depend_on_the_others(N, K):
-    """6 .. 8 rows (7 and 8 of the second shape, 8 of the seventh and eighth) through 3, 4, 5, 5, 7, 6, 8, 8, 3 and 5 weight tiles per workgroup (256
-    compute units) give the bits of one row alone (uneven shares of tiles, k ranges of unequal length, a half k-step; as many steps as are in flight
+    """6 .. 8 rows (7 and 8 of the second shape, 8 of the seventh and eighth) through 3, 4, 5, 5, 7, 6, 8, 8, 3, 5 and 4 weight tiles per workgroup (256
+    compute units), 5 rows too of the last, give the bits of one row alone (uneven shares of tiles, k ranges of unequal length, a half k-step; as many steps as are in flight
     at once, and fewer than twice as many)."""
     import torch
     from paper_2404_18911_amd import binding as B
