@@ -2390,23 +2390,28 @@ static int op_linear_launch(int dtype, const void *packed, int N, int K, const f
         hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, xd, n, (float *)stage);
         xd = (const float *)stage;
     }
+    const bool by_buffer = (size_t)M * K * 4 < BUFFER_NONE;      // (the kernels that read rows through a buffer address them by 31 bits)
     if (dtype == 1) {
         const dim3 grid(N / 16), block(64 * GEMV_WAVES);
         const u32x4_t *W = (const u32x4_t *)packed;
         const int KS = (K + 31) / 32;
+        const bool aligned = ((uintptr_t)xd & 15) == 0 && by_buffer;
         if (const int ntw = gemv_tiles(256, N, K, M); ntw > 1) {      // (an MI355X's compute units; the results do not depend on it)
             Epi e;
             memset(&e, 0, sizeof(e));
             e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;
-            if (((uintptr_t)xd & 15) == 0) launch_gemv_multi<FROM_ROWS>(W, N, KS, M, xd, K, e, ntw, s);
+            if (aligned) launch_gemv_multi<FROM_ROWS>(W, N, KS, M, xd, K, e, ntw, s);
             else launch_gemv_multi<FROM_ROWS_UNALIGNED>(W, N, KS, M, xd, K, e, ntw, s);
-        } else if (((uintptr_t)xd & 15) == 0) hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
+        } else if (aligned) hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
         else hipLaunchKernelGGL(gemv_bf16_rows_kernel<FROM_ROWS_UNALIGNED>, grid, block, 0, s, W, KS, M, xd, K, N, yd);
     } else {
         Epi e;
         memset(&e, 0, sizeof(e));
-        e.kind = EPI_PLAIN; e.M = M; e.N = N; e.out = yd;
-        launch_gemv_f32((const float *)packed, N, K, xd, e, s);
+        e.kind = EPI_PLAIN; e.M = by_buffer ? M : 1; e.N = N;
+        for (int m = 0; m < M; m += e.M) {          // (one row at a time gives the same bits)
+            e.out = yd + (size_t)m * N;
+            launch_gemv_f32((const float *)packed, N, K, xd + (size_t)m * K, e, s);
+        }
     }
     return hipGetLastError() == hipSuccess ? KG_OK : KG_EHIP;
 }

@@ -94,3 +94,24 @@ def test_a_row_of_an_fp32_product_does_not_depend_on_the_others(N, K):
         ref = x.double() @ w.double().T
         bound = (x.abs().double() @ w.abs().double().T) * (K + 8) * 2.0 ** -24 + K * 1.5e-45       # K + 8 roundings of a sum, and of subnormal products
         assert bool(((one.double() - ref).abs() <= bound).all()), scale
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_of_more_than_two_gib(dtype):
+    """Eight rows whose last lies beyond 2^31 bytes: the bits of that row alone."""
+    import torch
+    from paper_2404_18911_amd import binding as B
+    L, code = B.lib(), 1 if dtype == "bf16" else 0
+    N, K = 16, 76_800_000
+    s = torch.cuda.current_stream().cuda_stream
+    w = torch.empty(N, K, dtype=torch.bfloat16 if code else torch.float32, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+    packed = torch.empty(L.kg_op_packed_bytes(code, N, K), dtype=torch.uint8, device="cuda")
+    assert L.kg_op_pack(code, w.data_ptr(), N, K, packed.data_ptr(), s) == B.KG_OK
+    x = torch.empty(8, K, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(2))
+    y, one = torch.full((8, N), 7.0, device="cuda"), torch.full((8, N), 7.0, device="cuda")
+    assert L.kg_op_linear(code, packed.data_ptr(), N, K, x.data_ptr(), 8, y.data_ptr(), packed.data_ptr(), s) == B.KG_OK
+    for m in (0, 6, 7):
+        assert L.kg_op_linear(code, packed.data_ptr(), N, K, x[m].data_ptr(), 1, one[m].data_ptr(), packed.data_ptr(), s) == B.KG_OK
+        assert torch.equal(y[m], one[m]), m
+    ref = (x[7].double() * w[3].double()).sum()
+    assert abs(float(y[7, 3] - ref)) <= 1e-3 * K ** 0.5         # (sums of 7.7e7 products: their spread is K^0.5)
