@@ -1913,7 +1913,7 @@ static void launch_tr_gemm(TrGemm &g, int z, hipStream_t s, bool small = false)
 {
     const int tm = small ? TRG_SM : TRG_M, tn = small ? TRG_SN : TRG_N;
     g.gm = (g.M + tm - 1) / tm; g.gn = (g.N + tn - 1) / tn;
-    g.swz = !small && (g.gn % 8 == 0 || g.gn >= 16);        // else columns of C would leave XCDs idle
+    g.swz = !small && trg_by_column(g.gn);
     int tiles = g.swz ? 8 * g.gm * ((g.gn + 7) / 8) : g.gm * g.gn;
     if (g.causal) {
         tiles = 0;

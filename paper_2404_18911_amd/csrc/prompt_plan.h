@@ -67,21 +67,28 @@ inline Pf2Plan pf2_plan(int n_cus, int NT, int KS, int T, bool split)
 constexpr int TRG_K = 32, TRG_M = 128, TRG_N = 256;     // k per step and tile of C of tr_gemm_kernel
 constexpr int TR_SPLIT_MAX = 8;
 
+// Are the tiles of one column of C (of gn) dealt to one XCD, column c to XCD c % 8?  (Its L2 keeps that part of B; not where columns would
+// leave XCDs idle.)
+inline bool trg_by_column(int gn) { return gn % 8 == 0 || gn >= 16; }
+
 // Into how many slices of `chunk` numbers k a training contraction of M x N x K is cut: whole rounds of workgroups of one tile each (6 us
-// apart from their steps of 32 k: 1.9 us a step with all compute units at work, 1.4 against bf16 tiles), partial sums written and added at
-// 4.5 TB/s by a launch of 4 us.  So few tiles are cut to fill the device, and a launch whose last round is half empty to halve the rounds
-// (1000 x 12288 x 4096, 384 tiles on 256 compute units: 690 us -> 554 and 35 for the sums).  No slice is empty.
+// apart from their steps of 32 k: 1.9 us a step with all compute units at work, 1.4 against bf16 tiles), counted on the XCD with the most columns
+// (of 20 some have three and some two), partial sums written and added at 4.5 TB/s by a launch of 4 us.  So few tiles are cut to fill the
+// device, and a launch whose last round is half empty to halve the rounds (1000 x 12288 x 4096, 384 tiles on 256 compute units: 690 us -> 554 and 35
+// for the sums).  No slice is empty.  (700 x 5120 x 15360: 4 slices are 72 tiles on an XCD of 32 compute units, three rounds, 842 us; 2 slices are
+// 36, two rounds of twice the steps, 1067, which one round of 240 tiles on the device would have been faster than.)
 struct TrSlices { int slices, chunk; };
 inline TrSlices tr_slices(int n_cus, int M, int N, int K, bool tiles16, size_t part_floats)
 {
-    const int tiles = ((N + TRG_N - 1) / TRG_N) * ((M + TRG_M - 1) / TRG_M);
+    const int gm = (M + TRG_M - 1) / TRG_M, gn = (N + TRG_N - 1) / TRG_N;
+    const int tiles = trg_by_column(gn) ? gm * ((gn + 7) / 8) : gm * gn, cus = trg_by_column(gn) ? n_cus / 8 : n_cus;
     TrSlices best = {1, 0};
     double best_us = -1.0;
     for (int S = 1; S <= TR_SPLIT_MAX; S++) {
         if (S > 1 && (K / S < 128 || (size_t)S * M * N > part_floats)) break;
         const int chunk = ((K + S - 1) / S + TRG_K - 1) / TRG_K * TRG_K;
         if (S > 1 && (S - 1) * chunk >= K) continue;
-        const int rounds = (tiles * S + n_cus - 1) / n_cus;
+        const int rounds = (tiles * S + cus - 1) / cus;
         const double us = rounds * (chunk / TRG_K * (tiles16 ? 1.4 : 1.9) + 6.0) + (S > 1 ? 4.0 + (S + 1) * (double)M * N * 4 / 4.5e6 : 0.0);
         if (best_us < 0 || us < best_us) { best_us = us; best = {S, chunk}; }
     }

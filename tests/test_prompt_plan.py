@@ -95,3 +95,19 @@ def test_slices_of_a_training_contraction_hold_every_k_once(plan):
         assert S == 1 or (S * M * N <= part and K // S >= 128)
         assert S == 1 or (-(-M // 128) * -(-N // 256)) % 256 != 0
     assert seen == set(range(1, SLICES + 1))
+
+
+def test_slices_of_a_training_contraction_are_counted_on_the_busiest_xcd(plan):
+    """The tiles of column c of C go to XCD c % 8 (with 16 columns or more, or a multiple of 8): of 20 columns some XCDs have three, and 36 tiles are two rounds
+    on the 32 compute units of one where 240 would be one on the device.  The steps of the chosen number of slices against those of the best one:
+    at most a third more, which the partial sums may be worth."""
+    asked = [(T, d, k, t16, SLICES * min(T, 256) * 3 * d) for d in (2048, 4096, 5120, 6656, 8192) for T in (100, 150, 256, 333, 450, 500, 700, 1000, 1400)
+             for k, t16 in ((d, 0), (3 * d, 0), (d * 43 // 16, 0), (32000, 1))]
+    for M, N, K, t16, part, S, chunk in plan(asked, "train"):
+        gm, gn = -(-M // 128), -(-N // 256)
+        assert gn % 8 == 0 or gn >= 16
+
+        def steps(n):
+            return -(-gm * -(-gn // 8) * n // 32) * -(-(-(-K // n)) // 32)
+        best = min(steps(n) for n in range(1, SLICES + 1) if n == 1 or (K // n >= 128 and n * M * N <= part))
+        assert steps(S) <= 4 / 3 * best, (M, N, K, S, steps(S), best)
