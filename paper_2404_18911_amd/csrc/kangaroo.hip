@@ -358,6 +358,12 @@ void launch_gemv_multi(const u32x4_t *W, int N, int KS, int M, const void *act, 
     }
 }
 
+// Row tiles of about 256 KB (8192 features): the workgroups of a long launch walk theirs in step and ask for the same memory channels, and the
+// more each asks ahead the longer all wait.  us in a request at d_model 8192, one row, two chunks of loads in flight per wave / one: q,k,v
+// 71.8 / 65.1, gate+up of 22016 126 / 112, head 83.2 / 78.4; at 8064 as fast or faster by 1 %, at 7936 the same.  Launches that are all on the
+// device at once lose by it (8192 x 8192 24.7 / 26.3).
+inline bool gemv_one_chunk(int N, int K) { return K >= 8000 && K <= 8384 && N > 8192; }
+
 int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Epi &e, const Feature &ft = Feature())
 {
     if (N % 16) return fail(x, KG_EINVAL, "projection rows %d not a multiple of 16", N);
@@ -369,7 +375,7 @@ int launch_gemv(kg_ctx *x, size_t w_off, int N, int K, const void *act, const Ep
     else if (const int ntw = x->bf ? gemv_tiles(x->n_cus, N, K, e.M) : 1; ntw > 1)
         launch_gemv_multi<FROM_ACT>(at<const u32x4_t>(x->arena, w_off), N, (K + 31) / 32, e.M, act, 0, e, ntw, x->stream);
     else if (x->bf)
-        hipLaunchKernelGGL(gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream,
+        hipLaunchKernelGGL(gemv_one_chunk(N, K) ? gemv_bf16_one_kernel : gemv_bf16_kernel, dim3(N / 16), dim3(64 * GEMV_WAVES), 0, x->stream,
                            at<const u32x4_t>(x->arena, w_off), (K + 31) / 32, e.M, (const u32x4_t *)act, e.ssq_in, e.nt_in,
                            e.N, e.kind == EPI_RESID ? e.res : nullptr, e.gain, e);
     else

@@ -408,7 +408,8 @@ template <int SRC> struct BSource {
 
 #define GEMV_WAVES 8
 
-template <int SRC, bool FEATURE = false>
+// ONE: one chunk of weights in flight per wave, not two (gemv_one_chunk)
+template <int SRC, bool FEATURE = false, bool ONE = false>
 __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, int KS, int M, const void *__restrict__ act,
                                                const float *ssq_in, int nt_in, int N, const float *res, const float *gain,
                                                int K, const Epi &e, const Feature *ft = nullptr)
@@ -479,6 +480,13 @@ __device__ __forceinline__ void gemv_bf16_body(const u32x4_t *__restrict__ W, in
         } else if (rem) {
             load(a0, b0, 4);
         }
+        if constexpr (ONE)
+            for (; rem > 2; rem--) {
+                mul(a0, b0, 4);
+                GEMV_FENCE;
+                load(a0, b0, 4);
+                GEMV_FENCE;
+            }
         for (; rem > 2; rem -= 2) {
             load(a1, b1, 4);
             GEMV_FENCE;
@@ -533,6 +541,15 @@ __global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_kernel(const u32
                                                                    const float *res, const float *gain, Epi e)
 {
     gemv_bf16_body<FROM_ACT>(W, KS, M, act, ssq_in, nt_in, N, res, gain, 0, e);
+}
+
+// the same with one chunk of weights in flight (gemv_one_chunk)
+__global__ __launch_bounds__(64 * GEMV_WAVES, 2) void gemv_bf16_one_kernel(const u32x4_t *__restrict__ W, int KS, int M,
+                                                                       const u32x4_t *__restrict__ act,
+                                                                       const float *ssq_in, int nt_in, int N,
+                                                                       const float *res, const float *gain, Epi e)
+{
+    gemv_bf16_body<FROM_ACT, false, true>(W, KS, M, act, ssq_in, nt_in, N, res, gain, 0, e);
 }
 
 // the same for the projection that gives the early features (EPI_FEATURE)
