@@ -701,8 +701,9 @@ int pf_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off, 
         pa.act_out = actA; pa.act_blk_bytes = act_bytes(d);
         pa.act_pair = pf_pairs(x) ? 1 : 0;
         ProfScope ps(x, 1, 0.0);
-        // Workgroups of 128 rows where those alone give most compute units one, else of 32 rows (us, 32 / 128 rows; 32 heads: 400 rows
-        // 18 / 22, 512 rows 22 / 22, 640 rows 29 / 25, 1024 rows 46 / 34; 40 heads: 256 rows 15 / 17, 512 rows 27 / 24).
+        // Workgroups of 128 rows where those alone give most compute units one, else of 32 rows (us, 32 / 128 rows; 32 heads: 384 rows
+        // 17 / 18, 512 rows 21 / 21, 640 rows 27 / 24, 1024 rows 44 / 33; 40 heads: 256 rows 14 / 15, 512 rows 25 / 21.  A second pass behind 4096
+        // positions, 32 heads: 128 rows 60 / 105, 256 rows 59 / 108, 512 rows 105 / 116, 640 rows 149 / 119; 40 heads: 384 rows 107 / 117, 448 rows 153 / 118).
         if ((size_t)c.n_heads * ((T + 127) / 128) * 8 >= (size_t)x->n_cus * 5) {
             const dim3 grid(c.n_heads, (T + 127) / 128);
             if (c.head_dim == 128) hipLaunchKernelGGL(pf_attn_kernel<128>, grid, dim3(256), 0, x->stream, pa);
@@ -813,8 +814,10 @@ int run_block(kg_ctx *x, int slot, size_t qkv_off, size_t wo_off, size_t gu_off,
 // Rows of a prompt pass that the caller wants the last layer's output of.  Only keys and values of the others are read again.
 enum class PfRows { NONE, LAST, ALL };
 
-// Passes of more rows compute the query of their last row by itself (11 us for one row's input and one projection).
-// Queries of all rows in the last layer / the last one: 7B width, 256 rows: 58 / 38 + 11 us; 13B width, 777 rows: 245 / 165 + 12.
+// Passes of more rows compute the query of their last row by itself (11 us for one row's input and one projection) and not those of the
+// others.  us of whole passes through 3 layers, all queries / the last one: 7B width, 192 rows 651 / 653, 256 744 / 738, 384 922 / 915, 512 1112 /
+// 1099; 13B width, 192 rows 866 / 871, 256 994 / 996, 320 1144 / 1146, 384 1302 / 1295, 512 1595 / 1587: they cross between 200 and 350 rows, and the
+// line lies where the gain is sure at both widths.
 constexpr int PF_LAST_QUERY = 384;
 
 // The last layer of a pass of which only the last row goes on: keys and values of all rows, then that row through the decode kernels,

@@ -908,7 +908,8 @@ __global__ __launch_bounds__(512) void gemv_f32_kernel(const float *__restrict__
 // The same sums of one row on the vector units (a k slot's products one after another, slots and quarters of the steps in the order
 // above): 16 consecutive lanes read 256 bytes of a weight row, where the matrix instruction's operand has neighbouring lanes in four rows.
 // us, one row, matrix / vector: 2048 x 1024 4.18 / 3.78, 512 x 8192 17.6 / 9.9, 256 x 688 3.37 / 3.37; from two rows on the matrix form is as
-// fast or faster at the sizes of small models (2048 x 1024, two rows, 4.37 against 4.75 with two rows on the vector units).
+// fast or faster at the sizes of small models (2048 x 1024, two rows, 4.37 against 4.75 with two rows on the vector units).  Few rows of many
+// features take it from two rows on too (512 x 8192, 2, 4 and 8 rows 19.9, 23.3 and 30.7 us; with 16 threads to a weight row 33, 46 and 83).
 __global__ __launch_bounds__(256) void gemv_f32_row_kernel(const float *__restrict__ W, int K, const float *__restrict__ act, Epi e, Feature ft)
 {
     constexpr int D = 8;                    // steps of 64 k in flight

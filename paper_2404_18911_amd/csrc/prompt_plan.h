@@ -75,8 +75,8 @@ inline bool trg_by_column(int gn) { return gn % 8 == 0 || gn >= 16; }
 // apart from their steps of 32 k: 1.9 us a step with all compute units at work, 1.4 against bf16 tiles), counted on the XCD with the most columns
 // (of 20 some have three and some two), partial sums written and added at 4.5 TB/s by a launch of 4 us.  So few tiles are cut to fill the
 // device, and a launch whose last round is half empty to halve the rounds (1000 x 12288 x 4096, 384 tiles on 256 compute units: 690 us -> 554 and 35
-// for the sums).  No slice is empty.  (700 x 5120 x 15360: 4 slices are 72 tiles on an XCD of 32 compute units, three rounds, 842 us; 2 slices are
-// 36, two rounds of twice the steps, 1067, which one round of 240 tiles on the device would have been faster than.)
+// for the sums).  No slice is empty.  (700 x 5120 x 15360: 2 slices are 240 tiles, but 36 on an XCD of 32 compute units, two rounds, 1067 us; 4 are
+// 72, three rounds of half the steps, 842; 7 are 126, four rounds, 715 and 27 for the sums.)
 struct TrSlices { int slices, chunk; };
 inline TrSlices tr_slices(int n_cus, int M, int N, int K, bool tiles16, size_t part_floats)
 {
