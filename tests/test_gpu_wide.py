@@ -21,7 +21,7 @@ def test_rows_of_wide_projections(heads):
         t = (torch.ones(c, device="cuda") if norm else torch.randn(r, c, generator=g, device="cuda") * (1.0 if kind == I.KIND_EMBED else 0.01)).bfloat16()
         kg._chk(kg.L.kg_load_tensor(kg.h, kind, layer, t.data_ptr(), t.numel()))
     prompt = [int(t) for t in I.gen_prompt(shape.vocab, 20, seed=6)]
-    for gamma in (1, 2, 3, 6):
+    for gamma in (1, 2, 3, 4, 5, 6):
         p, _ = B.make_params(eta=0.0, gamma=gamma)
         chain = [kg.prefill(p, prompt)]
         for _ in range(gamma):
